@@ -10,9 +10,12 @@ LIB_PATH = os.path.join(HERE, "liblayoutcopy.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["layout.cpp", "algebra.cpp", "semimodule.cpp", "plan.cpp", "replay.cpp", "gemm_plan.cpp", "gemm_replay.cpp", "capi.cpp",
            "gemm_capi.cpp", "kernels.hip", "gemm_kernels.hip", "gemm_inst_bf16_256.hip", "gemm_inst_bf16_128.hip",
-           "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip"]
-HEADERS = ["layout.hpp", "algebra.hpp", "semimodule.hpp", "plan.hpp", "kernel_params.hpp", "gemm_plan.hpp", "gemm_params.hpp", "plan_cache.hpp"]
-KERNEL_HEADERS = {"gemm_kernel.hpp": "gemm_inst_"}   # header -> prefix of the only sources that include it
+           "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip", "gemm_inst_bf16_split.hip", "gemm_inst_f16_split.hip"]
+HEADERS = ["layout.hpp", "algebra.hpp", "semimodule.hpp", "plan.hpp", "kernel_params.hpp", "gemm_plan.hpp", "gemm_params.hpp", "plan_cache.hpp", "kernarg.hpp"]
+# header -> the only sources that include it
+_TILE = ["gemm_inst_bf16_256.hip", "gemm_inst_bf16_128.hip", "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip"]
+_SPLIT = ["gemm_inst_bf16_split.hip", "gemm_inst_f16_split.hip"]
+KERNEL_HEADERS = {"gemm_kernel.hpp": _TILE, "gemm_split_kernel.hpp": _SPLIT, "gemm_device.hpp": _TILE + _SPLIT}
 
 
 def _hipcc():
@@ -45,8 +48,8 @@ def build(force=True):
     for s in SOURCES:
         obj = os.path.join(OBJ_DIR, s + ".o")
         src_time = max(newest_common, os.path.getmtime(os.path.join(CSRC, s)))
-        for header, prefix in KERNEL_HEADERS.items():
-            if s.startswith(prefix):
+        for header, sources in KERNEL_HEADERS.items():
+            if s in sources:
                 src_time = max(src_time, os.path.getmtime(os.path.join(CSRC, header)))
         if force or not os.path.exists(obj) or os.path.getmtime(obj) < src_time:
             todo.append(s)

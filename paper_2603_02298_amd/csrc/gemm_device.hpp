@@ -1,0 +1,202 @@
+// Device helpers the GEMM kernels share: the matrix instruction, register transposes, LDS transpose loads, the barrier and
+// the step along an operand's k mode.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "gemm_params.hpp"
+
+namespace lc {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <bool BF16>
+__device__ __forceinline__ f32x16 mfma_32x32x16(u32x4 a, u32x4 b, f32x16 c) {
+  if constexpr (BF16)
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+// Row i of the transpose of an 8x8 block of 16-bit elements held as 8 vectors of 8 (in[j] = the 8 rows' elements
+// at column j): element j of the result is element i of in[j].  `odd` says whether i is odd (it may be a run-time
+// value: it only picks the halves of the dwords, never a register); half = i / 2 picks the dword.
+__device__ __forceinline__ u32x4 transposed_row_b16(const u32x4 (&in)[8], int half, bool odd) {
+  // v_perm_b32 picks 4 of the 8 bytes {in[2d+1] dword : in[2d] dword}: low halves of both, or high halves of both
+  const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
+  u32x4 out;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) out[d] = __builtin_amdgcn_perm(in[2 * d + 1][half], in[2 * d][half], sel);
+  return out;
+}
+
+// compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>); the accumulators are
+// only ever indexed with constants, so they stay in registers
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// One 32 x 16 fragment's share of a lane from a k-major tile (row k of the tile = BR elements, see gemm_rdirect_lds_offset):
+// two LDS transpose loads (ds_read_b64_tr_b16) of k .. k + 3 and k + 4 .. k + 7; `at` is the lane's address for the
+// tile's first 16 k, kk the k step.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+// The restrict qualifier gives the load alias information once inlined; without any, the compiler makes every such load wait
+// for all direct loads in flight (they write LDS too), although those go to the other stage.
+__device__ __forceinline__ s16x4 lds_transpose_load(lds_s16x4* __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16(p); }
+template <int BR, typename KK>
+__device__ __forceinline__ u32x4 lds_read_tr_16x8(const unsigned char* at, KK kk) {
+  const unsigned char* p = at + (uint32_t)kk * 16u * (BR * 2u);
+  const s16x4 lo = lds_transpose_load((lds_s16x4*)(p));
+  const s16x4 hi = lds_transpose_load((lds_s16x4*)(p + 4u * (BR * 2u)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 l = __builtin_bit_cast(u32x2, lo), h = __builtin_bit_cast(u32x2, hi);
+  return u32x4{l[0], l[1], h[0], h[1]};
+}
+
+__device__ __forceinline__ u32x4 select_or_zero(bool keep, u32x4 v) {
+  return u32x4{keep ? v[0] : 0u, keep ? v[1] : 0u, keep ? v[2] : 0u, keep ? v[3] : 0u};
+}
+
+// Workgroup barrier that orders LDS accesses only.  __syncthreads() would also wait for every load in flight (the direct
+// loads count as global loads), which is exactly what the ring of tiles must not do; the caller states its own wait.
+__device__ __forceinline__ void lds_barrier() {
+  // the empty statements are compiler-only fences: no memory access is moved across the barrier, nothing is emitted
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Byte offset of k tile t along an operand's k mode, for operands whose k tiles lie inside the mode's first leaf: stepping
+// to the next tile adds 64 strides of that leaf until the leaf is exhausted; only then is the layout function evaluated again.
+struct KTileOffset {
+  uint32_t bytes, step, left;   // left: k tiles from the current one to the end of the first leaf's run
+  __device__ __forceinline__ void seek(const GemmMode& k, uint32_t t) {
+    bytes = 2u * gemm_mode_eval(k, t * kGemmBK);
+    step = 2u * kGemmBK * k.lead_stride;
+    if (k.n == 1) {
+      left = 0xFFFFFFFFu;
+    } else {
+      uint32_t q, r;
+      fd_divmod(t * kGemmBK, k.div[0], &q, &r);
+      left = (k.div[0].div - r) / kGemmBK;
+    }
+  }
+  __device__ __forceinline__ void next(const GemmMode& k, uint32_t t) {
+    if (--left == 0) seek(k, t);
+    else bytes += step;
+  }
+};
+
+// One operand's tile of a k tile sent straight from global memory into LDS by WAVES wavefronts together: R instructions of
+// 1 KiB per wavefront (lane t's 16 bytes land at byte 16 t of the KiB).
+// Rows past the operand's extent, and k past K in a short last k tile, present an offset outside the buffer's range: zeros
+// arrive and no access is made.
+template <int BR, int LOAD, int WAVES>
+struct DirectTileLoader {
+  static constexpr int R = BR / 8 / WAVES;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t off[R];       // bytes from the k tile's first k
+  uint32_t tail_mask;    // bit i: instruction i of this lane asks for k below K in the last k tile
+
+  // t: the lane's index among the WAVES wavefronts' lanes
+  __device__ __forceinline__ void init(const uint16_t* p, const GemmMode& rmode, const GemmMode& kmode, uint32_t row0, uint32_t extent, uint32_t K,
+                                       uint32_t t) {
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, 0xFFFFFFFFu, 0x00020000);
+    tail_mask = 0u;
+    const uint32_t k_rem = K - (K - 1u) / kGemmBK * kGemmBK;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      uint32_t row, k, in_k;   // in_k: elements from the k tile's first k
+      if constexpr (LOAD == kLoadKDirect) {
+        row = gemm_direct_row(R, t, (uint32_t)i);
+        k = 8u * gemm_direct_kvec(row, t);
+        in_k = k;
+      } else {
+        gemm_rdirect_unit(BR, R, t, (uint32_t)i, &k, &row);
+        in_k = k * kmode.lead_stride;
+      }
+      const uint32_t r = row0 + row, at = 2u * (gemm_mode_eval(rmode, r < extent ? r : extent - 1u) + in_k);
+      off[i] = r < extent ? at : 0xFFFFFFFFu;
+      tail_mask |= (k < k_rem ? 1u : 0u) << i;
+    }
+  }
+  // k_bytes: the k tile's byte offset along the k mode (uniform); at: where this wavefront's first KiB of the tile lies in LDS (uniform)
+  __device__ __forceinline__ void fetch(uint32_t k_bytes, uint32_t at, bool tail) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    // dynamic LDS under a second name: the compiler sees no alias between these writes and the fragment reads and adds no
+    // waits of its own; the kernels state the order by hand
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
+    static_for<R>([&](auto i) {
+      const uint32_t voff = (tail && ((tail_mask >> (int)i) & 1u) == 0u) ? 0xFFFFFFFFu : off[i];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(lds_bytes + at + (uint32_t)i * 1024u), 16, (int)voff, (int)k_bytes, 0, 0);
+    });
+  }
+};
+
+// Fragment of rows row .. row + 31, k step kk of an operand's tile of BR rows at LDS address `tile`: this lane's 8 elements.
+// (A tile of 16 rows stands twice in its fragment; the second half's products are never looked at.)
+template <int BR, int LOAD, typename KK>
+__device__ __forceinline__ u32x4 direct_fragment(const unsigned char* tile, uint32_t lane, uint32_t row, KK kk) {
+  if constexpr (LOAD == kLoadRDirect)
+    return lds_read_tr_16x8<BR>(tile + gemm_rdirect_frag_offset(BR, lane, row, 8u * mfma_ab_kvec(lane)), kk);
+  else
+    return *reinterpret_cast<const u32x4*>(tile + gemm_lds_offset((row + mfma_ab_row(lane)) & (BR - 1u), 2u * (uint32_t)kk + mfma_ab_kvec(lane)));
+}
+
+// The units of a TM x TN tile of C that a lane of LANES adds sums to (gemm_sum_of): their old values are asked for ahead of
+// time, the sums come out of LDS and go back in whole runs of C.
+template <int TM, int TN, int LANES, bool C_VEC>
+struct SumUnits {
+  static constexpr int UNITS = TM * TN / 4, N = (UNITS + LANES - 1) / LANES;
+  f32x4 old[N];
+  uint32_t rows[N], unit[N], off[N][C_VEC ? 1 : 4];   // rows of the unit that exist (0: none)
+  __device__ __forceinline__ void request(const GemmParams& P, const float* C, uint32_t m0, uint32_t n0, uint32_t tid) {
+    static_for<N>([&](auto j) {
+      uint32_t m4, n;
+      gemm_sum_of(TM, TN, C_VEC, tid + (uint32_t)j * LANES, &m4, &n);
+      unit[j] = gemm_sum_unit(TM, TN, m4, n);
+      const uint32_t m = m0 + 4u * m4, left = P.M - (m < P.M ? m : P.M);
+      const bool in = (UNITS % LANES == 0 || tid + (uint32_t)j * LANES < (uint32_t)UNITS) && n0 + n < P.N;
+      rows[j] = in ? (left < 4u ? left : 4u) : 0u;
+      // units that do not exist read the last ones that do: no branch around the loads
+      const uint32_t n_off = gemm_mode_eval(P.c_n, n0 + n < P.N ? n0 + n : P.N - 1u);
+      if constexpr (C_VEC) {
+        off[j][0] = gemm_mode_eval(P.c_m, left > 0u ? m : P.M - 4u) + n_off;
+        old[j] = *reinterpret_cast<const f32x4*>(C + off[j][0]);
+      } else {
+        static_for<4>([&](auto v) {
+          off[j][(int)v] = gemm_mode_eval(P.c_m, (uint32_t)v < left ? m + (uint32_t)v : P.M - 1u) + n_off;
+          old[j][(int)v] = C[off[j][(int)v]];
+        });
+      }
+    });
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);   // the operands' loads come after these
+  }
+  template <typename F>
+  __device__ __forceinline__ void add(float* C, F&& sum_of) {
+    static_for<N>([&](auto j) {
+      if (rows[j] == 0u) return;
+      const f32x4 sum = sum_of(unit[j]) + old[j];
+      if constexpr (C_VEC) {
+        *reinterpret_cast<f32x4*>(C + off[j][0]) = sum;
+      } else {
+        static_for<4>([&](auto v) {
+          if ((uint32_t)v < rows[j]) C[off[j][(int)v]] = sum[(int)v];
+        });
+      }
+    });
+  }
+};
+
+}  // namespace lc

@@ -15,70 +15,12 @@
 
 #include <atomic>
 #include <string>
-#include <type_traits>
 
+#include "gemm_device.hpp"
 #include "gemm_plan.hpp"
 #include "plan.hpp"
 
 namespace lc {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-template <bool BF16>
-__device__ __forceinline__ f32x16 mfma_32x32x16(u32x4 a, u32x4 b, f32x16 c) {
-  if constexpr (BF16)
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-// Row i of the transpose of an 8x8 block of 16-bit elements held as 8 vectors of 8 (in[j] = the 8 rows' elements
-// at column j): element j of the result is element i of in[j].  `odd` says whether i is odd (it may be a run-time
-// value: it only picks the halves of the dwords, never a register); half = i / 2 picks the dword.
-__device__ __forceinline__ u32x4 transposed_row_b16(const u32x4 (&in)[8], int half, bool odd) {
-  // v_perm_b32 picks 4 of the 8 bytes {in[2d+1] dword : in[2d] dword}: low halves of both, or high halves of both
-  const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
-  u32x4 out;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) out[d] = __builtin_amdgcn_perm(in[2 * d + 1][half], in[2 * d][half], sel);
-  return out;
-}
-
-// compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>); the accumulators are
-// only ever indexed with constants, so they stay in registers
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
-// One 32 x 16 fragment's share of a lane from a k-major tile (row k of the tile = BR elements, see gemm_rdirect_lds_offset):
-// two LDS transpose loads (ds_read_b64_tr_b16) of k .. k + 3 and k + 4 .. k + 7; `at` is the lane's address for the
-// tile's first 16 k, kk the k step.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-// The restrict qualifier gives the load alias information once inlined; without any, the compiler makes every such load wait
-// for all direct loads in flight (they write LDS too), although those go to the other stage.
-__device__ __forceinline__ s16x4 lds_transpose_load(lds_s16x4* __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16(p); }
-template <int BR, typename KK>
-__device__ __forceinline__ u32x4 lds_read_tr_16x8(const unsigned char* at, KK kk) {
-  const unsigned char* p = at + (uint32_t)kk * 16u * (BR * 2u);
-  const s16x4 lo = lds_transpose_load((lds_s16x4*)(p));
-  const s16x4 hi = lds_transpose_load((lds_s16x4*)(p + 4u * (BR * 2u)));
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 l = __builtin_bit_cast(u32x2, lo), h = __builtin_bit_cast(u32x2, hi);
-  return u32x4{l[0], l[1], h[0], h[1]};
-}
-
-__device__ __forceinline__ u32x4 select_or_zero(bool keep, u32x4 v) {
-  return u32x4{keep ? v[0] : 0u, keep ? v[1] : 0u, keep ? v[2] : 0u, keep ? v[3] : 0u};
-}
 
 // One operand (A or B) of one workgroup: issues the global loads of a k tile into registers, parks them in LDS.
 // Loads are unconditional from clamped coordinates (always inside the tensor); what lies past K is zeroed
@@ -220,36 +162,6 @@ struct OperandLoader {
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) *reinterpret_cast<u32x4*>(tile + gemm_lds_offset(row_in_tile + 32u * (uint32_t)i, kv)) = regs[i];
     }
-  }
-};
-
-// Workgroup barrier that orders LDS accesses only.  __syncthreads() would also wait for every load in flight (the direct
-// loads count as global loads), which is exactly what the ring of tiles must not do; the caller states its own wait.
-__device__ __forceinline__ void lds_barrier() {
-  // the empty statements are compiler-only fences: no memory access is moved across the barrier, nothing is emitted
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Byte offset of k tile t along an operand's k mode, for operands whose k tiles lie inside the mode's first leaf: stepping
-// to the next tile adds 64 strides of that leaf until the leaf is exhausted; only then is the layout function evaluated again.
-struct KTileOffset {
-  uint32_t bytes, step, left;   // left: k tiles from the current one to the end of the first leaf's run
-  __device__ __forceinline__ void seek(const GemmMode& k, uint32_t t) {
-    bytes = 2u * gemm_mode_eval(k, t * kGemmBK);
-    step = 2u * kGemmBK * k.lead_stride;
-    if (k.n == 1) {
-      left = 0xFFFFFFFFu;
-    } else {
-      uint32_t q, r;
-      fd_divmod(t * kGemmBK, k.div[0], &q, &r);
-      left = (k.div[0].div - r) / kGemmBK;
-    }
-  }
-  __device__ __forceinline__ void next(const GemmMode& k, uint32_t t) {
-    if (--left == 0) seek(k, t);
-    else bytes += step;
   }
 };
 

@@ -115,13 +115,16 @@ LC_HD uint32_t gemm_lane_row(int32_t load, uint32_t lane, uint32_t i) {
 // (4 k rows x 32 bytes); with this XOR layout (Sec. 2.3.2) the two lane groups that share a pass (rows 0..15 and
 // 16..31 of a fragment) and their 4 k rows touch 16 distinct 16-byte bank groups.
 // ---------------------------------------------------------------------------------------------
-LC_HD uint32_t gemm_rdirect_lds_offset(uint32_t BR, uint32_t k, uint32_t row) { return k * (BR * 2u) + ((((row >> 3) ^ (4u * (k & 3u)))) << 4) + (row & 7u) * 2u; }
+// Narrower tiles hold several k rows per 256 bytes of banks: with 64 rows (8 slots per k) two k rows share them and the XOR
+// only has to part k rows 2 apart; with 32 rows (4 slots per k) four k rows fill them and nothing is folded.
+LC_HD uint32_t gemm_rdirect_fold(uint32_t BR, uint32_t k) { return BR >= 128u ? 4u * (k & 3u) : BR == 64u ? 2u * (k & 2u) : 0u; }
+LC_HD uint32_t gemm_rdirect_lds_offset(uint32_t BR, uint32_t k, uint32_t row) { return k * (BR * 2u) + ((((row >> 3) ^ gemm_rdirect_fold(BR, k))) << 4) + (row & 7u) * 2u; }
 // Instruction i of wavefront w fills 1 KiB = 64 slots; lane l's slot is unit (w R + i) 64 + l of the tile: its k row and
 // the 8-row group it must ask memory for.
 LC_HD void gemm_rdirect_unit(uint32_t BR, uint32_t rows_per_lane, uint32_t tid, uint32_t i, uint32_t* k, uint32_t* row) {
   const uint32_t unit = ((tid >> 6) * rows_per_lane + i) * 64u + (tid & 63u), slots = BR / 8u;
   *k = unit / slots;
-  *row = ((unit % slots) ^ (4u * (*k & 3u))) * 8u;
+  *row = ((unit % slots) ^ gemm_rdirect_fold(BR, *k)) * 8u;
 }
 // ds_read_b64_tr_b16 (checked on the GPU with an in-bounds probe): within each group of 16 lanes, result lane i element e
 // is element i % 4 of the 8 bytes that lane 4 e + i / 4 of the group points at.  Lane j of a group therefore points at
@@ -140,6 +143,28 @@ LC_HD uint32_t gemm_direct_kvec(uint32_t row, uint32_t tid) { return ((tid & 7u)
 LC_HD uint32_t gemm_clamp_row(int32_t load, uint32_t row, uint32_t extent) {
   const uint32_t last = load == kLoadRVec || load == kLoadRDirect ? extent - 8u : extent - 1u;
   return row < last ? row : last;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Split kernel: a workgroup of W wavefronts owns a TM x TN tile of C and its wavefronts share out the k tiles (wavefront w
+// takes k tiles w, w + W, ...).  Each wavefront keeps operand tiles of its own in LDS -- the arrangements above for one
+// wavefront: instruction i fills KiB i of the tile -- and a partial tile of C in registers; the partials are summed
+// through LDS in the order of the wavefronts.
+// Sums on their way to C through LDS (this kernel's partial tiles, the stream kernel's finished ones): TM x TN floats as
+// 16-byte units of four consecutive m; unit (m4, n) = four rows from 4 m4 of column n.  They are written as the matrix
+// instruction leaves them (8 lanes: 8 columns, one m4) and read back 16 lanes along m4 first (C contiguous along m) or
+// along n; the XOR keeps both free of bank conflicts: the 16 lanes of a read pass (4-lane groups 0,3,5,6 or 1,2,4,7 of
+// 32 lanes) hold 4 columns x 8 m4 (TM = 32), 2 x 16 (TM = 64) or 1 x 32 (TM >= 128).
+// ---------------------------------------------------------------------------------------------
+LC_HD uint32_t gemm_sum_unit(uint32_t TM, uint32_t TN, uint32_t m4, uint32_t n) {
+  const uint32_t far = TM == 32u ? 0u : TM == 64u ? 2u * ((m4 >> 3) & 1u) : (m4 >> 2) & 3u;
+  return m4 * TN + (n ^ (4u * (m4 & 3u)) ^ far);
+}
+// Unit u of the TM TN / 4 a workgroup adds to C: consecutive u run along m where C holds four consecutive m in a vector,
+// along n otherwise.
+LC_HD void gemm_sum_of(uint32_t TM, uint32_t TN, int32_t c_vec, uint32_t u, uint32_t* m4, uint32_t* n) {
+  *m4 = c_vec ? u % (TM / 4u) : u / TN;
+  *n = c_vec ? u / (TM / 4u) : u % TN;
 }
 
 // ---------------------------------------------------------------------------------------------

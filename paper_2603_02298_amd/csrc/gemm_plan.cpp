@@ -174,18 +174,32 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   plan.b_align = exchange ? need_a : need_b;
   plan.c_align = P.c_vec ? 16u : 4u;
 
-  // tile: 256 x 256 when that still gives every CU a tile, else 128 x 128
-  int tile = ((kM + 255) / 256) * ((kN + 255) / 256) * Lb >= 256 ? 256 : 128;
-  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
-  if (t_env == 128 || t_env == 256) tile = t_env;
-  plan.tile_m = plan.tile_n = tile;
-  P.tiles_m = (uint32_t)((kM + tile - 1) / tile);
-  P.tiles_n = (uint32_t)((kN + tile - 1) / tile);
+  // Tile.  Split kernel (direct loads only): while tiles of 64 x 64 leave a CU at most one workgroup, and then the smallest of
+  // its tiles that does: the k tiles of a workgroup's tile go to its wavefronts, more tiles only take LDS from each other.
+  // Measured on MI355X (bf16, start = 128 x 128 tiles): 512^3 11.1 us; 32 x 32 tiles (256 of them) 4.3, 32 x 64 4.7, 64 x 64
+  // 6.2.  16 x 8192 x 8192 78 us; 32 x 32 27.6, 64 x 64 36.  64 x 8192 x 8192 92 us; 32 x 32 (512 tiles) 42.8, 64 x 32 (256) 33.4.
+  // 1024^3 17.6 us; 32 x 64 (512 tiles) 10.8, 64 x 64 (256) 8.3.
+  // 256 x 256 when that still gives every CU a tile, else 128 x 128.
+  auto tiles_of = [&](int64_t tm, int64_t tn) { return (kM + tm - 1) / tm * ((kN + tn - 1) / tn) * Lb; };
+  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);   // 128, 256; split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432
+  auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
+  const bool thin = kN <= 16 && P.b_load == kLoadKVec;
+  if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
+  else if (direct && (t_env ? t_env == 3216 && thin : thin && tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
+  else if (direct && (t_env ? t_env == 32 : tiles_of(32, 32) <= 256)) take(32, 32, 8, 2);
+  else if (direct && (t_env ? t_env == 3264 : kM <= kN && tiles_of(32, 64) <= 256)) take(32, 64, 4, 3);
+  else if (direct && (t_env ? t_env == 6432 : kM > kN && tiles_of(64, 32) <= 256)) take(64, 32, 4, 3);
+  else if (direct && (t_env ? t_env == 64 : tiles_of(64, 64) <= 256)) take(64, 64, 4, 2);
+  else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);
+  else take(128, 128, 0, 0);
+  P.tiles_m = (uint32_t)((kM + plan.tile_m - 1) / plan.tile_m);
+  P.tiles_n = (uint32_t)((kN + plan.tile_n - 1) / plan.tile_n);
   P.k_tiles = (uint32_t)((K + kGemmBK - 1) / kGemmBK);
   if ((uint64_t)P.tiles_m * P.tiles_n >= (uint64_t(1) << 31)) return LC_ERR_TOO_LARGE;
   P.group_m = (uint32_t)std::max(1, env_int("LC_TUNE_GEMM_GROUP_M", 8));
   // two stages of (rows x 128 bytes) for A and B; direct loads: a ring of five operand tiles
-  plan.lds_bytes = direct ? 5u * (unsigned)plan.tile_m * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
+  // (split kernel: a ring per wavefront)
+  plan.lds_bytes = plan.split_waves ? (unsigned)(plan.split_waves * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)plan.tile_m * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
   plan.a_text = mode_text(a_r) + " x " + mode_text(a_k);
   plan.b_text = mode_text(b_r) + " x " + mode_text(b_k);
   plan.c_text = mode_text(c_m) + " x " + mode_text(c_n);
@@ -206,6 +220,7 @@ std::string describe(const lc_gemm_plan& plan) {
   if (plan.L != 1 || plan.a_text.find(" x ", plan.a_text.find(" x ") + 1) != std::string::npos) s += " L=" + std::to_string(plan.L);
   s += " exchanged=" + std::to_string((int)plan.exchanged);
   s += " tile=" + std::to_string(plan.tile_m) + "x" + std::to_string(plan.tile_n) + "x" + std::to_string(kGemmBK);
+  if (plan.split_waves) s += " split_waves=" + std::to_string(plan.split_waves) + " stages=" + std::to_string(plan.stages);
   s += " tiles=" + std::to_string(plan.params.tiles_m) + "x" + std::to_string(plan.params.tiles_n) + " k_tiles=" + std::to_string(plan.params.k_tiles);
   s += " group_m=" + std::to_string(plan.params.group_m);
   s += std::string(" a_load=") + load_name[plan.params.a_load] + (plan.params.a_direct ? "(direct-to-LDS)" : "");

@@ -37,18 +37,21 @@ struct Walker {
   bool ok = true;
 
   // loads one operand tile of k tile kt into the LDS model, lane by lane
+  // lanes: how many load a tile together (a workgroup, or one wavefront of the split kernel, whose lanes past the extent
+  // are answered with zeros instead of taking the last row)
   void stage(const uint16_t* base, int64_t elems, const GemmMode& rmode, const GemmMode& kmode, int32_t load, uint32_t row0, uint32_t extent,
-             uint32_t BR, uint32_t kt, unsigned char* tile) {
+             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock) {
+    const bool zero_rows = lanes == 64u;
     if (load == kLoadKDirect) {
       // every lane's 16 bytes land at byte 16 * lane of the 1 KiB its wavefront's instruction i fills
-      const uint32_t rows_per_lane = BR / 32;
-      for (uint32_t tid = 0; tid < (uint32_t)kBlock; ++tid)
+      const uint32_t rows_per_lane = BR * 8u / lanes;
+      for (uint32_t tid = 0; tid < lanes; ++tid)
         for (uint32_t i = 0; i < rows_per_lane; ++i) {
           const uint32_t row = gemm_direct_row(rows_per_lane, tid, i), kv = gemm_direct_kvec(row, tid);
           const int64_t off = (int64_t)gemm_mode_eval(rmode, gemm_clamp_row(load, row0 + row, extent)) + 8u * kv + gemm_mode_eval(kmode, kt * kGemmBK);
           const uint32_t lds_at = ((tid >> 6) * rows_per_lane + i) * 1024u + (tid & 63u) * 16u;
           if (lds_at != gemm_lds_offset(row, kv)) { ok = false; return; }
-          if (kt * kGemmBK + 8u * kv >= P.K) {   // past K in a short last k tile: the lane's offset is out of range, zeros arrive
+          if (kt * kGemmBK + 8u * kv >= P.K || (zero_rows && row0 + row >= extent)) {   // past K in a short last k tile: the lane's offset is out of range, zeros arrive
             std::memset(tile + lds_at, 0, 16);
             continue;
           }
@@ -59,8 +62,8 @@ struct Walker {
     }
     if (load == kLoadRDirect) {
       // k-major tile: lane l of instruction i of wavefront w fills 16-byte unit (w R + i) 64 + l
-      const uint32_t rows_per_lane = BR / 32;
-      for (uint32_t tid = 0; tid < (uint32_t)kBlock; ++tid)
+      const uint32_t rows_per_lane = BR * 8u / lanes;
+      for (uint32_t tid = 0; tid < lanes; ++tid)
         for (uint32_t i = 0; i < rows_per_lane; ++i) {
           uint32_t k, row;
           gemm_rdirect_unit(BR, rows_per_lane, tid, i, &k, &row);
@@ -68,7 +71,7 @@ struct Walker {
                               gemm_mode_eval(kmode, kt * kGemmBK);
           const uint32_t lds_at = ((tid >> 6) * rows_per_lane + i) * 1024u + (tid & 63u) * 16u;
           if (k >= (uint32_t)kGemmBK || row + 8 > BR || lds_at != gemm_rdirect_lds_offset(BR, k, row)) { ok = false; return; }
-          if (kt * kGemmBK + k >= P.K) {   // past K in a short last k tile: zeros arrive
+          if (kt * kGemmBK + k >= P.K || (zero_rows && row0 + row >= extent)) {   // past K in a short last k tile: zeros arrive
             std::memset(tile + lds_at, 0, 16);
             continue;
           }
@@ -134,7 +137,7 @@ struct Walker {
   void fragment(const unsigned char* tile, int32_t load, uint32_t BR, uint32_t row_base, uint32_t kk, uint16_t (*out)[8]) {
     for (uint32_t lane = 0; lane < 64; ++lane) {
       if (load != kLoadRDirect) {
-        std::memcpy(out[lane], tile + gemm_lds_offset(row_base + mfma_ab_row(lane), 2u * kk + mfma_ab_kvec(lane)), 16);
+        std::memcpy(out[lane], tile + gemm_lds_offset((row_base + mfma_ab_row(lane)) % BR, 2u * kk + mfma_ab_kvec(lane)), 16);
         continue;
       }
       for (uint32_t h = 0; h < 2; ++h)
@@ -148,6 +151,111 @@ struct Walker {
   }
 };
 
+// one 32 x 32 fragment product of k step kk, added to a TM x TN accumulator at (row, col)
+struct FragmentProduct {
+  Layout tv_a, tv_b, tv_c;
+  float (*to_float)(uint16_t);
+  bool run(Walker& w, const unsigned char* a_tile, int32_t a_kind, uint32_t BM, uint32_t row, const unsigned char* b_tile, int32_t b_kind,
+           uint32_t BN, uint32_t col, uint32_t kk, float* acc) {
+    // gather the two 32 x 16 fragments from the lanes' LDS reads, through the thread-value layouts
+    float fa[32][16], fb[32][16];
+    uint16_t va[64][8], vb[64][8];
+    w.fragment(a_tile, a_kind, BM, row, kk, va);
+    w.fragment(b_tile, b_kind, BN, col, kk, vb);
+    if (!w.ok) return false;
+    for (uint32_t lane = 0; lane < 64; ++lane)
+      for (uint32_t v = 0; v < 8; ++v) {
+        const int64_t ca = tv_a((int64_t)lane + 64 * v), cb = tv_b((int64_t)lane + 64 * v);   // row + 32 k
+        fa[ca % 32][ca / 32] = to_float(va[lane][v]);
+        fb[cb % 32][cb / 32] = to_float(vb[lane][v]);
+      }
+    // D = A B^T + D, then back to the lanes' accumulators through the C fragment layout
+    for (uint32_t lane = 0; lane < 64; ++lane)
+      for (uint32_t v = 0; v < 16; ++v) {
+        const int64_t cc = tv_c((int64_t)lane + 64 * v);   // m + 32 n
+        const uint32_t r = (uint32_t)(cc % 32), c = (uint32_t)(cc / 32);
+        if (r != mfma_c_row(lane, v) || c != mfma_c_col(lane)) return false;
+        float sum = 0.f;
+        if (col + c >= BN) continue;   // a tile of 16 columns stands twice in its fragment
+        for (uint32_t k = 0; k < 16; ++k) sum += fa[r][k] * fb[c][k];
+        acc[(size_t)(row + r) * BN + (col + c)] += sum;
+      }
+    return true;
+  }
+};
+
+// The split kernel: every wavefront's k tiles into a partial tile of its own, the partials into units of LDS, the units
+// summed in the order of the wavefronts and added to C.
+lc_status_t replay_split(const lc_gemm_plan& plan, Walker& w, FragmentProduct& product, float* c_all, int64_t c_all_elems) {
+  const GemmParams& P = w.P;
+  const uint32_t TM = (uint32_t)plan.tile_m, TN = (uint32_t)plan.tile_n, W = (uint32_t)plan.split_waves, units = TM * TN / 4u;
+  const int32_t a_kind = gemm_effective_load(P.a_load, P.a_direct), b_kind = gemm_effective_load(P.b_load, P.b_direct);
+  if (plan.stages < 1 || plan.lds_bytes != W * (unsigned)plan.stages * (TM + TN) * 128u || !P.a_direct || !P.b_direct) return LC_ERR_INVALID_ARG;
+  const uint32_t per_batch = P.tiles_m * P.tiles_n, n_tiles = per_batch * P.L;
+  std::vector<unsigned char> lds((TM + TN) * 128u);
+  std::vector<float> acc((size_t)TM * TN), parts((size_t)W * units * 4u);
+  std::vector<char> covered(n_tiles, 0);
+  const uint16_t *a_all = w.A, *b_all = w.B;
+  const int64_t a_elems = w.a_elems, b_elems = w.b_elems;
+  for (uint32_t block = 0; block < n_tiles; ++block) {
+    const uint32_t order = gemm_tile_order_of_block(block, n_tiles);
+    if (order >= n_tiles || covered[order]) return LC_ERR_INVALID_ARG;   // every tile exactly once
+    covered[order] = 1;
+    const uint32_t batch = order / per_batch;
+    uint32_t tm, tn;
+    gemm_tile_of_order(P, order - batch * per_batch, &tm, &tn);
+    if (tm >= P.tiles_m || tn >= P.tiles_n) return LC_ERR_INVALID_ARG;
+    const uint32_t m0 = tm * TM, n0 = tn * TN, ao = gemm_mode_eval(P.a_l, batch), bo = gemm_mode_eval(P.b_l, batch), co = gemm_mode_eval(P.c_l, batch);
+    if (ao > a_elems || bo > b_elems || co > c_all_elems) return LC_ERR_INVALID_ARG;
+    w.A = a_all + ao; w.a_elems = a_elems - ao;
+    w.B = b_all + bo; w.b_elems = b_elems - bo;
+    float* c = c_all + co;
+    const int64_t c_elems = c_all_elems - co;
+    for (uint32_t wave = 0; wave < W; ++wave) {
+      std::fill(acc.begin(), acc.end(), 0.f);
+      for (uint32_t kt = wave; kt < P.k_tiles; kt += W) {
+        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), 64u);
+        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, 64u);
+        if (!w.ok) return LC_ERR_INVALID_ARG;
+        for (uint32_t kk = 0; kk < kGemmBK / 16; ++kk)
+          for (uint32_t i = 0; i < TM / 32; ++i)
+            for (uint32_t j = 0; j < (TN + 31) / 32; ++j)
+              if (!product.run(w, lds.data(), a_kind, TM, 32u * i, lds.data() + TM * 128u, b_kind, TN, 32u * j, kk, acc.data())) return LC_ERR_INVALID_ARG;
+      }
+      std::vector<char> written(units, 0);
+      for (uint32_t lane = 0; lane < 64; ++lane)
+        for (uint32_t i = 0; i < TM / 32; ++i)
+          for (uint32_t j = 0; j < (TN + 31) / 32; ++j)
+            for (uint32_t g = 0; g < 4; ++g) {
+              const uint32_t row = 32u * i + mfma_c_row(lane, 4u * g), col = 32u * j + mfma_c_col(lane), unit = gemm_sum_unit(TM, TN, row / 4u, col);
+              if (col >= TN) continue;
+              if (row % 4u != 0 || unit >= units || written[unit]) return LC_ERR_INVALID_ARG;
+              written[unit] = 1;
+              for (uint32_t v = 0; v < 4; ++v) parts[((size_t)wave * units + unit) * 4u + v] = acc[(size_t)(row + v) * TN + col];
+            }
+    }
+    std::vector<char> added(units, 0);
+    for (uint32_t u = 0; u < units; ++u) {
+      uint32_t m4, nl;
+      gemm_sum_of(TM, TN, P.c_vec, u, &m4, &nl);
+      const uint32_t unit = gemm_sum_unit(TM, TN, m4, nl), m = m0 + 4u * m4, n = n0 + nl;
+      if (m4 >= TM / 4u || nl >= TN || unit >= units || added[unit]) return LC_ERR_INVALID_ARG;
+      added[unit] = 1;
+      for (uint32_t v = 0; v < 4; ++v) {
+        if (n >= P.N || m + v >= P.M) continue;
+        const int64_t off = (int64_t)gemm_mode_eval(P.c_m, m + v) + gemm_mode_eval(P.c_n, n);
+        if (off >= c_elems) return LC_ERR_INVALID_ARG;
+        // one 16-byte access per unit: the four rows are there and follow each other from an aligned place
+        if (P.c_vec && (m + 4u > P.M || off != (int64_t)gemm_mode_eval(P.c_m, m) + gemm_mode_eval(P.c_n, n) + v || (off - v) % 4 != 0)) return LC_ERR_INVALID_ARG;
+        float sum = 0.f;
+        for (uint32_t wave = 0; wave < W; ++wave) sum += parts[((size_t)wave * units + unit) * 4u + v];
+        c[off] += sum;
+      }
+    }
+  }
+  return LC_OK;
+}
+
 }  // namespace
 
 lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int64_t a_elems, const uint16_t* b, int64_t b_elems, float* c,
@@ -157,13 +265,14 @@ lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int
   const GemmParams& P = plan.params;
   Walker w{plan, P, plan.exchanged ? b : a, plan.exchanged ? a : b, c, plan.exchanged ? b_elems : a_elems,
            plan.exchanged ? a_elems : b_elems, c_elems};
+  FragmentProduct product;
+  mfma_fragment_layout(0, &product.tv_a);
+  mfma_fragment_layout(1, &product.tv_b);
+  mfma_fragment_layout(2, &product.tv_c);
+  product.to_float = plan.ab_dtype == LC_BF16 ? bf16_to_float : f16_to_float;
+  if (plan.split_waves > 0) return replay_split(plan, w, product, c, c_elems);
   const uint32_t BM = (uint32_t)plan.tile_m, BN = (uint32_t)plan.tile_n, WMB = BM / 64, WNB = BN / 64;
   if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u) || (P.a_direct && BM != BN)) return LC_ERR_INVALID_ARG;
-  Layout tv_a, tv_b, tv_c;
-  mfma_fragment_layout(0, &tv_a);
-  mfma_fragment_layout(1, &tv_b);
-  mfma_fragment_layout(2, &tv_c);
-  auto to_float = plan.ab_dtype == LC_BF16 ? bf16_to_float : f16_to_float;
   std::vector<unsigned char> lds((BM + BN) * 128u);   // one k tile of A and B is enough for a sequential walk
   std::vector<float> acc((size_t)BM * BN);
   std::vector<char> covered((size_t)P.tiles_m * P.tiles_n, 0);
@@ -201,30 +310,10 @@ lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int
         const uint32_t wm = wave & 1u, wn = wave >> 1;
         for (uint32_t kk = 0; kk < kGemmBK / 16; ++kk)
           for (uint32_t i = 0; i < WMB; ++i)
-            for (uint32_t j = 0; j < WNB; ++j) {
-              // gather the two 32 x 16 fragments from the lanes' LDS reads, through the thread-value layouts
-              float fa[32][16], fb[32][16];
-              uint16_t va[64][8], vb[64][8];
-              w.fragment(lds.data(), a_kind, BM, wm * WMB * 32u + 32u * i, kk, va);
-              w.fragment(lds.data() + BM * 128u, b_kind, BN, wn * WNB * 32u + 32u * j, kk, vb);
-              if (!w.ok) return LC_ERR_INVALID_ARG;
-              for (uint32_t lane = 0; lane < 64; ++lane)
-                for (uint32_t v = 0; v < 8; ++v) {
-                  const int64_t ca = tv_a((int64_t)lane + 64 * v), cb = tv_b((int64_t)lane + 64 * v);   // row + 32 k
-                  fa[ca % 32][ca / 32] = to_float(va[lane][v]);
-                  fb[cb % 32][cb / 32] = to_float(vb[lane][v]);
-                }
-              // D = A B^T + D, then back to the lanes' accumulators through the C fragment layout
-              for (uint32_t lane = 0; lane < 64; ++lane)
-                for (uint32_t v = 0; v < 16; ++v) {
-                  const int64_t cc = tv_c((int64_t)lane + 64 * v);   // m + 32 n
-                  const uint32_t r = (uint32_t)(cc % 32), col = (uint32_t)(cc / 32);
-                  if (r != mfma_c_row(lane, v) || col != mfma_c_col(lane)) return LC_ERR_INVALID_ARG;
-                  float s = 0.f;
-                  for (uint32_t k = 0; k < 16; ++k) s += fa[r][k] * fb[col][k];
-                  acc[(size_t)(wm * WMB * 32u + 32u * i + r) * BN + (wn * WNB * 32u + 32u * j + col)] += s;
-                }
-            }
+            for (uint32_t j = 0; j < WNB; ++j)
+              if (!product.run(w, lds.data(), a_kind, BM, wm * WMB * 32u + 32u * i, lds.data() + BM * 128u, b_kind, BN, wn * WNB * 32u + 32u * j, kk,
+                               acc.data()))
+                return LC_ERR_INVALID_ARG;
       }
     }
     // epilogue, lane by lane

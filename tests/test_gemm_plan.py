@@ -250,3 +250,43 @@ def test_lds_arrangements_are_xor_layouts_without_bank_conflicts(oracle):
                 for half in (0, 32):
                     got = banks([(addr(2, rows, half + l, row_base, k_base), 8) for l in range(32)])
                     assert sorted(got) == list(range(64)), (rows, row_base, k_base, half)
+
+
+# (name, sizes): one short k tile; fewer k tiles than wavefronts; more than the rings hold; ragged rows, columns and batches
+SPLIT_CASES = [("tn", (33, 13, 8)), ("tn", (200, 16, 584)), ("nt", (40, 72, 648)), ("nt", (8, 8, 8)), ("nn_rowmajor_c", (72, 141, 640)),
+               ("gett", (192, 100, 48)), ("strided_batch", (136, 72, 40, 3)), ("shared_b", (64, 40, 24, 4))]
+
+
+@pytest.mark.parametrize("tile", [3216, 32, 3264, 6432, 64])
+@pytest.mark.parametrize("name,sizes", SPLIT_CASES)
+def test_walk_split_kernel(oracle, name, sizes, tile):
+    # workgroups whose wavefronts share out the k tiles of one small tile of C; tiles of 16 columns need at most 16
+    w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values="ints")
+    if tile == 3216 and w.N > 16:
+        pytest.skip("more than 16 columns")
+    shape = {3216: "32x16", 3264: "32x64", 6432: "64x32"}.get(tile, "%dx%d" % (tile, tile))
+    _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, [] if tile == 3216 and name != "tn" else ["tile=%sx64 split_waves=" % shape])
+
+
+def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile():
+    def tile(M, N, K, L=1):
+        d = lc.GemmPlan("(%d,%d,%d):(%d,1,%d)" % (M, K, L, K, M * K), "(%d,%d,%d):(%d,1,%d)" % (N, K, L, K, N * K), "(%d,%d,%d):(1,%d,%d)" % (M, N, L, M, M * N)).describe()
+        return d.split("tile=")[1].split()[0], "split_waves" in d
+    assert tile(8192, 16, 64) == ("32x16x64", True) and tile(8192, 17, 64) == ("32x32x64", True)
+    assert tile(512, 512, 512) == ("32x32x64", True) and tile(513, 512, 512) == ("64x32x64", True) and tile(512, 513, 512) == ("32x64x64", True)
+    assert tile(1024, 1024, 64) == ("64x64x64", True) and tile(1024, 1025, 64)[1] is False
+    assert tile(64, 64, 64, 64) == ("32x32x64", True) and tile(64, 64, 64, 257)[1] is False
+
+
+def test_narrow_k_major_tiles_are_free_of_bank_conflicts():
+    # k-major tiles of 32 and 64 rows: slots are a permutation of the tile, and the lanes of a transpose-load pass (32 lanes,
+    # 8 bytes each) touch each of the 64 banks once
+    from paper_2603_02298_amd.binding import lib
+    addr = lib().lc_debug_gemm_lds_address
+    for rows in (32, 64):
+        assert sorted(addr(1, rows, 0, k, 8 * g) // 16 for k in range(64) for g in range(rows // 8)) == list(range(8 * rows))
+        for row_base in range(0, rows, 32):
+            for k_base in range(0, 64, 4):
+                for half in (0, 32):
+                    banks = [addr(2, rows, half + l, row_base, k_base) // 4 % 64 + d for l in range(32) for d in range(2)]
+                    assert sorted(banks) == list(range(64)), (rows, row_base, k_base, half)

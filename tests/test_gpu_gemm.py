@@ -224,3 +224,20 @@ def test_gemm_full_size_sampled(oracle, name):
         else:
             bound = oracle.gemm_at(np.abs(a64), w.a_layout, np.abs(b64), w.b_layout, np.abs(c64), w.c_layout, ms, ns)
             assert (np.abs(have - want) <= K * 2.0 ** -23 * bound).all(), desc
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [3216, 32, 3264, 6432, 64])
+def test_gemm_split_kernel(oracle, tile, values):
+    # the wavefronts of a workgroup share out the k tiles of one small tile of C: one short k tile, fewer k tiles than
+    # wavefronts, more than the rings hold, ragged rows and columns, batches, both kinds of operand, C with and without vectors
+    cases = [("tn", (33, 13, 8)), ("tn", (200, 16, 584)), ("tn", (1, 3, 1608)), ("nt", (40, 72, 648)), ("nn_rowmajor_c", (72, 141, 640)),
+             ("gett", (192, 100, 48)), ("strided_batch", (136, 72, 104, 3)), ("shared_b", (64, 40, 24, 4))]
+    for name, sizes in cases:
+        w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values=values)
+        if tile == 3216 and w.N > 16:
+            continue
+        for env in ({}, {"LC_TUNE_GEMM_CVEC": 0}):
+            assert "split_waves=" in _parity(oracle, w, dict(env, LC_TUNE_GEMM_TILE=tile))
+    w = W.gemm_workload("tn", 96, 16, 200, ab_dtype="f16", values=values)
+    assert "split_waves=" in _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
