@@ -159,23 +159,20 @@ template <int TM, int TN, int LANES, bool C_VEC>
 struct SumUnits {
   static constexpr int UNITS = TM * TN / 4, N = (UNITS + LANES - 1) / LANES;
   f32x4 old[N];
-  uint32_t rows[N], unit[N], off[N][C_VEC ? 1 : 4];   // rows of the unit that exist (0: none)
+  uint32_t off[N][C_VEC ? 1 : 4];
   __device__ __forceinline__ void request(const GemmParams& P, const float* C, uint32_t m0, uint32_t n0, uint32_t tid) {
     static_for<N>([&](auto j) {
       uint32_t m4, n;
       gemm_sum_of(TM, TN, C_VEC, tid + (uint32_t)j * LANES, &m4, &n);
-      unit[j] = gemm_sum_unit(TM, TN, m4, n);
-      const uint32_t m = m0 + 4u * m4, left = P.M - (m < P.M ? m : P.M);
-      const bool in = (UNITS % LANES == 0 || tid + (uint32_t)j * LANES < (uint32_t)UNITS) && n0 + n < P.N;
-      rows[j] = in ? (left < 4u ? left : 4u) : 0u;
+      const uint32_t m = m0 + 4u * m4;
       // units that do not exist read the last ones that do: no branch around the loads
       const uint32_t n_off = gemm_mode_eval(P.c_n, n0 + n < P.N ? n0 + n : P.N - 1u);
       if constexpr (C_VEC) {
-        off[j][0] = gemm_mode_eval(P.c_m, left > 0u ? m : P.M - 4u) + n_off;
+        off[j][0] = gemm_mode_eval(P.c_m, m < P.M ? m : P.M - 4u) + n_off;
         old[j] = *reinterpret_cast<const f32x4*>(C + off[j][0]);
       } else {
         static_for<4>([&](auto v) {
-          off[j][(int)v] = gemm_mode_eval(P.c_m, (uint32_t)v < left ? m + (uint32_t)v : P.M - 1u) + n_off;
+          off[j][(int)v] = gemm_mode_eval(P.c_m, m + (uint32_t)v < P.M ? m + (uint32_t)v : P.M - 1u) + n_off;
           old[j][(int)v] = C[off[j][(int)v]];
         });
       }
@@ -184,15 +181,22 @@ struct SumUnits {
     __builtin_amdgcn_sched_barrier(0);   // the operands' loads come after these
   }
   template <typename F>
-  __device__ __forceinline__ void add(float* C, F&& sum_of) {
+  __device__ __forceinline__ void add(const GemmParams& P, float* C, uint32_t m0, uint32_t n0, uint32_t tid, F&& sum_of) {
+    static_for<N>([&](auto j) {   // every sum first: a wait behind each would make a chain of LDS round trips
+      uint32_t m4, n;
+      gemm_sum_of(TM, TN, C_VEC, (tid + (uint32_t)j * LANES) % UNITS, &m4, &n);
+      old[j] += sum_of(gemm_sum_unit(TM, TN, m4, n));
+    });
     static_for<N>([&](auto j) {
-      if (rows[j] == 0u) return;
-      const f32x4 sum = sum_of(unit[j]) + old[j];
+      uint32_t m4, n;
+      gemm_sum_of(TM, TN, C_VEC, tid + (uint32_t)j * LANES, &m4, &n);
+      const uint32_t m = m0 + 4u * m4;
+      const bool in = (UNITS % LANES == 0 || tid + (uint32_t)j * LANES < (uint32_t)UNITS) && n0 + n < P.N;
       if constexpr (C_VEC) {
-        *reinterpret_cast<f32x4*>(C + off[j][0]) = sum;
+        if (in && m < P.M) *reinterpret_cast<f32x4*>(C + off[j][0]) = old[j];
       } else {
         static_for<4>([&](auto v) {
-          if ((uint32_t)v < rows[j]) C[off[j][(int)v]] = sum[(int)v];
+          if (in && m + (uint32_t)v < P.M) C[off[j][(int)v]] = old[j][(int)v];
         });
       }
     });

@@ -15,6 +15,8 @@ hipError_t launch_gemm_f16_256(const lc_gemm_plan& plan, const uint16_t* a, cons
 hipError_t launch_gemm_f16_128(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_bf16_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 
 static bool gemm_hip_failed(hipError_t e, const char* what) {
   if (e == hipSuccess) return false;
@@ -40,6 +42,8 @@ lc_status_t execute_gemm_plan(const lc_gemm_plan& plan, const void* a, const voi
   const unsigned tiles_in_lds = plan.params.a_direct ? 5u : 4u;
   if (plan.split_waves > 0)   // (the launcher checks the rings against LDS)
     pre = bf16 ? launch_gemm_bf16_split(plan, ka, kb, kc, s) : launch_gemm_f16_split(plan, ka, kb, kc, s);
+  else if (plan.stages > 0)
+    pre = bf16 ? launch_gemm_bf16_stream(plan, ka, kb, kc, s) : launch_gemm_f16_stream(plan, ka, kb, kc, s);
   else if (plan.tile_m == 256 && plan.tile_n == 256 && plan.lds_bytes == tiles_in_lds * 256u * 128u)
     pre = bf16 ? launch_gemm_bf16_256(plan, ka, kb, kc, s) : launch_gemm_f16_256(plan, ka, kb, kc, s);
   else if (plan.tile_m == 128 && plan.tile_n == 128 && plan.lds_bytes == tiles_in_lds * 128u * 128u)

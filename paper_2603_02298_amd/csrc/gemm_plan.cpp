@@ -179,18 +179,50 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   // Measured on MI355X (bf16, start = 128 x 128 tiles): 512^3 11.1 us; 32 x 32 tiles (256 of them) 4.3, 32 x 64 4.7, 64 x 64
   // 6.2.  16 x 8192 x 8192 78 us; 32 x 32 27.6, 64 x 64 36.  64 x 8192 x 8192 92 us; 32 x 32 (512 tiles) 42.8, 64 x 32 (256) 33.4.
   // 1024^3 17.6 us; 32 x 64 (512 tiles) 10.8, 64 x 64 (256) 8.3.
-  // 256 x 256 when that still gives every CU a tile, else 128 x 128.
   auto tiles_of = [&](int64_t tm, int64_t tn) { return (kM + tm - 1) / tm * ((kN + tn - 1) / tn) * Lb; };
-  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);   // 128, 256; split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432
+  // LC_TUNE_GEMM_TILE: 256, 128, 12864 (128 x 64), 64128; split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
+  // stream kernel's 64 x 64
+  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
   const bool thin = kN <= 16 && P.b_load == kLoadKVec;
-  if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
-  else if (direct && (t_env ? t_env == 3216 && thin : thin && tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
-  else if (direct && (t_env ? t_env == 32 : tiles_of(32, 32) <= 256)) take(32, 32, 8, 2);
-  else if (direct && (t_env ? t_env == 3264 : kM <= kN && tiles_of(32, 64) <= 256)) take(32, 64, 4, 3);
-  else if (direct && (t_env ? t_env == 6432 : kM > kN && tiles_of(64, 32) <= 256)) take(64, 32, 4, 3);
-  else if (direct && (t_env ? t_env == 64 : tiles_of(64, 64) <= 256)) take(64, 64, 4, 2);
-  else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);
+  const bool free_choice = t_env == 0;
+  if (direct && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
+  else if (direct && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, 2);
+  else if (direct && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, 3);
+  else if (direct && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, 3);
+  else if (direct && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, 2);
+  else if (direct && t_env != 256) {
+    // Larger problems.  The CU that is given the most tiles decides, so a tile's cost is how many of them that CU takes times
+    // its area, times what its k loop costs per product against the 128 x 128 stream kernel's: smaller tiles read more of LDS
+    // per product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1, 1.2, 1.3 and 64 x 64: 1.3,
+    // 1.4, 1.65 below K = 1024, below 2048 and from there on); a lone workgroup on a CU has nobody to cover its waits (1.25,
+    // 1.25, 1.5); the 256 x 256 kernel reads least, but its short k loops wait (1.0 below K = 2048, 0.9 below 3000, 0.8 from
+    // there on), and with fewer tiles than CUs it runs at a higher clock (down to 0.7).
+    // Measured on MI355X (bf16; 128 x 128, 128 x 64, 64 x 64 stream, 256 x 256, in us): 2048^3 27.4, 26.1, 29.2, 55;
+    // 1536^2 x 4096 42.6, 39.4, 35.2, 87; 16 x (1000 x 1504 x 776) 83, 97, 110, 98; 128 x 100352 x 576 (convolution) 34.1,
+    // 32.6, 34.2, 57.5; 4 x 1024^3 18.2, 16.5, 17.8, 39.6; 4096^2 x 1024 49, 56, 62, 52; 4096^3 149.5, 187, 232, 129;
+    // 5000^2 x 3000 240, 296, 347, 195; 6144 x 3072 x 2048 100, 115, 139, 132; 3000^3 96, 95, 120, 77.5;
+    // 2200^2 x 8192 113, 119, 146, 156; 4096 x 2048 x 4096 71, 96, 112, 89; 1100^2 x 8192 77, 67, 60, 145.
+    struct Choice { int tm, tn; double per_product; };
+    const double half = K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3, quarter = K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65, lone = K < 2048 ? 1.25 : 1.5;
+    const Choice choices[] = {{128, 128, 1.0}, {128, 64, half}, {64, 128, half}, {64, 64, quarter}};
+    auto cost = [&](const Choice& c, bool lone_waits) {
+      const int64_t per_cu = (tiles_of(c.tm, c.tn) + 255) / 256;
+      return (double)per_cu * c.tm * c.tn * c.per_product * (lone_waits && per_cu == 1 ? lone : 1.0);
+    };
+    const Choice* best = nullptr;
+    for (const Choice& c : choices)
+      if (!best || cost(c, true) < cost(*best, true)) best = &c;
+    const Choice big = {256, 256, (K < 2048 ? 1.0 : K < 3000 ? 0.9 : 0.8) * std::min(1.0, 0.7 + 0.3 * (double)tiles_of(256, 256) / 256.0)};
+    if (free_choice && cost(big, false) <= cost(*best, true)) take(256, 256, 0, 0);
+    else if (t_env == 128) take(128, 128, 0, 2);
+    else if (t_env == 12864) take(128, 64, 0, 2);
+    else if (t_env == 64128) take(64, 128, 0, 2);
+    else if (t_env == 6464) take(64, 64, 0, 2);
+    else take(best->tm, best->tn, 0, 2);
+  }
+  else if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
+  else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);   // through registers: 256 x 256 when that gives every CU a tile
   else take(128, 128, 0, 0);
   P.tiles_m = (uint32_t)((kM + plan.tile_m - 1) / plan.tile_m);
   P.tiles_n = (uint32_t)((kN + plan.tile_n - 1) / plan.tile_n);
@@ -198,8 +230,8 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   if ((uint64_t)P.tiles_m * P.tiles_n >= (uint64_t(1) << 31)) return LC_ERR_TOO_LARGE;
   P.group_m = (uint32_t)std::max(1, env_int("LC_TUNE_GEMM_GROUP_M", 8));
   // two stages of (rows x 128 bytes) for A and B; direct loads: a ring of five operand tiles
-  // (split kernel: a ring per wavefront)
-  plan.lds_bytes = plan.split_waves ? (unsigned)(plan.split_waves * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)plan.tile_m * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
+  // (split and stream kernels: rings of pairs of tiles, one per wavefront or one for all)
+  plan.lds_bytes = plan.stages ? (unsigned)(std::max(1, plan.split_waves) * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)plan.tile_m * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
   plan.a_text = mode_text(a_r) + " x " + mode_text(a_k);
   plan.b_text = mode_text(b_r) + " x " + mode_text(b_k);
   plan.c_text = mode_text(c_m) + " x " + mode_text(c_n);
@@ -220,6 +252,7 @@ std::string describe(const lc_gemm_plan& plan) {
   if (plan.L != 1 || plan.a_text.find(" x ", plan.a_text.find(" x ") + 1) != std::string::npos) s += " L=" + std::to_string(plan.L);
   s += " exchanged=" + std::to_string((int)plan.exchanged);
   s += " tile=" + std::to_string(plan.tile_m) + "x" + std::to_string(plan.tile_n) + "x" + std::to_string(kGemmBK);
+  if (plan.stages && !plan.split_waves) s += " stream stages=" + std::to_string(plan.stages);
   if (plan.split_waves) s += " split_waves=" + std::to_string(plan.split_waves) + " stages=" + std::to_string(plan.stages);
   s += " tiles=" + std::to_string(plan.params.tiles_m) + "x" + std::to_string(plan.params.tiles_n) + " k_tiles=" + std::to_string(plan.params.k_tiles);
   s += " group_m=" + std::to_string(plan.params.group_m);

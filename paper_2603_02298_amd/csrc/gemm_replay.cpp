@@ -37,11 +37,10 @@ struct Walker {
   bool ok = true;
 
   // loads one operand tile of k tile kt into the LDS model, lane by lane
-  // lanes: how many load a tile together (a workgroup, or one wavefront of the split kernel, whose lanes past the extent
-  // are answered with zeros instead of taking the last row)
+  // lanes: how many load a tile together (a workgroup, or one wavefront of the split kernel); zero_rows: lanes past the
+  // extent are answered with zeros instead of taking the last row
   void stage(const uint16_t* base, int64_t elems, const GemmMode& rmode, const GemmMode& kmode, int32_t load, uint32_t row0, uint32_t extent,
-             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock) {
-    const bool zero_rows = lanes == 64u;
+             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock, bool zero_rows = false) {
     if (load == kLoadKDirect) {
       // every lane's 16 bytes land at byte 16 * lane of the 1 KiB its wavefront's instruction i fills
       const uint32_t rows_per_lane = BR * 8u / lanes;
@@ -185,12 +184,15 @@ struct FragmentProduct {
 };
 
 // The split kernel: every wavefront's k tiles into a partial tile of its own, the partials into units of LDS, the units
-// summed in the order of the wavefronts and added to C.
-lc_status_t replay_split(const lc_gemm_plan& plan, Walker& w, FragmentProduct& product, float* c_all, int64_t c_all_elems) {
+// summed in the order of the wavefronts and added to C.  The stream kernel: one tile, loaded by four wavefronts that hold
+// a quarter of its sums each, through the same units.
+lc_status_t replay_sums(const lc_gemm_plan& plan, Walker& w, FragmentProduct& product, float* c_all, int64_t c_all_elems) {
   const GemmParams& P = w.P;
-  const uint32_t TM = (uint32_t)plan.tile_m, TN = (uint32_t)plan.tile_n, W = (uint32_t)plan.split_waves, units = TM * TN / 4u;
+  const uint32_t TM = (uint32_t)plan.tile_m, TN = (uint32_t)plan.tile_n, units = TM * TN / 4u;
+  const bool split = plan.split_waves > 0;
+  const uint32_t W = split ? (uint32_t)plan.split_waves : 1u, lanes = split ? 64u : (uint32_t)kBlock, QM = split ? TM : TM / 2u, QN = split ? TN : TN / 2u;
   const int32_t a_kind = gemm_effective_load(P.a_load, P.a_direct), b_kind = gemm_effective_load(P.b_load, P.b_direct);
-  if (plan.stages < 1 || plan.lds_bytes != W * (unsigned)plan.stages * (TM + TN) * 128u || !P.a_direct || !P.b_direct) return LC_ERR_INVALID_ARG;
+  if (plan.stages < 1 || TM * TN * 4u > plan.lds_bytes || plan.lds_bytes != W * (unsigned)plan.stages * (TM + TN) * 128u || !P.a_direct || !P.b_direct) return LC_ERR_INVALID_ARG;
   const uint32_t per_batch = P.tiles_m * P.tiles_n, n_tiles = per_batch * P.L;
   std::vector<unsigned char> lds((TM + TN) * 128u);
   std::vector<float> acc((size_t)TM * TN), parts((size_t)W * units * 4u);
@@ -214,8 +216,8 @@ lc_status_t replay_split(const lc_gemm_plan& plan, Walker& w, FragmentProduct& p
     for (uint32_t wave = 0; wave < W; ++wave) {
       std::fill(acc.begin(), acc.end(), 0.f);
       for (uint32_t kt = wave; kt < P.k_tiles; kt += W) {
-        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), 64u);
-        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, 64u);
+        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), lanes, true);
+        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, lanes, true);
         if (!w.ok) return LC_ERR_INVALID_ARG;
         for (uint32_t kk = 0; kk < kGemmBK / 16; ++kk)
           for (uint32_t i = 0; i < TM / 32; ++i)
@@ -223,11 +225,12 @@ lc_status_t replay_split(const lc_gemm_plan& plan, Walker& w, FragmentProduct& p
               if (!product.run(w, lds.data(), a_kind, TM, 32u * i, lds.data() + TM * 128u, b_kind, TN, 32u * j, kk, acc.data())) return LC_ERR_INVALID_ARG;
       }
       std::vector<char> written(units, 0);
-      for (uint32_t lane = 0; lane < 64; ++lane)
-        for (uint32_t i = 0; i < TM / 32; ++i)
-          for (uint32_t j = 0; j < (TN + 31) / 32; ++j)
+      for (uint32_t tid = 0; tid < lanes; ++tid)
+        for (uint32_t i = 0; i < QM / 32; ++i)
+          for (uint32_t j = 0; j < (QN + 31) / 32; ++j)
             for (uint32_t g = 0; g < 4; ++g) {
-              const uint32_t row = 32u * i + mfma_c_row(lane, 4u * g), col = 32u * j + mfma_c_col(lane), unit = gemm_sum_unit(TM, TN, row / 4u, col);
+              const uint32_t lane = tid & 63u, wm = (tid >> 6) & 1u, wn = tid >> 7;
+              const uint32_t row = wm * QM + 32u * i + mfma_c_row(lane, 4u * g), col = wn * QN + 32u * j + mfma_c_col(lane), unit = gemm_sum_unit(TM, TN, row / 4u, col);
               if (col >= TN) continue;
               if (row % 4u != 0 || unit >= units || written[unit]) return LC_ERR_INVALID_ARG;
               written[unit] = 1;
@@ -270,9 +273,9 @@ lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int
   mfma_fragment_layout(1, &product.tv_b);
   mfma_fragment_layout(2, &product.tv_c);
   product.to_float = plan.ab_dtype == LC_BF16 ? bf16_to_float : f16_to_float;
-  if (plan.split_waves > 0) return replay_split(plan, w, product, c, c_elems);
+  if (plan.stages > 0) return replay_sums(plan, w, product, c, c_elems);
   const uint32_t BM = (uint32_t)plan.tile_m, BN = (uint32_t)plan.tile_n, WMB = BM / 64, WNB = BN / 64;
-  if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u) || (P.a_direct && BM != BN)) return LC_ERR_INVALID_ARG;
+  if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u) || (P.a_direct && (BM != 256 || BN != 256))) return LC_ERR_INVALID_ARG;
   std::vector<unsigned char> lds((BM + BN) * 128u);   // one k tile of A and B is enough for a sequential walk
   std::vector<float> acc((size_t)BM * BN);
   std::vector<char> covered((size_t)P.tiles_m * P.tiles_n, 0);

@@ -66,14 +66,16 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
 
   const uint32_t ring = wave * RING;
   const uint32_t n_mine = P.k_tiles > wave ? (P.k_tiles - wave + (WAVES - 1u)) / WAVES : 0u;
-  auto request = [&](uint32_t t, uint32_t at) {   // this wavefront's t-th k tile, to the stage at LDS offset `at`
-    const uint32_t kt = wave + t * WAVES;
+  uint32_t next = n_mine > 0u ? order % n_mine : 0u;
+  auto request = [&](uint32_t at) {   // this wavefront's next k tile, to the stage at LDS offset `at`
+    const uint32_t kt = wave + next * WAVES;
+    next = next + 1u == n_mine ? 0u : next + 1u;
     const bool tail = kt + 1u == P.k_tiles;
     la.fetch(2u * gemm_mode_eval(P.a_k, kt * kGemmBK), at, tail);
     lb.fetch(2u * gemm_mode_eval(P.b_k, kt * kGemmBK), at + A_BYTES, tail);
   };
   static_for<STAGES>([&](auto s) {
-    if ((uint32_t)s < n_mine) request((uint32_t)s, ring + (uint32_t)s * STAGE);
+    if ((uint32_t)s < n_mine) request(ring + (uint32_t)s * STAGE);
   });
   uint32_t at = ring;
   for (uint32_t t = 0; t < n_mine; ++t) {
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
     });
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the fragments are in registers, the stage may be filled again
     asm volatile("" ::: "memory");
-    if (t + STAGES < n_mine) request(t + STAGES, at);
+    if (t + STAGES < n_mine) request(at);
     static_for<KSTEPS>([&](auto kk) {
       static_for<FM>([&](auto i) {
         static_for<FN>([&](auto j) { acc[i][j] = mfma_32x32x16<BF16>(af[i][kk], bf[j][kk], acc[i][j]); });
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
     });
   });
   __syncthreads();
-  units.add(C, [&](uint32_t unit) {   // (a wavefront without a k tile left zeros)
+  units.add(P, C, m0, n0, tid, [&](uint32_t unit) {   // (a wavefront without a k tile left zeros)
     f32x4 part[WAVES];
     static_for<WAVES>([&](auto w) { part[w] = *reinterpret_cast<const f32x4*>(lds + (uint32_t)w * RING + unit * 16u); });
     f32x4 sum = part[0];

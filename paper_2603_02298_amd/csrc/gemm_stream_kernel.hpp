@@ -1,0 +1,161 @@
+// Device code of the stream GEMM: C(m,n) += A(m,k) * B(n,k) (Sec. 2.6.2 of "CuTe Layout Representation and Algebra") for
+// operands that go straight into LDS, on problems with tiles for every CU but a k loop too short, or sides too small, for
+// the 256 x 256 kernel.
+//
+// Four wavefronts own a BM x BN tile, wavefront (wm, wn) a quarter of it.  LDS holds STAGES pairs of operand tiles; one
+// barrier per k tile, after which the tile before it is overwritten by the one STAGES - 1 ahead.  Two or more workgroups
+// share a CU: one's start, its C update and its waits at the barrier lie under the others' products.  The old values of C
+// are asked for before the k loop, the sums pass through LDS and C is updated in whole runs.
+// What bounds it: for a short k loop C's way from and to HBM (128 x 100352 x 64: 5.4-6.3 TB/s), for a longer one LDS (a 64 x 64
+// quarter per wavefront reads 128 bytes per clock and CU at the matrix cores' full rate, all that LDS gives).
+// Measured on MI355X (bf16, whole ring kernel of 128 x 128 tiles -> this kernel's 128 x 128): 16 x (1000 x 1504 x 776) 100 -> 83 us,
+// a 3 x 3 convolution of 128 x 100352 x 576 39 -> 34 us (128 x 64 tiles: 32.6), 4096^3 158 -> 149 us.  Three stages and more
+// (fewer workgroups per CU) measured slower wherever there are more tiles than CUs.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
+#include "gemm_device.hpp"
+#include "gemm_plan.hpp"
+#include "kernarg.hpp"
+
+namespace lc {
+
+template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD, bool C_VEC>
+__global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) void gemm_stream_kernel(GemmParams P, const uint16_t* __restrict__ A,
+                                                                                                   const uint16_t* __restrict__ B, float* __restrict__ C) {
+  constexpr int FM = BM / 64, FN = BN / 64, KSTEPS = kGemmBK / 16;
+  constexpr uint32_t A_BYTES = BM * 128u, STAGE = (BM + BN) * 128u;
+  constexpr int R = (BM + BN) / 32;   // load instructions per wavefront and k tile
+  static_assert(STAGES >= 2 && BM * BN * 4 <= STAGES * (BM + BN) * 128, "the sums of the tile fit the ring");
+  static_assert((STAGES - 2) * R < 64, "vmcnt has six bits");
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  touch_kernel_arguments<(int)sizeof(GemmParams) + 24>();
+
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t wm = wave & 1u, wn = wave >> 1;
+  // one order over the tiles of all batch entries: an XCD (its own L2) takes a stretch of it, i.e. whole batch entries
+  // where there are several, so that no operand is fetched by more XCDs than it must be
+  const uint32_t per_batch = P.tiles_m * P.tiles_n;
+  const uint32_t order = gemm_tile_order_of_block(blockIdx.x, per_batch * P.L);
+  const uint32_t batch = order / per_batch;
+  uint32_t tm, tn;
+  gemm_tile_of_order(P, order - batch * per_batch, &tm, &tn);
+  const uint32_t m0 = tm * BM, n0 = tn * BN;
+  A += gemm_mode_eval(P.a_l, batch);
+  B += gemm_mode_eval(P.b_l, batch);
+  C += gemm_mode_eval(P.c_l, batch);
+
+  DirectTileLoader<BM, A_LOAD, 4> la;
+  DirectTileLoader<BN, B_LOAD, 4> lb;
+  SumUnits<BM, BN, kBlock, C_VEC> units;
+  // (element by element the old values' addresses would not leave the registers the products need: asked for at the end then)
+  if constexpr (C_VEC) units.request(P, C, m0, n0, tid);
+  la.init(A, P.a_r, P.a_k, m0, P.M, P.K, tid);
+  lb.init(B, P.b_r, P.b_k, n0, P.N, P.K, tid);
+
+  f32x16 acc[FM][FN];
+  static_for<FM>([&](auto i) {
+    static_for<FN>([&](auto j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    });
+  });
+
+  KTileOffset ka, kb;   // of the next k tile to request
+  ka.seek(P.a_k, 0u);
+  kb.seek(P.b_k, 0u);
+  uint32_t asked = 0;
+  const uint32_t a_at = wave * (BM * 32u), b_at = A_BYTES + wave * (BN * 32u);   // this wavefront's quarter of either tile
+  auto request = [&](uint32_t at) {   // the next k tile, to the stage at LDS offset `at`
+    const bool tail = asked + 1u == P.k_tiles;
+    la.fetch(ka.bytes, at + a_at, tail);
+    lb.fetch(kb.bytes, at + b_at, tail);
+    ++asked;
+    if (asked < P.k_tiles) {
+      ka.next(P.a_k, asked);
+      kb.next(P.b_k, asked);
+    }
+  };
+  static_for<STAGES - 1>([&](auto s) {
+    if ((uint32_t)s < P.k_tiles) request((uint32_t)s * STAGE);
+  });
+  uint32_t at = 0, free_at = (STAGES - 1) * STAGE;   // the stage being multiplied, the one before it
+  for (uint32_t t = 0; t < P.k_tiles; ++t) {
+    // k tile t has landed: all but the STAGES - 2 younger ones (towards the end there are fewer), for every wavefront past
+    // the barrier, which also has its fragments of k tile t - 1 in registers: that stage may be filled again
+    constexpr int N = (STAGES - 2) * R;
+    if (t + (STAGES - 1) <= P.k_tiles) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
+    else __builtin_amdgcn_s_waitcnt(0x0070);
+    lds_barrier();
+    if (asked < P.k_tiles) request(free_at);
+    static_for<KSTEPS>([&](auto kk) {
+      u32x4 af[FM], bf[FN];
+      static_for<FM>([&](auto i) { af[i] = direct_fragment<BM, A_LOAD>(lds + at, lane, wm * (BM / 2) + 32u * (uint32_t)i, kk); });
+      static_for<FN>([&](auto j) { bf[j] = direct_fragment<BN, B_LOAD>(lds + at + A_BYTES, lane, wn * (BN / 2) + 32u * (uint32_t)j, kk); });
+      static_for<FM>([&](auto i) {
+        static_for<FN>([&](auto j) { acc[i][j] = mfma_32x32x16<BF16>(af[i], bf[j], acc[i][j]); });
+      });
+    });
+    free_at = at;
+    at = at + STAGE == STAGES * STAGE ? 0u : at + STAGE;
+  }
+
+  if constexpr (!C_VEC) units.request(P, C, m0, n0, tid);
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+  lds_barrier();   // every fragment has been read: the sums take the ring's place
+  static_for<FM>([&](auto i) {
+    static_for<FN>([&](auto j) {
+      static_for<4>([&](auto g) {
+        const uint32_t m4 = wm * (BM / 8) + 8u * (uint32_t)i + mfma_c_row(lane, 4u * (uint32_t)g) / 4u;
+        const uint32_t n = wn * (BN / 2) + 32u * (uint32_t)j + mfma_c_col(lane);
+        f32x4 v;
+        static_for<4>([&](auto e) { v[(int)e] = acc[i][j][4 * g + e]; });
+        *reinterpret_cast<f32x4*>(lds + gemm_sum_unit(BM, BN, m4, n) * 16u) = v;
+      });
+    });
+  });
+  __syncthreads();
+  units.add(P, C, m0, n0, tid, [&](uint32_t unit) { return *reinterpret_cast<const f32x4*>(lds + unit * 16u); });
+}
+
+template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD, bool C_VEC>
+static inline hipError_t launch_stream_abc(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
+  if (plan.lds_bytes != (unsigned)(STAGES * (BM + BN) * 128)) return hipErrorInvalidValue;
+  static std::atomic<bool> raised{false};   // one flag per instantiation: the attribute belongs to the kernel function
+  if (plan.lds_bytes > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_stream_kernel<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, C_VEC>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    raised.store(true, std::memory_order_release);
+  }
+  const unsigned grid = plan.params.tiles_m * plan.params.tiles_n * plan.params.L;
+  hipLaunchKernelGGL((gemm_stream_kernel<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, C_VEC>), dim3(grid), dim3(kBlock), plan.lds_bytes, s, plan.params, a, b, c);
+  return hipSuccess;
+}
+template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD>
+static inline hipError_t launch_stream_ab(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
+  return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
+                           : launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
+}
+template <bool BF16, int BM, int BN, int STAGES>
+static inline hipError_t launch_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
+  const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
+  if (la == kLoadKDirect && lb == kLoadKDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadKDirect, kLoadKDirect>(plan, a, b, c, s);
+  if (la == kLoadKDirect && lb == kLoadRDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadKDirect, kLoadRDirect>(plan, a, b, c, s);
+  if (la == kLoadRDirect && lb == kLoadKDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadRDirect, kLoadKDirect>(plan, a, b, c, s);
+  if (la == kLoadRDirect && lb == kLoadRDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadRDirect, kLoadRDirect>(plan, a, b, c, s);
+  return hipErrorInvalidValue;
+}
+template <bool BF16>
+static inline hipError_t launch_stream_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
+  if (plan.stages != 2) return hipErrorInvalidValue;
+  if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, 2>(plan, a, b, c, s);
+  if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, 2>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, 2>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_stream<BF16, 64, 64, 2>(plan, a, b, c, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace lc

@@ -290,3 +290,13 @@ def test_narrow_k_major_tiles_are_free_of_bank_conflicts():
                 for half in (0, 32):
                     banks = [addr(2, rows, half + l, row_base, k_base) // 4 % 64 + d for l in range(32) for d in range(2)]
                     assert sorted(banks) == list(range(64)), (rows, row_base, k_base, half)
+
+
+@pytest.mark.parametrize("tile,shape", [(128, "128x128"), (12864, "128x64"), (64128, "64x128"), (6464, "64x64")])
+@pytest.mark.parametrize("name,sizes", [("tn", (200, 136, 8)), ("nt", (136, 264, 328)), ("nn_rowmajor_c", (72, 141, 200)), ("gett", (192, 100, 64)),
+                                        ("strided_batch", (136, 72, 40, 3)), ("shared_b", (128, 140, 136, 9))])
+def test_walk_stream_kernel(oracle, name, sizes, tile, shape):
+    # one to six k tiles through a ring of two pairs of tiles, ragged rows and columns, one order over the tiles of all batch
+    # entries, sums through LDS units
+    w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values="ints")
+    _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, ["tile=%sx64 stream" % shape])

@@ -241,3 +241,18 @@ def test_gemm_split_kernel(oracle, tile, values):
             assert "split_waves=" in _parity(oracle, w, dict(env, LC_TUNE_GEMM_TILE=tile))
     w = W.gemm_workload("tn", 96, 16, 200, ab_dtype="f16", values=values)
     assert "split_waves=" in _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [128, 12864, 64128, 6464])
+def test_gemm_stream_kernel(oracle, tile, values):
+    # one barrier per k tile over a ring of two pairs of tiles: one to six k tiles, ragged rows and columns, batches in one
+    # order with the tiles, both kinds of operand, C with and without vectors
+    cases = [("tn", (200, 136, 8)), ("tn", (1, 3, 72)), ("nt", (136, 264, 328)), ("nn_rowmajor_c", (72, 141, 200)), ("gett", (192, 100, 64)),
+             ("strided_batch", (136, 72, 40, 3)), ("shared_b", (128, 140, 136, 9))]
+    for name, sizes in cases:
+        w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values=values)
+        for env in ({}, {"LC_TUNE_GEMM_CVEC": 0}):
+            assert " stream " in _parity(oracle, w, dict(env, LC_TUNE_GEMM_TILE=tile))
+    w = W.conv_gemm_workload(2, 14, 12, 64, 136, 3, 3, "krsc", ab_dtype="f16", values=values)
+    assert " stream " in _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
