@@ -11,12 +11,13 @@ OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["layout.cpp", "algebra.cpp", "semimodule.cpp", "plan.cpp", "replay.cpp", "gemm_plan.cpp", "gemm_replay.cpp", "capi.cpp",
            "gemm_capi.cpp", "kernels.hip", "gemm_kernels.hip", "gemm_inst_bf16_256.hip", "gemm_inst_bf16_128.hip",
            "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip", "gemm_inst_bf16_split.hip", "gemm_inst_f16_split.hip",
-           "gemm_inst_bf16_stream.hip", "gemm_inst_f16_stream.hip"]
+           "gemm_inst_bf16_stream.hip", "gemm_inst_f16_stream.hip", "gemm_inst_bf16_split_any.hip", "gemm_inst_f16_split_any.hip",
+           "gemm_inst_bf16_stream_any.hip", "gemm_inst_f16_stream_any.hip"]
 HEADERS = ["layout.hpp", "algebra.hpp", "semimodule.hpp", "plan.hpp", "kernel_params.hpp", "gemm_plan.hpp", "gemm_params.hpp", "plan_cache.hpp", "kernarg.hpp"]
 # header -> the only sources that include it
 _TILE = ["gemm_inst_bf16_256.hip", "gemm_inst_bf16_128.hip", "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip"]
-_SPLIT = ["gemm_inst_bf16_split.hip", "gemm_inst_f16_split.hip"]
-_STREAM = ["gemm_inst_bf16_stream.hip", "gemm_inst_f16_stream.hip"]
+_SPLIT = ["gemm_inst_%s_split%s.hip" % (t, a) for t in ("bf16", "f16") for a in ("", "_any")]
+_STREAM = ["gemm_inst_%s_stream%s.hip" % (t, a) for t in ("bf16", "f16") for a in ("", "_any")]
 KERNEL_HEADERS = {"gemm_kernel.hpp": _TILE, "gemm_split_kernel.hpp": _SPLIT, "gemm_stream_kernel.hpp": _STREAM, "gemm_device.hpp": _TILE + _SPLIT + _STREAM}
 
 

@@ -143,11 +143,102 @@ struct DirectTileLoader {
   }
 };
 
+// The 8 elements of v moved down by n elements (0 .. 8), zeros from above.
+__device__ __forceinline__ u32x4 move_down_b16(u32x4 v, uint32_t n) {
+  uint64_t lo = (uint64_t)v[0] | ((uint64_t)v[1] << 32), hi = (uint64_t)v[2] | ((uint64_t)v[3] << 32);
+  if (n >= 4u) { lo = hi; hi = 0u; }
+  const uint32_t bits = 16u * (n & 3u);
+  lo = bits ? (lo >> bits) | (hi << (64u - bits)) : lo;
+  hi >>= bits;
+  if (n >= 8u) lo = hi = 0u;
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// The same tile brought in through registers, for operands whose vectors lie at any 2-byte-aligned address (kLoadKAny,
+// kLoadRAny): the units a lane loads and where they lie in LDS are those of the direct loads.
+template <int BR, int LOAD, int WAVES>
+struct AnyTileLoader {
+  static constexpr int R = BR / 8 / WAVES;
+  typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+  const unsigned char* base;
+  uint32_t off[R];       // bytes from the k tile's first k
+  uint32_t K, k_step, row0, extent, t;   // k_step: bytes from one k to the next
+  u32x4 regs[R];
+
+  // unit i of this lane: its row, and its k inside the k tile (along k: of its first element)
+  __device__ __forceinline__ void unit(uint32_t i, uint32_t* row, uint32_t* k) const {
+    if constexpr (LOAD == kLoadKAny) {
+      *row = gemm_direct_row(R, t, i);
+      *k = 8u * gemm_direct_kvec(*row, t);
+    } else {
+      gemm_rdirect_unit(BR, R, t, i, k, row);
+    }
+  }
+  __device__ __forceinline__ void init(const uint16_t* p, const GemmMode& rmode, const GemmMode& kmode, uint32_t first_row, uint32_t rows, uint32_t Ktot,
+                                       uint32_t lane) {
+    base = reinterpret_cast<const unsigned char*>(p);
+    K = Ktot;
+    k_step = 2u * kmode.lead_stride;
+    row0 = first_row;
+    extent = rows;
+    t = lane;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      uint32_t row, k, move;
+      unit((uint32_t)i, &row, &k);
+      if constexpr (LOAD == kLoadKAny) {
+        off[i] = 2u * (gemm_mode_eval(rmode, row0 + row < extent ? row0 + row : extent - 1u) + k);
+      } else {   // (with K below the k tile the k rows past it read the last one: no offset leaves the operand)
+        off[i] = 2u * gemm_mode_eval(rmode, gemm_any_start(row0 + row, extent, &move)) + (k < K ? k : K - 1u) * k_step;
+      }
+    }
+  }
+  // asks for k tile kt
+  __device__ __forceinline__ void fetch(uint32_t kt) {
+    const uint32_t k0 = kt * kGemmBK;
+    const unsigned char* p = base + (uint64_t)k0 * k_step;   // (uniform)
+    if (k0 + kGemmBK > K) {   // the short last k tile: what lies past K is read where it ends with K
+      uint32_t back[R];   // bytes
+      static_for<R>([&](auto i) {
+        uint32_t row, k, move;
+        unit((uint32_t)i, &row, &k);
+        if constexpr (LOAD == kLoadKAny) {
+          back[i] = 2u * (k0 + k - gemm_any_start(k0 + k, K, &move));
+        } else {
+          k = k0 + (k < K ? k : K - 1u);
+          back[i] = k < K ? 0u : (k - (K - 1u)) * k_step;
+        }
+      });
+      static_for<R>([&](auto i) { regs[i] = *reinterpret_cast<const u32x4_any*>(p + ((int64_t)off[i] - (int64_t)back[i])); });
+    } else {
+      static_for<R>([&](auto i) { regs[i] = *reinterpret_cast<const u32x4_any*>(p + off[i]); });
+    }
+  }
+  // parks k tile kt, which was asked for last: at = where this wavefront's first KiB of the tile lies in LDS
+  __device__ __forceinline__ void park(unsigned char* at, uint32_t kt) {
+    const uint32_t k0 = kt * kGemmBK;
+    u32x4* slot = reinterpret_cast<u32x4*>(at + (t & 63u) * 16u);
+    if (k0 + kGemmBK > K || (LOAD == kLoadRAny && extent % 8u != 0u && row0 + BR > extent)) {   // (uniform) an end to be moved or zeroed
+      static_for<R>([&](auto i) {
+        uint32_t row, k, move;
+        unit((uint32_t)i, &row, &k);
+        if constexpr (LOAD == kLoadKAny) gemm_any_start(k0 + k, K, &move);
+        else gemm_any_start(row0 + row, extent, &move);
+        slot[(int)i * 64] = select_or_zero(k0 + k < K, move_down_b16(regs[i], move));
+      });
+    } else {
+      static_for<R>([&](auto i) { slot[(int)i * 64] = regs[i]; });
+    }
+  }
+};
+template <int BR, int LOAD, int WAVES>
+using TileLoader = std::conditional_t<gemm_load_is_any(LOAD), AnyTileLoader<BR, LOAD, WAVES>, DirectTileLoader<BR, LOAD, WAVES>>;
+
 // Fragment of rows row .. row + 31, k step kk of an operand's tile of BR rows at LDS address `tile`: this lane's 8 elements.
 // (A tile of 16 rows stands twice in its fragment; the second half's products are never looked at.)
 template <int BR, int LOAD, typename KK>
 __device__ __forceinline__ u32x4 direct_fragment(const unsigned char* tile, uint32_t lane, uint32_t row, KK kk) {
-  if constexpr (LOAD == kLoadRDirect)
+  if constexpr (gemm_load_is_k_major(LOAD))
     return lds_read_tr_16x8<BR>(tile + gemm_rdirect_frag_offset(BR, lane, row, 8u * mfma_ab_kvec(lane)), kk);
   else
     return *reinterpret_cast<const u32x4*>(tile + gemm_lds_offset((row + mfma_ab_row(lane)) & (BR - 1u), 2u * (uint32_t)kk + mfma_ab_kvec(lane)));

@@ -14,9 +14,13 @@ hipError_t launch_gemm_bf16_128(const lc_gemm_plan& plan, const uint16_t* a, con
 hipError_t launch_gemm_f16_256(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_128(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_bf16_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_split_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_split_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_bf16_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_stream_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_stream_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 
 static bool gemm_hip_failed(hipError_t e, const char* what) {
   if (e == hipSuccess) return false;
@@ -37,13 +41,21 @@ lc_status_t execute_gemm_plan(const lc_gemm_plan& plan, const void* a, const voi
   (void)hipGetLastError();
   hipError_t pre;
   const bool bf16 = plan.ab_dtype == LC_BF16;
-  // LDS the kernels assume: two stages of an A and a B tile, or (direct loads, always as a pair) a ring of five tiles
-  if (plan.params.a_direct != plan.params.b_direct) return LC_ERR_INVALID_ARG;
+  // LDS the tile kernels assume: two stages of an A and a B tile, or (direct loads, always as a pair) a ring of five tiles;
+  // the split and stream launchers check theirs
+  const bool any = plan.params.a_direct >= 2;
+  if (any != (plan.params.b_direct >= 2) || (!any && plan.params.a_direct != plan.params.b_direct)) return LC_ERR_INVALID_ARG;
   const unsigned tiles_in_lds = plan.params.a_direct ? 5u : 4u;
-  if (plan.split_waves > 0)   // (the launcher checks the rings against LDS)
+  if (plan.split_waves > 0 && any)
+    pre = bf16 ? launch_gemm_bf16_split_any(plan, ka, kb, kc, s) : launch_gemm_f16_split_any(plan, ka, kb, kc, s);
+  else if (plan.split_waves > 0)
     pre = bf16 ? launch_gemm_bf16_split(plan, ka, kb, kc, s) : launch_gemm_f16_split(plan, ka, kb, kc, s);
+  else if (plan.stages > 0 && any)
+    pre = bf16 ? launch_gemm_bf16_stream_any(plan, ka, kb, kc, s) : launch_gemm_f16_stream_any(plan, ka, kb, kc, s);
   else if (plan.stages > 0)
     pre = bf16 ? launch_gemm_bf16_stream(plan, ka, kb, kc, s) : launch_gemm_f16_stream(plan, ka, kb, kc, s);
+  else if (any)
+    return LC_ERR_INVALID_ARG;
   else if (plan.tile_m == 256 && plan.tile_n == 256 && plan.lds_bytes == tiles_in_lds * 256u * 128u)
     pre = bf16 ? launch_gemm_bf16_256(plan, ka, kb, kc, s) : launch_gemm_f16_256(plan, ka, kb, kc, s);
   else if (plan.tile_m == 128 && plan.tile_n == 128 && plan.lds_bytes == tiles_in_lds * 128u * 128u)

@@ -22,8 +22,15 @@ enum GemmLoad : int32_t {
   kLoadKDirect = 3,
   // kLoadRVec without the registers: the tile goes into LDS as it lies in memory (k rows of BR contiguous elements) and the
   // fragments are read with the LDS transpose load (ds_read_b64_tr_b16).  Same conditions; a plan still says kLoadRVec.
-  kLoadRDirect = 4
+  kLoadRDirect = 4,
+  // Vectors at any alignment, for operands with a contiguous mode whose rows do not start on 16-byte boundaries (odd sizes,
+  // offset pointers): 16-byte loads from 2-byte-aligned addresses into registers, parked in the arrangement of kLoadKDirect
+  // (along k) or kLoadRDirect (along the row mode).  Needs a k mode of one leaf; a plan still says kLoadElem.
+  kLoadKAny = 5,
+  kLoadRAny = 6
 };
+LC_HD constexpr bool gemm_load_is_any(int32_t load) { return load == kLoadKAny || load == kLoadRAny; }
+LC_HD constexpr bool gemm_load_is_k_major(int32_t load) { return load == kLoadRDirect || load == kLoadRAny; }
 
 // One coalesced mode: integral coordinate -> offset in elements (all offsets of a GEMM operand fit 31 bits).
 // The leaves but the last are reduced modulo their extents, the last one takes what is left (Eq. idx2crd).
@@ -54,7 +61,8 @@ struct GemmParams {
   uint32_t M, N, K, L;
   uint32_t tiles_m, tiles_n, k_tiles;
   int32_t a_load, b_load;                  // GemmLoad
-  int32_t a_direct, b_direct;              // 1: the operand goes straight into LDS (kLoadKVec -> kLoadKDirect, kLoadRVec -> kLoadRDirect)
+  int32_t a_direct, b_direct;              // 1: the operand goes straight into LDS (kLoadKVec -> kLoadKDirect, kLoadRVec -> kLoadRDirect);
+                                           // 2, 3: vectors at any alignment along k, along the row mode (kLoadKAny, kLoadRAny)
   int32_t c_vec;                           // 1: four consecutive m are contiguous and 16-byte aligned in C
   uint32_t group_m;                        // tile rows walked together before moving on along n
 };
@@ -62,6 +70,7 @@ struct GemmParams {
 // the load the kernel runs for an operand the plan classified as `load`
 LC_HD int32_t gemm_effective_load(int32_t load, int32_t direct) {
   if (!direct) return load;
+  if (direct >= 2) return direct == 2 ? (int32_t)kLoadKAny : (int32_t)kLoadRAny;
   return load == kLoadKVec ? (int32_t)kLoadKDirect : (load == kLoadRVec ? (int32_t)kLoadRDirect : load);
 }
 
@@ -140,6 +149,15 @@ LC_HD uint32_t gemm_rdirect_frag_offset(uint32_t BR, uint32_t lane, uint32_t row
 // asks for the k vector that lives in that slot: kv = slot ^ row ^ (row >> 3).
 LC_HD uint32_t gemm_direct_row(uint32_t rows_per_lane, uint32_t tid, uint32_t i) { return ((tid >> 6) * rows_per_lane + i) * 8u + ((tid & 63u) >> 3); }
 LC_HD uint32_t gemm_direct_kvec(uint32_t row, uint32_t tid) { return ((tid & 7u) ^ row ^ (row >> 3)) & 7u; }
+// Vectors at any alignment: a vector that would reach past the end of its mode is read where it ends with the mode (both
+// ends of it are then inside) and moved down by what it was read early; what moves in from above is zero.  A vector that
+// starts past the end reads the last one (rows: feeds entries of C that are never stored; k: zeroed).
+// at: first coordinate of the vector, extent: of the mode (8 or more) -> where to read it, and by how many elements to move it
+LC_HD uint32_t gemm_any_start(uint32_t at, uint32_t extent, uint32_t* move) {
+  const uint32_t last = extent - 8u, from = at < last ? at : last;
+  *move = at < extent ? at - from : 0u;
+  return from;
+}
 LC_HD uint32_t gemm_clamp_row(int32_t load, uint32_t row, uint32_t extent) {
   const uint32_t last = load == kLoadRVec || load == kLoadRDirect ? extent - 8u : extent - 1u;
   return row < last ? row : last;

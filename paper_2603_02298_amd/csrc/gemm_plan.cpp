@@ -126,6 +126,9 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     return c_align % 16 == 0 && leads_contiguous(lead, 4) && strides_aligned(lead, with_batch(other, c_l), 4);
   };
   bool exchange = !c_vec_ok(c_m, c_n) && c_vec_ok(c_n, c_m);
+  // Without vectors of four m the lanes of an update run along n, element by element: C's contiguous mode goes there (not
+  // for a few columns, whose thin tiles are worth more).
+  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) exchange = c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
   if (env_int("LC_TUNE_GEMM_EXCHANGE", -1) >= 0) exchange = env_int("LC_TUNE_GEMM_EXCHANGE", 0) != 0;
   unsigned ka_align = a_align, kb_align = b_align;
   if (exchange) {
@@ -167,6 +170,20 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   auto direct_on = [&](int load) { return (direct_env & (load == kLoadKVec ? 1 : 2)) != 0; };
   const bool direct = direct_ok(P.a_load, a_k) && direct_ok(P.b_load, b_k) && direct_on(P.a_load) && direct_on(P.b_load);
   P.a_direct = P.b_direct = direct ? 1 : 0;
+  // Operands with a contiguous mode that vectors do not fit (odd sizes, offset pointers): 16-byte loads at any alignment, for
+  // pairs that both have one.  Measured on MI355X (bf16), element by element -> this: 1001 x 2003 x 1537 (all odd) 211 -> 22 us,
+  // 3500^3 (no multiple of 8) 891 -> 158 us, 301 x 401 x 501 30 -> 5.5 us.
+  auto any_kind = [&](const Modes& row, const Modes& k) -> int32_t {
+    if (k.size() != 1) return 0;
+    if (k[0].stride == 1 && K >= 8) return 2;
+    const bool whole = row[0].extent % 8 == 0 || (row.size() == 1 && row[0].extent >= 8);
+    return row[0].stride == 1 && whole ? 3 : 0;
+  };
+  const bool any = P.a_load == kLoadElem && force != kLoadElem && any_kind(a_r, a_k) != 0 && any_kind(b_r, b_k) != 0;
+  if (any) {
+    P.a_direct = any_kind(a_r, a_k);
+    P.b_direct = any_kind(b_r, b_k);
+  }
   P.c_vec = c_vec_ok(c_m, c_n) ? 1 : 0;
   if (env_int("LC_TUNE_GEMM_CVEC", 1) == 0) P.c_vec = 0;
   unsigned need_a = P.a_load == kLoadElem ? 2u : 16u, need_b = P.b_load == kLoadElem ? 2u : 16u;
@@ -184,14 +201,14 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   // stream kernel's 64 x 64
   const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
-  const bool thin = kN <= 16 && P.b_load == kLoadKVec;
+  const bool thin = kN <= 16 && (P.b_load == kLoadKVec || P.b_direct == 2), vectors = direct || any;
   const bool free_choice = t_env == 0;
-  if (direct && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
-  else if (direct && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, 2);
-  else if (direct && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, 3);
-  else if (direct && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, 3);
-  else if (direct && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, 2);
-  else if (direct && t_env != 256) {
+  if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
+  else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, 2);
+  else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, 3);
+  else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, 3);
+  else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, 2);
+  else if (vectors && (any || t_env != 256)) {
     // Larger problems.  The CU that is given the most tiles decides, so a tile's cost is how many of them that CU takes times
     // its area, times what its k loop costs per product against the 128 x 128 stream kernel's: smaller tiles read more of LDS
     // per product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1, 1.2, 1.3 and 64 x 64: 1.3,
@@ -214,7 +231,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     for (const Choice& c : choices)
       if (!best || cost(c, true) < cost(*best, true)) best = &c;
     const Choice big = {256, 256, (K < 2048 ? 1.0 : K < 3000 ? 0.9 : 0.8) * std::min(1.0, 0.7 + 0.3 * (double)tiles_of(256, 256) / 256.0)};
-    if (free_choice && cost(big, false) <= cost(*best, true)) take(256, 256, 0, 0);
+    if (direct && free_choice && cost(big, false) <= cost(*best, true)) take(256, 256, 0, 0);
     else if (t_env == 128) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);
     else if (t_env == 64128) take(64, 128, 0, 2);
@@ -246,6 +263,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
 
 std::string describe(const lc_gemm_plan& plan) {
   static const char* load_name[] = {"k-vectors", "row-vectors+transpose", "elements"};
+  static const char* any_name[] = {"(in unaligned k-vectors)", "(in unaligned row-vectors)"};
   std::string s = "class=gemm-mfma32x32x16 ab=";
   s += plan.ab_dtype == LC_BF16 ? "bf16" : "f16";
   s += " c=f32 M=" + std::to_string(plan.M) + " N=" + std::to_string(plan.N) + " K=" + std::to_string(plan.K);
@@ -256,8 +274,8 @@ std::string describe(const lc_gemm_plan& plan) {
   if (plan.split_waves) s += " split_waves=" + std::to_string(plan.split_waves) + " stages=" + std::to_string(plan.stages);
   s += " tiles=" + std::to_string(plan.params.tiles_m) + "x" + std::to_string(plan.params.tiles_n) + " k_tiles=" + std::to_string(plan.params.k_tiles);
   s += " group_m=" + std::to_string(plan.params.group_m);
-  s += std::string(" a_load=") + load_name[plan.params.a_load] + (plan.params.a_direct ? "(direct-to-LDS)" : "");
-  s += std::string(" b_load=") + load_name[plan.params.b_load] + (plan.params.b_direct ? "(direct-to-LDS)" : "");
+  s += std::string(" a_load=") + load_name[plan.params.a_load] + (plan.params.a_direct >= 2 ? any_name[plan.params.a_direct - 2] : plan.params.a_direct ? "(direct-to-LDS)" : "");
+  s += std::string(" b_load=") + load_name[plan.params.b_load] + (plan.params.b_direct >= 2 ? any_name[plan.params.b_direct - 2] : plan.params.b_direct ? "(direct-to-LDS)" : "");
   s += " c_vec=" + std::to_string(plan.params.c_vec) + " lds_bytes=" + std::to_string(plan.lds_bytes);
   s += " A=[" + plan.a_text + "] B=[" + plan.b_text + "] C=[" + plan.c_text + "]";
   return s;

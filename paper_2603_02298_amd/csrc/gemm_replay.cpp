@@ -84,6 +84,40 @@ struct Walker {
         }
       return;
     }
+    if (gemm_load_is_any(load)) {
+      // the same units, read where they end with their mode when they would reach past it, and moved down
+      const uint32_t R = BR * 8u / lanes;
+      for (uint32_t tid = 0; tid < lanes; ++tid)
+        for (uint32_t i = 0; i < R; ++i) {
+          uint32_t k, row, move = 0, k_move = 0;
+          if (load == kLoadKAny) {
+            row = gemm_direct_row(R, tid, i);
+            k = 8u * gemm_direct_kvec(row, tid);
+          } else {
+            gemm_rdirect_unit(BR, R, tid, i, &k, &row);
+          }
+          const uint32_t lds_at = ((tid >> 6) * R + i) * 1024u + (tid & 63u) * 16u, at_k = kt * kGemmBK + k;
+          if (lds_at != (load == kLoadKAny ? gemm_lds_offset(row, k / 8u) : gemm_rdirect_lds_offset(BR, k, row))) { ok = false; return; }
+          int64_t off;
+          if (load == kLoadKAny) {
+            off = (int64_t)gemm_mode_eval(rmode, row0 + row < extent ? row0 + row : extent - 1u) + gemm_any_start(at_k, P.K, &k_move);
+          } else {
+            const uint32_t from = gemm_any_start(row0 + row, extent, &move);
+            off = (int64_t)gemm_mode_eval(rmode, from) + (int64_t)(at_k < P.K ? at_k : P.K - 1u) * kmode.lead_stride;
+            for (uint32_t e = 0; e < 8; ++e)   // eight neighbours in memory
+              if (gemm_mode_eval(rmode, from + e) != gemm_mode_eval(rmode, from) + e) { ok = false; return; }
+          }
+          if (off < 0 || off + 8 > elems || move > 8u || k_move > 8u) { ok = false; return; }
+          uint16_t v[8];
+          std::memcpy(v, base + off, 16);
+          for (uint32_t e = 0; e < 8; ++e) {
+            const uint32_t from = e + move + k_move;
+            const uint16_t x = from < 8u && at_k < P.K ? v[from] : 0;
+            std::memcpy(tile + lds_at + 2u * e, &x, 2);
+          }
+        }
+      return;
+    }
     for (uint32_t tid = 0; tid < (uint32_t)kBlock; ++tid) {
       const uint32_t kv = gemm_lane_kvec(load, tid), k0 = kt * kGemmBK + kv * 8u;
       if (load == kLoadRVec) {
@@ -135,7 +169,7 @@ struct Walker {
   // 16 lanes, lane i's element e is element i % 4 of the 8 bytes lane 4 e + i / 4 points at.
   void fragment(const unsigned char* tile, int32_t load, uint32_t BR, uint32_t row_base, uint32_t kk, uint16_t (*out)[8]) {
     for (uint32_t lane = 0; lane < 64; ++lane) {
-      if (load != kLoadRDirect) {
+      if (!gemm_load_is_k_major(load)) {
         std::memcpy(out[lane], tile + gemm_lds_offset((row_base + mfma_ab_row(lane)) % BR, 2u * kk + mfma_ab_kvec(lane)), 16);
         continue;
       }

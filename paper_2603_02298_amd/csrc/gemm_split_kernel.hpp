@@ -29,7 +29,9 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
   constexpr int FM = TM / 32, FN = (TN + 31) / 32, KSTEPS = kGemmBK / 16;
   constexpr uint32_t A_BYTES = TM * 128u, STAGE = (TM + TN) * 128u, RING = STAGES * STAGE, PARTIAL = TM * TN * 4u;
   constexpr int R = (TM + TN) / 8;   // load instructions per k tile
-  static_assert(TN != 16 || B_LOAD == kLoadKDirect, "16 rows: row-major tiles only");
+  constexpr bool ANY = gemm_load_is_any(A_LOAD);
+  static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
+  static_assert(TN != 16 || !gemm_load_is_k_major(B_LOAD), "16 rows: row-major tiles only");
   static_assert(PARTIAL <= RING, "a wavefront's partial tile takes the place of its own ring");
   static_assert((STAGES - 1) * R < 64, "vmcnt has six bits");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -51,8 +53,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
   SumUnits<TM, TN, 64 * WAVES, C_VEC> units;
   units.request(P, C, m0, n0, tid);
 
-  DirectTileLoader<TM, A_LOAD, 1> la;
-  DirectTileLoader<TN, B_LOAD, 1> lb;
+  TileLoader<TM, A_LOAD, 1> la;
+  TileLoader<TN, B_LOAD, 1> lb;
   la.init(A, P.a_r, P.a_k, m0, P.M, P.K, lane);
   lb.init(B, P.b_r, P.b_k, n0, P.N, P.K, lane);
 
@@ -67,38 +69,68 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
   const uint32_t ring = wave * RING;
   const uint32_t n_mine = P.k_tiles > wave ? (P.k_tiles - wave + (WAVES - 1u)) / WAVES : 0u;
   uint32_t next = n_mine > 0u ? order % n_mine : 0u;
-  auto request = [&](uint32_t at) {   // this wavefront's next k tile, to the stage at LDS offset `at`
-    const uint32_t kt = wave + next * WAVES;
-    next = next + 1u == n_mine ? 0u : next + 1u;
-    const bool tail = kt + 1u == P.k_tiles;
-    la.fetch(2u * gemm_mode_eval(P.a_k, kt * kGemmBK), at, tail);
-    lb.fetch(2u * gemm_mode_eval(P.b_k, kt * kGemmBK), at + A_BYTES, tail);
-  };
-  static_for<STAGES>([&](auto s) {
-    if ((uint32_t)s < n_mine) request(ring + (uint32_t)s * STAGE);
-  });
-  uint32_t at = ring;
-  for (uint32_t t = 0; t < n_mine; ++t) {
-    // all but the STAGES - 1 youngest k tiles have landed (vmcnt counts the newer ones; towards the end there are fewer)
-    constexpr int N = (STAGES - 1) * R;
-    if (t + STAGES <= n_mine) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
-    asm volatile("" ::: "memory");
-    u32x4 af[FM][KSTEPS], bf[FN][KSTEPS];
+  u32x4 af[FM][KSTEPS], bf[FN][KSTEPS];
+  auto read_fragments = [&](const unsigned char* stage) {
     static_for<KSTEPS>([&](auto kk) {
-      static_for<FM>([&](auto i) { af[i][kk] = direct_fragment<TM, A_LOAD>(lds + at, lane, 32u * (uint32_t)i, kk); });
-      static_for<FN>([&](auto j) { bf[j][kk] = direct_fragment<TN, B_LOAD>(lds + at + A_BYTES, lane, 32u * (uint32_t)j, kk); });
+      static_for<FM>([&](auto i) { af[i][kk] = direct_fragment<TM, A_LOAD>(stage, lane, 32u * (uint32_t)i, kk); });
+      static_for<FN>([&](auto j) { bf[j][kk] = direct_fragment<TN, B_LOAD>(stage + A_BYTES, lane, 32u * (uint32_t)j, kk); });
     });
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the fragments are in registers, the stage may be filled again
-    asm volatile("" ::: "memory");
-    if (t + STAGES < n_mine) request(at);
+  };
+  auto multiply = [&]() {
     static_for<KSTEPS>([&](auto kk) {
       static_for<FM>([&](auto i) {
         static_for<FN>([&](auto j) { acc[i][j] = mfma_32x32x16<BF16>(af[i][kk], bf[j][kk], acc[i][j]); });
       });
     });
-    at += STAGE;
-    if (at == ring + RING) at = ring;
+  };
+  if constexpr (ANY) {
+    // Through registers: a k tile is parked in the wavefront's ring, the next one asked for, then its fragments are read.
+    uint32_t kt = 0, asked = 0;   // the k tile being parked, the one asked for
+    auto fetch = [&]() {
+      asked = wave + next * WAVES;
+      next = next + 1u == n_mine ? 0u : next + 1u;
+      la.fetch(asked);
+      lb.fetch(asked);
+    };
+    if (n_mine > 0u) fetch();
+    for (uint32_t t = 0; t < n_mine; ++t) {
+      unsigned char* stage = lds + ring;
+      kt = asked;
+      la.park(stage, kt);
+      lb.park(stage + A_BYTES, kt);
+      if (t + 1u < n_mine) fetch();
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): parked (a wavefront's LDS accesses are carried out in order)
+      asm volatile("" ::: "memory");
+      read_fragments(stage);
+      asm volatile("" ::: "memory");
+      multiply();
+    }
+  } else {
+    auto request = [&](uint32_t at) {   // this wavefront's next k tile, to the stage at LDS offset `at`
+      const uint32_t kt = wave + next * WAVES;
+      next = next + 1u == n_mine ? 0u : next + 1u;
+      const bool tail = kt + 1u == P.k_tiles;
+      la.fetch(2u * gemm_mode_eval(P.a_k, kt * kGemmBK), at, tail);
+      lb.fetch(2u * gemm_mode_eval(P.b_k, kt * kGemmBK), at + A_BYTES, tail);
+    };
+    static_for<STAGES>([&](auto s) {
+      if ((uint32_t)s < n_mine) request(ring + (uint32_t)s * STAGE);
+    });
+    uint32_t at = ring;
+    for (uint32_t t = 0; t < n_mine; ++t) {
+      // all but the STAGES - 1 youngest k tiles have landed (vmcnt counts the newer ones; towards the end there are fewer)
+      constexpr int N = (STAGES - 1) * R;
+      if (t + STAGES <= n_mine) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      asm volatile("" ::: "memory");
+      read_fragments(lds + at);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the fragments are in registers, the stage may be filled again
+      asm volatile("" ::: "memory");
+      if (t + STAGES < n_mine) request(at);
+      multiply();
+      at += STAGE;
+      if (at == ring + RING) at = ring;
+    }
   }
 
   // the partial tile, into the place of the wavefront's own ring (every load has landed and every read has returned)
@@ -143,26 +175,25 @@ static inline hipError_t launch_split_ab(const lc_gemm_plan& plan, const uint16_
   return plan.params.c_vec ? launch_split_abc<BF16, TM, TN, WAVES, STAGES, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
                            : launch_split_abc<BF16, TM, TN, WAVES, STAGES, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
-template <bool BF16, int TM, int TN, int WAVES, int STAGES>
+// K_LOAD, R_LOAD: the pair of load kinds (straight into LDS, or vectors at any alignment) this translation unit holds
+template <bool BF16, int TM, int TN, int WAVES, int STAGES, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
-  if (la == kLoadKDirect && lb == kLoadKDirect) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, kLoadKDirect, kLoadKDirect>(plan, a, b, c, s);
-  if (la == kLoadKDirect && lb == kLoadRDirect) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, kLoadKDirect, kLoadRDirect>(plan, a, b, c, s);
-  if (la == kLoadRDirect && lb == kLoadKDirect) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, kLoadRDirect, kLoadKDirect>(plan, a, b, c, s);
-  if (la == kLoadRDirect && lb == kLoadRDirect) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, kLoadRDirect, kLoadRDirect>(plan, a, b, c, s);
+  if (la == K_LOAD && lb == K_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, K_LOAD, K_LOAD>(plan, a, b, c, s);
+  if (la == R_LOAD && lb == K_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, R_LOAD, K_LOAD>(plan, a, b, c, s);
+  if constexpr (TN >= 32) {
+    if (la == K_LOAD && lb == R_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, K_LOAD, R_LOAD>(plan, a, b, c, s);
+    if (la == R_LOAD && lb == R_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, R_LOAD, R_LOAD>(plan, a, b, c, s);
+  }
   return hipErrorInvalidValue;
 }
-template <bool BF16>
+template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_split_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  if (plan.tile_m == 32 && plan.tile_n == 16) {
-    if (gemm_effective_load(plan.params.b_load, plan.params.b_direct) != kLoadKDirect) return hipErrorInvalidValue;
-    return gemm_effective_load(plan.params.a_load, plan.params.a_direct) == kLoadKDirect ? launch_split_ab<BF16, 32, 16, 8, 3, kLoadKDirect, kLoadKDirect>(plan, a, b, c, s)
-                                                                                         : launch_split_ab<BF16, 32, 16, 8, 3, kLoadRDirect, kLoadKDirect>(plan, a, b, c, s);
-  }
-  if (plan.tile_m == 32 && plan.tile_n == 32) return launch_split<BF16, 32, 32, 8, 2>(plan, a, b, c, s);
-  if (plan.tile_m == 32 && plan.tile_n == 64) return launch_split<BF16, 32, 64, 4, 3>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 32) return launch_split<BF16, 64, 32, 4, 3>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_split<BF16, 64, 64, 4, 2>(plan, a, b, c, s);
+  if (plan.tile_m == 32 && plan.tile_n == 16) return launch_split<BF16, 32, 16, 8, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 32 && plan.tile_n == 32) return launch_split<BF16, 32, 32, 8, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 32 && plan.tile_n == 64) return launch_split<BF16, 32, 64, 4, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 32) return launch_split<BF16, 64, 32, 4, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_split<BF16, 64, 64, 4, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
 

@@ -29,6 +29,8 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
   constexpr uint32_t A_BYTES = BM * 128u, STAGE = (BM + BN) * 128u;
   constexpr int R = (BM + BN) / 32;   // load instructions per wavefront and k tile
   static_assert(STAGES >= 2 && BM * BN * 4 <= STAGES * (BM + BN) * 128, "the sums of the tile fit the ring");
+  constexpr bool ANY = gemm_load_is_any(A_LOAD);
+  static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
   static_assert((STAGES - 2) * R < 64, "vmcnt has six bits");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   touch_kernel_arguments<(int)sizeof(GemmParams) + 24>();
@@ -47,11 +49,13 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
   B += gemm_mode_eval(P.b_l, batch);
   C += gemm_mode_eval(P.c_l, batch);
 
-  DirectTileLoader<BM, A_LOAD, 4> la;
-  DirectTileLoader<BN, B_LOAD, 4> lb;
+  TileLoader<BM, A_LOAD, 4> la;
+  TileLoader<BN, B_LOAD, 4> lb;
   SumUnits<BM, BN, kBlock, C_VEC> units;
-  // (element by element the old values' addresses would not leave the registers the products need: asked for at the end then)
-  if constexpr (C_VEC) units.request(P, C, m0, n0, tid);
+  // (element by element, or with k tiles on their way through registers, the old values would not leave the products the
+  // registers they need: asked for at the end then)
+  constexpr bool EARLY_C = C_VEC && !ANY;
+  if constexpr (EARLY_C) units.request(P, C, m0, n0, tid);
   la.init(A, P.a_r, P.a_k, m0, P.M, P.K, tid);
   lb.init(B, P.b_r, P.b_k, n0, P.N, P.K, tid);
 
@@ -63,46 +67,75 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
     });
   });
 
-  KTileOffset ka, kb;   // of the next k tile to request
-  ka.seek(P.a_k, 0u);
-  kb.seek(P.b_k, 0u);
-  uint32_t asked = 0;
-  const uint32_t a_at = wave * (BM * 32u), b_at = A_BYTES + wave * (BN * 32u);   // this wavefront's quarter of either tile
-  auto request = [&](uint32_t at) {   // the next k tile, to the stage at LDS offset `at`
-    const bool tail = asked + 1u == P.k_tiles;
-    la.fetch(ka.bytes, at + a_at, tail);
-    lb.fetch(kb.bytes, at + b_at, tail);
-    ++asked;
-    if (asked < P.k_tiles) {
-      ka.next(P.a_k, asked);
-      kb.next(P.b_k, asked);
-    }
-  };
-  static_for<STAGES - 1>([&](auto s) {
-    if ((uint32_t)s < P.k_tiles) request((uint32_t)s * STAGE);
-  });
-  uint32_t at = 0, free_at = (STAGES - 1) * STAGE;   // the stage being multiplied, the one before it
-  for (uint32_t t = 0; t < P.k_tiles; ++t) {
-    // k tile t has landed: all but the STAGES - 2 younger ones (towards the end there are fewer), for every wavefront past
-    // the barrier, which also has its fragments of k tile t - 1 in registers: that stage may be filled again
-    constexpr int N = (STAGES - 2) * R;
-    if (t + (STAGES - 1) <= P.k_tiles) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
-    else __builtin_amdgcn_s_waitcnt(0x0070);
-    lds_barrier();
-    if (asked < P.k_tiles) request(free_at);
+  auto multiply = [&](const unsigned char* stage) {
     static_for<KSTEPS>([&](auto kk) {
       u32x4 af[FM], bf[FN];
-      static_for<FM>([&](auto i) { af[i] = direct_fragment<BM, A_LOAD>(lds + at, lane, wm * (BM / 2) + 32u * (uint32_t)i, kk); });
-      static_for<FN>([&](auto j) { bf[j] = direct_fragment<BN, B_LOAD>(lds + at + A_BYTES, lane, wn * (BN / 2) + 32u * (uint32_t)j, kk); });
+      static_for<FM>([&](auto i) { af[i] = direct_fragment<BM, A_LOAD>(stage, lane, wm * (BM / 2) + 32u * (uint32_t)i, kk); });
+      static_for<FN>([&](auto j) { bf[j] = direct_fragment<BN, B_LOAD>(stage + A_BYTES, lane, wn * (BN / 2) + 32u * (uint32_t)j, kk); });
       static_for<FM>([&](auto i) {
         static_for<FN>([&](auto j) { acc[i][j] = mfma_32x32x16<BF16>(af[i], bf[j], acc[i][j]); });
       });
     });
-    free_at = at;
-    at = at + STAGE == STAGES * STAGE ? 0u : at + STAGE;
+  };
+  const uint32_t a_at = wave * (BM * 32u), b_at = A_BYTES + wave * (BN * 32u);   // this wavefront's quarter of either tile
+  if constexpr (ANY) {
+    // Through registers: k tile t + 1 is parked in the stage k tile t - 1 leaves, k tile t + 2 asked for, then k tile t multiplied.
+    static_assert(STAGES == 2, "registers hold the third k tile");
+    la.fetch(0u);
+    lb.fetch(0u);
+    la.park(lds + a_at, 0u);
+    lb.park(lds + b_at, 0u);
+    if (P.k_tiles > 1u) {
+      la.fetch(1u);
+      lb.fetch(1u);
+    }
+    for (uint32_t t = 0; t < P.k_tiles; ++t) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): parked, and the fragments of k tile t - 1 read
+      lds_barrier();
+      if (t + 1u < P.k_tiles) {
+        unsigned char* next = lds + ((t + 1u) & 1u) * STAGE;
+        la.park(next + a_at, t + 1u);
+        lb.park(next + b_at, t + 1u);
+        if (t + 2u < P.k_tiles) {
+          la.fetch(t + 2u);
+          lb.fetch(t + 2u);
+        }
+      }
+      multiply(lds + (t & 1u) * STAGE);
+    }
+  } else {
+    KTileOffset ka, kb;   // of the next k tile to request
+    ka.seek(P.a_k, 0u);
+    kb.seek(P.b_k, 0u);
+    uint32_t asked = 0;
+    auto request = [&](uint32_t at) {   // the next k tile, to the stage at LDS offset `at`
+      const bool tail = asked + 1u == P.k_tiles;
+      la.fetch(ka.bytes, at + a_at, tail);
+      lb.fetch(kb.bytes, at + b_at, tail);
+      ++asked;
+      if (asked < P.k_tiles) {
+        ka.next(P.a_k, asked);
+        kb.next(P.b_k, asked);
+      }
+    };
+    static_for<STAGES - 1>([&](auto s) {
+      if ((uint32_t)s < P.k_tiles) request((uint32_t)s * STAGE);
+    });
+    uint32_t at = 0, free_at = (STAGES - 1) * STAGE;   // the stage being multiplied, the one before it
+    for (uint32_t t = 0; t < P.k_tiles; ++t) {
+      // k tile t has landed: all but the STAGES - 2 younger ones (towards the end there are fewer), for every wavefront past
+      // the barrier, which also has its fragments of k tile t - 1 in registers: that stage may be filled again
+      constexpr int N = (STAGES - 2) * R;
+      if (t + (STAGES - 1) <= P.k_tiles) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+      lds_barrier();
+      if (asked < P.k_tiles) request(free_at);
+      multiply(lds + at);
+      free_at = at;
+      at = at + STAGE == STAGES * STAGE ? 0u : at + STAGE;
+    }
   }
 
-  if constexpr (!C_VEC) units.request(P, C, m0, n0, tid);
   __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
   lds_barrier();   // every fragment has been read: the sums take the ring's place
   static_for<FM>([&](auto i) {
@@ -116,6 +149,8 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
       });
     });
   });
+  asm volatile("" ::: "memory");
+  if constexpr (!EARLY_C) units.request(P, C, m0, n0, tid);   // (the products' registers are free now)
   __syncthreads();
   units.add(P, C, m0, n0, tid, [&](uint32_t unit) { return *reinterpret_cast<const f32x4*>(lds + unit * 16u); });
 }
@@ -139,22 +174,23 @@ static inline hipError_t launch_stream_ab(const lc_gemm_plan& plan, const uint16
   return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
                            : launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
-template <bool BF16, int BM, int BN, int STAGES>
+// K_LOAD, R_LOAD: the pair of load kinds (straight into LDS, or vectors at any alignment) this translation unit holds
+template <bool BF16, int BM, int BN, int STAGES, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
-  if (la == kLoadKDirect && lb == kLoadKDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadKDirect, kLoadKDirect>(plan, a, b, c, s);
-  if (la == kLoadKDirect && lb == kLoadRDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadKDirect, kLoadRDirect>(plan, a, b, c, s);
-  if (la == kLoadRDirect && lb == kLoadKDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadRDirect, kLoadKDirect>(plan, a, b, c, s);
-  if (la == kLoadRDirect && lb == kLoadRDirect) return launch_stream_ab<BF16, BM, BN, STAGES, kLoadRDirect, kLoadRDirect>(plan, a, b, c, s);
+  if (la == K_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, K_LOAD, K_LOAD>(plan, a, b, c, s);
+  if (la == K_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (la == R_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, R_LOAD, K_LOAD>(plan, a, b, c, s);
+  if (la == R_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, R_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
-template <bool BF16>
+template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   if (plan.stages != 2) return hipErrorInvalidValue;
-  if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, 2>(plan, a, b, c, s);
-  if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, 2>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, 2>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_stream<BF16, 64, 64, 2>(plan, a, b, c, s);
+  if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_stream<BF16, 64, 64, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
 

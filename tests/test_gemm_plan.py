@@ -273,7 +273,7 @@ def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile():
         d = lc.GemmPlan("(%d,%d,%d):(%d,1,%d)" % (M, K, L, K, M * K), "(%d,%d,%d):(%d,1,%d)" % (N, K, L, K, N * K), "(%d,%d,%d):(1,%d,%d)" % (M, N, L, M, M * N)).describe()
         return d.split("tile=")[1].split()[0], "split_waves" in d
     assert tile(8192, 16, 64) == ("32x16x64", True) and tile(8192, 17, 64) == ("32x32x64", True)
-    assert tile(512, 512, 512) == ("32x32x64", True) and tile(513, 512, 512) == ("64x32x64", True) and tile(512, 513, 512) == ("32x64x64", True)
+    assert tile(512, 512, 512) == ("32x32x64", True) and tile(516, 512, 512) == ("64x32x64", True) and tile(512, 513, 512) == ("32x64x64", True)
     assert tile(1024, 1024, 64) == ("64x64x64", True) and tile(1024, 1025, 64)[1] is False
     assert tile(64, 64, 64, 64) == ("32x32x64", True) and tile(64, 64, 64, 257)[1] is False
 
@@ -300,3 +300,39 @@ def test_walk_stream_kernel(oracle, name, sizes, tile, shape):
     # entries, sums through LDS units
     w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values="ints")
     _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, ["tile=%sx64 stream" % shape])
+
+
+ANY_CASES = [  # (form, M, N, K): both along k, both along the rows, mixed; edges of vectors, tiles and k tiles; fewer rows than a vector along k
+    ("tt", 33, 65, 9), ("tt", 67, 131, 129), ("tt", 5, 3, 1537), ("nn", 67, 131, 61), ("nn", 9, 11, 1), ("nn", 129, 65, 200), ("nt", 131, 70, 77),
+    ("tn", 70, 131, 65), ("tt", 64, 64, 63), ("tt", 100, 72, 100), ("nt", 64, 9, 300)]
+
+
+def _odd_workload(form, M, N, K, c="col", ab_dtype="bf16", values="ints"):
+    a = "(%d,%d):" % (M, K) + ("(%d,1)" % K if form[0] == "t" else "(1,%d)" % M)
+    b = "(%d,%d):" % (N, K) + ("(%d,1)" % K if form[1] == "t" else "(1,%d)" % N)
+    return W.GemmWorkload("odd_" + form, ab_dtype, a, b, "(%d,%d):" % (M, N) + ("(1,%d)" % M if c == "col" else "(%d,1)" % N), M * K, N * K, M * N, M, N, K, values)
+
+
+@pytest.mark.parametrize("tile", [0, 3216, 32, 3264, 64, 128, 64128, 6464])
+@pytest.mark.parametrize("case", ANY_CASES)
+def test_walk_vectors_at_any_alignment(oracle, case, tile):
+    # a contiguous mode whose rows start anywhere: 16-byte loads that never leave the operand (the walk checks every one),
+    # moved where they would have reached past their mode
+    for c in ("col", "row"):
+        text = _walk_and_compare(oracle, _odd_workload(*case, c=c), {"LC_TUNE_GEMM_TILE": tile})
+        assert text.count("elements(in unaligned") == 2, text
+
+
+def test_which_operands_take_vectors_at_any_alignment():
+    def loads(*layouts, **kw):
+        d = lc.GemmPlan(*layouts, **kw).describe()
+        return d.split("a_load=")[1].split(" b_load=")[0], d.split("b_load=")[1].split(" c_vec")[0]
+    k, r = "elements(in unaligned k-vectors)", "elements(in unaligned row-vectors)"
+    assert loads("(70,9):(9,1)", "(33,9):(1,33)", "(70,33):(33,1)") == (k, r)
+    assert loads("(64,64):(64,1)", "(64,64):(1,64)", "(64,64):(1,64)", a_align=2) == (k, r)      # an aligned partner comes along
+    assert loads("(70,7):(7,1)", "(33,7):(7,1)", "(70,33):(33,1)") == ("elements", "elements")   # K below one vector
+    assert loads("(70,9):(9,1)", "(33,9):(3,100)", "(70,33):(33,1)") == ("elements", "elements") # a partner without a contiguous mode
+    assert loads("((5,14),9):((1,5),71)", "(33,9):(9,1)", "(70,33):(33,1)") == (r, k)            # (coalesces to 70:1)
+    assert loads("((5,14),9):((1,6),84)", "(33,9):(9,1)", "(70,33):(33,1)")[0] == "elements"     # vectors would straddle the leaves
+    assert loads("((8,9),9):((1,9),81)", "(33,9):(9,1)", "(72,33):(33,1)")[0] == r
+    assert loads("(70,(3,3)):(12,(1,4))", "(33,9):(9,1)", "(70,33):(33,1)")[0] == "elements"     # k of two leaves

@@ -256,3 +256,26 @@ def test_gemm_stream_kernel(oracle, tile, values):
             assert " stream " in _parity(oracle, w, dict(env, LC_TUNE_GEMM_TILE=tile))
     w = W.conv_gemm_workload(2, 14, 12, 64, 136, 3, 3, "krsc", ab_dtype="f16", values=values)
     assert " stream " in _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [3216, 32, 3264, 6432, 64, 128, 12864, 64128, 6464])
+def test_gemm_vectors_at_any_alignment(oracle, tile, values):
+    # odd sizes: 16-byte loads from any 2-byte-aligned address through registers, on the split and the stream kernel; edges
+    # of vectors, tiles and k tiles, and pointers off by one element
+    from test_gemm_plan import ANY_CASES, _odd_workload
+    for n, case in enumerate(ANY_CASES):
+        w = _odd_workload(*case, c=("col", "row")[n % 2], ab_dtype=("bf16", "f16")[n // 2 % 2], values=values)
+        assert _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile}).count("elements(in unaligned") == 2
+    if tile == 64:
+        w = _odd_workload("tn", 72, 136, 64, values=values)
+        a, b, c0 = W.gemm_operand_bits(w, "a"), W.gemm_operand_bits(w, "b"), W.gemm_c_values(w)
+        dev = torch.device("cuda:0")
+        a_t = torch.from_numpy(np.concatenate([a[:1], a]).view(np.int16)).to(dev).view(torch.bfloat16)[1:]
+        b_t = torch.from_numpy(b.view(np.int16)).to(dev).view(torch.bfloat16)
+        c_t = torch.from_numpy(c0.copy()).to(dev)
+        lc.gemm_tensor(a_t, w.a_layout, b_t, w.b_layout, c_t, w.c_layout)
+        a64, b64 = W.bits_to_float64(a, "bf16"), W.bits_to_float64(b, "bf16")
+        want = oracle.gemm(a64, w.a_layout, b64, w.b_layout, c0.astype(np.float64), w.c_layout)
+        bound = oracle.gemm(np.abs(a64), w.a_layout, np.abs(b64), w.b_layout, np.abs(c0).astype(np.float64), w.c_layout)
+        assert (np.abs(c_t.cpu().numpy().astype(np.float64) - want) <= (0 if values == "ints" else w.K * 2.0 ** -23 * bound)).all()
