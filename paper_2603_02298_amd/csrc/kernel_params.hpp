@@ -154,6 +154,11 @@ struct TransposeParams {
   uint32_t rag_extent[2];          // extent of the mode (elements)
   uint32_t rag_tile[2];            // tile extent along it (elements, < 2^15)
   int32_t rag_rest[2];             // which rest mode counts the tiles along it (-1: the mode has a single tile)
+  // Shifted tiles: the other way to cover such modes.  The last tile along the mode is moved back so that it ends with the
+  // mode: every tile is whole and no access is predicated; the tile overlaps its neighbour and writes the same values there.
+  // rag_rest says which rest mode; at its last position the origins step back by these (elements).
+  int32_t n_shifted;
+  int64_t back_a[2], back_b[2];
   uint32_t cw_s[kMaxModes];        // coordinate step (packed) of one step of source-order micro mode k
   uint32_t cw_d[kMaxModes + 1];    // the same for the destination-order modes
 };
@@ -321,6 +326,30 @@ LC_HD void tile_origin(const TransposeParams& P, uint32_t tile, int64_t* so, int
     s += (int64_t)r * P.ra[k];
     d += (int64_t)r * P.rb[k];
     tile = q;
+  }
+  *so = s;
+  *dof = d;
+}
+
+// The tile a workgroup starts on, of a grid that sweeps the tiles together: workgroups go to the 8 XCDs (an L2 each) in
+// turn, and neighbouring shifted tiles share cache lines at their edges, so an XCD's workgroups take neighbouring tiles.
+LC_HD uint32_t shifted_first_tile(uint32_t wg, uint32_t grid) { return grid % 8u == 0u ? (wg % 8u) * (grid / 8u) + wg / 8u : wg; }
+// the same for shifted tiles: the last tile along such a mode ends with the mode
+LC_HD void tile_origin_shifted(const TransposeParams& P, uint32_t tile, int64_t* so, int64_t* dof) {
+  int64_t s = 0, d = 0;
+#pragma unroll
+  for (int k = 0; k < kMaxModes; ++k) {
+    if (k < P.n_rest) {
+      uint32_t q, r;
+      fd_divmod(tile, P.rdiv[k], &q, &r);
+      s += (int64_t)r * P.ra[k];
+      d += (int64_t)r * P.rb[k];
+      if (r + 1u == P.rdiv[k].div) {
+        if (P.rag_rest[0] == k) { s -= P.back_a[0]; d -= P.back_b[0]; }
+        if (P.rag_rest[1] == k) { s -= P.back_a[1]; d -= P.back_b[1]; }
+      }
+      tile = q;
+    }
   }
   *so = s;
   *dof = d;

@@ -38,6 +38,19 @@ __device__ __forceinline__ void gstore(T* p, T v) {
   if (NT & 2) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
+// the same at an address that is a multiple of ALIGN bytes only
+template <int NT, int ALIGN, typename T>
+__device__ __forceinline__ T gload_at(const unsigned char* p) {
+  typedef T __attribute__((aligned(ALIGN))) Loose;
+  if (NT & 1) return __builtin_nontemporal_load(reinterpret_cast<const Loose*>(p));
+  return *reinterpret_cast<const Loose*>(p);
+}
+template <int NT, int ALIGN, typename T>
+__device__ __forceinline__ void gstore_at(unsigned char* p, T v) {
+  typedef T __attribute__((aligned(ALIGN))) Loose;
+  if (NT & 2) __builtin_nontemporal_store(v, reinterpret_cast<Loose*>(p));
+  else *reinterpret_cast<Loose*>(p) = v;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Element-wise: both layouts evaluated per element (idx2crd + inner_product, Eq. idx2crd / Eq. innerprod).
@@ -380,7 +393,8 @@ __device__ __forceinline__ void micro_transpose(const uint32_t (&r)[V][V * ES / 
 // DYN: tiles past the first rounds come from the queue (FULL tiles only); 0: the queue's code is not in the kernel; 1: one
 // counter, the first round of the grid by index (the planner's default: a loop without the general form's branches, which
 // measured 2-3 % faster on the fp16 tiled-partition workload); 2: the general form (several rounds, several counters).
-template <int ES, int V, int MT, int NT, bool FULL, int DYN>
+// ANY: shifted tiles (see TransposeParams): vectors lie at any multiple of the element's width on both sides.
+template <int ES, int V, int MT, int NT, bool FULL, int DYN, bool ANY = false>
 __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* __restrict__ src, uint32_t h_ctl, int32_t h_aq, int32_t h_sa0,
                                                           int32_t h_sa1, int32_t h_sa2, int32_t h_sa3, uint32_t h_mul, uint32_t h_div,
                                                           int64_t h_ra0, int64_t h_ra1, TransposeParams P,
@@ -389,8 +403,13 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
   constexpr int DW = V * ES / 4;                 // dwords per vector
   constexpr int SLOT = V * ES;                   // bytes per vector
   typedef typename Word<SLOT>::type Vec;
+  constexpr int GALIGN = ANY ? ES : SLOT;        // alignment of a vector in global memory
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   uint32_t r[MT][V][DW];
+  auto origin = [&](uint32_t t, int64_t* so, int64_t* dof) {
+    if constexpr (ANY) tile_origin_shifted(P, t, so, dof);
+    else tile_origin(P, t, so, dof);
+  };
   bool early = false;
   if constexpr (MT == 1) {
     if (h_ctl & 1u) {
@@ -446,7 +465,7 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
       if (FULL || act[m]) {
 #pragma unroll
         for (int iq = 0; iq < V; ++iq) {
-          Vec v = gload<NT>(reinterpret_cast<const Vec*>(base + ((int64_t)src_in[m] + (int64_t)iq * P.a_q) * ES));
+          Vec v = gload_at<NT, GALIGN, Vec>(base + ((int64_t)src_in[m] + (int64_t)iq * P.a_q) * ES);
           const uint32_t* w = reinterpret_cast<const uint32_t*>(&v);
 #pragma unroll
           for (int k = 0; k < DW; ++k) r[m][iq][k] = w[k];
@@ -482,11 +501,12 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
 #pragma unroll
     for (int j = 0; j < MT * V; ++j) {
       const uint32_t g = threadIdx.x + (uint32_t)j * kBlock;
-      if (FULL || g < P.n_vec) gstore<NT>(reinterpret_cast<Vec*>(base + (int64_t)dst_in[j] * ES), v[j]);
+      if (FULL || g < P.n_vec) gstore_at<NT, GALIGN, Vec>(base + (int64_t)dst_in[j] * ES, v[j]);
     }
   };
 
   uint32_t tile = blockIdx.x, tile_step = gridDim.x, tile_end = P.n_tiles;
+  if constexpr (ANY && DYN == 0) tile = shifted_first_tile(blockIdx.x, gridDim.x);
   if (P.blocked) {
     const uint32_t per_wg = (P.n_tiles + gridDim.x - 1) / gridDim.x;
     tile = blockIdx.x * per_wg;
@@ -548,7 +568,7 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
     unsigned int* tiles_out = queue + 1;
     if (threadIdx.x == 0) asked = atomicAdd(tiles_out, grab);
     int64_t so, dof;
-    tile_origin(P, tile, &so, &dof);
+    origin(tile, &so, &dof);
     load_tile(so);
     asm volatile("" ::: "memory");
     destination_side();
@@ -564,7 +584,7 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
       const bool new_batch = left == 0;   // `next` is the first tile of a batch: ask for the batch after it
       if (new_batch && threadIdx.x == 0) asked = atomicAdd(tiles_out, grab);
       int64_t dof_next;
-      tile_origin(P, next, &so, &dof_next);
+      origin(next, &so, &dof_next);
       load_tile(so);
       __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of every store in program order
       store_tile(dof);
@@ -590,7 +610,7 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
   bool ask = dynamic && tile + G >= static_end;   // the first tile is this workgroup's last tile by index
   if (ask && threadIdx.x == 0) asked = atomicAdd(counter, grab);
   int64_t so, dof;
-  tile_origin(P, tile, &so, &dof);
+  origin(tile, &so, &dof);
   if (!early) load_tile(so);
   // The destination side of the lane state is worked out while the first loads are in flight.  The
   // empty statement below counts as a possible store, so the compiler cannot sink the loads past it.
@@ -613,7 +633,7 @@ __global__ __launch_bounds__(kBlock) void transpose_kernel(const unsigned char* 
     ask = dynamic && (by_index ? next + G >= static_end : left == 0);
     if (ask && threadIdx.x == 0) asked = atomicAdd(counter, grab);
     int64_t dof_next;
-    tile_origin(P, next, &so, &dof_next);
+    origin(next, &so, &dof_next);
     load_tile(so);
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of every store in program order
     store_tile(dof);
@@ -929,6 +949,60 @@ static PreLaunch launch_transpose(const lc_plan& plan, const void* src, void* ds
   return PreLaunch{hipErrorInvalidValue, "kernel selection (micro-tiles per lane)"};
 }
 
+// shifted tiles: the transposing kernel on vectors at any alignment
+template <int ES, int V, int MT, int NT>
+static PreLaunch launch_shifted_n(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+  const unsigned char* sp = static_cast<const unsigned char*>(src);
+  unsigned char* dp = static_cast<unsigned char*>(dst);
+  PreLaunch pre;
+  unsigned int* queue = nullptr;
+  unsigned lds_bytes = plan.lds_bytes;
+  if (plan.tile_queue && grid < plan.transpose.n_tiles) {
+    pre.status = tile_queue_of_stream(s, &queue, &pre.call);
+    if (pre.status != hipSuccess) return pre;
+    if (queue) lds_bytes += 16;   // the word that carries the next tile to the other lanes
+  }
+  if (lds_bytes > 64 * 1024) {
+    static std::atomic<bool> raised{false};
+    if (!raised.load(std::memory_order_acquire)) {
+      pre.call = "hipFuncSetAttribute";
+      pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, NT, true, 0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (pre.status == hipSuccess)
+        pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, NT, true, 1, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (pre.status != hipSuccess) return pre;
+      raised.store(true, std::memory_order_release);
+    }
+  }
+  const uint32_t grab = (uint32_t)std::max(1, plan.tile_queue);
+  if (queue)
+    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, NT, true, 1, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
+                       plan.transpose, dp, queue, plan.lds_bytes, grab, 1u, 1u, 0u);
+  else
+    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, NT, true, 0, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
+                       plan.transpose, dp, queue, plan.lds_bytes, grab, 1u, 1u, 0u);
+  return pre;
+}
+template <int ES, int V, int MT>
+static PreLaunch launch_shifted_m(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+  switch (plan.nontemporal) {
+    case 0: return launch_shifted_n<ES, V, MT, 0>(plan, src, dst, grid, s);
+    case 1: return launch_shifted_n<ES, V, MT, 1>(plan, src, dst, grid, s);
+    case 2: return launch_shifted_n<ES, V, MT, 2>(plan, src, dst, grid, s);
+    default: return launch_shifted_n<ES, V, MT, 3>(plan, src, dst, grid, s);
+  }
+}
+template <int ES, int V>
+static PreLaunch launch_shifted(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+  if (plan.transpose.n_micro == (uint32_t)plan.micro_per_thread * kBlock) {   // whole workgroups: the planner keeps them so
+    switch (plan.micro_per_thread) {
+      case 1: return launch_shifted_m<ES, V, 1>(plan, src, dst, grid, s);
+      case 2: return launch_shifted_m<ES, V, 2>(plan, src, dst, grid, s);
+      case 4: return launch_shifted_m<ES, V, 4>(plan, src, dst, grid, s);
+    }
+  }
+  return PreLaunch{hipErrorInvalidValue, "kernel selection (shifted tiles)"};
+}
+
 template <int ES, int V, int MT>
 static PreLaunch launch_ragged_m(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
   const unsigned char* sp = static_cast<const unsigned char*>(src);
@@ -1078,7 +1152,11 @@ static lc_status_t execute_with(const lc_plan& plan, const void* src, void* dst,
   } else {
     unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(plan.transpose.n_tiles, plan.grid_override > 0 ? (uint64_t)plan.grid_override : (uint64_t)cus * plan.wgs_per_cu));
     const int key = plan.tile_elem_bytes * 100 + plan.V;
-    if (plan.transpose.n_ragged > 0 || (plan.V == 1 && plan.tile_elem_bytes != 16)) {
+    if (plan.shifted) {
+      if (key == 404) pre = launch_shifted<4, 4>(plan, src, dst, grid, s);
+      else if (key == 208) pre = launch_shifted<2, 8>(plan, src, dst, grid, s);
+      else return LC_ERR_UNSUPPORTED_DTYPE;
+    } else if (plan.transpose.n_ragged > 0 || (plan.V == 1 && plan.tile_elem_bytes != 16)) {
       switch (key) {
         case 1601: pre = launch_ragged<16, 1>(plan, src, dst, grid, s); break;
         case 801: pre = launch_ragged<8, 1>(plan, src, dst, grid, s); break;

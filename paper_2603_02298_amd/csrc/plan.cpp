@@ -29,6 +29,7 @@ Tuning tuning_from_env() {
   t.grid = env_int("LC_TUNE_GRID", t.grid);
   t.early_loads = env_int("LC_TUNE_EARLY_LOADS", t.early_loads);
   t.gather = env_int("LC_TUNE_GATHER", t.gather);
+  t.shifted = env_int("LC_TUNE_SHIFTED", t.shifted);
   t.direct_queue = env_int("LC_TUNE_DIRECT_QUEUE", t.direct_queue);
   t.max_items = env_int("LC_TUNE_MAX_ITEMS", (int)t.max_items);
   if (const char* v = std::getenv("LC_TUNE_TILE")) {
@@ -306,8 +307,12 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
 // destination side.  Fills the plan and returns true, or leaves the class undecided.
 // ragged: tile extents are powers of two (times V along p and q) and need not divide the extents; the
 // grid has ceil(extent / tile) tiles along such a mode and the kernel checks coordinates at the edge.
+// shifted: likewise, for vectors at any alignment (V need not divide anything); the last tile along such a mode is moved back
+// until it ends with the mode, so the kernel without predicates runs them; whole workgroups only.
+enum class Tiling { Exact, Ragged, Shifted };
 static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, int q, int64_t n, const Tuning& tune, lc_plan* plan,
-                       bool ragged = false) {
+                       Tiling tiling = Tiling::Exact) {
+  const bool ragged = tiling != Tiling::Exact, shifted = tiling == Tiling::Shifted;
   const int nj = (int)J.size();
   // Tile size: up to 4 micro-tiles per lane (64 KiB of fp32), but never so large that fewer than
   // ~1024 tiles remain for the 256 CUs; growth stops early once both sides move >= 512-byte runs.
@@ -315,7 +320,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
   // the HBM peak on a 4001 x 4003 fp32 transpose against 26 % with 8 and 24 % with 1)
   const int max_per_lane = V == 1 ? (es == 16 ? 8 : 4) : 4;
   int64_t target = (int64_t)max_per_lane * kBlock;
-  while (target > 64 && n / (target * V * V) < 1024) target /= 2;
+  if (shifted) target = kBlock;   // one micro-tile per lane: more made no size faster by more than 3 %
+  while (!shifted && target > 64 && n / (target * V * V) < 1024) target /= 2;
   if (tune.micro_per_thread == 1 || tune.micro_per_thread == 2 || tune.micro_per_thread == 4 || (tune.micro_per_thread == 8 && V == 1))
     target = (int64_t)kBlock * tune.micro_per_thread;
   const int64_t enough_run_bytes = 512;
@@ -347,6 +353,7 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
       const int64_t e = J[(size_t)k].extent, old = t[(size_t)k];
       if (old >= e) continue;
       const int64_t grown = std::min<int64_t>(old * 2, e);
+      if (shifted && (grown != old * 2 || (k != p && k != q && e % grown != 0))) continue;
       t[(size_t)k] = grown;
       const bool fits = spans_fit(t) && micro_of(t) <= target && grown < (1 << 15);
       int64_t rs = run_length(J, src_order, t, true), rd = run_length(J, dst_order, t, false);
@@ -440,7 +447,15 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     ts = Layout::flat(tsm); td = Layout::flat(tdm); rs_ = Layout::flat(rsm); rd_ = Layout::flat(rdm);
     ok = ragged && ragged_modes.size() <= 2;
     for (int k : ragged_modes)   // whole vectors only: the extent along p and q is a multiple of V by the choice of V
-      if ((k == p || k == q) && J[(size_t)k].extent % V != 0) ok = false;
+      if ((k == p || k == q) && J[(size_t)k].extent % V != 0 && !shifted) ok = false;
+  }
+  if (shifted) {
+    int64_t m2 = 1;
+    for (int k = 0; k < nj; ++k) {
+      if (t[(size_t)k] > J[(size_t)k].extent) ok = false;   // a vector longer than its mode
+      m2 *= (k == p || k == q) ? t[(size_t)k] / V : t[(size_t)k];
+    }
+    if (m2 != kBlock && m2 != 2 * kBlock && m2 != 4 * kBlock) ok = false;
   }
   TransposeParams& P = plan->transpose;
   std::memset(&P, 0, sizeof(P));
@@ -546,15 +561,22 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     // Tile ids run fastest along the smallest SOURCE stride: resident workgroups then read one
     // contiguous region together (measured 1-3 % better than destination order; writes are combined
     // by the caches anyway).
-    if (tune.rest_order != 0)
+    // Shifted tiles share the cache lines at their edges: destination order keeps the two writers of a line on one XCD.
+    if (shifted ? tune.rest_order == 1 : tune.rest_order != 0)
       std::stable_sort(rest.begin(), rest.end(), [](const RM& x, const RM& y) { return x.a < y.a; });
     int64_t tiles = 1;
     for (const RM& r : rest) tiles *= r.ext;
     if (rest.size() > (size_t)kMaxModes || tiles >= (1ll << 31)) ok = false;
     if (ragged_modes.empty() ? tiles * (int64_t)P.n_micro * V * V != n : tiles * (int64_t)P.n_micro * V * V < n) ok = false;
     if (ok) {
-      P.n_ragged = (int32_t)ragged_modes.size();
+      P.n_ragged = shifted ? 0 : (int32_t)ragged_modes.size();
+      P.n_shifted = shifted ? (int32_t)ragged_modes.size() : 0;
+      P.rag_rest[0] = P.rag_rest[1] = -1;
       for (size_t j = 0; j < ragged_modes.size(); ++j) {
+        const JointMode& m = J[(size_t)ragged_modes[j]];
+        const int64_t tk = t[(size_t)ragged_modes[j]], over = (m.extent + tk - 1) / tk * tk - m.extent;
+        P.back_a[j] = over * m.a;
+        P.back_b[j] = over * m.b;
         P.rag_extent[j] = (uint32_t)J[(size_t)ragged_modes[j]].extent;
         P.rag_tile[j] = (uint32_t)t[(size_t)ragged_modes[j]];
         P.rag_rest[j] = -1;
@@ -665,12 +687,17 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     plan->dst_run_bytes = run_length(J, dst_order, t, false) * es;
     // nontemporal stores only when every store instruction covers whole 128-byte lines
     if (tune.nontemporal < 0 && plan->dst_run_bytes % 128 == 0) plan->nontemporal |= 2;
+    if (tune.nontemporal < 0 && shifted) plan->nontemporal = 0;   // the L2 merges the lines two tiles share
     // Measured on MI355X: HBM efficiency is best with ONE resident workgroup per CU (its next tile's
     // loads overlap its current tile's stores); short grids need more workgroups to fill the chip.
     int fit = (int)(160 * 1024 / std::max(1u, plan->lds_bytes));
     int want = P.n_tiles >= 16384 ? 1 : (P.n_tiles >= 4096 ? 2 : (P.n_tiles >= 2048 ? 3 : 4));
     // the ragged / element-wise kernel has no software pipeline: resident workgroups overlap each other instead
     if (P.n_ragged > 0 || (V == 1 && es != 16)) want = 8;
+    // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
+    // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
+    if (shifted) want = P.n_tiles >= 8192 ? 1 : (P.n_tiles >= 1280 ? 2 : 4);
+    plan->shifted = shifted;
     plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : std::max(1, std::min(std::min(8, fit), want));
     // Long grids of large tiles: workgroups drift apart over hundreds of tiles, and asking a device-side queue for the
     // next tiles (one request ahead) evens that out.  Measured on MI355X: one request per 64 KiB of tile data is best
@@ -685,9 +712,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     plan->queue_static_rounds = tune.queue_rounds >= 1 ? tune.queue_rounds : 1;
     plan->queue_counters = tune.queue_counters >= 1 ? tune.queue_counters : 1;
     plan->leftover_lead = tune.leftover_lead >= 0 ? tune.leftover_lead : 0;
-    plan->src_align = (unsigned)(V * es);
-    plan->dst_align = (unsigned)(V * es);
-    if (tune.early_loads != 0) fill_transpose_head(P, plan->micro_per_thread, &plan->head);
+    plan->src_align = plan->dst_align = (unsigned)(shifted ? es : V * es);
+    if (tune.early_loads != 0 && !shifted) fill_transpose_head(P, plan->micro_per_thread, &plan->head);
     return true;
   }
   return false;
@@ -886,16 +912,39 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
     }
     int V = common_pow2(cap, need);
     while (V >= 2 && !transpose_instantiated(es, V)) V /= 2;
+    // Shifted tiles: 16-byte vectors at any alignment, for sides that vectors or tiles do not divide.  They are taken where whole
+    // tiles of 16-byte vectors with cache-line runs and work for every lane do not exist, from 2^19 elements on (2^22 where only
+    // lanes are idle); below, every way takes a launch's time.  Measured on MI355X, before -> shifted, in us: 8001 x 8003 bf16
+    // (single elements) 167 -> 64, fp32 285 -> 118; 8002 x 8006 bf16 (4-byte vectors) 134 -> 62; 8000 x 8008 bf16 (ragged tiles)
+    // 70.5 -> 58; 4000^2 bf16 (80 of 256 lanes) 18.3 -> 12.0; 1001 x 1003 fp32 8.0 -> 4.7; NCHW -> NHWC 16 x 200 x 113^2 f16
+    // 94 -> 42, 64 x 256 x 14^2 f16 (8-byte vectors) 6.8 -> 5.0.  Whole tiles stay ahead: 4000^2 fp32 25.8 against 27.5.
+    auto take_shifted = [&]() {
+      if ((es != 2 && es != 4) || tune.max_vec_bytes > 0 || tune.tile.size() == (size_t)nj) return false;
+      lc_plan sh = *plan;
+      sh.cls = KernelClass::Generic;
+      if (!plan_tiled(J, es, 16 / es, p, q, n, tune, &sh, Tiling::Shifted)) return false;
+      *plan = sh;
+      return true;
+    };
+    if (tune.shifted > 0 && take_shifted()) return LC_OK;
+    const bool may_shift = tune.shifted < 0 && n >= (1 << 19);
+    if (may_shift && V * es < 16 && take_shifted()) return LC_OK;
     if (V >= 2) {
       const bool exact = plan_tiled(J, es, V, p, q, n, tune, plan);
       // Whole tiles need extents with small factors.  When they leave runs shorter than a cache line
       // (prime-ish extents) the ragged tiling is tried too and taken if its shorter run is at least twice
       // as long (its kernel is not pipelined: 4000 x 4000 fp32 runs at 63 % with whole 160 x 32 tiles and
       // at 57 % with ragged 128 x 64 tiles, but 8000 x 8008 bf16 at 34 % against 46 %).
-      if (exact && (std::min(plan->src_run_bytes, plan->dst_run_bytes) >= 128 || tune.tile.size() == (size_t)nj)) return LC_OK;
+      const bool long_runs = exact && std::min(plan->src_run_bytes, plan->dst_run_bytes) >= 128;
+      if (may_shift && (!long_runs || (n >= (1 << 22) && plan->transpose.n_micro < (uint32_t)kBlock))) {
+        lc_plan whole = *plan;
+        if (take_shifted()) return LC_OK;
+        *plan = whole;
+      }
+      if (exact && (long_runs || tune.tile.size() == (size_t)nj)) return LC_OK;
       lc_plan rag = *plan;
       rag.cls = KernelClass::Generic;
-      if (plan_tiled(J, es, V, p, q, n, tune, &rag, true) && rag.transpose.n_ragged > 0 &&
+      if (plan_tiled(J, es, V, p, q, n, tune, &rag, Tiling::Ragged) && rag.transpose.n_ragged > 0 &&
           (!exact || std::min(rag.src_run_bytes, rag.dst_run_bytes) >= 2 * std::min(plan->src_run_bytes, plan->dst_run_bytes))) {
         *plan = rag;
         return LC_OK;
@@ -906,7 +955,7 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       // No vector on one side (odd strides or extents): single elements through the same tiles (V = 1).
       // In destination order a lane would read one element per source line; a tile reads and writes runs.
       lc_plan rag = *plan;
-      if (ragged_instantiated(es, 1) && plan_tiled(J, es, 1, p, q, n, tune, &rag, true) &&
+      if (ragged_instantiated(es, 1) && plan_tiled(J, es, 1, p, q, n, tune, &rag, Tiling::Ragged) &&
           std::min(rag.src_run_bytes, rag.dst_run_bytes) >= 8 * es) {
         *plan = rag;
         return LC_OK;
@@ -1101,7 +1150,8 @@ std::string describe(const lc_plan& plan) {
     }
     s += " modelled_lds_conflicts=" + std::to_string(transpose_swizzle_cost(plan.transpose, plan.V, plan.tile_elem_bytes, 1u << 20, 64));
     s += " lane_split=" + std::to_string(plan.transpose.src_split) + "/" + std::to_string(plan.transpose.dst_split);
-    s += " ragged_modes=" + std::to_string(plan.transpose.n_ragged);
+    s += " ragged_modes=" + std::to_string(plan.transpose.n_ragged + plan.transpose.n_shifted);
+    if (plan.shifted) s += " shifted_tiles=1";
     s += " early_loads=" + std::to_string(plan.head.ctl & 1u);
     s += " src_run_bytes=" + std::to_string(plan.src_run_bytes) + " dst_run_bytes=" + std::to_string(plan.dst_run_bytes);
   } else if (plan.cls == KernelClass::Direct) {

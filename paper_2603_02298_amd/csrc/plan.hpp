@@ -36,6 +36,7 @@ struct Tuning {
   int leftover_lead = -1;      // transpose, fixed order: the tiles left after the last whole round go to this many leading workgroups
   int direct_queue = -1;       // direct: KiB of destination per chunk handed out on request; 0 = grid-stride order
   int gather = -1;             // direct: 1 = a small source stride along the destination-contiguous mode is read in whole 16-byte words (gather_kernel)
+  int shifted = -1;            // transpose: 1 = shifted tiles whatever the size, 0 = never
   int early_loads = -1;        // transpose: 0 = the first loads wait for the whole argument block (no TransposeHead)
 };
 Tuning tuning_from_env();
@@ -78,6 +79,7 @@ struct lc_plan {
   lc::TransposeParams transpose{};
   lc::TransposeHead head{};                // what the first loads need, for the kernel's leading arguments (ctl = 0: not in use)
   unsigned lds_bytes = 0;
+  bool shifted = false;                    // shifted tiles of vectors at any alignment (transpose.n_shifted modes the tile does not divide)
   bool swizzle_derived = false;            // the LDS slot layout came out of the park layout's bits (else: searched against the bank model)
   int64_t src_run_bytes = 0, dst_run_bytes = 0;
 

@@ -80,6 +80,7 @@ lc_status_t replay_on_host(const lc_plan& plan, const void* src, int64_t src_lo,
     const int V = plan.V, slot = V * es;
     std::vector<unsigned char> lds((size_t)plan.lds_bytes);
     const uint32_t lanes = (uint32_t)kBlock * (uint32_t)plan.micro_per_thread;
+    if (plan.shifted && (P.n_micro != lanes || P.n_ragged != 0)) return LC_ERR_INVALID_ARG;   // whole workgroups, no predicates
     if (plan.head.ctl & 1u) {
       // the first loads of a workgroup are addressed from the head alone: it has to agree with the argument block for every
       // lane and for every tile id a workgroup can start on
@@ -100,6 +101,7 @@ lc_status_t replay_on_host(const lc_plan& plan, const void* src, int64_t src_lo,
       int64_t sbase, dbase;
       uint32_t rem0 = 0x10000u, rem1 = 0x10000u;
       if (P.n_ragged > 0) tile_origin_ragged(P, tile, &sbase, &dbase, &rem0, &rem1);
+      else if (plan.shifted) tile_origin_shifted(P, tile, &sbase, &dbase);
       else tile_origin(P, tile, &sbase, &dbase);
       // load phase: lane u reads V vectors along p (one per step along q), parks V vectors along q
       for (uint32_t u = 0; u < lanes; ++u) {

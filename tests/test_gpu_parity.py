@@ -431,3 +431,19 @@ def test_tile_queue_on_several_streams(oracle, monkeypatch):
     torch.cuda.synchronize()
     for d in dsts:
         assert (d.cpu().numpy().view(src_bits.dtype) == want).all()
+
+
+@pytest.mark.parametrize("queue", [0, 1, 3])
+@pytest.mark.parametrize("dt,micro", [("f32", 1), ("f32", 2), ("f32", 4), ("bf16", 1), ("f16", 2), ("bf16", 4)])
+def test_shifted_tiles(oracle, monkeypatch, dt, micro, queue):
+    """Vectors at any alignment through tiles the sides need not hold a whole number of: the last tile along a side ends with
+    it.  Odd, even and padded sides, batches, both orders of the tiles, tiles by index and from the queue."""
+    monkeypatch.setenv("LC_TUNE_SHIFTED", "1")
+    monkeypatch.setenv("LC_TUNE_MICRO_PER_THREAD", str(micro))
+    monkeypatch.setenv("LC_TUNE_TILE_QUEUE", str(queue))
+    for n, (M, N, B, pad) in enumerate([(301, 517, 1, 0), (1025, 260, 3, 1), (258, 999, 2, 3), (256, 4100, 1, 2)]):
+        monkeypatch.setenv("LC_TUNE_REST_ORDER", str(n % 2))
+        monkeypatch.setenv("LC_TUNE_GRID", str((0, 16, 7, 24)[n]))
+        s = "(%d,%d,%d):(1,%d,%d)" % (M, N, B, M + pad, (M + pad) * N)
+        d = "(%d,%d,%d):(%d,1,%d)" % (M, N, B, N + pad, M * (N + pad))
+        assert "shifted_tiles=1" in _parity(oracle, s, d, dt, seed=n)

@@ -399,3 +399,29 @@ def test_gather_with_small_source_stride_moves_whole_words(oracle, monkeypatch):
     monkeypatch.delenv("LC_TUNE_GATHER")
     desc, _ = _check(oracle, "4096:3", "4096:1", "f32", "direct")
     assert "gather_stride" not in desc and "width_bytes=4 " in desc, desc
+
+
+@pytest.mark.parametrize("M,N,B,dt,micro", [(129, 130, 1, "f32", 1), (301, 517, 1, "bf16", 1), (64, 64, 3, "f32", 1), (65, 333, 2, "f16", 2), (1025, 36, 5, "bf16", 1),
+                                            (128, 257, 1, "f32", 4), (300, 131, 1, "bf16", 1), (67, 2048, 1, "f32", 2)])
+def test_shifted_tiles(oracle, monkeypatch, M, N, B, dt, micro):
+    # vectors at any alignment: the last tile along a mode the tile does not divide is moved back until it ends with the mode;
+    # every access of every tile stays inside buffers that are exactly as long as the layouts reach, padded sides included
+    monkeypatch.setenv("LC_TUNE_SHIFTED", "1")
+    monkeypatch.setenv("LC_TUNE_MICRO_PER_THREAD", str(micro))
+    for pad, flip in ((0, 0), (1, 0), (3, 1)):
+        s = "(%d,%d,%d):(1,%d,%d)" % (M, N, B, M + pad, (M + pad) * N)
+        d = "(%d,%d,%d):(%d,1,%d)" % (M, N, B, N + pad, M * (N + pad))
+        desc, conflicts = _check(oracle, *((d, s) if flip else (s, d)), dt, "transpose", seed=M + pad)
+        assert "shifted_tiles=1" in desc and "width_bytes=16" in desc and conflicts == 0, desc
+
+
+def test_shifted_tiles_are_the_choice_for_large_sides_that_vectors_do_not_divide(monkeypatch):
+    def desc(M, N, dt, **kw):
+        return lc.Plan("(%d,%d):(1,%d)" % (M, N, M), "(%d,%d):(%d,1)" % (M, N, N), dt, **kw).describe()
+    assert "shifted_tiles=1" in desc(8001, 8003, "bf16") and "shifted_tiles=1" in desc(4002, 4006, "f32") and "shifted_tiles=1" in desc(8000, 8008, "bf16")
+    assert "shifted_tiles=1" in desc(1024, 1024, "f32", src_align=4) and "shifted_tiles=1" in desc(4000, 4000, "bf16")
+    assert "shifted" not in desc(301, 517, "bf16") and "shifted" not in desc(4000, 4000, "f32") and "shifted" not in desc(1024, 1024, "f32")
+    assert "shifted" not in desc(4001, 4003, "b8") and "shifted" not in desc(2001, 2003, "b64")
+    assert "shifted" not in lc.Plan("(7,1000003):(1,7)", "(7,1000003):(1000003,1)", "bf16").describe()   # a side shorter than a vector
+    monkeypatch.setenv("LC_TUNE_SHIFTED", "0")
+    assert "V=1" in desc(8001, 8003, "bf16")
