@@ -694,6 +694,7 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     int want = P.n_tiles >= 16384 ? 1 : (P.n_tiles >= 4096 ? 2 : (P.n_tiles >= 2048 ? 3 : 4));
     // the ragged / element-wise kernel has no software pipeline: resident workgroups overlap each other instead
     if (P.n_ragged > 0 || (V == 1 && es != 16)) want = 8;
+    if (V == 1 && es == 16 && P.n_tiles < 16384) want = 4;
     // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
     // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
     if (shifted) want = P.n_tiles >= 8192 ? 1 : (P.n_tiles >= 1280 ? 2 : 4);
@@ -706,7 +707,9 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     // 16 bytes of LDS behind the tile carry the answer to the other lanes.  tile_queue = tiles per request, 0 = fixed order.
     const bool queue_fits = (uint64_t)(plan->lds_bytes + 16u) * (unsigned)plan->wgs_per_cu <= 160u * 1024u && !P.blocked &&
                             P.n_ragged == 0 && !(V == 1 && es != 16);   // the kernel without predicates only
-    const bool queue_pays = plan->lds_bytes >= 32u * 1024u && P.n_tiles >= 4096u;
+    // Word tiles (V = 1) have no transpose to hide a wait behind: four workgroups a CU in the fixed order up to 16384 tiles
+    // (heads 8 x 4096 x 32 x 64 f16, 4096 tiles: 56.6 us with two and the queue, 48.6; 8 x 8192 x 32 x 32 56.7 -> 49.0).
+    const bool queue_pays = plan->lds_bytes >= 32u * 1024u && P.n_tiles >= (V == 1 ? 16384u : 4096u);
     const int per_request = (int)std::max(1u, 65536u / std::max(1u, plan->lds_bytes));
     plan->tile_queue = queue_fits ? (tune.tile_queue >= 0 ? tune.tile_queue : (queue_pays ? per_request : 0)) : 0;
     plan->queue_static_rounds = tune.queue_rounds >= 1 ? tune.queue_rounds : 1;
@@ -999,12 +1002,13 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
   // The common vector keeps whole 16-byte words together on both sides (p = q), but it is short: in
   // destination order the source would be read in pieces of K elements.  With the word as the
   // element the copy is a permutation of words, and a tile through LDS (V = 1: nothing to transpose
-  // inside a word) reads and writes runs of many words.  Measured on MI355X (2^25..2^27 bf16 elements):
-  // 128-byte pieces 59 % of the HBM peak in destination order, 71 % through tiles; 256-byte pieces
-  // run at 72-73 % either way and stay with the direct class.
+  // inside a word) reads and writes runs of many words.  Measured on MI355X (attention heads, us): pieces of up to 128 bytes
+  // through tiles as fast as in destination order or faster (8 x 8192 x 32 x 32 f16 49.0 against 49.7, 8 x 4096 x 32 x 64 48.6
+  // against 47.4); longer pieces (4 x 3000 x 32 x 96 31.2 against 29.4) and copies too short for tiles of 16 KiB (8 x 668 x
+  // 12 x 64 5.9 against 5.1) go in destination order.
   {
     const int64_t direct_run_bytes = q >= 0 ? J[(size_t)q].extent * es : es;
-    bool stage = VEC * es == 16 && q >= 0 && p == q && nj >= 3 && direct_run_bytes < 256 && tune.force_class != 1;
+    bool stage = VEC * es == 16 && q >= 0 && p == q && nj >= 3 && direct_run_bytes <= (tune.force_class == 2 ? 255 : 128) && tune.force_class != 1;
     for (int k = 0; k < nj && stage; ++k)
       if (J[(size_t)k].a == 0) stage = false;   // broadcasts are looped inside a lane by the direct class
     if (stage) {
@@ -1022,7 +1026,7 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       lc_plan staged = *plan;
       if (W.size() >= 2 && plan_tiled(W, 16, 1, pw, qw, n / VEC, tune, &staged) &&
           (tune.force_class == 2 || (staged.src_run_bytes >= 4 * direct_run_bytes && staged.dst_run_bytes >= 4 * direct_run_bytes &&
-                                     staged.transpose.n_tiles >= 256))) {
+                                     staged.transpose.n_tiles >= 256 && staged.micro_per_thread >= 4))) {
         *plan = staged;
         return LC_OK;
       }
@@ -1085,6 +1089,10 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
   // about 16 KiB of accesses in flight per CU measured best on MI355X: unroll x workgroups = 64 / width
   const int W = VEC * es;
   int dflt_unroll = W >= 16 ? 2 : (W >= 4 ? 4 : 8), dflt_wgs = W >= 8 ? 3 : 4;   // 3 x 256 CUs: a grid that is not a power of two
+  // Several joint modes in whole words: the index arithmetic wants more wavefronts with one item each (heads 6 x 5775 x 32 x 128
+  // f16 99.6 -> 96.3 us, 4 x 1024 x 16 x 128 9.5 -> 7.9, 8 x 2048 x 8 x 96 12.1 -> 10.6), up to copies of half a GiB, which run
+  // as before (8 x 8192 x 32 x 128 181 us against 186).
+  if (W >= 16 && P.n_modes > 1 && P.loop_extent == 1 && items * W < (1ll << 29)) { dflt_unroll = 1; dflt_wgs = 5; }
   plan->unroll = (tune.unroll == 1 || tune.unroll == 2 || tune.unroll == 4 || tune.unroll == 8) ? tune.unroll : dflt_unroll;
   plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : dflt_wgs;
   // Contiguous copies of 2 GiB and more per side: the grid-stride order lets workgroups drift apart, chunks of 32 KiB handed
