@@ -368,7 +368,9 @@ class Plan:
 def lc_copy(src_ptr, src_layout, dst_ptr, dst_layout, dtype, stream=0):
     """COPY on the GPU: dst(i) = src(i) for device pointers src_ptr / dst_ptr."""
     sl, dl = _as_layout(src_layout), _as_layout(dst_layout)
-    _check(lib().lc_copy(src_ptr, sl._h, dst_ptr, dl._h, DTYPES[dtype], stream), "lc_copy(%s -> %s)" % (sl, dl))
+    status = lib().lc_copy(src_ptr, sl._h, dst_ptr, dl._h, DTYPES[dtype], stream)
+    if status != 0:   # (printing two layouts takes longer than a small copy)
+        raise LayoutCopyError(status, "lc_copy(%s -> %s)" % (sl, dl))
 
 
 def copy_tensor(src, src_layout, dst, dst_layout, dtype=None, src_origin=0, dst_origin=0):
@@ -434,8 +436,9 @@ class GemmPlan:
 def lc_gemm(a_ptr, a_layout, b_ptr, b_layout, c_ptr, c_layout, ab_dtype="bf16", stream=0):
     """GEMM on the GPU for device pointers: C(m,n) += A(m,k) * B(n,k)."""
     la, lb, lc_ = _as_layout(a_layout), _as_layout(b_layout), _as_layout(c_layout)
-    _check(lib().lc_gemm(a_ptr, la._h, b_ptr, lb._h, c_ptr, lc_._h, DTYPES[ab_dtype], stream),
-           "lc_gemm(%s, %s, %s)" % (la, lb, lc_))
+    status = lib().lc_gemm(a_ptr, la._h, b_ptr, lb._h, c_ptr, lc_._h, DTYPES[ab_dtype], stream)
+    if status != 0:
+        raise LayoutCopyError(status, "lc_gemm(%s, %s, %s)" % (la, lb, lc_))
 
 
 def lc_mfma_fragment_layout(which):

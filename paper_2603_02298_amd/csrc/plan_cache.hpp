@@ -1,14 +1,39 @@
-// Plans of recent one-shot calls (lc_copy, lc_gemm), keyed by everything a plan depends on: the layouts' text, the element
+// Plans of recent one-shot calls (lc_copy, lc_gemm), keyed by everything a plan depends on: the layouts' contents, the element
 // type, the pointers' alignment and the tuning settings in force.  Planning is pure host work, so a hit changes nothing
 // but the time of the call.  Thread-safe; bounded: when full it is emptied (callers with many distinct layouts should
 // hold plan handles themselves).
 #pragma once
+#include <unistd.h>
+
+#include <cstring>
 #include <memory>
 #include <mutex>
 #include <string>
 #include <unordered_map>
 
+#include "layout.hpp"
+
 namespace lc {
+
+// Is any tuning setting in the environment?  One pass over its names; asked for one by one the twenty-odd settings cost a call
+// more than the rest of its look-up.
+inline bool tuning_in_environment() {
+  for (char** e = environ; e && *e; ++e)
+    if (std::strncmp(*e, "LC_TUNE_", 8) == 0) return true;
+  return false;
+}
+
+// Keys are bytes: numbers as they lie in memory, sequences behind their lengths, so that no two different keys read the same.
+inline void key_number(std::string* key, int64_t v) { key->append(reinterpret_cast<const char*>(&v), sizeof(v)); }
+inline void key_layout(std::string* key, const Layout& L) {
+  key_number(key, (int64_t)L.profile.size());
+  key->append(reinterpret_cast<const char*>(L.profile.data()), L.profile.size() * sizeof(L.profile[0]));
+  key_number(key, (int64_t)L.leaves.size());
+  for (const Mode& m : L.leaves) {
+    key_number(key, m.extent);
+    key_number(key, m.stride);
+  }
+}
 
 template <typename Plan>
 class PlanCache {
