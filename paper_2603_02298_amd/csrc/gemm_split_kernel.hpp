@@ -10,8 +10,8 @@
 // TN = 16 (at most 16 columns, contiguous along k): the 16 rows of B stand twice in their fragment, so no load is spent on
 // rows that do not exist and the LDS they would take deepens the ring.
 // What bounds it: the weights' way from HBM for a thin M (each element is used once), launch and latency for small problems.
-// Measured on MI355X (bf16, whole 128 x 128 tiles -> this kernel): 512^3 11.1 -> 4.5 us, 16 x 8192 x 8192 78.2 -> 27.2 us
-// (1.7 -> 5.0 TB/s), 1024^3 17.6 -> 8.3 us, 128 x 2048 x 2048 25.2 -> 6.4 us.
+// Measured on MI355X (bf16, whole 128 x 128 tiles -> this kernel): 512^3 11.1 -> 4.5 us, 16 x 8192 x 8192 78.2 -> 26.0 us
+// (1.7 -> 5.2 TB/s), 1024^3 17.6 -> 8.3 us, 128 x 2048 x 2048 25.2 -> 6.4 us.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -2,15 +2,17 @@
 // operands that go straight into LDS, on problems with tiles for every CU but a k loop too short, or sides too small, for
 // the 256 x 256 kernel.
 //
-// Four wavefronts own a BM x BN tile, wavefront (wm, wn) a quarter of it.  LDS holds STAGES pairs of operand tiles; one
-// barrier per k tile, after which the tile before it is overwritten by the one STAGES - 1 ahead.  Two or more workgroups
+// Four wavefronts own a BM x BN tile, wavefront (wm, wn) a quarter of it.  LDS holds two pairs of operand tiles; one
+// barrier per k tile, after which the pair before it is overwritten by the next.  Two or more workgroups
 // share a CU: one's start, its C update and its waits at the barrier lie under the others' products.  The old values of C
 // are asked for before the k loop, the sums pass through LDS and C is updated in whole runs.
 // What bounds it: for a short k loop C's way from and to HBM (128 x 100352 x 64: 5.4-6.3 TB/s), for a longer one LDS (a 64 x 64
 // quarter per wavefront reads 128 bytes per clock and CU at the matrix cores' full rate, all that LDS gives).
 // Measured on MI355X (bf16, whole ring kernel of 128 x 128 tiles -> this kernel's 128 x 128): 16 x (1000 x 1504 x 776) 100 -> 83 us,
 // a 3 x 3 convolution of 128 x 100352 x 576 39 -> 34 us (128 x 64 tiles: 32.6), 4096^3 158 -> 149 us.  Three stages and more
-// (fewer workgroups per CU) measured slower wherever there are more tiles than CUs.
+// (fewer workgroups per CU) measured slower wherever there are more tiles than CUs, and gained 0-7 % where there are not; so did
+// 256 x 128 tiles of eight wavefronts (the batched problem 82, but 4 x 1024^3 16.5 -> 21.5) and old values of C asked for two
+// units per k step (82, but 4 x 1024^3 16.5 -> 18.1).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -27,11 +29,9 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
                                                                                                    const uint16_t* __restrict__ B, float* __restrict__ C) {
   constexpr int FM = BM / 64, FN = BN / 64, KSTEPS = kGemmBK / 16;
   constexpr uint32_t A_BYTES = BM * 128u, STAGE = (BM + BN) * 128u;
-  constexpr int R = (BM + BN) / 32;   // load instructions per wavefront and k tile
-  static_assert(STAGES >= 2 && BM * BN * 4 <= STAGES * (BM + BN) * 128, "the sums of the tile fit the ring");
+  static_assert(STAGES == 2 && BM * BN * 4 <= STAGES * (BM + BN) * 128, "the sums of the tile fit the ring");
   constexpr bool ANY = gemm_load_is_any(A_LOAD);
   static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
-  static_assert((STAGES - 2) * R < 64, "vmcnt has six bits");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   touch_kernel_arguments<(int)sizeof(GemmParams) + 24>();
 
@@ -80,7 +80,6 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
   const uint32_t a_at = wave * (BM * 32u), b_at = A_BYTES + wave * (BN * 32u);   // this wavefront's quarter of either tile
   if constexpr (ANY) {
     // Through registers: k tile t + 1 is parked in the stage k tile t - 1 leaves, k tile t + 2 asked for, then k tile t multiplied.
-    static_assert(STAGES == 2, "registers hold the third k tile");
     la.fetch(0u);
     lb.fetch(0u);
     la.park(lds + a_at, 0u);
@@ -118,21 +117,14 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
         kb.next(P.b_k, asked);
       }
     };
-    static_for<STAGES - 1>([&](auto s) {
-      if ((uint32_t)s < P.k_tiles) request((uint32_t)s * STAGE);
-    });
-    uint32_t at = 0, free_at = (STAGES - 1) * STAGE;   // the stage being multiplied, the one before it
+    request(0u);
     for (uint32_t t = 0; t < P.k_tiles; ++t) {
-      // k tile t has landed: all but the STAGES - 2 younger ones (towards the end there are fewer), for every wavefront past
-      // the barrier, which also has its fragments of k tile t - 1 in registers: that stage may be filled again
-      constexpr int N = (STAGES - 2) * R;
-      if (t + (STAGES - 1) <= P.k_tiles) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
-      else __builtin_amdgcn_s_waitcnt(0x0070);
+      // k tile t has landed, for every wavefront past the barrier, which also has its fragments of k tile t - 1 in registers:
+      // that stage may be filled again
+      __builtin_amdgcn_s_waitcnt(0x0070);
       lds_barrier();
-      if (asked < P.k_tiles) request(free_at);
-      multiply(lds + at);
-      free_at = at;
-      at = at + STAGE == STAGES * STAGE ? 0u : at + STAGE;
+      if (asked < P.k_tiles) request((asked & 1u) * STAGE);
+      multiply(lds + (t & 1u) * STAGE);
     }
   }
 
