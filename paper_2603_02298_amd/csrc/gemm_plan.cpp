@@ -213,13 +213,16 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     // its area, times what its k loop costs per product against the 128 x 128 stream kernel's: smaller tiles read more of LDS
     // per product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1, 1.2, 1.3 and 64 x 64: 1.3,
     // 1.4, 1.65 below K = 1024, below 2048 and from there on); a lone workgroup on a CU has nobody to cover its waits (1.25,
-    // 1.25, 1.5); the 256 x 256 kernel reads least, but its short k loops wait (1.0 below K = 2048, 0.9 below 3000, 0.8 from
-    // there on), and with fewer tiles than CUs it runs at a higher clock (down to 0.7).
+    // 1.25, 1.5); the 256 x 256 kernel reads least, but its short k loops wait and nothing covers its C update (1.1 below K = 768,
+    // 1.0 below 2048, 0.9 below 3000, 0.8 from there on), and with fewer tiles than CUs it runs at a higher clock (down to 0.7).
     // Measured on MI355X (bf16; 128 x 128, 128 x 64, 64 x 64 stream, 256 x 256, in us): 2048^3 27.4, 26.1, 29.2, 55;
     // 1536^2 x 4096 42.6, 39.4, 35.2, 87; 16 x (1000 x 1504 x 776) 83, 97, 110, 98; 128 x 100352 x 576 (convolution) 34.1,
     // 32.6, 34.2, 57.5; 4 x 1024^3 18.2, 16.5, 17.8, 39.6; 4096^2 x 1024 49, 56, 62, 52; 4096^3 149.5, 187, 232, 129;
     // 5000^2 x 3000 240, 296, 347, 195; 6144 x 3072 x 2048 100, 115, 139, 132; 3000^3 96, 95, 120, 77.5;
     // 2200^2 x 8192 113, 119, 146, 156; 4096 x 2048 x 4096 71, 96, 112, 89; 1100^2 x 8192 77, 67, 60, 145.
+    // Short k loops with 256 tiles of 256 x 256 and more (128 x 128 stream, 256 x 256): 4096^2 x 64 23.3, 32.7, x 256 29.9, 36.2,
+    // x 512 37.9, 41.8, x 1024 51.5, 52.9, x 1536 70.4, 69.0; 8192^2 x 256 120, 149; 16 x 2048^2 x 256 136, 150;
+    // 32 x 1024^2 x 512 87, 94; 5000^2 x 1000 104, 102.
     struct Choice { int tm, tn; double per_product; };
     const double half = K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3, quarter = K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65, lone = K < 2048 ? 1.25 : 1.5;
     const Choice choices[] = {{128, 128, 1.0}, {128, 64, half}, {64, 128, half}, {64, 64, quarter}};
@@ -230,7 +233,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     const Choice* best = nullptr;
     for (const Choice& c : choices)
       if (!best || cost(c, true) < cost(*best, true)) best = &c;
-    const Choice big = {256, 256, (K < 2048 ? 1.0 : K < 3000 ? 0.9 : 0.8) * std::min(1.0, 0.7 + 0.3 * (double)tiles_of(256, 256) / 256.0)};
+    const Choice big = {256, 256, (K < 768 ? 1.1 : K < 2048 ? 1.0 : K < 3000 ? 0.9 : 0.8) * std::min(1.0, 0.7 + 0.3 * (double)tiles_of(256, 256) / 256.0)};
     if (direct && free_choice && cost(big, false) <= cost(*best, true)) take(256, 256, 0, 0);
     else if (t_env == 128) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);

@@ -268,7 +268,7 @@ def test_walk_split_kernel(oracle, name, sizes, tile):
     _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, [] if tile == 3216 and name != "tn" else ["tile=%sx64 split_waves=" % shape])
 
 
-def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile():
+def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile_and_the_ring_for_long_k():
     def tile(M, N, K, L=1):
         d = lc.GemmPlan("(%d,%d,%d):(%d,1,%d)" % (M, K, L, K, M * K), "(%d,%d,%d):(%d,1,%d)" % (N, K, L, K, N * K), "(%d,%d,%d):(1,%d,%d)" % (M, N, L, M, M * N)).describe()
         return d.split("tile=")[1].split()[0], "split_waves" in d
@@ -276,6 +276,8 @@ def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile():
     assert tile(512, 512, 512) == ("32x32x64", True) and tile(516, 512, 512) == ("64x32x64", True) and tile(512, 513, 512) == ("32x64x64", True)
     assert tile(1024, 1024, 64) == ("64x64x64", True) and tile(1024, 1025, 64)[1] is False
     assert tile(64, 64, 64, 64) == ("32x32x64", True) and tile(64, 64, 64, 257)[1] is False
+    # with tiles for every CU either way: the stream kernel's where C's update outweighs the k loop, the ring's from K = 768 on
+    assert tile(4096, 4096, 760) == ("128x128x64", False) and tile(4096, 4096, 768) == ("256x256x64", False)
 
 
 def test_narrow_k_major_tiles_are_free_of_bank_conflicts():
