@@ -184,13 +184,9 @@ struct AnyTileLoader {
     t = lane;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      uint32_t row, k, move;
+      uint32_t row, k;
       unit((uint32_t)i, &row, &k);
-      if constexpr (LOAD == kLoadKAny) {
-        off[i] = 2u * (gemm_mode_eval(rmode, row0 + row < extent ? row0 + row : extent - 1u) + k);
-      } else {   // (with K below the k tile the k rows past it read the last one: no offset leaves the operand)
-        off[i] = 2u * gemm_mode_eval(rmode, gemm_any_start(row0 + row, extent, &move)) + (k < K ? k : K - 1u) * k_step;
-      }
+      off[i] = gemm_any_offset(LOAD, rmode, row0 + row, extent, k, K, k_step);
     }
   }
   // asks for k tile kt
@@ -198,16 +194,11 @@ struct AnyTileLoader {
     const uint32_t k0 = kt * kGemmBK;
     const unsigned char* p = base + (uint64_t)k0 * k_step;   // (uniform)
     if (k0 + kGemmBK > K) {   // the short last k tile: what lies past K is read where it ends with K
-      uint32_t back[R];   // bytes
+      uint32_t back[R];
       static_for<R>([&](auto i) {
-        uint32_t row, k, move;
+        uint32_t row, k;
         unit((uint32_t)i, &row, &k);
-        if constexpr (LOAD == kLoadKAny) {
-          back[i] = 2u * (k0 + k - gemm_any_start(k0 + k, K, &move));
-        } else {
-          k = k0 + (k < K ? k : K - 1u);
-          back[i] = k < K ? 0u : (k - (K - 1u)) * k_step;
-        }
+        back[i] = gemm_any_back(LOAD, k0, k, K, k_step);
       });
       static_for<R>([&](auto i) { regs[i] = *reinterpret_cast<const u32x4_any*>(p + ((int64_t)off[i] - (int64_t)back[i])); });
     } else {

@@ -158,6 +158,22 @@ LC_HD uint32_t gemm_any_start(uint32_t at, uint32_t extent, uint32_t* move) {
   *move = at < extent ? at - from : 0u;
   return from;
 }
+// Where a lane reads unit (row, k) of the k tile that starts at k0, in bytes from the operand's first element:
+// k0 * k_step + offset - back.  The offset is worked out once per workgroup and stays inside the operand for every k of a
+// k tile (with K below the k tile it is already the place the last vector, or the last k row, is read at), so it fits 32 bits
+// however close to 2^31 elements the operand ends; back is zero but in the short last k tile.
+// row: of the vector's first element in the whole mode; k: its k inside the k tile; k_step: bytes from one k to the next
+LC_HD uint32_t gemm_any_offset(int32_t load, const GemmMode& rmode, uint32_t row, uint32_t extent, uint32_t k, uint32_t K, uint32_t k_step) {
+  uint32_t move;
+  if (load == kLoadKAny) return 2u * (gemm_mode_eval(rmode, row < extent ? row : extent - 1u) + (K < (uint32_t)kGemmBK ? gemm_any_start(k, K, &move) : k));
+  return 2u * gemm_mode_eval(rmode, gemm_any_start(row, extent, &move)) + (k < K ? k : K - 1u) * k_step;
+}
+LC_HD uint32_t gemm_any_back(int32_t load, uint32_t k0, uint32_t k, uint32_t K, uint32_t k_step) {
+  uint32_t move;
+  if (k0 + kGemmBK <= K || K < (uint32_t)kGemmBK) return 0u;
+  if (load == kLoadKAny) return 2u * (k0 + k - gemm_any_start(k0 + k, K, &move));
+  return k0 + k < K ? 0u : (k0 + k - (K - 1u)) * k_step;
+}
 LC_HD uint32_t gemm_clamp_row(int32_t load, uint32_t row, uint32_t extent) {
   const uint32_t last = load == kLoadRVec || load == kLoadRDirect ? extent - 8u : extent - 1u;
   return row < last ? row : last;

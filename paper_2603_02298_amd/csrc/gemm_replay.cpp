@@ -98,6 +98,10 @@ struct Walker {
           }
           const uint32_t lds_at = ((tid >> 6) * R + i) * 1024u + (tid & 63u) * 16u, at_k = kt * kGemmBK + k;
           if (lds_at != (load == kLoadKAny ? gemm_lds_offset(row, k / 8u) : gemm_rdirect_lds_offset(BR, k, row))) { ok = false; return; }
+          // the address as the lane forms it, in its own 32-bit steps; it has to be the place the two modes name
+          const uint32_t k_step = 2u * kmode.lead_stride;
+          const int64_t bytes = (int64_t)((uint64_t)(kt * kGemmBK) * k_step) + gemm_any_offset(load, rmode, row0 + row, extent, k, P.K, k_step) -
+                                (int64_t)gemm_any_back(load, kt * kGemmBK, k, P.K, k_step);
           int64_t off;
           if (load == kLoadKAny) {
             off = (int64_t)gemm_mode_eval(rmode, row0 + row < extent ? row0 + row : extent - 1u) + gemm_any_start(at_k, P.K, &k_move);
@@ -107,6 +111,7 @@ struct Walker {
             for (uint32_t e = 0; e < 8; ++e)   // eight neighbours in memory
               if (gemm_mode_eval(rmode, from + e) != gemm_mode_eval(rmode, from) + e) { ok = false; return; }
           }
+          if (bytes != 2 * off) { ok = false; return; }
           if (off < 0 || off + 8 > elems || move > 8u || k_move > 8u) { ok = false; return; }
           uint16_t v[8];
           std::memcpy(v, base + off, 16);

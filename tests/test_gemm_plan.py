@@ -325,6 +325,32 @@ def test_walk_vectors_at_any_alignment(oracle, case, tile):
         assert text.count("elements(in unaligned") == 2, text
 
 
+@pytest.mark.parametrize("which,layout,expect", [("a", "(2,9):(2147483638,1)", "k-vectors"), ("a", "(2,56):(2147483591,1)", "k-vectors"),
+                                                 ("a", "(9,9):(1,268435454)", "row-vectors"), ("b", "(2,9):(2147483638,1)", "k-vectors")])
+def test_walk_vectors_at_any_alignment_of_an_operand_that_ends_at_the_offset_limit(which, layout, expect):
+    # K below a k tile, and the operand's last offset just below 2^31: the lanes past K form no address past the operand, not
+    # even on the way (the walk takes the device's 32-bit steps); the pages the walk does not touch are never made
+    L = lc.Layout(layout)
+    rows, K = (9, 9) if layout.startswith("(9,9)") else (2, int(layout[1:].split(")")[0].split(",")[1]))
+    far = np.zeros(L.cosize, dtype=np.uint16)
+    assert 2 ** 31 - 64 < far.size < 2 ** 31
+    offsets = np.array([[L(r + rows * k) for k in range(K)] for r in range(rows)])
+    values = np.random.default_rng(K).integers(-4, 5, (rows, K))
+    far[offsets] = (values.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)   # bf16
+    near = np.random.default_rng(1).integers(-4, 5, (3, K))
+    near_bits = (near.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16).ravel()
+    near_layout = "(3,%d):(%d,1)" % (K, K)
+    c = np.zeros(rows * 3, dtype=np.float32)
+    if which == "a":
+        plan = lc.GemmPlan(layout, near_layout, "(%d,3):(1,%d)" % (rows, rows))
+        plan.debug_replay_on_host(far, near_bits, c)
+    else:
+        plan = lc.GemmPlan(near_layout, layout, "(3,%d):(%d,1)" % (rows, rows))
+        plan.debug_replay_on_host(near_bits, far, c)
+    assert "(in unaligned %s)" % expect in plan.describe(), plan.describe()
+    assert (c.reshape(3, rows).T == values @ near.T).all()
+
+
 def test_which_operands_take_vectors_at_any_alignment():
     def loads(*layouts, **kw):
         d = lc.GemmPlan(*layouts, **kw).describe()

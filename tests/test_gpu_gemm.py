@@ -279,3 +279,18 @@ def test_gemm_vectors_at_any_alignment(oracle, tile, values):
         want = oracle.gemm(a64, w.a_layout, b64, w.b_layout, c0.astype(np.float64), w.c_layout)
         bound = oracle.gemm(np.abs(a64), w.a_layout, np.abs(b64), w.b_layout, np.abs(c0).astype(np.float64), w.c_layout)
         assert (np.abs(c_t.cpu().numpy().astype(np.float64) - want) <= (0 if values == "ints" else w.K * 2.0 ** -23 * bound)).all()
+
+
+@pytest.mark.parametrize("layout,rows,K", [("(2,9):(2147483638,1)", 2, 9), ("(9,9):(1,268435454)", 9, 9)])
+def test_gemm_vectors_at_any_alignment_of_an_operand_that_ends_at_the_offset_limit(layout, rows, K):
+    # K below a k tile and a last offset just below 2^31 (the walk of the same layouts checks every address on the host)
+    L, dev = lc.Layout(layout), torch.device("cuda:0")
+    far = torch.zeros(L.cosize, dtype=torch.bfloat16, device=dev)
+    index = torch.tensor([[L(r + rows * k) for k in range(K)] for r in range(rows)], device=dev)
+    values = torch.randint(-4, 5, (rows, K), device=dev)
+    far[index] = values.to(torch.bfloat16)
+    near = torch.randint(-4, 5, (3, K), device=dev)
+    c = torch.zeros(rows * 3, device=dev)
+    print("case", layout, flush=True)
+    lc.gemm_tensor(far, layout, near.to(torch.bfloat16).ravel(), "(3,%d):(%d,1)" % (K, K), c, "(%d,3):(1,%d)" % (rows, rows))
+    assert (c.reshape(3, rows).T.cpu() == (values.cpu().float() @ near.cpu().float().T)).all()
