@@ -722,6 +722,46 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
   return false;
 }
 
+// How many times the elements that the plain plan's tiles cover (its idle lanes included) the shifted tiles may cover.  What
+// they are better at is 16-byte accesses in place of narrow ones and full workgroups; what they cost is elements moved twice and
+// runs cut at a tile's edge, which counts for more the wider the plain plan's vectors are.  Measured on MI355X over 1500 copies
+// of 2^19 to 2^27 elements (transposes with a side of 5 to 520, of random sides and pitches, NCHW <-> NHWC; both directions),
+// in us, plain -> shifted, share of elements moved twice in brackets:
+//   single 2-byte elements: always ahead but once (17 x 1973760 [1.88] 81 -> 54, 594 x 9 x 56^2 [2.3] 45 -> 28); 4 bytes wide: ahead
+//   to about 1.8 for bf16 pairs and 2.0 for fp32 (bf16 34 x 780154 pitch 98 [1.88] 51 -> 66; fp32 2377 x 9 x 28^2 [2.3] 52 -> 57,
+//   65 x 32256 [1.97] 12.3 -> 6.2);
+//   8 bytes wide: whole tiles to 1.1 (bf16 100 x 335488 [1.28] 40.9 -> 39.7, but 12 x 2796160 [1.33] 39 -> 47, 3 x 100 x 224^2
+//   [1.28] 15.2 -> 22.1), further where runs are short and lanes idle (100 x 20928 [1.28] 8.2 -> 5.2); ragged tiles to 1.2
+//   beyond their own idle lanes (648 x 132 x 14^2 [2.53, idle 2.53] 36 -> 22, but 20 x 2175752 [1.6] 57 -> 67);
+//   16 bytes wide, ragged: bf16 to 1.2 (2944 x 2320 [1.05] 11.5 -> 7.2, 8000 x 8008 70.5 -> 58; 160 x 103488 [1.33 times the idle] 19 -> 22), fp32
+//   to 1.1 in tiles that leave lanes idle, 1.05 in full ones of copies of 2^23 elements (316 x 22184 15.7 -> 18.1, 3356 x 11812 83 -> 72);
+//   16 bytes wide, whole tiles: full workgroups stay ahead (4000^2 fp32 25.8 -> 27.5, 136 x 246720 bf16 [1.88] 27 -> 46), and so do bf16
+//   ones from 64 lanes on (83 x 256 x 28^2 [1.14] 15.7 -> 21.8); fewer lanes, or fp32 without elements moved twice: shifted
+//   (4000^2 bf16 with 80 lanes and 64-byte runs 18.3 -> 12.0, 832 x 10512 [1.09] 11.8 -> 10.3, 64 x 280928 fp32 49 -> 31), and bf16
+//   sources of one or two vectors a row (8 x 4040080 50 -> 30, NHWC -> NCHW 20 x 16 x 224^2 17.9 -> 15.1).
+// Copies below 2^19 elements take a launch's time either way.
+constexpr int64_t kShiftedMinElems = 1 << 19;
+static double narrow_shifted_limit(int width, int es, bool ragged) {
+  if (width <= 2) return 2.5;
+  if (width == 4) return es == 2 ? 1.8 : 2.0;
+  return ragged ? 1.2 : 1.1;
+}
+static double shifted_limit(const lc_plan& plain_plan, bool plain, int es, int64_t n) {
+  if (!plain) return 1.0;   // (what is left would be single elements in destination order)
+  const TransposeParams& P = plain_plan.transpose;
+  const int width = plain_plan.V * es;
+  const bool ragged = P.n_ragged > 0, short_runs = std::min(plain_plan.src_run_bytes, plain_plan.dst_run_bytes) < 128;
+  const bool idle = P.n_micro < (uint32_t)kBlock, mostly_idle = P.n_micro < (uint32_t)kBlock / 4;
+  if (width < 16) return width == 8 && short_runs && idle ? 1.6 : narrow_shifted_limit(width, es, ragged);
+  if (ragged) return es == 2 ? 1.2 : idle ? 1.1 : n >= (1 << 23) ? 1.05 : 0.0;
+  if (!idle) return 0.0;
+  if (short_runs) return mostly_idle ? 1.3 : es == 2 ? 1.0 : 1.1;
+  if (n < (1 << 22)) return 0.0;
+  const int64_t row_bytes = plain_plan.joint[(size_t)plain_plan.p_mode].extent * es;
+  const bool few_vectors = row_bytes <= 32 && plain_plan.src_run_bytes > row_bytes;   // (rows that continue each other)
+  return es == 2 ? (mostly_idle ? 1.3 : few_vectors ? 1.02 : 0.0) : 1.01;
+}
+
 // a3: refine both shapes to one shape F by composing each layout with the identity layout of F (Sec. 3.3.1); then every
 // mode of F has one stride on each side.  False when the shapes have no common refinement or a composition is not admissible.
 static bool joint_modes(const Modes& S, const Modes& D, std::vector<JointMode>* J) {
@@ -915,56 +955,85 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
     }
     int V = common_pow2(cap, need);
     while (V >= 2 && !transpose_instantiated(es, V)) V /= 2;
-    // Shifted tiles: 16-byte vectors at any alignment, for sides that vectors or tiles do not divide.  They are taken where whole
-    // tiles of 16-byte vectors with cache-line runs and work for every lane do not exist, from 2^19 elements on (2^22 where only
-    // lanes are idle); below, every way takes a launch's time.  Measured on MI355X, before -> shifted, in us: 8001 x 8003 bf16
-    // (single elements) 167 -> 64, fp32 285 -> 118; 8002 x 8006 bf16 (4-byte vectors) 134 -> 62; 8000 x 8008 bf16 (ragged tiles)
-    // 70.5 -> 58; 4000^2 bf16 (80 of 256 lanes) 18.3 -> 12.0; 1001 x 1003 fp32 8.0 -> 4.7; NCHW -> NHWC 16 x 200 x 113^2 f16
-    // 94 -> 42, 64 x 256 x 14^2 f16 (8-byte vectors) 6.8 -> 5.0.  Whole tiles stay ahead: 4000^2 fp32 25.8 against 27.5.
-    auto take_shifted = [&]() {
-      if ((es != 2 && es != 4) || tune.max_vec_bytes > 0 || tune.tile.size() == (size_t)nj) return false;
-      lc_plan sh = *plan;
-      sh.cls = KernelClass::Generic;
-      if (!plan_tiled(J, es, 16 / es, p, q, n, tune, &sh, Tiling::Shifted)) return false;
-      *plan = sh;
-      return true;
-    };
-    if (tune.shifted > 0 && take_shifted()) return LC_OK;
-    const bool may_shift = tune.shifted < 0 && n >= (1 << 19);
-    if (may_shift && V * es < 16 && take_shifted()) return LC_OK;
-    if (V >= 2) {
-      const bool exact = plan_tiled(J, es, V, p, q, n, tune, plan);
-      // Whole tiles need extents with small factors.  When they leave runs shorter than a cache line
-      // (prime-ish extents) the ragged tiling is tried too and taken if its shorter run is at least twice
-      // as long (its kernel is not pipelined: 4000 x 4000 fp32 runs at 63 % with whole 160 x 32 tiles and
-      // at 57 % with ragged 128 x 64 tiles, but 8000 x 8008 bf16 at 34 % against 46 %).
-      const bool long_runs = exact && std::min(plan->src_run_bytes, plan->dst_run_bytes) >= 128;
-      if (may_shift && (!long_runs || (n >= (1 << 22) && plan->transpose.n_micro < (uint32_t)kBlock))) {
-        lc_plan whole = *plan;
-        if (take_shifted()) return LC_OK;
-        *plan = whole;
+    // the way without shifted tiles: whole tiles, ragged tiles or (no vector on one side) single elements
+    auto plan_plain = [&]() {
+      if (V >= 2) {
+        const bool exact = plan_tiled(J, es, V, p, q, n, tune, plan);
+        // Whole tiles need extents with small factors.  When they leave runs shorter than a cache line
+        // (prime-ish extents) the ragged tiling is tried too and taken if its shorter run is at least twice
+        // as long (its kernel is not pipelined: 4000 x 4000 fp32 runs at 63 % with whole 160 x 32 tiles and
+        // at 57 % with ragged 128 x 64 tiles, but 8000 x 8008 bf16 at 34 % against 46 %).
+        if (exact && (std::min(plan->src_run_bytes, plan->dst_run_bytes) >= 128 || tune.tile.size() == (size_t)nj)) return true;
+        lc_plan rag = *plan;
+        rag.cls = KernelClass::Generic;
+        if (plan_tiled(J, es, V, p, q, n, tune, &rag, Tiling::Ragged) && rag.transpose.n_ragged > 0 &&
+            (!exact || std::min(rag.src_run_bytes, rag.dst_run_bytes) >= 2 * std::min(plan->src_run_bytes, plan->dst_run_bytes))) {
+          *plan = rag;
+          return true;
+        }
+        if (!exact) plan->note = "tile did not fit the transpose kernel's index ranges";
+        return exact;
       }
-      if (exact && (long_runs || tune.tile.size() == (size_t)nj)) return LC_OK;
-      lc_plan rag = *plan;
-      rag.cls = KernelClass::Generic;
-      if (plan_tiled(J, es, V, p, q, n, tune, &rag, Tiling::Ragged) && rag.transpose.n_ragged > 0 &&
-          (!exact || std::min(rag.src_run_bytes, rag.dst_run_bytes) >= 2 * std::min(plan->src_run_bytes, plan->dst_run_bytes))) {
-        *plan = rag;
-        return LC_OK;
-      }
-      if (exact) return LC_OK;
-      plan->note = "tile did not fit the transpose kernel's index ranges";
-    } else {
       // No vector on one side (odd strides or extents): single elements through the same tiles (V = 1).
       // In destination order a lane would read one element per source line; a tile reads and writes runs.
       lc_plan rag = *plan;
       if (ragged_instantiated(es, 1) && plan_tiled(J, es, 1, p, q, n, tune, &rag, Tiling::Ragged) &&
           std::min(rag.src_run_bytes, rag.dst_run_bytes) >= 8 * es) {
         *plan = rag;
-        return LC_OK;
+        return true;
       }
       plan->note = "no common vector on both sides for a transposing tile";
+      return false;
+    };
+    auto plan_shifted = [&](lc_plan* sh) {
+      if ((es != 2 && es != 4) || tune.max_vec_bytes > 0 || tune.tile.size() == (size_t)nj) return false;
+      sh->cls = KernelClass::Generic;
+      return plan_tiled(J, es, 16 / es, p, q, n, tune, sh, Tiling::Shifted);
+    };
+    lc_plan shifted = *plan;
+    if (tune.shifted > 0 && plan_shifted(&shifted)) {
+      *plan = shifted;
+      return LC_OK;
     }
+    // Shifted tiles move some elements twice: they are taken when the elements their tiles cover are at most `limit` times those
+    // the plain plan's tiles cover.
+    auto covered = [](const lc_plan& t) {
+      double c = t.transpose.n_tiles;
+      for (int64_t e : t.tile_extent) c *= (double)e;
+      return c;
+    };
+    const bool may_shift = tune.shifted < 0 && n >= kShiftedMinElems;
+    const bool long_sides = std::min(J[(size_t)p].extent, J[(size_t)q].extent) >= 256;   // no plain tile holds either whole
+    bool shifts = false;
+    if (may_shift && V * es < 16 && long_sides) {   // the plain plan covers n at the least: mostly it need not be known (half of the planning)
+      shifts = plan_shifted(&shifted);
+      if (shifts && covered(shifted) <= narrow_shifted_limit(V * es, es, false) * (double)n) {
+        *plan = shifted;
+        return LC_OK;
+      }
+    }
+    const bool plain = plan_plain();
+    const double limit = may_shift ? shifted_limit(*plan, plain, es, n) : 0.0;
+    // Short rows with gaps of their own length and more behind them, which the plain plan's tiles hold whole, against runs of lines
+    // on the other side: cut in two, both halves' ends fetch lines of their own (bf16 44 x 746152 pitch 108 43 -> 65 us, 14 x 354432
+    // pitch 78 18 -> 21; with small gaps the halves share them: 60 x 80226 pitch 68 12.6 -> 7.7).
+    auto cuts_rows = [&](int k, bool src_side, int64_t run_bytes, int64_t other_run_bytes) {
+      const int64_t row = J[(size_t)k].extent;
+      int64_t pitch = INT64_MAX;
+      for (int j = 0; j < nj; ++j) {
+        const int64_t stride = std::abs(src_side ? J[(size_t)j].a : J[(size_t)j].b);
+        if (j != k && stride > 0) pitch = std::min(pitch, stride);
+      }
+      return plan->tile_extent[(size_t)k] == row && shifted.tile_extent[(size_t)k] < row && run_bytes == row * es && other_run_bytes >= 128 &&
+             pitch >= 2 * row;
+    };
+    if (limit > 0.0 && (shifts || plan_shifted(&shifted)) &&
+        (!plain || (covered(shifted) <= limit * covered(*plan) && !cuts_rows(p, true, plan->src_run_bytes, plan->dst_run_bytes) &&
+                    !cuts_rows(q, false, plan->dst_run_bytes, plan->src_run_bytes)))) {
+      *plan = shifted;
+      return LC_OK;
+    }
+    if (plain) return LC_OK;
   }
   if (tune.force_class == 0) return plan_generic(S, D, n, plan, "forced");
 

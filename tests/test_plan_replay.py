@@ -425,3 +425,33 @@ def test_shifted_tiles_are_the_choice_for_large_sides_that_vectors_do_not_divide
     assert "shifted" not in lc.Plan("(7,1000003):(1,7)", "(7,1000003):(1000003,1)", "bf16").describe()   # a side shorter than a vector
     monkeypatch.setenv("LC_TUNE_SHIFTED", "0")
     assert "V=1" in desc(8001, 8003, "bf16")
+
+
+def _nchw(N, C, hw, dt):
+    return lc.Plan("(%d,%d,%d):(%d,%d,1)" % (N, C, hw, C * hw, hw), "(%d,%d,%d):(%d,1,%d)" % (N, C, hw, C * hw, C), dt).describe()
+
+
+@pytest.mark.parametrize("dt,sides,pitch", [
+    ("f32", (6, 4194304), 0), ("f32", (10, 4194304), 0), ("bf16", (20, 4194304), 0), ("bf16", (36, 932032), 0), ("bf16", (136, 246720), 0), ("bf16", (160, 209664), 0),
+    ("bf16", (96, 349504), 0), ("f32", (36, 932032), 0), ("f32", (12, 1000004), 0), ("bf16", (68, 151200), 0), ("f32", (316, 22184), 0),
+    ("bf16", (44, 746152), 64), ("bf16", (14, 354432), 64), ("f32", (48, 1368212), 64)])
+def test_narrow_sides_stay_with_tiles_that_hold_them_whole(dt, sides, pitch):
+    # shifted tiles would move up to twice the elements, or cut rows in two that whole tiles move at once (each measured slower)
+    a, b = sides
+    wide, tall = "(%d,%d):(1,%d)" % (a, b, a + pitch), "(%d,%d):(%d,1)" % (a, b, b)
+    for s, d in ((wide, tall), (tall, wide)):
+        desc = lc.Plan(s, d, dt).describe()
+        assert "class=transpose" in desc and "shifted" not in desc, desc
+
+
+def test_shifted_tiles_are_weighed_against_the_plain_plan():
+    # NCHW -> NHWC of channels and images just above a tile: by the elements moved twice beyond the plain plan's own idle lanes
+    for N, C, hw, dt in ((83, 256, 784, "bf16"), (1, 256, 50176, "bf16"), (594, 36, 784, "f32"), (1069, 20, 784, "f32"), (13, 24, 50176, "bf16"),
+                         (1258, 68, 196, "f32"), (167, 32, 3136, "f32"), (64, 12, 16384, "bf16")):
+        assert "shifted" not in _nchw(N, C, hw, dt), (N, C, hw, dt)
+    for N, C, hw, dt in ((162, 132, 784, "bf16"), (648, 132, 196, "bf16"), (648, 33, 784, "bf16"), (16, 200, 12769, "f16"), (64, 256, 196, "f16"), (162, 33, 3136, "f32")):
+        assert "shifted_tiles=1" in _nchw(N, C, hw, dt), (N, C, hw, dt)
+    for a, b, dt in ((65, 32256, "f32"), (17, 1973760, "bf16"), (2944, 2320, "bf16"), (16, 332016, "bf16"), (3356, 11812, "f32"),
+                     (8, 4040080, "bf16")):
+        assert "shifted_tiles=1" in lc.Plan("(%d,%d):(1,%d)" % (a, b, a), "(%d,%d):(%d,1)" % (a, b, b), dt).describe(), (a, b, dt)
+    assert "shifted_tiles=1" in lc.Plan("(60,80226):(1,68)", "(60,80226):(80226,1)", "bf16").describe()   # small gaps: the halves of a row share lines
