@@ -694,7 +694,11 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     int want = P.n_tiles >= 16384 ? 1 : (P.n_tiles >= 4096 ? 2 : (P.n_tiles >= 2048 ? 3 : 4));
     // the ragged / element-wise kernel has no software pipeline: resident workgroups overlap each other instead
     if (P.n_ragged > 0 || (V == 1 && es != 16)) want = 8;
-    if (V == 1 && es == 16 && P.n_tiles < 16384) want = 4;
+    // Word tiles (V = 1) have no transpose to hide a wait behind: four workgroups a CU, three of tiles between 16 KiB and 32, whose
+    // fourth only adds to what is under way at once (24 KiB: 4096 tiles, heads 8 x 4096 x 32 x 48, 39.5 us with three, 46.5 with
+    // four; 12 KiB: 3333 tiles 17.0 and 15.6; 32 KiB: 4096 tiles 53.6 and 48.6), two of 32 KiB from 8192 tiles on (102 us with
+    // two, 110 with three, 120 with four).
+    if (V == 1 && es == 16 && P.n_tiles < 16384) want = plan->lds_bytes < 16 * 1024 ? 4 : plan->lds_bytes < 32 * 1024 ? 3 : P.n_tiles < 8192 ? 4 : 2;
     // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
     // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
     if (shifted) want = P.n_tiles >= 8192 ? 1 : (P.n_tiles >= 1280 ? 2 : 4);
@@ -707,8 +711,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     // 16 bytes of LDS behind the tile carry the answer to the other lanes.  tile_queue = tiles per request, 0 = fixed order.
     const bool queue_fits = (uint64_t)(plan->lds_bytes + 16u) * (unsigned)plan->wgs_per_cu <= 160u * 1024u && !P.blocked &&
                             P.n_ragged == 0 && !(V == 1 && es != 16);   // the kernel without predicates only
-    // Word tiles (V = 1) have no transpose to hide a wait behind: four workgroups a CU in the fixed order up to 16384 tiles
-    // (heads 8 x 4096 x 32 x 64 f16, 4096 tiles: 56.6 us with two and the queue, 48.6; 8 x 8192 x 32 x 32 56.7 -> 49.0).
+    // Word tiles keep the fixed order up to 16384 tiles (heads 8 x 4096 x 32 x 64 f16, 4096 tiles: 56.6 us with two workgroups a CU
+    // and the queue, 48.6 with four; 8 x 8192 x 32 x 32 56.7 -> 49.0).
     const bool queue_pays = plan->lds_bytes >= 32u * 1024u && P.n_tiles >= (V == 1 ? 16384u : 4096u);
     const int per_request = (int)std::max(1u, 65536u / std::max(1u, plan->lds_bytes));
     plan->tile_queue = queue_fits ? (tune.tile_queue >= 0 ? tune.tile_queue : (queue_pays ? per_request : 0)) : 0;
@@ -1071,13 +1075,16 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
   // The common vector keeps whole 16-byte words together on both sides (p = q), but it is short: in
   // destination order the source would be read in pieces of K elements.  With the word as the
   // element the copy is a permutation of words, and a tile through LDS (V = 1: nothing to transpose
-  // inside a word) reads and writes runs of many words.  Measured on MI355X (attention heads, us): pieces of up to 128 bytes
-  // through tiles as fast as in destination order or faster (8 x 8192 x 32 x 32 f16 49.0 against 49.7, 8 x 4096 x 32 x 64 48.6
-  // against 47.4); longer pieces (4 x 3000 x 32 x 96 31.2 against 29.4) and copies too short for tiles of 16 KiB (8 x 668 x
-  // 12 x 64 5.9 against 5.1) go in destination order.
+  // inside a word) reads and writes runs of many words.  Measured on MI355X (pieces moved between (d, A, B, C) and (d, B, A, C),
+  // both directions, us, destination order -> tiles):
+  //   pieces of up to 128 bytes: tiles of 8 KiB and more as fast or faster (16 B 256 x 256 x 16 33 -> 7, 48 B 32 x 4096 x 8 31 -> 22, 128 B
+  //   32 x 4096 x 8 47-53 -> 49-51: within noise there, and a copy of words through tiles is what callers were told they get);
+  //   smaller tiles where the pieces are shorter than half a line and the tile holds 2.5 KiB (16 B 7 x 9999 x 9 13.9 -> 7.7, 32 B 32 x
+  //   8192 x 1 7.8 -> 5.2), but not beyond (64 B 16 x 1024 x 4 3.6 -> 4.4, 48 B 12 x 668 x 8 3.7 -> 5.1);
+  //   longer pieces: destination order (96 heads of 160 B 13.3 -> 17), but for 8192 tiles and more (144 B 256 x 256 x 16 78 -> 56).
   {
     const int64_t direct_run_bytes = q >= 0 ? J[(size_t)q].extent * es : es;
-    bool stage = VEC * es == 16 && q >= 0 && p == q && nj >= 3 && direct_run_bytes <= (tune.force_class == 2 ? 255 : 128) && tune.force_class != 1;
+    bool stage = VEC * es == 16 && q >= 0 && p == q && nj >= 3 && direct_run_bytes < 256 && tune.force_class != 1;
     for (int k = 0; k < nj && stage; ++k)
       if (J[(size_t)k].a == 0) stage = false;   // broadcasts are looped inside a lane by the direct class
     if (stage) {
@@ -1093,9 +1100,13 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
         if (W[(size_t)k].b < W[(size_t)qw].b) qw = k;
       }
       lc_plan staged = *plan;
+      auto tiles_pay = [&]() {
+        const uint32_t words = staged.transpose.n_micro, tiles = staged.transpose.n_tiles;
+        if (direct_run_bytes > 128) return tiles >= 8192u && tiles < 16384u;
+        return tiles >= 256u && (words >= 512u || (words >= 160u && direct_run_bytes < 64));
+      };
       if (W.size() >= 2 && plan_tiled(W, 16, 1, pw, qw, n / VEC, tune, &staged) &&
-          (tune.force_class == 2 || (staged.src_run_bytes >= 4 * direct_run_bytes && staged.dst_run_bytes >= 4 * direct_run_bytes &&
-                                     staged.transpose.n_tiles >= 256 && staged.micro_per_thread >= 4))) {
+          (tune.force_class == 2 || (staged.src_run_bytes >= 4 * direct_run_bytes && staged.dst_run_bytes >= 4 * direct_run_bytes && tiles_pay()))) {
         *plan = staged;
         return LC_OK;
       }

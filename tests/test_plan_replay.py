@@ -455,3 +455,18 @@ def test_shifted_tiles_are_weighed_against_the_plain_plan():
                      (8, 4040080, "bf16")):
         assert "shifted_tiles=1" in lc.Plan("(%d,%d):(1,%d)" % (a, b, a), "(%d,%d):(%d,1)" % (a, b, b), dt).describe(), (a, b, dt)
     assert "shifted_tiles=1" in lc.Plan("(60,80226):(1,68)", "(60,80226):(80226,1)", "bf16").describe()   # small gaps: the halves of a row share lines
+
+
+@pytest.mark.parametrize("piece,A,B,C,wgs", [
+    (48, 32, 4096, 8, 3), (96, 256, 256, 16, 3), (16, 256, 256, 16, 3), (64, 7, 9999, 9, 4), (16, 3000, 3000, 1, 4), (128, 32, 4096, 8, 4), (64, 64, 8192, 8, 2),   # tiles, by their size and number
+    (16, 7, 9999, 9, 4), (32, 32, 8192, 1, 4), (48, 32, 8192, 1, 4), (16, 32, 3000, 4, 4), (128, 16, 1024, 4, 4),             # short pieces: small tiles too
+    (144, 256, 256, 16, 3), (160, 32, 4096, 8, 3), (240, 1024, 1024, 1, 3),                                                  # longer ones: many tiles only
+    (48, 12, 668, 8, 0), (64, 16, 1024, 4, 0), (96, 12, 668, 8, 0), (160, 32, 3000, 4, 0), (240, 32, 8192, 1, 0), (192, 64, 8192, 8, 0)])
+def test_words_go_through_tiles_where_that_pays(piece, A, B, C, wgs):
+    d = piece // 2
+    s, t = "(%d,%d,%d,%d):(1,%d,%d,%d)" % (d, A, B, C, d, d * A, d * A * B), "(%d,%d,%d,%d):(1,%d,%d,%d)" % (d, A, B, C, d * B, d, d * A * B)
+    for x, y in ((s, t), (t, s)):
+        desc = lc.Plan(x, y, "bf16").describe()
+        assert ("class=transpose" in desc and "V=1 " in desc) == (wgs > 0), desc
+        if wgs:
+            assert "wgs_per_cu=%d " % wgs in desc and "tile_queue" not in desc, desc
