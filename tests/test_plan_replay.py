@@ -470,3 +470,10 @@ def test_words_go_through_tiles_where_that_pays(piece, A, B, C, wgs):
         assert ("class=transpose" in desc and "V=1 " in desc) == (wgs > 0), desc
         if wgs:
             assert "wgs_per_cu=%d " % wgs in desc and "tile_queue" not in desc, desc
+
+
+def test_large_windows_of_words_keep_two_items_a_lane():
+    # one item and five workgroups a CU below 128 MiB, two and three from there on (rows of 512 bytes swapped over 32)
+    for rows, unroll, wgs in ((2048, 1, 5), (8191, 1, 5), (8192, 2, 3), (16384, 2, 3)):
+        desc = lc.Plan("(256,%d,32):(1,8192,256)" % rows, "(256,%d,32):(1,256,%d)" % (rows, 256 * rows), "bf16").describe()
+        assert "class=direct" in desc and "unroll=%d " % unroll in desc and "wgs_per_cu=%d " % wgs in desc, desc
