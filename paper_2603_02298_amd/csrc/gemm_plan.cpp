@@ -57,6 +57,51 @@ int env_int(const char* name, int dflt) {
   return (v && *v) ? std::atoi(v) : dflt;
 }
 
+// How a pair of operands is brought in.
+struct Loads {
+  int a, b;                  // GemmLoad, what a plan says
+  int a_direct, b_direct;    // see GemmParams
+  bool direct, any;          // both straight into LDS, both in vectors at any alignment
+};
+Loads choose_loads(const Modes& a_r, const Modes& a_k, const Modes& a_l, unsigned a_align, const Modes& b_r, const Modes& b_k, const Modes& b_l,
+                   unsigned b_align, int64_t K) {
+  Loads l;
+  l.a = classify_operand(a_r, a_k, a_l, a_align);
+  l.b = classify_operand(b_r, b_k, b_l, b_align);
+  const int force = env_int("LC_TUNE_GEMM_LOAD", -1);   // tests: force the element-wise loads
+  // element loads are compiled for both operands together: one operand that needs them takes the other along
+  if (force == kLoadElem || l.a == kLoadElem || l.b == kLoadElem) l.a = l.b = kLoadElem;
+  // straight into LDS: k tiles that are contiguous along k
+  // (for row vectors: each of the tile's 64 k rows one even step of the k mode's first leaf from the tile's first);
+  // compiled for pairs of operands that both qualify
+  // A k mode of a single leaf may end in a short k tile: the lanes whose piece lies past K are answered with zeros
+  // (k vectors: K a multiple of 8, so that no vector straddles K).
+  auto direct_ok = [&](int load, const Modes& k) {
+    if (load == kLoadElem) return false;
+    if (K % kGemmBK == 0 && k[0].extent % kGemmBK == 0) return true;
+    return k.size() == 1 && (load == kLoadRVec || K % 8 == 0) && env_int("LC_TUNE_GEMM_KTAIL", 1) != 0;
+  };
+  const int direct_env = env_int("LC_TUNE_GEMM_DIRECT", 3);   // bit 0: k vectors, bit 1: row vectors
+  auto direct_on = [&](int load) { return (direct_env & (load == kLoadKVec ? 1 : 2)) != 0; };
+  l.direct = direct_ok(l.a, a_k) && direct_ok(l.b, b_k) && direct_on(l.a) && direct_on(l.b);
+  l.a_direct = l.b_direct = l.direct ? 1 : 0;
+  // Operands with a contiguous mode that vectors do not fit (odd sizes, offset pointers): 16-byte loads at any alignment, for
+  // pairs that both have one.  Measured on MI355X (bf16), element by element -> this: 1001 x 2003 x 1537 (all odd) 211 -> 22 us,
+  // 3500^3 (no multiple of 8) 891 -> 158 us, 301 x 401 x 501 30 -> 5.5 us.
+  auto any_kind = [&](const Modes& row, const Modes& k) -> int32_t {
+    if (k.size() != 1) return 0;
+    if (k[0].stride == 1 && K >= 8) return 2;
+    const bool whole = row[0].extent % 8 == 0 || (row.size() == 1 && row[0].extent >= 8);
+    return row[0].stride == 1 && whole ? 3 : 0;
+  };
+  l.any = l.a == kLoadElem && force != kLoadElem && any_kind(a_r, a_k) != 0 && any_kind(b_r, b_k) != 0;
+  if (l.any) {
+    l.a_direct = any_kind(a_r, a_k);
+    l.b_direct = any_kind(b_r, b_k);
+  }
+  return l;
+}
+
 }  // namespace
 
 lc_status_t mfma_fragment_layout(int which, Layout* out) {
@@ -126,17 +171,19 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     return c_align % 16 == 0 && leads_contiguous(lead, 4) && strides_aligned(lead, with_batch(other, c_l), 4);
   };
   bool exchange = !c_vec_ok(c_m, c_n) && c_vec_ok(c_n, c_m);
-  // Without vectors of four m the lanes of an update run along n, element by element: C's contiguous mode goes there (not
-  // for a few columns, whose thin tiles are worth more).
-  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) exchange = c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
+  Loads loads = choose_loads(a_r, a_k, a_l, a_align, b_r, b_k, b_l, b_align, K);
+  // Without vectors of four m the lanes of the split and stream kernels' update run along n, element by element: C's contiguous
+  // mode goes there (not for a few columns, whose thin tiles are worth more).  The tile kernels of staged and element loads
+  // measured slower that way round (2 x 5560 x 64 10.8 -> 15.2 us, a convolution of 35 x 13500 x 288 16.8 -> 21.4).
+  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) exchange = (loads.direct || loads.any) && c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
   if (env_int("LC_TUNE_GEMM_EXCHANGE", -1) >= 0) exchange = env_int("LC_TUNE_GEMM_EXCHANGE", 0) != 0;
-  unsigned ka_align = a_align, kb_align = b_align;
   if (exchange) {
     std::swap(a_r, b_r);
     std::swap(a_k, b_k);
     std::swap(a_l, b_l);
     std::swap(c_m, c_n);
-    std::swap(ka_align, kb_align);
+    std::swap(loads.a, loads.b);
+    std::swap(loads.a_direct, loads.b_direct);
   }
   plan.exchanged = exchange;
   const int64_t kM = exchange ? N : M, kN = exchange ? M : N;
@@ -151,39 +198,11 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   P.N = (uint32_t)kN;
   P.K = (uint32_t)K;
   P.L = (uint32_t)Lb;
-  P.a_load = classify_operand(a_r, a_k, a_l, ka_align);
-  P.b_load = classify_operand(b_r, b_k, b_l, kb_align);
-  const int force = env_int("LC_TUNE_GEMM_LOAD", -1);   // tests: force the element-wise loads
-  // element loads are compiled for both operands together: one operand that needs them takes the other along
-  if (force == kLoadElem || P.a_load == kLoadElem || P.b_load == kLoadElem) P.a_load = P.b_load = kLoadElem;
-  // straight into LDS: k tiles that are contiguous along k
-  // (for row vectors: each of the tile's 64 k rows one even step of the k mode's first leaf from the tile's first);
-  // compiled for pairs of operands that both qualify
-  // A k mode of a single leaf may end in a short k tile: the lanes whose piece lies past K are answered with zeros
-  // (k vectors: K a multiple of 8, so that no vector straddles K).
-  auto direct_ok = [&](int load, const Modes& k) {
-    if (load == kLoadElem) return false;
-    if (K % kGemmBK == 0 && k[0].extent % kGemmBK == 0) return true;
-    return k.size() == 1 && (load == kLoadRVec || K % 8 == 0) && env_int("LC_TUNE_GEMM_KTAIL", 1) != 0;
-  };
-  const int direct_env = env_int("LC_TUNE_GEMM_DIRECT", 3);   // bit 0: k vectors, bit 1: row vectors
-  auto direct_on = [&](int load) { return (direct_env & (load == kLoadKVec ? 1 : 2)) != 0; };
-  const bool direct = direct_ok(P.a_load, a_k) && direct_ok(P.b_load, b_k) && direct_on(P.a_load) && direct_on(P.b_load);
-  P.a_direct = P.b_direct = direct ? 1 : 0;
-  // Operands with a contiguous mode that vectors do not fit (odd sizes, offset pointers): 16-byte loads at any alignment, for
-  // pairs that both have one.  Measured on MI355X (bf16), element by element -> this: 1001 x 2003 x 1537 (all odd) 211 -> 22 us,
-  // 3500^3 (no multiple of 8) 891 -> 158 us, 301 x 401 x 501 30 -> 5.5 us.
-  auto any_kind = [&](const Modes& row, const Modes& k) -> int32_t {
-    if (k.size() != 1) return 0;
-    if (k[0].stride == 1 && K >= 8) return 2;
-    const bool whole = row[0].extent % 8 == 0 || (row.size() == 1 && row[0].extent >= 8);
-    return row[0].stride == 1 && whole ? 3 : 0;
-  };
-  const bool any = P.a_load == kLoadElem && force != kLoadElem && any_kind(a_r, a_k) != 0 && any_kind(b_r, b_k) != 0;
-  if (any) {
-    P.a_direct = any_kind(a_r, a_k);
-    P.b_direct = any_kind(b_r, b_k);
-  }
+  P.a_load = loads.a;
+  P.b_load = loads.b;
+  P.a_direct = loads.a_direct;
+  P.b_direct = loads.b_direct;
+  const bool direct = loads.direct, any = loads.any;
   P.c_vec = c_vec_ok(c_m, c_n) ? 1 : 0;
   if (env_int("LC_TUNE_GEMM_CVEC", 1) == 0) P.c_vec = 0;
   unsigned need_a = P.a_load == kLoadElem ? 2u : 16u, need_b = P.b_load == kLoadElem ? 2u : 16u;

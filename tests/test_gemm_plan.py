@@ -364,3 +364,16 @@ def test_which_operands_take_vectors_at_any_alignment():
     assert loads("((5,14),9):((1,6),84)", "(33,9):(9,1)", "(70,33):(33,1)")[0] == "elements"     # vectors would straddle the leaves
     assert loads("((8,9),9):((1,9),81)", "(33,9):(9,1)", "(72,33):(33,1)")[0] == r
     assert loads("(70,(3,3)):(12,(1,4))", "(33,9):(9,1)", "(70,33):(33,1)")[0] == "elements"     # k of two leaves
+
+
+def test_c_without_vectors_is_exchanged_where_the_update_passes_through_lds_only():
+    # C contiguous along m, but without whole vectors of it: the split and stream kernels take its contiguous mode along n, the
+    # tile kernels of staged and element loads keep the roles (slower the other way round)
+    def exchanged(*layouts):
+        return lc.GemmPlan(*layouts).describe().split("exchanged=")[1][0]
+    assert exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(1,70)") == "1" and exchanged("(70,9):(9,1)", "(45,9):(9,1)", "(70,45):(1,70)") == "1"
+    assert exchanged("(70,64):(64,1)", "(16,64):(64,1)", "(70,16):(1,70)") == "0"                 # a few columns: thin tiles
+    assert exchanged("(2,64):(1,2)", "(5560,64):(64,1)", "(2,5560):(1,2)") == "0"                 # element loads
+    assert exchanged("(70,9):(3,211)", "(45,9):(9,1)", "(70,45):(1,70)") == "0"
+    assert exchanged("(35,144):(144,1)", "(450,(16,3,3)):(800,(1,32,128))", "(35,450):(1,35)") == "0"   # staged k vectors
+    assert exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(45,1)") == "0"                 # contiguous along n already
