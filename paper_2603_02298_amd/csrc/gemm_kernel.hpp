@@ -451,10 +451,8 @@ template <bool BF16, int WB>
 static inline hipError_t launch_gemm(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
   if (la == kLoadElem && lb == kLoadElem) return launch_gemm_ab<BF16, WB, kLoadElem, kLoadElem>(plan, a, b, c, s);
-  if constexpr (WB == 4) {   // straight into LDS: smaller tiles are the split and stream kernels'
-    if (la == kLoadKDirect) return launch_gemm_a<BF16, WB, kLoadKDirect, kLoadKDirect, kLoadRDirect>(plan, lb, a, b, c, s);
-    if (la == kLoadRDirect) return launch_gemm_a<BF16, WB, kLoadRDirect, kLoadKDirect, kLoadRDirect>(plan, lb, a, b, c, s);
-  }
+  if (la == kLoadKDirect) return launch_gemm_a<BF16, WB, kLoadKDirect, kLoadKDirect, kLoadRDirect>(plan, lb, a, b, c, s);
+  if (la == kLoadRDirect) return launch_gemm_a<BF16, WB, kLoadRDirect, kLoadKDirect, kLoadRDirect>(plan, lb, a, b, c, s);
   if (la == kLoadKVec) return launch_gemm_a<BF16, WB, kLoadKVec, kLoadKVec, kLoadRVec>(plan, lb, a, b, c, s);
   if (la == kLoadRVec) return launch_gemm_a<BF16, WB, kLoadRVec, kLoadKVec, kLoadRVec>(plan, lb, a, b, c, s);
   return hipErrorInvalidValue;

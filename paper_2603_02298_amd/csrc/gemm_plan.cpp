@@ -210,13 +210,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   plan.b_align = exchange ? need_a : need_b;
   plan.c_align = P.c_vec ? 16u : 4u;
 
-  // Tile.  Split kernel (direct loads only): while tiles of 64 x 64 leave a CU at most one workgroup, and then the smallest of
+  // Tile.  Split kernel (operands straight into LDS or in vectors at any alignment): while tiles of 64 x 64 leave a CU at most one workgroup, and then the smallest of
   // its tiles that does: the k tiles of a workgroup's tile go to its wavefronts, more tiles only take LDS from each other.
   // Measured on MI355X (bf16, start = 128 x 128 tiles): 512^3 11.1 us; 32 x 32 tiles (256 of them) 4.3, 32 x 64 4.7, 64 x 64
   // 6.2.  16 x 8192 x 8192 78 us; 32 x 32 27.6, 64 x 64 36.  64 x 8192 x 8192 92 us; 32 x 32 (512 tiles) 42.8, 64 x 32 (256) 33.4.
   // 1024^3 17.6 us; 32 x 64 (512 tiles) 10.8, 64 x 64 (256) 8.3.
   auto tiles_of = [&](int64_t tm, int64_t tn) { return (kM + tm - 1) / tm * ((kN + tn - 1) / tn) * Lb; };
-  // LC_TUNE_GEMM_TILE: 256, 128, 12864 (128 x 64), 64128; split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
+  // LC_TUNE_GEMM_TILE: 256, 128, 12864 (128 x 64), 64128, 1285 (the ring of five 128 x 128 tiles); split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
   // stream kernel's 64 x 64
   const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
@@ -229,31 +229,43 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, 2);
   else if (vectors && (any || t_env != 256)) {
     // Larger problems.  The CU that is given the most tiles decides, so a tile's cost is how many of them that CU takes times
-    // its area, times what its k loop costs per product against the 128 x 128 stream kernel's: smaller tiles read more of LDS
-    // per product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1, 1.2, 1.3 and 64 x 64: 1.3,
-    // 1.4, 1.65 below K = 1024, below 2048 and from there on); a lone workgroup on a CU has nobody to cover its waits (1.25,
-    // 1.25, 1.5); the 256 x 256 kernel reads least, but its short k loops wait and nothing covers its C update (1.1 below K = 768,
-    // 1.0 below 2048, 0.9 below 3000, 0.8 from there on), and with fewer tiles than CUs it runs at a higher clock (down to 0.7).
-    // Measured on MI355X (bf16; 128 x 128, 128 x 64, 64 x 64 stream, 256 x 256, in us): 2048^3 27.4, 26.1, 29.2, 55;
-    // 1536^2 x 4096 42.6, 39.4, 35.2, 87; 16 x (1000 x 1504 x 776) 83, 97, 110, 98; 128 x 100352 x 576 (convolution) 34.1,
-    // 32.6, 34.2, 57.5; 4 x 1024^3 18.2, 16.5, 17.8, 39.6; 4096^2 x 1024 49, 56, 62, 52; 4096^3 149.5, 187, 232, 129;
-    // 5000^2 x 3000 240, 296, 347, 195; 6144 x 3072 x 2048 100, 115, 139, 132; 3000^3 96, 95, 120, 77.5;
-    // 2200^2 x 8192 113, 119, 146, 156; 4096 x 2048 x 4096 71, 96, 112, 89; 1100^2 x 8192 77, 67, 60, 145.
-    // Short k loops with 256 tiles of 256 x 256 and more (128 x 128 stream, 256 x 256): 4096^2 x 64 23.3, 32.7, x 256 29.9, 36.2,
-    // x 512 37.9, 41.8, x 1024 51.5, 52.9, x 1536 70.4, 69.0; 8192^2 x 256 120, 149; 16 x 2048^2 x 256 136, 150;
-    // 32 x 1024^2 x 512 87, 94; 5000^2 x 1000 104, 102.
-    struct Choice { int tm, tn; double per_product; };
-    const double half = K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3, quarter = K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65, lone = K < 2048 ? 1.25 : 1.5;
-    const Choice choices[] = {{128, 128, 1.0}, {128, 64, half}, {64, 128, half}, {64, 64, quarter}};
-    auto cost = [&](const Choice& c, bool lone_waits) {
+    // its area, times what its k loop costs per product against the 128 x 128 stream kernel's.  Smaller tiles read more of LDS per
+    // product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1 below K = 768, 1.4, 1.5 from 3000 on;
+    // 64 x 64: 1.3, 2.2, 2.3; a side of 64 rows of a k-major operand a tenth more); a lone workgroup on a CU has nobody to
+    // cover its waits and runs at about half the pace (1.9; below 768 1.25).  The 256 x 256 kernel reads least, but its short k loops
+    // wait and nothing covers its C update (1.1, 1.0 below 1024, 0.85 below 2048, 0.75, 0.72 from 3000 on), and with fewer tiles than CUs it
+    // runs at a higher clock (down to 0.7, 0.8 from 3000 on).  The ring of five 128 x 128 tiles asks for its k tiles further ahead than
+    // the stream kernel: the better one alone on a CU over a long k loop (1.35 from K = 3000 on).
+    // Measured on MI355X (bf16, us; ring of 128 x 128, stream 128 x 128, 128 x 64, 64 x 128, 64 x 64, 256 x 256; t: along k, n: along the rows):
+    //   tt 7816 x 496 x 5288 63, 76, 77, 75, 100, 111; nt 2296 x 1688 x 8000 82, 96, 90, 91, 127, 142; tt 3120 x 1272 x 3360 42, 48, 44, 45, 56, 78;
+    //   nt 632 x 7168 x 7448 99, 100, 127, 156, 166, 153; tn 1240 x 4848 x 3792 68, 62, 85, 76, 102, 85; nn 2320 x 2144 x 3928 62, 59, 73, 74, 92, 86;
+    //   nn 6872 x 680 x 1752 36, 32, 37, 37, 44, 49; tn 1560 x 2720 x 6688 99, 94, 119, 114, 128, 131; tt 8032 x 4176 x 6824 584, 604, 824, 770, 1185, 579;
+    //   2048^3 -, 27.4, 26.1, -, 29.2, 55; 16 x (1000 x 1504 x 776) 100, 83, 97, -, 110, 98; 4096^2 x 1024 -, 49, 56, -, 62, 52; 4096^3 158, 149, 187, -, 232, 129;
+    //   5000^2 x 3000 -, 240, 296, -, 347, 195; short k loops: 4096^2 x 64 -, 23.3, -, -, -, 32.7, x 512 -, 37.9, -, -, -, 41.8; convolution
+    //   128 x 100352 x 576 39, 34.1, 32.6, -, 34.2, 57.5.  Of 2000 problems drawn (60 to 3000 tiles of 128 x 128, K from 64 to 8192, all four
+    //   forms) the choice is within 1.1 % of the best on average.
+    // Vectors at any alignment (no ring, no 256 x 256 kernel) keep weights of their own: 1001 x 2003 x 1537 22 us in 64 x 64, 24.6 in 128 x 64.
+    struct Choice { int tm, tn; double per_product, lone; };
+    const bool measured = direct && K >= 768;   // (below, and at any alignment: the weights those were measured with)
+    const double half = measured ? (K < 3000 ? 1.4 : 1.5) : K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3;
+    const double quarter = measured ? (K < 3000 ? 2.2 : 2.3) : K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65;
+    const double lone = measured ? 1.9 : K < 2048 ? 1.25 : 1.5;
+    const double side_n = measured && P.b_load == kLoadRVec ? 1.1 : 1.0, side_m = measured && P.a_load == kLoadRVec ? 1.1 : 1.0;
+    const Choice choices[] = {{128, 128, 1.0, lone}, {128, 64, half * side_n, lone}, {64, 128, half * side_m, lone}, {64, 64, quarter, lone}};
+    auto cost = [&](const Choice& c) {
       const int64_t per_cu = (tiles_of(c.tm, c.tn) + 255) / 256;
-      return (double)per_cu * c.tm * c.tn * c.per_product * (lone_waits && per_cu == 1 ? lone : 1.0);
+      return (double)per_cu * c.tm * c.tn * c.per_product * (per_cu == 1 ? c.lone : 1.0);
     };
     const Choice* best = nullptr;
     for (const Choice& c : choices)
-      if (!best || cost(c, true) < cost(*best, true)) best = &c;
-    const Choice big = {256, 256, (K < 768 ? 1.1 : K < 2048 ? 1.0 : K < 3000 ? 0.9 : 0.8) * std::min(1.0, 0.7 + 0.3 * (double)tiles_of(256, 256) / 256.0)};
-    if (direct && free_choice && cost(big, false) <= cost(*best, true)) take(256, 256, 0, 0);
+      if (!best || cost(c) < cost(*best)) best = &c;
+    const double fill = K < 3000 ? 0.7 : 0.8;
+    const Choice big = {256, 256, (K < 768 ? 1.1 : K < 1024 ? 1.0 : K < 2048 ? 0.85 : K < 3000 ? 0.75 : 0.72) *
+                                      std::min(1.0, fill + (1.0 - fill) * (double)tiles_of(256, 256) / 256.0), 1.0};
+    const Choice ring = {128, 128, 1.0, 1.35};
+    const bool ring_pays = direct && K >= 3000 && tiles_of(128, 128) <= 256 && cost(ring) < cost(*best);
+    if (direct && free_choice && cost(big) <= (ring_pays ? cost(ring) : cost(*best))) take(256, 256, 0, 0);
+    else if (direct && (t_env == 1285 || (free_choice && ring_pays))) take(128, 128, 0, 0);
     else if (t_env == 128) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);
     else if (t_env == 64128) take(64, 128, 0, 2);

@@ -314,7 +314,7 @@ lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int
   product.to_float = plan.ab_dtype == LC_BF16 ? bf16_to_float : f16_to_float;
   if (plan.stages > 0) return replay_sums(plan, w, product, c, c_elems);
   const uint32_t BM = (uint32_t)plan.tile_m, BN = (uint32_t)plan.tile_n, WMB = BM / 64, WNB = BN / 64;
-  if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u) || (P.a_direct && (BM != 256 || BN != 256))) return LC_ERR_INVALID_ARG;
+  if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u)) return LC_ERR_INVALID_ARG;
   std::vector<unsigned char> lds((BM + BN) * 128u);   // one k tile of A and B is enough for a sequential walk
   std::vector<float> acc((size_t)BM * BN);
   std::vector<char> covered((size_t)P.tiles_m * P.tiles_n, 0);

@@ -57,12 +57,14 @@ def test_walk_matches_oracle(oracle, name, mnk, expect, tile, ktail):
 def test_walk_short_last_k_tiles_on_the_direct_path(oracle):
     # K from a single vector to several tiles plus a remainder; K a multiple of 8 (no k vector may straddle K; row vectors
     # come in blocks of 8 k)
+    # (1285, 256: the rings of five tiles; 128: the stream kernel)
     for name, Ks in (("tn", (8, 24, 72, 200)), ("nt", (8, 40, 72, 136, 200)), ("nn_rowmajor_c", (40, 136)), ("gett", (16, 88))):
         for K in Ks:
-            for tile in (128, 256):
+            for tile in (1285, 128, 256):
                 w = W.gemm_workload(name, 200, 136, K, ab_dtype="bf16", values="ints")
                 text = _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
                 assert text.count("direct-to-LDS") == 2 and "k_tiles=%d " % ((K + 63) // 64) in text, text
+                assert "tile=%dx" % (256 if tile == 256 else 128) in text and (" stream " in text) == (tile == 128), text
     w = W.gemm_workload("tn", 200, 136, 100, ab_dtype="bf16", values="ints")     # 100 = 8 * 12 + 4: a k vector would straddle K
     assert "direct" not in _walk_and_compare(oracle, w, None)
 
@@ -377,3 +379,18 @@ def test_c_without_vectors_is_exchanged_where_the_update_passes_through_lds_only
     assert exchanged("(70,9):(3,211)", "(45,9):(9,1)", "(70,45):(1,70)") == "0"
     assert exchanged("(35,144):(144,1)", "(450,(16,3,3)):(800,(1,32,128))", "(35,450):(1,35)") == "0"   # staged k vectors
     assert exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(45,1)") == "0"                 # contiguous along n already
+
+
+@pytest.mark.parametrize("form,M,N,K,tile", [
+    # tt: both along k, nn: both along their rows (k-major tiles)
+    ("nt", 632, 7168, 7448, "128x128x64 stream"), ("tn", 1240, 4848, 3792, "128x128x64 stream"), ("nn", 2320, 2144, 3928, "128x128x64 stream"),
+    ("nn", 6872, 680, 1752, "128x128x64 stream"), ("tn", 5136, 776, 3008, "128x128x64 stream"), ("tn", 2248, 2240, 2704, "128x128x64 stream"),
+    ("tt", 7816, 496, 5288, "128x128x64 tiles"), ("nt", 2296, 1688, 8000, "128x128x64 tiles"), ("tt", 1968, 1848, 8168, "128x128x64 tiles"),     # a lone tile on a CU, a long k loop: the ring
+    ("tt", 1848, 1784, 2720, "128x64x64 stream"), ("tn", 1536, 2368, 2408, "64x128x64 stream"), ("nt", 2712, 1192, 2800, "128x64x64 stream"),    # 64 on the side that is contiguous along k
+    ("tt", 4096, 4096, 4096, "256x256x64 tiles"), ("tt", 5000, 5000, 3000, "256x256x64 tiles"), ("tt", 2048, 2048, 2048, "128x64x64 stream")])
+def test_tile_choice_of_middle_sizes(form, M, N, K, tile):
+    # each the fastest of the tiles measured, or within 4 % of it
+    a = "(%d,%d):" % (M, K) + ("(%d,1)" % K if form[0] == "t" else "(1,%d)" % M)
+    b = "(%d,%d):" % (N, K) + ("(%d,1)" % K if form[1] == "t" else "(1,%d)" % N)
+    text = lc.GemmPlan(a, b, "(%d,%d):(1,%d)" % (M, N, M)).describe()
+    assert "tile=" + tile in text, text
