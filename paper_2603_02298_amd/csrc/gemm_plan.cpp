@@ -131,7 +131,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   const bool batched = A_in.rank() == 3;
   const int64_t Lb = batched ? A_in.mode(2).size() : 1;
   if (batched && (Lb != B_in.mode(2).size() || Lb != C_in.mode(2).size())) return LC_ERR_SIZE_MISMATCH;
-  if (Lb > 65535) return LC_ERR_TOO_LARGE;   // the batch index is the second grid dimension
+  if (Lb > 65535) return LC_ERR_TOO_LARGE;   // the tile kernels' second grid dimension is the batch index
   lc_gemm_plan plan;
   plan.ab_dtype = ab_dtype;
   plan.M = M;
@@ -275,6 +275,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   else if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
   else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);   // through registers: 256 x 256 when that gives every CU a tile
   else take(128, 128, 0, 0);
+  // The split and stream kernels put every batch entry's tiles into one dimension of the grid, which counts lanes in 32 bits; where
+  // thin problems in many batch entries have more tiles than that, the tile kernels, whose batch is a dimension of its own, take them
+  // (vectors at any alignment element by element).
+  if (plan.stages && (uint64_t)tiles_of(plan.tile_m, plan.tile_n) * (plan.split_waves ? 64u * (unsigned)plan.split_waves : (unsigned)kBlock) > 0xFFFFFFFFull) {
+    if (any) P.a_direct = P.b_direct = 0;
+    take(256, 256, 0, 0);
+  }
   P.tiles_m = (uint32_t)((kM + plan.tile_m - 1) / plan.tile_m);
   P.tiles_n = (uint32_t)((kN + plan.tile_n - 1) / plan.tile_n);
   P.k_tiles = (uint32_t)((K + kGemmBK - 1) / kGemmBK);

@@ -394,3 +394,22 @@ def test_tile_choice_of_middle_sizes(form, M, N, K, tile):
     b = "(%d,%d):" % (N, K) + ("(%d,1)" % K if form[1] == "t" else "(1,%d)" % N)
     text = lc.GemmPlan(a, b, "(%d,%d):(1,%d)" % (M, N, M)).describe()
     assert "tile=" + tile in text, text
+
+
+@pytest.mark.parametrize("K", [8, 9])
+@pytest.mark.parametrize("N,L,tile", [(53687, 40000, 0), (53684, 40000, 0), (16385, 65535, 32), (16385, 65535, 3264), (16385, 65535, 6464)])
+def test_thin_problems_in_many_batch_entries_fit_a_grid(K, N, L, tile, monkeypatch):
+    # one row in tens of thousands of batch entries: more than 2^24 tiles, and one dimension of a grid holds no more workgroups of 256
+    # lanes; the kernels with the batch in a dimension of its own take them
+    if tile:
+        monkeypatch.setenv("LC_TUNE_GEMM_TILE", str(tile))
+    text = lc.GemmPlan("(1,%d,%d):(%d,1,%d)" % (K, L, K, K), "(%d,%d,%d):(%d,1,0)" % (N, K, L, K), "(1,%d,%d):(1,1,%d)" % (N, L, N)).describe()
+    tiles_m, tiles_n = (int(x) for x in text.split(" tiles=")[1].split()[0].split("x"))
+    assert " stream " not in text and "split_waves" not in text and "tile=256x256" in text and tiles_m * tiles_n * 256 < 2 ** 32, text
+    assert ("direct-to-LDS" in text) == (K == 8) and "unaligned" not in text, text
+
+
+def test_as_many_tiles_as_one_dimension_of_a_grid_holds(monkeypatch):
+    monkeypatch.setenv("LC_TUNE_GEMM_TILE", "6464")
+    text = lc.GemmPlan("(1,8,65535):(8,1,8)", "(16384,8,65535):(8,1,0)", "(1,16384,65535):(1,1,16384)").describe()
+    assert " stream " in text and "L=65535" in text and "tiles=256x1 " in text, text   # 256 x 65535 workgroups of 256 lanes
