@@ -698,7 +698,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     // fourth only adds to what is under way at once (24 KiB: 4096 tiles, heads 8 x 4096 x 32 x 48, 39.5 us with three, 46.5 with
     // four; 12 KiB: 3333 tiles 17.0 and 15.6; 32 KiB: 4096 tiles 53.6 and 48.6), two of 32 KiB from 8192 tiles on (102 us with
     // two, 110 with three, 120 with four).
-    if (V == 1 && es == 16 && P.n_tiles < 16384) want = plan->lds_bytes < 16 * 1024 ? 4 : plan->lds_bytes < 32 * 1024 ? 3 : P.n_tiles < 8192 ? 4 : 2;
+    // Ragged ones (16-byte elements) four whatever their size (2000 x 3000: 47.8 us with the five that fit, 42.8; 331 x 5077 15.5 and 15.7, 17.2 with three).
+    if (V == 1 && es == 16 && P.n_tiles < 16384) want = P.n_ragged > 0 || plan->lds_bytes < 16 * 1024 ? 4 : plan->lds_bytes < 32 * 1024 ? 3 : P.n_tiles < 8192 ? 4 : 2;
     // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
     // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
     if (shifted) want = P.n_tiles >= 8192 ? 1 : (P.n_tiles >= 1280 ? 2 : 4);

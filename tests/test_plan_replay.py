@@ -477,3 +477,10 @@ def test_large_windows_of_words_keep_two_items_a_lane():
     for rows, unroll, wgs in ((2048, 1, 5), (8191, 1, 5), (8192, 2, 3), (16384, 2, 3)):
         desc = lc.Plan("(256,%d,32):(1,8192,256)" % rows, "(256,%d,32):(1,256,%d)" % (rows, 256 * rows), "bf16").describe()
         assert "class=direct" in desc and "unroll=%d " % unroll in desc and "wgs_per_cu=%d " % wgs in desc, desc
+
+
+def test_tiles_of_16_byte_elements_by_their_kind():
+    for a, b in ((331, 5077), (1001, 1003), (3001, 4003)):
+        desc = lc.Plan("(%d,%d):(1,%d)" % (a, b, a), "(%d,%d):(%d,1)" % (a, b, b), "b128").describe()
+        assert "ragged_modes=2" in desc and "wgs_per_cu=4 " in desc, desc
+    assert "wgs_per_cu=3 " in lc.Plan("(1024,1024):(1,1024)", "(1024,1024):(1024,1)", "b128").describe()   # whole tiles of 16 KiB
