@@ -327,6 +327,32 @@ def test_walk_vectors_at_any_alignment(oracle, case, tile):
         assert text.count("elements(in unaligned") == 2, text
 
 
+def odd_batches_and_folded_rows(values="ints"):
+    """Unaligned operands whose batch entries start at odd offsets, with one operand shared by all of them, and with a row mode of
+    several leaves that hold whole vectors."""
+    def w(name, dt, a, b, c, M, N, K, L=1):
+        return W.GemmWorkload(name, dt, a, b, c, *(lc.Layout(x).cosize for x in (a, b, c)), M, N, K, values, "", L)
+    return [
+        w("odd_batch_kk", "bf16", "(33,77,3):(77,1,2543)", "(70,77,3):(77,1,5391)", "(33,70,3):(1,33,2311)", 33, 70, 77, 3),
+        w("odd_batch_kr", "f16", "(67,61,4):(61,1,4089)", "(131,61,4):(1,131,7993)", "(67,131,4):(131,1,8777)", 67, 131, 61, 4),
+        w("odd_batch_rr", "bf16", "(9,200,5):(1,9,1801)", "(129,200,5):(1,131,26201)", "(9,129,5):(1,9,1163)", 9, 129, 200, 5),
+        w("odd_shared_b", "bf16", "(67,9,4):(9,1,605)", "(130,9,4):(9,1,0)", "(67,130,4):(1,67,8711)", 67, 130, 9, 4),
+        w("odd_shared_a", "f16", "(70,75,3):(1,70,0)", "(13,75,3):(75,1,977)", "(70,13,3):(1,70,911)", 70, 13, 75, 3),
+        w("folded_rows", "bf16", "((8,9),61):((1,11),99)", "(65,61):(61,1)", "(72,65):(1,72)", 72, 65, 61),
+        w("folded_rows_both", "f16", "((16,5),70):((1,19),95)", "((8,17),70):((1,9),153)", "(80,136):(1,80)", 80, 136, 70)]
+
+
+@pytest.mark.parametrize("tile", [0, 3216, 32, 3264, 6432, 64, 128, 12864, 64128, 6464])
+def test_walk_vectors_at_any_alignment_in_batches_and_folded_rows(oracle, tile):
+    for w in odd_batches_and_folded_rows():
+        text = _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
+        assert text.count("elements(in unaligned") == 2, text
+        if tile in (128, 12864, 64128, 6464):
+            assert " stream " in text, text
+        elif tile in (32, 3264, 6432, 64):
+            assert "split_waves" in text, text
+
+
 @pytest.mark.parametrize("which,layout,expect", [("a", "(2,9):(2147483638,1)", "k-vectors"), ("a", "(2,56):(2147483591,1)", "k-vectors"),
                                                  ("a", "(9,9):(1,268435454)", "row-vectors"), ("b", "(2,9):(2147483638,1)", "k-vectors")])
 def test_walk_vectors_at_any_alignment_of_an_operand_that_ends_at_the_offset_limit(which, layout, expect):

@@ -283,6 +283,14 @@ def test_gemm_vectors_at_any_alignment(oracle, tile, values):
         assert (np.abs(c_t.cpu().numpy().astype(np.float64) - want) <= (0 if values == "ints" else w.K * 2.0 ** -23 * bound)).all()
 
 
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [0, 32, 64, 128, 6464])
+def test_gemm_vectors_at_any_alignment_in_batches_and_folded_rows(oracle, tile, values):
+    from test_gemm_plan import odd_batches_and_folded_rows
+    for w in odd_batches_and_folded_rows(values):
+        assert _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile}).count("elements(in unaligned") == 2
+
+
 @pytest.mark.parametrize("layout,rows,K", [("(2,9):(2147483638,1)", 2, 9), ("(9,9):(1,268435454)", 9, 9)])
 def test_gemm_vectors_at_any_alignment_of_an_operand_that_ends_at_the_offset_limit(layout, rows, K):
     # K below a k tile and a last offset just below 2^31 (the walk of the same layouts checks every address on the host)
