@@ -949,9 +949,9 @@ static PreLaunch launch_transpose(const lc_plan& plan, const void* src, void* ds
   return PreLaunch{hipErrorInvalidValue, "kernel selection (micro-tiles per lane)"};
 }
 
-// shifted tiles: the transposing kernel on vectors at any alignment
-template <int ES, int V, int MT, int NT>
-static PreLaunch launch_shifted_n(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+// shifted tiles: the transposing kernel on vectors at any alignment (no nontemporal accesses: the L2 merges the lines two tiles share)
+template <int ES, int V, int MT>
+static PreLaunch launch_shifted_m(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
   const unsigned char* sp = static_cast<const unsigned char*>(src);
   unsigned char* dp = static_cast<unsigned char*>(dst);
   PreLaunch pre;
@@ -966,30 +966,21 @@ static PreLaunch launch_shifted_n(const lc_plan& plan, const void* src, void* ds
     static std::atomic<bool> raised{false};
     if (!raised.load(std::memory_order_acquire)) {
       pre.call = "hipFuncSetAttribute";
-      pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, NT, true, 0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, 0, true, 0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (pre.status == hipSuccess)
-        pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, NT, true, 1, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        pre.status = hipFuncSetAttribute(reinterpret_cast<const void*>(&transpose_kernel<ES, V, MT, 0, true, 1, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (pre.status != hipSuccess) return pre;
       raised.store(true, std::memory_order_release);
     }
   }
   const uint32_t grab = (uint32_t)std::max(1, plan.tile_queue);
   if (queue)
-    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, NT, true, 1, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
+    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, 0, true, 1, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
                        plan.transpose, dp, queue, plan.lds_bytes, grab, 1u, 1u, 0u);
   else
-    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, NT, true, 0, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
+    hipLaunchKernelGGL((transpose_kernel<ES, V, MT, 0, true, 0, true>), dim3(grid), dim3(kBlock), lds_bytes, s, sp, 0u, 0, 0, 0, 0, 0, 0u, 0u, (int64_t)0, (int64_t)0,
                        plan.transpose, dp, queue, plan.lds_bytes, grab, 1u, 1u, 0u);
   return pre;
-}
-template <int ES, int V, int MT>
-static PreLaunch launch_shifted_m(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
-  switch (plan.nontemporal) {
-    case 0: return launch_shifted_n<ES, V, MT, 0>(plan, src, dst, grid, s);
-    case 1: return launch_shifted_n<ES, V, MT, 1>(plan, src, dst, grid, s);
-    case 2: return launch_shifted_n<ES, V, MT, 2>(plan, src, dst, grid, s);
-    default: return launch_shifted_n<ES, V, MT, 3>(plan, src, dst, grid, s);
-  }
 }
 template <int ES, int V>
 static PreLaunch launch_shifted(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {

@@ -687,7 +687,7 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     plan->dst_run_bytes = run_length(J, dst_order, t, false) * es;
     // nontemporal stores only when every store instruction covers whole 128-byte lines
     if (tune.nontemporal < 0 && plan->dst_run_bytes % 128 == 0) plan->nontemporal |= 2;
-    if (tune.nontemporal < 0 && shifted) plan->nontemporal = 0;   // the L2 merges the lines two tiles share
+    if (shifted) plan->nontemporal = 0;   // the L2 merges the lines two tiles share
     // Measured on MI355X: HBM efficiency is best with ONE resident workgroup per CU (its next tile's
     // loads overlap its current tile's stores); short grids need more workgroups to fill the chip.
     int fit = (int)(160 * 1024 / std::max(1u, plan->lds_bytes));
