@@ -145,7 +145,7 @@ LC_HD uint32_t gemm_rdirect_frag_offset(uint32_t BR, uint32_t lane, uint32_t row
 }
 
 // kLoadKDirect: instruction i of wavefront w fills the 1 KiB of LDS that holds rows 8 (w R + i) .. + 7 of the tile
-// (R = BR / 32 instructions per lane); lane l lands at byte 16 l of it, i.e. row + l / 8, slot l % 8, and therefore
+// (R = BR / 32 instructions per lane of four wavefronts, BR / 8 of one); lane l lands at byte 16 l of it, i.e. row + l / 8, slot l % 8, and therefore
 // asks for the k vector that lives in that slot: kv = slot ^ row ^ (row >> 3).
 LC_HD uint32_t gemm_direct_row(uint32_t rows_per_lane, uint32_t tid, uint32_t i) { return ((tid >> 6) * rows_per_lane + i) * 8u + ((tid & 63u) >> 3); }
 LC_HD uint32_t gemm_direct_kvec(uint32_t row, uint32_t tid) { return ((tid & 7u) ^ row ^ (row >> 3)) & 7u; }

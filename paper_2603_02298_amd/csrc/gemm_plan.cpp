@@ -222,11 +222,11 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
   const bool thin = kN <= 16 && (P.b_load == kLoadKVec || P.b_direct == 2), vectors = direct || any;
   const bool free_choice = t_env == 0;
-  if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, 3);
-  else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, 2);
-  else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, 3);
-  else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, 3);
-  else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, 2);
+  if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, any ? 1 : 3);
+  else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, any ? 1 : 2);
+  else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, any ? 1 : 3);
+  else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, any ? 1 : 3);
+  else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, any ? 1 : 2);
   else if (vectors && (any || t_env != 256)) {
     // Larger problems.  The CU that is given the most tiles decides, so a tile's cost is how many of them that CU takes times
     // its area, times what its k loop costs per product against the 128 x 128 stream kernel's.  Smaller tiles read more of LDS per

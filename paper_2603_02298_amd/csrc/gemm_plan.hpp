@@ -16,7 +16,7 @@ struct lc_gemm_plan {
   int64_t a_cosize = 0, b_cosize = 0, c_cosize = 0; // elements addressable behind the caller's A, B, C
   std::string a_text, b_text, c_text;               // the three layouts coalesced by mode, as the kernel sees them
   int split_waves = 0;               // > 0: the split kernel, whose wavefronts share out the k tiles of the workgroup's tile
-  int stages = 0;                    // ... k tiles in flight per wavefront
+  int stages = 0;                    // > 0: the split or the stream kernel; pairs of operand tiles in LDS (split: per wavefront)
 };
 
 namespace lc {

@@ -4,7 +4,7 @@
 //
 // A workgroup of WAVES wavefronts owns a TM x TN tile of C (32 or 64 a side); its wavefronts share out the k tiles of 64
 // (wavefront w takes w, w + WAVES, ...), each through a ring of STAGES tile pairs of its own that the memory pipeline fills
-// straight into LDS.  Nothing is shared in the k loop, so it has no barrier: a wavefront waits for its own loads only.  The
+// straight into LDS (vectors at any alignment: one pair, filled from registers that hold the next k tile meanwhile).  Nothing is shared in the k loop, so it has no barrier: a wavefront waits for its own loads only.  The
 // partial tiles are then summed through LDS in the order of the wavefronts (the same result every time) and added to C, whose
 // old values were asked for before the first operand load.
 // TN = 16 (at most 16 columns, contiguous along k): the 16 rows of B stand twice in their fragment, so no load is spent on
@@ -34,6 +34,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
   static_assert(TN != 16 || !gemm_load_is_k_major(B_LOAD), "16 rows: row-major tiles only");
   static_assert(PARTIAL <= RING, "a wavefront's partial tile takes the place of its own ring");
   static_assert((STAGES - 1) * R < 64, "vmcnt has six bits");
+  static_assert(!ANY || STAGES == 1, "through registers: one pair of tiles");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   touch_kernel_arguments<(int)sizeof(GemmParams) + 24>();
 
@@ -189,11 +190,12 @@ static inline hipError_t launch_split(const lc_gemm_plan& plan, const uint16_t* 
 }
 template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_split_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  if (plan.tile_m == 32 && plan.tile_n == 16) return launch_split<BF16, 32, 16, 8, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 32 && plan.tile_n == 32) return launch_split<BF16, 32, 32, 8, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 32 && plan.tile_n == 64) return launch_split<BF16, 32, 64, 4, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 32) return launch_split<BF16, 64, 32, 4, 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_split<BF16, 64, 64, 4, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  constexpr bool ANY = gemm_load_is_any(K_LOAD);   // the k tile after the parked one waits in registers: one pair of tiles each
+  if (plan.tile_m == 32 && plan.tile_n == 16) return launch_split<BF16, 32, 16, 8, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 32 && plan.tile_n == 32) return launch_split<BF16, 32, 32, 8, ANY ? 1 : 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 32 && plan.tile_n == 64) return launch_split<BF16, 32, 64, 4, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 32) return launch_split<BF16, 64, 32, 4, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_split<BF16, 64, 64, 4, ANY ? 1 : 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
 

@@ -1,6 +1,6 @@
 // Device code of the stream GEMM: C(m,n) += A(m,k) * B(n,k) (Sec. 2.6.2 of "CuTe Layout Representation and Algebra") for
 // operands that go straight into LDS, on problems with tiles for every CU but a k loop too short, or sides too small, for
-// the 256 x 256 kernel.
+// the 256 x 256 kernel, and for operands in vectors at any alignment, which pass through registers on their way into LDS.
 //
 // Four wavefronts own a BM x BN tile, wavefront (wm, wn) a quarter of it.  LDS holds two pairs of operand tiles; one
 // barrier per k tile, after which the pair before it is overwritten by the next.  Two or more workgroups
@@ -24,12 +24,14 @@
 
 namespace lc {
 
-template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD, bool C_VEC>
-__global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) void gemm_stream_kernel(GemmParams P, const uint16_t* __restrict__ A,
+constexpr int kStreamStages = 2;   // pairs of operand tiles in LDS: one being multiplied, one on its way
+
+template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC>
+__global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 128)) void gemm_stream_kernel(GemmParams P, const uint16_t* __restrict__ A,
                                                                                                    const uint16_t* __restrict__ B, float* __restrict__ C) {
   constexpr int FM = BM / 64, FN = BN / 64, KSTEPS = kGemmBK / 16;
   constexpr uint32_t A_BYTES = BM * 128u, STAGE = (BM + BN) * 128u;
-  static_assert(STAGES == 2 && BM * BN * 4 <= STAGES * (BM + BN) * 128, "the sums of the tile fit the ring");
+  static_assert(BM * BN * 4 <= kStreamStages * (BM + BN) * 128, "the sums of the tile fit the ring");
   constexpr bool ANY = gemm_load_is_any(A_LOAD);
   static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -147,42 +149,42 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (STAGES * (BM + BN) * 128)) vo
   units.add(P, C, m0, n0, tid, [&](uint32_t unit) { return *reinterpret_cast<const f32x4*>(lds + unit * 16u); });
 }
 
-template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD, bool C_VEC>
+template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC>
 static inline hipError_t launch_stream_abc(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  if (plan.lds_bytes != (unsigned)(STAGES * (BM + BN) * 128)) return hipErrorInvalidValue;
+  if (plan.lds_bytes != (unsigned)(kStreamStages * (BM + BN) * 128)) return hipErrorInvalidValue;
   static std::atomic<bool> raised{false};   // one flag per instantiation: the attribute belongs to the kernel function
   if (plan.lds_bytes > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_stream_kernel<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, C_VEC>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised.store(true, std::memory_order_release);
   }
   const unsigned grid = plan.params.tiles_m * plan.params.tiles_n * plan.params.L;
-  hipLaunchKernelGGL((gemm_stream_kernel<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, C_VEC>), dim3(grid), dim3(kBlock), plan.lds_bytes, s, plan.params, a, b, c);
+  hipLaunchKernelGGL((gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC>), dim3(grid), dim3(kBlock), plan.lds_bytes, s, plan.params, a, b, c);
   return hipSuccess;
 }
-template <bool BF16, int BM, int BN, int STAGES, int A_LOAD, int B_LOAD>
+template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD>
 static inline hipError_t launch_stream_ab(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
-                           : launch_stream_abc<BF16, BM, BN, STAGES, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
+  return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
+                           : launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
 // K_LOAD, R_LOAD: the pair of load kinds (straight into LDS, or vectors at any alignment) this translation unit holds
-template <bool BF16, int BM, int BN, int STAGES, int K_LOAD, int R_LOAD>
+template <bool BF16, int BM, int BN, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
-  if (la == K_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, K_LOAD, K_LOAD>(plan, a, b, c, s);
-  if (la == K_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (la == R_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, R_LOAD, K_LOAD>(plan, a, b, c, s);
-  if (la == R_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, STAGES, R_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (la == K_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, K_LOAD, K_LOAD>(plan, a, b, c, s);
+  if (la == K_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (la == R_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, R_LOAD, K_LOAD>(plan, a, b, c, s);
+  if (la == R_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, R_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
 template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  if (plan.stages != 2) return hipErrorInvalidValue;
-  if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
-  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_stream<BF16, 64, 64, 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.stages != kStreamStages) return hipErrorInvalidValue;
+  if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  if (plan.tile_m == 64 && plan.tile_n == 64) return launch_stream<BF16, 64, 64, K_LOAD, R_LOAD>(plan, a, b, c, s);
   return hipErrorInvalidValue;
 }
 
