@@ -1176,9 +1176,19 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
   int dflt_unroll = W >= 16 ? 2 : (W >= 4 ? 4 : 8), dflt_wgs = W >= 8 ? 3 : 4;   // 3 x 256 CUs: a grid that is not a power of two
   // Several joint modes in whole words: the index arithmetic wants more wavefronts with one item each, on copies below 128 MiB
   // (us, two items and three workgroups -> one and five: windows of 64 B to 16 KiB rows and rows swapped, 16 MiB 8.7 -> 8.1, 32 MiB 15 -> 13.6,
-  // 64 MiB 26 -> 25; heads 4 x 1024 x 16 x 128 9.5 -> 7.9, 8 x 2048 x 8 x 96 12.1 -> 10.6).  From there on it depends on the
-  // strides: 256 MiB of 512 B rows swapped over 32 92 -> 101, 16 KiB rows into every other one 89 -> 96, but 512 B rows out of every other one 101 -> 93.
-  if (W >= 16 && P.n_modes > 1 && P.loop_extent == 1 && items * W < (1ll << 27)) { dflt_unroll = 1; dflt_wgs = 5; }
+  // 64 MiB 26 -> 25; heads 4 x 1024 x 16 x 128 9.5 -> 7.9, 8 x 2048 x 8 x 96 12.1 -> 10.6), and on rows permuted over two modes and more up to
+  // half a GiB (heads 7 x 4562 x 32 x 96 87.1 -> 81.6, 6 x 5775 x 32 x 128 99.6 -> 96.3) unless the first destination stride of 64 KiB and
+  // more is a multiple of that, where more under way at once meets in the same channels (256 MiB of 512 B rows swapped over 32 92 -> 101).  Windows of that
+  // size go either way (16 KiB rows into every other one 89 -> 96, 512 B rows out of every other one 101 -> 93) and keep two items.
+  if (W >= 16 && P.n_modes > 1 && P.loop_extent == 1) {
+    bool channel_steps = false;
+    for (int k = 0; k < P.n_modes; ++k)
+      if (P.sb[k] * W >= 65536) {   // (in the order of the destination's strides)
+        channel_steps = P.sb[k] * W % 65536 == 0;
+        break;
+      }
+    if (items * W < (1ll << 27) || (P.n_modes >= 3 && !channel_steps && items * W < (1ll << 29))) { dflt_unroll = 1; dflt_wgs = 5; }
+  }
   plan->unroll = (tune.unroll == 1 || tune.unroll == 2 || tune.unroll == 4 || tune.unroll == 8) ? tune.unroll : dflt_unroll;
   plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : dflt_wgs;
   // Contiguous copies of 2 GiB and more per side: the grid-stride order lets workgroups drift apart, chunks of 32 KiB handed

@@ -485,3 +485,10 @@ def test_tiles_of_16_byte_elements_by_their_kind():
         desc = lc.Plan("(%d,%d):(1,%d)" % (a, b, a), "(%d,%d):(%d,1)" % (a, b, b), "b128").describe()
         assert "ragged_modes=2" in desc and "wgs_per_cu=4 " in desc, desc
     assert "wgs_per_cu=4 " in lc.Plan("(1024,1024):(1,1024)", "(1024,1024):(1024,1)", "b128").describe()   # 1024 whole tiles of 16 KiB
+
+
+def test_large_permutes_of_rows_run_one_item_a_lane_unless_they_step_between_channels():
+    for S, H, D, unroll in ((4562, 32, 96, 1), (5775, 32, 128, 1), (5776, 32, 128, 1), (4096, 32, 128, 2), (8192, 32, 128, 2)):
+        s, d = "(%d,%d,%d,6):(1,%d,%d,%d)" % (D, H, S, D, D * H, D * H * S), "(%d,%d,%d,6):(1,%d,%d,%d)" % (D, H, S, D * S, D, D * S * H)
+        desc = lc.Plan(s, d, "bf16").describe()
+        assert "class=direct" in desc and "unroll=%d " % unroll in desc, desc
