@@ -740,7 +740,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
 //   to about 1.8 for bf16 pairs and 2.0 for fp32 (bf16 34 x 780154 pitch 98 [1.88] 51 -> 66; fp32 2377 x 9 x 28^2 [2.3] 52 -> 57,
 //   65 x 32256 [1.97] 12.3 -> 6.2);
 //   8 bytes wide: whole tiles to 1.1 (bf16 100 x 335488 [1.28] 40.9 -> 39.7, but 12 x 2796160 [1.33] 39 -> 47, 3 x 100 x 224^2
-//   [1.28] 15.2 -> 22.1), further where runs are short and lanes idle (100 x 20928 [1.28] 8.2 -> 5.2); ragged tiles to 1.2
+//   [1.28] 15.2 -> 22.1), further where runs are short and lanes idle (100 x 20928 [1.28] 8.2 -> 5.2, 148 x 114^2 [1.6] 6.8 -> 5.9) and to
+//   2.0 for narrow bf16 destinations in tiles of three and four vectors' squares a lane (64 x 132 x 248^2 [1.94] 680 -> 535, 51 x 52 x 142^2 60 -> 48); ragged tiles to 1.2
 //   beyond their own idle lanes (648 x 132 x 14^2 [2.53, idle 2.53] 36 -> 22, but 20 x 2175752 [1.6] 57 -> 67);
 //   16 bytes wide, ragged: bf16 to 1.2, 1.35 up to 2^22 elements, 1.45 where tiles have fewer than 64 lanes (27 x 232 x 12^2 [1.33 times the idle] 4.9 -> 4.4, 44 x 24 x 76^2 [1.39] 10.9 -> 7.4, 2944 x 2320 [1.05] 11.5 -> 7.2, 8000 x 8008 70.5 -> 58; 160 x 103488 [1.33 times the idle] 19 -> 22), fp32
 //   to 1.1 in tiles that leave lanes idle, 1.05 in full ones of copies of 2^23 elements (316 x 22184 15.7 -> 18.1, 3356 x 11812 83 -> 72);
@@ -761,12 +762,15 @@ static double shifted_limit(const lc_plan& plain_plan, bool plain, int es, int64
   const int width = plain_plan.V * es;
   const bool ragged = P.n_ragged > 0, short_runs = std::min(plain_plan.src_run_bytes, plain_plan.dst_run_bytes) < 128;
   const bool idle = P.n_micro < (uint32_t)kBlock, mostly_idle = P.n_micro < (uint32_t)kBlock / 4;
-  if (width < 16) return width == 8 && short_runs && idle ? 1.6 : narrow_shifted_limit(width, es, ragged);
+  if (width == 8 && short_runs && idle) return 1.65;
+  const JointMode &mp = plain_plan.joint[(size_t)plain_plan.p_mode], &mq = plain_plan.joint[(size_t)plain_plan.q_mode];
+  if (width == 8 && es == 2 && !ragged && P.n_micro > 2u * kBlock && mq.extent < mp.extent) return 2.0;
+  if (width < 16) return narrow_shifted_limit(width, es, ragged);
   if (ragged) return es == 2 ? (mostly_idle ? 1.45 : n <= (1 << 22) ? 1.35 : 1.2) : idle ? 1.1 : n >= (1 << 23) ? 1.05 : 0.0;
   if (!idle) return 0.0;
-  if (short_runs) return mostly_idle ? 1.3 : es == 2 ? 1.0 : 1.1;
+  if (short_runs) return mostly_idle ? (es == 2 ? 1.3 : 1.6) : es == 2 ? 1.0 : 1.1;
   if (n < (1 << 22)) return 0.0;
-  const int64_t row_bytes = plain_plan.joint[(size_t)plain_plan.p_mode].extent * es;
+  const int64_t row_bytes = mp.extent * es;
   const bool few_vectors = row_bytes <= 32 && plain_plan.src_run_bytes > row_bytes;   // (rows that continue each other)
   return es == 2 ? (mostly_idle ? 1.3 : few_vectors ? 1.02 : 0.0) : 1.01;
 }
