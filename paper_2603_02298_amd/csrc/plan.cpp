@@ -1183,7 +1183,8 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
   // 64 MiB 26 -> 25; heads 4 x 1024 x 16 x 128 9.5 -> 7.9, 8 x 2048 x 8 x 96 12.1 -> 10.6), and on rows permuted over two modes and more up to
   // half a GiB (heads 7 x 4562 x 32 x 96 87.1 -> 81.6, 6 x 5775 x 32 x 128 99.6 -> 96.3) unless the first destination stride of 64 KiB and
   // more is a multiple of that, where more under way at once meets in the same channels (256 MiB of 512 B rows swapped over 32 92 -> 101).  Windows of that
-  // size go either way (16 KiB rows into every other one 89 -> 96, 512 B rows out of every other one 101 -> 93) and keep two items.
+  // size: out of pitches that are no power of two (256 MiB, 512 B rows of 528 100 -> 93, 16 KiB rows of 16400 96 -> 92; of 1024 86 -> 89) and rows
+  // of up to 512 B into them (256 B rows of 272 139 -> 132; 16 KiB rows 89 -> 96).
   if (W >= 16 && P.n_modes > 1 && P.loop_extent == 1) {
     bool channel_steps = false;
     for (int k = 0; k < P.n_modes; ++k)
@@ -1191,7 +1192,11 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
         channel_steps = P.sb[k] * W % 65536 == 0;
         break;
       }
-    if (items * W < (1ll << 27) || (P.n_modes >= 3 && !channel_steps && items * W < (1ll << 29))) { dflt_unroll = 1; dflt_wgs = 5; }
+    auto odd_pitch = [&](int64_t words) { return (words * W & (words * W - 1)) != 0; };
+    const int64_t row = P.div[0].div;
+    const bool window = P.n_modes == 2 && P.sa[0] == 1 && P.sb[0] == 1 &&
+                        ((P.sb[1] == row && P.sa[1] > row && odd_pitch(P.sa[1])) || (P.sa[1] == row && P.sb[1] > row && row * W <= 512 && odd_pitch(P.sb[1])));
+    if (items * W < (1ll << 27) || (((P.n_modes >= 3 && !channel_steps) || window) && items * W < (1ll << 29))) { dflt_unroll = 1; dflt_wgs = 5; }
   }
   plan->unroll = (tune.unroll == 1 || tune.unroll == 2 || tune.unroll == 4 || tune.unroll == 8) ? tune.unroll : dflt_unroll;
   plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : dflt_wgs;

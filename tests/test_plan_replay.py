@@ -493,3 +493,11 @@ def test_large_permutes_of_rows_run_one_item_a_lane_unless_they_step_between_cha
         s, d = "(%d,%d,%d,6):(1,%d,%d,%d)" % (D, H, S, D, D * H, D * H * S), "(%d,%d,%d,6):(1,%d,%d,%d)" % (D, H, S, D * S, D, D * S * H)
         desc = lc.Plan(s, d, "bf16").describe()
         assert "class=direct" in desc and "unroll=%d " % unroll in desc, desc
+
+
+def test_large_windows_by_their_pitch():
+    for row, pitch, out_of, into in ((256, 264, 1, 1), (256, 512, 2, 2), (8192, 8200, 1, 2), (128, 136, 1, 1)):   # bf16 elements, 2^27 of them
+        n = (1 << 27) // row
+        a, b = "(%d,%d):(1,%d)" % (row, n, pitch), "(%d,%d):(1,%d)" % (row, n, row)
+        for s, d, unroll in ((a, b, out_of), (b, a, into)):
+            assert "unroll=%d " % unroll in lc.Plan(s, d, "bf16").describe(), (row, pitch, s)
