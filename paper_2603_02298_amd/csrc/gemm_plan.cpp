@@ -234,7 +234,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     // 64 x 64: 1.3, 2.2, 2.3; a side of 64 rows of a k-major operand a tenth more); a lone workgroup on a CU has nobody to
     // cover its waits and runs at about half the pace (1.9; below 768 1.25).  The 256 x 256 kernel reads least, but its short k loops
     // wait and nothing covers its C update (1.1, 1.0 below 1024, 0.85 below 2048, 0.77, 0.72 from 3000 on), and with fewer tiles than CUs it
-    // runs at a higher clock (down to 0.7, 0.8 from 3000 on).  The ring of five 128 x 128 tiles asks for its k tiles further ahead than
+    // runs at a higher clock (down to 0.9 below K = 2048, 0.7, 0.8 from 3000 on).  The ring of five 128 x 128 tiles asks for its k tiles further ahead than
     // the stream kernel: the better one alone on a CU over a long k loop (1.35 from K = 3000 on).
     // Measured on MI355X (bf16, us; ring of 128 x 128, stream 128 x 128, 128 x 64, 64 x 128, 64 x 64, 256 x 256; t: along k, n: along the rows):
     //   tt 7816 x 496 x 5288 63, 76, 77, 75, 100, 111; nt 2296 x 1688 x 8000 82, 96, 90, 91, 127, 142; tt 3120 x 1272 x 3360 42, 48, 44, 45, 56, 78;
@@ -259,7 +259,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     const Choice* best = nullptr;
     for (const Choice& c : choices)
       if (!best || cost(c) < cost(*best)) best = &c;
-    const double fill = K < 3000 ? 0.7 : 0.8;
+    const double fill = K < 2048 ? 0.9 : K < 3000 ? 0.7 : 0.8;
     const Choice big = {256, 256, (K < 768 ? 1.1 : K < 1024 ? 1.0 : K < 2048 ? 0.85 : K < 3000 ? 0.77 : 0.72) *
                                       std::min(1.0, fill + (1.0 - fill) * (double)tiles_of(256, 256) / 256.0), 1.0};
     const Choice ring = {128, 128, 1.0, 1.35};
