@@ -6,8 +6,9 @@
 // barrier per k tile, after which the pair before it is overwritten by the next.  Two or more workgroups
 // share a CU: one's start, its C update and its waits at the barrier lie under the others' products.  The old values of C
 // are asked for before the k loop, the sums pass through LDS and C is updated in whole runs.
-// What bounds it: for a short k loop C's way from and to HBM (128 x 100352 x 64: 5.4-6.3 TB/s), for a longer one LDS (a 64 x 64
-// quarter per wavefront reads 128 bytes per clock and CU at the matrix cores' full rate, all that LDS gives).
+// What bounds it: for a short k loop C's way from and to HBM (128 x 100352 x 64: 5.4-6.3 TB/s), for a longer one the waits: for
+// a k tile asked for one k tile before, for C's old values ahead of the first, at the barrier (16 x (1000 x 1504 x 776): wavefronts wait
+// half of their time, matrix cores are busy 19 % of the clocks, LDS 12 %).
 // Measured on MI355X (bf16, whole ring kernel of 128 x 128 tiles -> this kernel's 128 x 128): 16 x (1000 x 1504 x 776) 100 -> 83 us,
 // a 3 x 3 convolution of 128 x 100352 x 576 39 -> 34 us (128 x 64 tiles: 32.6), 4096^3 158 -> 149 us.  Three stages and more
 // (fewer workgroups per CU) measured slower wherever there are more tiles than CUs, and gained 0-7 % where there are not; so did
