@@ -694,15 +694,15 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     int want = P.n_tiles >= 16384 ? 1 : (P.n_tiles >= 4096 ? 2 : (P.n_tiles >= 2048 ? 3 : 4));
     // the ragged / element-wise kernel has no software pipeline: resident workgroups overlap each other instead
     if (P.n_ragged > 0 || (V == 1 && es != 16)) want = 8;
-    // Word tiles (V = 1) have no transpose to hide a wait behind: four workgroups a CU, three of tiles between 16 KiB and 32 from 1536
+    // Word tiles (V = 1) have no transpose to hide a wait behind: four workgroups a CU, three of tiles between 16 KiB and 32 from 1792
     // of them on, whose fourth only adds to what is under way at once (24 KiB: 4096 tiles, heads 8 x 4096 x 32 x 48, 39.5 us with three,
-    // 46.5 with four; 30 KiB: 1122 tiles, one round and a bit with four, 18.8 and 17.2; 12 KiB: 3333 tiles 17.0 and 15.6; 32 KiB: 4096 tiles 53.6 and 48.6), two of 32 KiB from 8192 tiles on (102 us with
+    // 46.5 with four; 30 KiB: 1122 tiles 18.8 and 17.2, 2000 27.9 and 30.7; 22 KiB: 1545 tiles 18.7 and 17.5; 12 KiB: 3333 tiles 17.0 and 15.6; 32 KiB: 4096 tiles 53.6 and 48.6), two of 32 KiB from 8192 tiles on (102 us with
     // two, 110 with three, 120 with four).
     // Ragged ones (16-byte elements) four whatever their size (2000 x 3000: 47.8 us with the five that fit, 42.8; 331 x 5077 15.5 and 15.7, 17.2 with three).
     if (V == 1 && es == 16 && P.n_tiles < 16384) {
       const bool middle = plan->lds_bytes >= 16 * 1024 && plan->lds_bytes < 32 * 1024;
       if (P.n_ragged > 0) want = 4;
-      else want = middle && P.n_tiles >= 1536 ? 3 : plan->lds_bytes >= 32 * 1024 && P.n_tiles >= 8192 ? 2 : 4;
+      else want = middle && P.n_tiles >= 1792 ? 3 : plan->lds_bytes >= 32 * 1024 && P.n_tiles >= 8192 ? 2 : 4;
     }
     // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
     // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)

@@ -460,7 +460,7 @@ def test_shifted_tiles_are_weighed_against_the_plain_plan():
 
 
 @pytest.mark.parametrize("piece,A,B,C,wgs", [
-    (48, 32, 4096, 8, 3), (96, 256, 256, 16, 3), (16, 256, 256, 16, 4), (128, 12, 3740, 6, 4), (64, 7, 9999, 9, 4), (16, 3000, 3000, 1, 4), (128, 32, 4096, 8, 4), (64, 64, 8192, 8, 2),   # tiles, by their size and number
+    (48, 32, 4096, 8, 3), (96, 256, 256, 16, 3), (16, 256, 256, 16, 4), (128, 12, 3740, 6, 4), (128, 12, 7725, 3, 4), (64, 7, 9999, 9, 4), (16, 3000, 3000, 1, 4), (128, 32, 4096, 8, 4), (64, 64, 8192, 8, 2),   # tiles, by their size and number
     (16, 7, 9999, 9, 4), (32, 32, 8192, 1, 4), (48, 32, 8192, 1, 4), (16, 32, 3000, 4, 4), (128, 16, 1024, 4, 4),             # short pieces: small tiles too
     (144, 256, 256, 16, 3), (160, 32, 4096, 8, 3), (240, 1024, 1024, 1, 3),                                                  # longer ones: many tiles only
     (48, 12, 668, 8, 0), (64, 16, 1024, 4, 0), (96, 12, 668, 8, 0), (160, 32, 3000, 4, 0), (240, 32, 8192, 1, 0), (192, 64, 8192, 8, 0)])
