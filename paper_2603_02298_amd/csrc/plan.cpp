@@ -735,20 +735,24 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
 // they are better at is 16-byte accesses in place of narrow ones and full workgroups; what they cost is elements moved twice and
 // runs cut at a tile's edge, which counts for more the wider the plain plan's vectors are.  Measured on MI355X over 1500 copies
 // of 2^19 to 2^27 elements (transposes with a side of 5 to 520, of random sides and pitches, NCHW <-> NHWC; both directions),
-// in us, plain -> shifted, share of elements moved twice in brackets:
-//   single 2-byte elements: always ahead but once (17 x 1973760 [1.88] 81 -> 54, 594 x 9 x 56^2 [2.3] 45 -> 28); 4 bytes wide: ahead
-//   to about 1.8 for bf16 pairs and 2.0 for fp32 (bf16 34 x 780154 pitch 98 [1.88] 51 -> 66; fp32 2377 x 9 x 28^2 [2.3] 52 -> 57,
-//   65 x 32256 [1.97] 12.3 -> 6.2);
+// in us, plain -> shifted, elements the shifted tiles cover over elements copied in brackets:
+//   single 2-byte elements: always ahead but once (17 x 1973760 [1.88] 81 -> 54, 594 x 9 x 56^2 [2.3] 45 -> 28); 4 bytes wide:
+//     ahead to about 1.8 for bf16 pairs and 2.0 for fp32 (bf16 34 x 780154 pitch 98 [1.88] 51 -> 66; fp32 2377 x 9 x 28^2 [2.3]
+//     52 -> 57, 65 x 32256 [1.97] 12.3 -> 6.2);
 //   8 bytes wide: whole tiles to 1.1 (bf16 100 x 335488 [1.28] 40.9 -> 39.7, but 12 x 2796160 [1.33] 39 -> 47, 3 x 100 x 224^2
-//   [1.28] 15.2 -> 22.1), further where runs are short and lanes idle (100 x 20928 [1.28] 8.2 -> 5.2, 148 x 114^2 [1.6] 6.8 -> 5.9) and to
-//   2.0 for narrow bf16 destinations in tiles of three and four vectors' squares a lane (64 x 132 x 248^2 [1.94] 680 -> 535, 51 x 52 x 142^2 60 -> 48); ragged tiles to 1.2
-//   beyond their own idle lanes (648 x 132 x 14^2 [2.53, idle 2.53] 36 -> 22, but 20 x 2175752 [1.6] 57 -> 67);
-//   16 bytes wide, ragged: bf16 to 1.2, 1.35 up to 2^22 elements, 1.45 where tiles have fewer than 64 lanes (27 x 232 x 12^2 [1.33 times the idle] 4.9 -> 4.4, 44 x 24 x 76^2 [1.39] 10.9 -> 7.4, 2944 x 2320 [1.05] 11.5 -> 7.2, 8000 x 8008 70.5 -> 58; 160 x 103488 [1.33 times the idle] 19 -> 22), fp32
-//   to 1.1 in tiles that leave lanes idle, 1.05 in full ones of copies of 2^23 elements (316 x 22184 15.7 -> 18.1, 3356 x 11812 83 -> 72);
-//   16 bytes wide, whole tiles: full workgroups stay ahead (4000^2 fp32 25.8 -> 27.5, 136 x 246720 bf16 [1.88] 27 -> 46), and so do bf16
-//   ones from 64 lanes on (83 x 256 x 28^2 [1.14] 15.7 -> 21.8); fewer lanes, or fp32 without elements moved twice: shifted
-//   (4000^2 bf16 with 80 lanes and 64-byte runs 18.3 -> 12.0, 832 x 10512 [1.09] 11.8 -> 10.3, 64 x 280928 fp32 49 -> 31), and bf16
-//   sources of one or two vectors a row (8 x 4040080 50 -> 30, NHWC -> NCHW 20 x 16 x 224^2 17.9 -> 15.1).
+//     [1.28] 15.2 -> 22.1), further where runs are short and lanes idle (100 x 20928 [1.28] 8.2 -> 5.2, 148 x 114^2 [1.6] 6.8 ->
+//     5.9) and to 2.0 for narrow bf16 destinations in tiles of three and four vectors' squares a lane (64 x 132 x 248^2 [1.94]
+//     680 -> 535, 51 x 52 x 142^2 60 -> 48); ragged tiles to 1.2 beyond their own idle lanes (648 x 132 x 14^2 [2.53, idle 2.53]
+//     36 -> 22, but 20 x 2175752 [1.6] 57 -> 67);
+//   16 bytes wide, ragged: bf16 to 1.2, 1.35 up to 2^22 elements, 1.45 where tiles have fewer than 64 lanes (27 x 232 x 12^2
+//     [1.33 times the idle] 4.9 -> 4.4, 44 x 24 x 76^2 [1.39] 10.9 -> 7.4, 2944 x 2320 [1.05] 11.5 -> 7.2, 8000 x 8008 70.5 ->
+//     58; 160 x 103488 [1.33 times the idle] 19 -> 22), fp32 to 1.1 in tiles that leave lanes idle (1.25 below 64 lanes: 34 x 28
+//     x 44^2 6.6 -> 5.9), 1.05 in full ones of copies of 2^23 elements (316 x 22184 15.7 -> 18.1, 3356 x 11812 83 -> 72);
+//   16 bytes wide, whole tiles: full workgroups stay ahead (4000^2 fp32 25.8 -> 27.5, 136 x 246720 bf16 [1.88] 27 -> 46), and
+//     so do bf16 ones from 64 lanes on (83 x 256 x 28^2 [1.14] 15.7 -> 21.8); fewer lanes, or fp32 without elements moved twice
+//     or with short runs: shifted (4000^2 bf16 with 80 lanes and 64-byte runs 18.3 -> 12.0, 832 x 10512 [1.09] 11.8 -> 10.3,
+//     fp32 20 x 196 x 24^2 [1.3] 7.1 -> 6.1, 64 x 280928 fp32 49 -> 31), and bf16 sources of one or two vectors a row (8 x
+//     4040080 50 -> 30, NHWC -> NCHW 20 x 16 x 224^2 17.9 -> 15.1).
 // Copies below 2^19 elements take a launch's time either way.
 constexpr int64_t kShiftedMinElems = 1 << 19;
 static double narrow_shifted_limit(int width, int es, bool ragged) {
@@ -766,9 +770,10 @@ static double shifted_limit(const lc_plan& plain_plan, bool plain, int es, int64
   const JointMode &mp = plain_plan.joint[(size_t)plain_plan.p_mode], &mq = plain_plan.joint[(size_t)plain_plan.q_mode];
   if (width == 8 && es == 2 && !ragged && P.n_micro > 2u * kBlock && mq.extent < mp.extent) return 2.0;
   if (width < 16) return narrow_shifted_limit(width, es, ragged);
-  if (ragged) return es == 2 ? (mostly_idle ? 1.45 : n <= (1 << 22) ? 1.35 : 1.2) : idle ? 1.1 : n >= (1 << 23) ? 1.05 : 0.0;
+  if (ragged && mostly_idle) return es == 2 ? 1.45 : 1.25;
+  if (ragged) return es == 2 ? (n <= (1 << 22) ? 1.35 : 1.2) : idle ? 1.1 : n >= (1 << 23) ? 1.05 : 0.0;
   if (!idle) return 0.0;
-  if (short_runs) return mostly_idle ? (es == 2 ? 1.3 : 1.6) : es == 2 ? 1.0 : 1.1;
+  if (short_runs) return mostly_idle ? (es == 2 ? 1.3 : 1.6) : es == 2 ? 1.0 : 1.35;
   if (n < (1 << 22)) return 0.0;
   const int64_t row_bytes = mp.extent * es;
   const bool few_vectors = row_bytes <= 32 && plain_plan.src_run_bytes > row_bytes;   // (rows that continue each other)

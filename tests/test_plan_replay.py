@@ -451,7 +451,8 @@ def test_shifted_tiles_are_weighed_against_the_plain_plan():
         assert "shifted" not in _nchw(N, C, hw, dt), (N, C, hw, dt)
     for N, C, hw, dt in ((162, 132, 784, "bf16"), (648, 132, 196, "bf16"), (648, 33, 784, "bf16"), (16, 200, 12769, "f16"), (64, 256, 196, "f16"), (162, 33, 3136, "f32"),
                          (44, 24, 5776, "bf16"), (27, 232, 144, "f16"),
-                         (64, 132, 61504, "f16"), (51, 52, 20164, "f16"), (21, 156, 7744, "bf16"), (1, 148, 12996, "bf16"), (50, 224, 100, "f32")):
+                         (64, 132, 61504, "f16"), (51, 52, 20164, "f16"), (21, 156, 7744, "bf16"), (1, 148, 12996, "bf16"), (50, 224, 100, "f32"),
+                         (20, 196, 576, "f32"), (34, 28, 1936, "f32")):
         assert "shifted_tiles=1" in _nchw(N, C, hw, dt), (N, C, hw, dt)
     for a, b, dt in ((65, 32256, "f32"), (17, 1973760, "bf16"), (2944, 2320, "bf16"), (16, 332016, "bf16"), (3356, 11812, "f32"),
                      (8, 4040080, "bf16")):
