@@ -143,6 +143,39 @@ struct DirectTileLoader {
   }
 };
 
+// The same over any k mode whose first leaf holds whole vectors: lane l evaluates the mode for k vector l % 8 of the tile, the
+// others read it from there.  (Measured on MI355X, us; staged through registers -> this: convolutions of 128 x 90750 x 144 47 -> 22.6, of
+// 232 x 33856 x 288 30.6 -> 21.9; in vectors gathered through registers 256 x 115200 x 288 takes 80, this 67-70.)
+template <int BR, int WAVES>
+struct LeavesTileLoader {
+  static constexpr int R = BR / 8 / WAVES;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t off[R];       // bytes of the lane's row; 0xFFFFFFFF: no such row
+  uint32_t K, t;
+  __device__ __forceinline__ void init(const uint16_t* p, const GemmMode& rmode, const GemmMode&, uint32_t row0, uint32_t extent, uint32_t Ktot, uint32_t lane) {
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, 0xFFFFFFFFu, 0x00020000);
+    K = Ktot;
+    t = lane;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const uint32_t r = row0 + gemm_direct_row(R, t, (uint32_t)i);
+      off[i] = r < extent ? 2u * gemm_mode_eval(rmode, r) : 0xFFFFFFFFu;
+    }
+  }
+  __device__ __forceinline__ void fetch(uint32_t kt, const GemmMode& kmode, uint32_t at) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];   // (see DirectTileLoader)
+    const uint32_t k0 = kt * kGemmBK, mine = k0 + 8u * (t & 7u);
+    const uint32_t k_off = mine < K ? 2u * gemm_mode_eval(kmode, mine) : 0xFFFFFFFFu;
+    static_for<R>([&](auto i) {
+      const uint32_t kv = gemm_direct_kvec(gemm_direct_row(R, t, (uint32_t)i), t);
+      const uint32_t theirs = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * kv), (int)k_off);
+      const uint32_t voff = off[i] != 0xFFFFFFFFu && theirs != 0xFFFFFFFFu ? off[i] + theirs : 0xFFFFFFFFu;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(lds_bytes + at + (uint32_t)i * 1024u), 16, (int)voff, 0, 0, 0);
+    });
+  }
+};
+
 // The 8 elements of v moved down by n elements (0 .. 8), zeros from above.
 __device__ __forceinline__ u32x4 move_down_b16(u32x4 v, uint32_t n) {
   uint64_t lo = (uint64_t)v[0] | ((uint64_t)v[1] << 32), hi = (uint64_t)v[2] | ((uint64_t)v[3] << 32);
@@ -222,8 +255,119 @@ struct AnyTileLoader {
     }
   }
 };
+
+// The same tile for operands without vectors (or with vectors over a k mode of several short leaves), through registers.  Every
+// load is an element (or a vector) at a 32-bit offset from the operand: the lanes' own part in a vector register, the part
+// all lanes share in a scalar one.  One lane evaluates the k mode for one k of the tile; the others' offsets are read from it.
+// Rows past the operand's extent, and k past K, present an offset outside the buffer's range: zeros arrive.
+// What bounds it: the vector memory path takes 64 addresses per instruction whatever their size, so an element costs what a
+// vector costs; the lanes run along the mode whose neighbours share lines, and the eight elements a lane packs along the other.
+// Measured on MI355X (bf16, us; element loads of 128 x 128 tiles -> this): no contiguous mode, 162 x 114 x 972 174 -> 10, 1024^3 183 -> 25,
+// 4096^2 x 1024 524 -> 222; filters stored K,C,R,S, 64 x 115200 x 576 184 -> 43, 256 x 115200 x 1152 522 -> 244.
 template <int BR, int LOAD, int WAVES>
-using TileLoader = std::conditional_t<gemm_load_is_any(LOAD), AnyTileLoader<BR, LOAD, WAVES>, DirectTileLoader<BR, LOAD, WAVES>>;
+struct GatherTileLoader {
+  static constexpr int R = BR / 8 / WAVES;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t K, t;
+  bool vectors;          // (uniform)
+  uint32_t off[R];       // bytes; elements along k: off[0] is the offset of row 8 R wave + lane, for the others to read
+  uint32_t raw[8 * R];   // elements one a register; vectors four registers each
+
+  __device__ __forceinline__ void init(const uint16_t* p, const GemmMode& rmode, uint32_t first_row, uint32_t rows, uint32_t Ktot, uint32_t lane,
+                                       int32_t direct) {
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, 0xFFFFFFFFu, 0x00020000);
+    K = Ktot;
+    t = lane;
+    vectors = gemm_gather_vectors(direct);
+    if (LOAD == kLoadRGather && !vectors) {
+      const uint32_t r = first_row + (t >> 6) * (R * 8u) + (t & 63u);   // (rows that do not exist: products nobody looks at)
+      off[0] = 2u * gemm_mode_eval(rmode, r < rows ? r : rows - 1u);
+      asm volatile("");   // (see fetch)
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      uint32_t row, k;
+      gemm_gather_unit(LOAD, vectors, BR, R, t, (uint32_t)i, &row, &k);
+      const uint32_t r = first_row + row;
+      off[i] = r < rows ? 2u * gemm_mode_eval(rmode, r) : 0xFFFFFFFFu;
+    }
+  }
+  // asks for k tile kt
+  __device__ __forceinline__ void fetch(uint32_t kt, const GemmMode& kmode) {
+    const uint32_t k0 = kt * kGemmBK, lane = t & 63u;
+    if (vectors) {
+      // lane l stands for k vector l % 8, or for k l, of the tile
+      const uint32_t kl = k0 + (LOAD == kLoadKGather ? 8u * (lane & 7u) : lane);
+      const uint32_t k_off = 2u * gemm_mode_eval(kmode, kl < K ? kl : 0u);
+      static_for<R>([&](auto i) {
+        uint32_t row, k;
+        gemm_gather_unit(LOAD, true, BR, R, t, (uint32_t)i, &row, &k);
+        const uint32_t theirs = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (LOAD == kLoadKGather ? k / 8u : k)), (int)k_off);
+        const uint32_t at = off[i] != 0xFFFFFFFFu && k0 + k < K ? off[i] + theirs : 0xFFFFFFFFu;
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 0, 0));
+        static_for<4>([&](auto d) { raw[4 * i + d] = v[(int)d]; });
+      });
+      asm volatile("");   // (keeps the compiler from merging the two branches' last stores to `raw` into one at a variable index, which would put it in memory)
+      return;
+    }
+    const uint32_t k_off = k0 + lane < K ? 2u * gemm_mode_eval(kmode, k0 + lane) : 0xFFFFFFFFu;   // of k k0 + lane
+    static_for<R>([&](auto i) {
+      static_for<8>([&](auto j) {
+        uint32_t at, shared = 0u;   // the lane's part, the part of all lanes
+        if constexpr (LOAD == kLoadRGather) {
+          at = k_off;
+          shared = (uint32_t)__builtin_amdgcn_readlane((int)off[0], 8 * i + j);
+        } else {
+          const uint32_t first = ((uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6)) * R + (uint32_t)i) * 64u / BR * 8u + (uint32_t)j;   // k inside the tile, of lane 0
+          uint32_t its = (uint32_t)__builtin_amdgcn_readlane((int)k_off, (int)first);
+          if constexpr (BR < 64) {
+            const uint32_t upper = (uint32_t)__builtin_amdgcn_readlane((int)k_off, (int)first + 8);
+            its = lane >= (uint32_t)BR ? upper : its;
+            at = its != 0xFFFFFFFFu && off[i] != 0xFFFFFFFFu ? off[i] + its : 0xFFFFFFFFu;
+          } else {
+            at = its != 0xFFFFFFFFu ? off[i] : 0xFFFFFFFFu;
+            shared = its != 0xFFFFFFFFu ? its : 0u;
+          }
+        }
+        raw[8 * i + j] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)at, (int)shared, 0);
+      });
+    });
+  }
+  // parks the k tile that was asked for last: at = where this wavefront's share of the tile lies in LDS
+  __device__ __forceinline__ void park(unsigned char* at, uint32_t) {
+    if (vectors) {
+      u32x4* slot = reinterpret_cast<u32x4*>(at + (t & 63u) * 16u);
+      static_for<R>([&](auto i) { slot[(int)i * 64] = u32x4{raw[4 * i], raw[4 * i + 1], raw[4 * i + 2], raw[4 * i + 3]}; });
+      return;
+    }
+    unsigned char* tile = at - (t >> 6) * (R * 1024u);
+    static_for<R>([&](auto i) {
+      uint32_t row, k;
+      gemm_gather_unit(LOAD, false, BR, R, t, (uint32_t)i, &row, &k);
+      u32x4 v;
+      static_for<4>([&](auto d) { v[(int)d] = raw[8 * i + 2 * d] | (raw[8 * i + 2 * d + 1] << 16); });
+      *reinterpret_cast<u32x4*>(tile + (LOAD == kLoadKGather ? gemm_lds_offset(row, k / 8u) : gemm_rdirect_lds_offset(BR, k, row))) = v;
+    });
+  }
+};
+template <int BR, int LOAD, int WAVES>
+using TileLoader = std::conditional_t<
+    LOAD == kLoadKLeaves, LeavesTileLoader<BR, WAVES>,
+    std::conditional_t<gemm_load_is_gather(LOAD), GatherTileLoader<BR, LOAD, WAVES>,
+                       std::conditional_t<gemm_load_is_any(LOAD), AnyTileLoader<BR, LOAD, WAVES>, DirectTileLoader<BR, LOAD, WAVES>>>>;
+// (which loads an operand without vectors takes is a matter of its plan, not of the kernel)
+template <int LOAD, typename Loader>
+__device__ __forceinline__ void init_loader(Loader& l, const uint16_t* p, const GemmMode& rmode, const GemmMode& kmode, uint32_t row0, uint32_t rows,
+                                            uint32_t K, uint32_t lane, int32_t direct) {
+  if constexpr (gemm_load_is_gather(LOAD)) l.init(p, rmode, row0, rows, K, lane, direct);
+  else l.init(p, rmode, kmode, row0, rows, K, lane);
+}
+template <int LOAD, typename Loader>
+__device__ __forceinline__ void fetch_tile(Loader& l, uint32_t kt, const GemmMode& kmode) {
+  if constexpr (gemm_load_is_gather(LOAD)) l.fetch(kt, kmode);
+  else l.fetch(kt);
+}
 
 // Fragment of rows row .. row + 31, k step kk of an operand's tile of BR rows at LDS address `tile`: this lane's 8 elements.
 // (A tile of 16 rows stands twice in its fragment; the second half's products are never looked at.)

@@ -21,6 +21,14 @@ hipError_t launch_gemm_bf16_stream(const lc_gemm_plan& plan, const uint16_t* a, 
 hipError_t launch_gemm_bf16_stream_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_stream_any(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_split_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_stream_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_split_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_stream_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_split_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_stream_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_split_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_stream_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 
 static bool gemm_hip_failed(hipError_t e, const char* what) {
   if (e == hipSuccess) return false;
@@ -43,10 +51,21 @@ lc_status_t execute_gemm_plan(const lc_gemm_plan& plan, const void* a, const voi
   const bool bf16 = plan.ab_dtype == LC_BF16;
   // LDS the tile kernels assume: two stages of an A and a B tile, or (direct loads, always as a pair) a ring of five tiles;
   // the split and stream launchers check theirs
-  const bool any = plan.params.a_direct >= 2;
-  if (any != (plan.params.b_direct >= 2) || (!any && plan.params.a_direct != plan.params.b_direct)) return LC_ERR_INVALID_ARG;
+  // (operands go the same way in pairs)
+  auto way_of = [](int direct) { return direct < 2 ? direct : direct < 4 ? 2 : direct < 8 ? 4 : 8; };
+  const int way = way_of(plan.params.a_direct);
+  if (way != way_of(plan.params.b_direct)) return LC_ERR_INVALID_ARG;
+  const bool any = way == 2, gather = way == 4, leaves = way == 8;
   const unsigned tiles_in_lds = plan.params.a_direct ? 5u : 4u;
-  if (plan.split_waves > 0 && any)
+  if (plan.split_waves > 0 && gather)
+    pre = bf16 ? launch_gemm_bf16_split_gather(plan, ka, kb, kc, s) : launch_gemm_f16_split_gather(plan, ka, kb, kc, s);
+  else if (plan.stages > 0 && gather)
+    pre = bf16 ? launch_gemm_bf16_stream_gather(plan, ka, kb, kc, s) : launch_gemm_f16_stream_gather(plan, ka, kb, kc, s);
+  else if (plan.split_waves > 0 && leaves)
+    pre = bf16 ? launch_gemm_bf16_split_leaves(plan, ka, kb, kc, s) : launch_gemm_f16_split_leaves(plan, ka, kb, kc, s);
+  else if (plan.stages > 0 && leaves)
+    pre = bf16 ? launch_gemm_bf16_stream_leaves(plan, ka, kb, kc, s) : launch_gemm_f16_stream_leaves(plan, ka, kb, kc, s);
+  else if (plan.split_waves > 0 && any)
     pre = bf16 ? launch_gemm_bf16_split_any(plan, ka, kb, kc, s) : launch_gemm_f16_split_any(plan, ka, kb, kc, s);
   else if (plan.split_waves > 0)
     pre = bf16 ? launch_gemm_bf16_split(plan, ka, kb, kc, s) : launch_gemm_f16_split(plan, ka, kb, kc, s);
@@ -54,7 +73,7 @@ lc_status_t execute_gemm_plan(const lc_gemm_plan& plan, const void* a, const voi
     pre = bf16 ? launch_gemm_bf16_stream_any(plan, ka, kb, kc, s) : launch_gemm_f16_stream_any(plan, ka, kb, kc, s);
   else if (plan.stages > 0)
     pre = bf16 ? launch_gemm_bf16_stream(plan, ka, kb, kc, s) : launch_gemm_f16_stream(plan, ka, kb, kc, s);
-  else if (any)
+  else if (way > 1)
     return LC_ERR_INVALID_ARG;
   else if (plan.tile_m == 256 && plan.tile_n == 256 && plan.lds_bytes == tiles_in_lds * 256u * 128u)
     pre = bf16 ? launch_gemm_bf16_256(plan, ka, kb, kc, s) : launch_gemm_f16_256(plan, ka, kb, kc, s);

@@ -27,10 +27,20 @@ enum GemmLoad : int32_t {
   // offset pointers): 16-byte loads from 2-byte-aligned addresses into registers, parked in the arrangement of kLoadKDirect
   // (along k) or kLoadRDirect (along the row mode).  Needs a k mode of one leaf; a plan still says kLoadElem.
   kLoadKAny = 5,
-  kLoadRAny = 6
+  kLoadRAny = 6,
+  // Whatever neither of these takes, through registers into the arrangement of kLoadKDirect (kLoadKGather) or kLoadRDirect
+  // (kLoadRGather): element by element with the lanes along the mode whose neighbours share more lines, or 16-byte vectors
+  // whose k mode has leaves that k tiles are not whole in.  Any k mode; a plan still says what it found (gemm_gather_vectors).
+  kLoadKGather = 7,
+  kLoadRGather = 8,
+  // kLoadKDirect over a k mode of leaves that k tiles are not whole in (a convolution's channels, where there are few): every
+  // lane adds the offset of its own k vector.  The first leaf holds whole vectors; a plan still says kLoadKVec.
+  kLoadKLeaves = 9
 };
 LC_HD constexpr bool gemm_load_is_any(int32_t load) { return load == kLoadKAny || load == kLoadRAny; }
-LC_HD constexpr bool gemm_load_is_k_major(int32_t load) { return load == kLoadRDirect || load == kLoadRAny; }
+LC_HD constexpr bool gemm_load_is_gather(int32_t load) { return load == kLoadKGather || load == kLoadRGather; }
+LC_HD constexpr bool gemm_load_in_registers(int32_t load) { return gemm_load_is_any(load) || gemm_load_is_gather(load); }
+LC_HD constexpr bool gemm_load_is_k_major(int32_t load) { return load == kLoadRDirect || load == kLoadRAny || load == kLoadRGather; }
 
 // One coalesced mode: integral coordinate -> offset in elements (all offsets of a GEMM operand fit 31 bits).
 // The leaves but the last are reduced modulo their extents, the last one takes what is left (Eq. idx2crd).
@@ -63,6 +73,9 @@ struct GemmParams {
   int32_t a_load, b_load;                  // GemmLoad
   int32_t a_direct, b_direct;              // 1: the operand goes straight into LDS (kLoadKVec -> kLoadKDirect, kLoadRVec -> kLoadRDirect);
                                            // 2, 3: vectors at any alignment along k, along the row mode (kLoadKAny, kLoadRAny)
+                                           // 4, 5: element by element, lanes along the row mode, along k (kLoadKGather, kLoadRGather)
+                                           // 6, 7: k vectors, row vectors over any k mode (kLoadKGather, kLoadRGather)
+                                           // 8: k vectors straight into LDS over any k mode (kLoadKLeaves)
   int32_t c_vec;                           // 1: four consecutive m are contiguous and 16-byte aligned in C
   uint32_t group_m;                        // tile rows walked together before moving on along n
 };
@@ -70,9 +83,13 @@ struct GemmParams {
 // the load the kernel runs for an operand the plan classified as `load`
 LC_HD int32_t gemm_effective_load(int32_t load, int32_t direct) {
   if (!direct) return load;
+  if (direct == 8) return (int32_t)kLoadKLeaves;
+  if (direct >= 4) return direct % 2 == 0 ? (int32_t)kLoadKGather : (int32_t)kLoadRGather;
   if (direct >= 2) return direct == 2 ? (int32_t)kLoadKAny : (int32_t)kLoadRAny;
   return load == kLoadKVec ? (int32_t)kLoadKDirect : (load == kLoadRVec ? (int32_t)kLoadRDirect : load);
 }
+
+LC_HD bool gemm_gather_vectors(int32_t direct) { return direct == 6 || direct == 7; }
 
 // ---------------------------------------------------------------------------------------------
 // Workgroup -> tile.  Workgroups are handed to the 8 XCDs round-robin and every XCD has its own L2,
@@ -173,6 +190,26 @@ LC_HD uint32_t gemm_any_back(int32_t load, uint32_t k0, uint32_t k, uint32_t K, 
   if (k0 + kGemmBK <= K || K < (uint32_t)kGemmBK) return 0u;
   if (load == kLoadKAny) return 2u * (k0 + k - gemm_any_start(k0 + k, K, &move));
   return k0 + k < K ? 0u : (k0 + k - (K - 1u)) * k_step;
+}
+// kLoadKGather / kLoadRGather element by element: unit i of a lane is eight elements that it packs into one 16-byte slot.
+// Lanes along the row mode (kLoadKGather): eight k of one row, 64 neighbouring lanes = 64 rows (32 rows at two k vectors for
+// a tile of 32), so every load instruction runs along the rows.  Lanes along k (kLoadRGather): eight rows at one k, the 64
+// lanes = the 64 k of the tile, so every load runs along k.  Vectors: the units of kLoadKDirect / kLoadRDirect.
+// *row, *k: first row and first k of the unit inside the tile
+LC_HD void gemm_gather_unit(int32_t load, bool vectors, uint32_t BR, uint32_t units_per_lane, uint32_t tid, uint32_t i, uint32_t* row, uint32_t* k) {
+  if (vectors && load == kLoadKGather) {
+    *row = gemm_direct_row(units_per_lane, tid, i);
+    *k = 8u * gemm_direct_kvec(*row, tid);
+  } else if (vectors) {
+    gemm_rdirect_unit(BR, units_per_lane, tid, i, k, row);
+  } else if (load == kLoadKGather) {
+    const uint32_t slot = ((tid >> 6) * units_per_lane + i) * 64u + (tid & 63u);
+    *row = slot % BR;
+    *k = 8u * (slot / BR);
+  } else {
+    *row = 8u * ((tid >> 6) * units_per_lane + i);
+    *k = tid & 63u;
+  }
 }
 LC_HD uint32_t gemm_clamp_row(int32_t load, uint32_t row, uint32_t extent) {
   const uint32_t last = load == kLoadRVec || load == kLoadRDirect ? extent - 8u : extent - 1u;

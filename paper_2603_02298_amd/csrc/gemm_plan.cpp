@@ -61,14 +61,31 @@ int env_int(const char* name, int dflt) {
 struct Loads {
   int a, b;                  // GemmLoad, what a plan says
   int a_direct, b_direct;    // see GemmParams
-  bool direct, any;          // both straight into LDS, both in vectors at any alignment
+  int a_gather, b_gather;    // what they are for gathered operands
+  bool direct, any, gather;  // both straight into LDS, both in vectors at any alignment, both gathered through registers
 };
+
+// lines of 128 bytes that the first 64 coordinates of a mode touch (elements of 2 bytes)
+int lines_of(const Modes& m) {
+  int64_t size = 1;
+  for (const Mode& x : m) size *= x.extent;
+  std::vector<int64_t> lines;
+  for (int64_t i = 0; i < std::min<int64_t>(size, 64); ++i) {
+    int64_t at = 0, rest = i;
+    for (const Mode& x : m) { at += rest % x.extent * x.stride; rest /= x.extent; }
+    lines.push_back(at / 64);
+  }
+  std::sort(lines.begin(), lines.end());
+  return (int)(std::unique(lines.begin(), lines.end()) - lines.begin());
+}
+
 Loads choose_loads(const Modes& a_r, const Modes& a_k, const Modes& a_l, unsigned a_align, const Modes& b_r, const Modes& b_k, const Modes& b_l,
                    unsigned b_align, int64_t K) {
   Loads l;
   l.a = classify_operand(a_r, a_k, a_l, a_align);
   l.b = classify_operand(b_r, b_k, b_l, b_align);
   const int force = env_int("LC_TUNE_GEMM_LOAD", -1);   // tests: force the element-wise loads
+  const int a_own = l.a, b_own = l.b;
   // element loads are compiled for both operands together: one operand that needs them takes the other along
   if (force == kLoadElem || l.a == kLoadElem || l.b == kLoadElem) l.a = l.b = kLoadElem;
   // straight into LDS: k tiles that are contiguous along k
@@ -99,6 +116,18 @@ Loads choose_loads(const Modes& a_r, const Modes& a_k, const Modes& a_l, unsigne
     l.a_direct = any_kind(a_r, a_k);
     l.b_direct = any_kind(b_r, b_k);
   }
+  // What is left -- no contiguous mode, a k mode of several leaves beside an unaligned one, vectors whose k mode has leaves
+  // that k tiles are not whole in -- is gathered through registers, each operand in its own way (lanes along the mode whose 64
+  // neighbours touch fewer lines), on the split and stream kernels: faster than the tile kernels' element and staged loads at
+  // every size measured (figures beside the loaders).
+  l.gather = !l.direct && !l.any && force != kLoadElem && direct_env == 3 && env_int("LC_TUNE_GEMM_KTAIL", 1) != 0;
+  auto gather_kind = [&](int own, const Modes& row, const Modes& k) -> int32_t {
+    if (own != kLoadElem) return own == kLoadKVec ? 6 : 7;
+    return lines_of(row) <= lines_of(k) ? 4 : 5;
+  };
+  l.a_gather = gather_kind(a_own, a_r, a_k);
+  l.b_gather = gather_kind(b_own, b_r, b_k);
+  if (l.a_gather == 6 && l.b_gather == 6) l.a_gather = l.b_gather = 8;   // k vectors on both sides: straight into LDS
   return l;
 }
 
@@ -172,10 +201,21 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   };
   bool exchange = !c_vec_ok(c_m, c_n) && c_vec_ok(c_n, c_m);
   Loads loads = choose_loads(a_r, a_k, a_l, a_align, b_r, b_k, b_l, b_align, K);
+  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
+  const bool free_choice = t_env == 0;
+  const bool indirect = loads.gather && (free_choice ? env_int("LC_TUNE_GEMM_GATHER", 1) != 0 : t_env != 128 && t_env != 256 && t_env != 1285 && t_env != 3216);
+  const bool leaves = indirect && loads.a_gather == 8, gather = indirect && !leaves;
+  if (indirect) {
+    loads.a_direct = loads.a_gather;
+    loads.b_direct = loads.b_gather;
+  }
   // Without vectors of four m the lanes of the split and stream kernels' update run along n, element by element: C's contiguous
   // mode goes there (not for a few columns, whose thin tiles are worth more).  The tile kernels of staged and element loads
   // measured slower that way round (2 x 5560 x 64 10.8 -> 15.2 us, a convolution of 35 x 13500 x 288 16.8 -> 21.4).
-  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) exchange = (loads.direct || loads.any) && c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
+  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) {
+    if (gather) exchange = c_m[0].stride != 1 && lines_of(c_m) < lines_of(c_n);   // (no contiguous mode: the closer one)
+    else exchange = (loads.direct || loads.any) && c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
+  }
   if (env_int("LC_TUNE_GEMM_EXCHANGE", -1) >= 0) exchange = env_int("LC_TUNE_GEMM_EXCHANGE", 0) != 0;
   if (exchange) {
     std::swap(a_r, b_r);
@@ -216,18 +256,26 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   // 6.2.  16 x 8192 x 8192 78 us; 32 x 32 27.6, 64 x 64 36.  64 x 8192 x 8192 92 us; 32 x 32 (512 tiles) 42.8, 64 x 32 (256) 33.4.
   // 1024^3 17.6 us; 32 x 64 (512 tiles) 10.8, 64 x 64 (256) 8.3.
   auto tiles_of = [&](int64_t tm, int64_t tn) { return (kM + tm - 1) / tm * ((kN + tn - 1) / tn) * Lb; };
-  // LC_TUNE_GEMM_TILE: 256, 128, 12864 (128 x 64), 64128, 1285 (the ring of five 128 x 128 tiles); split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
+  // LC_TUNE_GEMM_TILE: 256, 128 (gathered operands: 1282), 12864 (128 x 64), 64128, 1285 (the ring of five 128 x 128 tiles); split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
   // stream kernel's 64 x 64
-  const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
-  const bool thin = kN <= 16 && (P.b_load == kLoadKVec || P.b_direct == 2), vectors = direct || any;
-  const bool free_choice = t_env == 0;
-  if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, any ? 1 : 3);
-  else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, any ? 1 : 2);
-  else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, any ? 1 : 3);
-  else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, any ? 1 : 3);
-  else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, any ? 1 : 2);
-  else if (vectors && (any || t_env != 256)) {
+  const bool thin = kN <= 16 && !indirect && (P.b_load == kLoadKVec || P.b_direct == 2), vectors = direct || any || indirect;
+  const bool regs = any || gather;   // through registers: one pair of tiles
+  // Gathered operands: an element costs the vector memory path what a vector costs, so a side of elements weighs eight times a side
+  // of vectors, and tiles reach further along the vectors' side.
+  const bool a_elem = gather && P.a_direct < 6, b_elem = gather && P.b_direct < 6, mixed = a_elem != b_elem;
+  if (mixed && free_choice && tiles_of(32, 32) > 256) {
+    // Measured on MI355X (bf16, us; filters stored K,C,R,S as elements, the activation in vectors; 32 x 64 split, 64 x 64, 128 x 64, 64 x 128, 128 x 128):
+    // convolutions of 128 x 7128 x 144 6.9, 7.4, 10.2, 8.7, 12.2; 40 x 12696 x 1152 18.9, 29.6, 40.5, 33.1, 45.6; 64 x 17600 x 144 10.0, 8.8, 14.3, 8.9, 12.2;
+    // 256 x 115200 x 1152 423, 360, 353, 244, 256; 64 x 115200 x 576 66, 56, 99, 43, 72; 256 x 25088 x 1152 96, 92, 103, 73, 71.
+    if (a_elem ? tiles_of(32, 64) <= 512 : tiles_of(64, 32) <= 512) take(a_elem ? 32 : 64, a_elem ? 64 : 32, 4, 1);
+    else take(a_elem ? 64 : 128, a_elem ? 128 : 64, 0, 2);
+  } else if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, regs ? 1 : 3);
+  else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, regs ? 1 : 2);
+  else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, regs ? 1 : 3);
+  else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, regs ? 1 : 3);
+  else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, regs ? 1 : 2);
+  else if (vectors && (any || indirect || t_env != 256)) {
     // Larger problems.  The CU that is given the most tiles decides, so a tile's cost is how many of them that CU takes times
     // its area, times what its k loop costs per product against the 128 x 128 stream kernel's.  Smaller tiles read more of LDS per
     // product, which weighs more the longer K is and the less C's own way does (128 x 64: 1.1 below K = 768, 1.4, 1.5 from 3000 on;
@@ -246,10 +294,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     //   forms) the choice is within 1.1 % of the best on average.
     // Vectors at any alignment (no ring, no 256 x 256 kernel) keep weights of their own: 1001 x 2003 x 1537 22 us in 64 x 64, 24.6 in 128 x 64.
     struct Choice { int tm, tn; double per_product, lone; };
+    // Elements on both sides: bound by their loads, 1.3 in 64 x 64, 1.12 in 128 x 64 and 64 x 128 (2048^2 x 512 43.5, 41.9, 41.3, 128 x 128 44.6;
+    // 2000 x 3000 x 1000 104, 89, 88, 95; 4096^2 x 1024 290, 249, 246, 222; 128 x 128 element tiles before these 101, 202, 524).
+    const bool elements = a_elem && b_elem;
     const bool measured = direct && K >= 768;   // (below, and at any alignment: the weights those were measured with)
-    const double half = measured ? (K < 3000 ? 1.4 : 1.5) : K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3;
-    const double quarter = measured ? (K < 3000 ? 2.2 : 2.3) : K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65;
-    const double lone = measured ? 1.9 : K < 2048 ? 1.25 : 1.5;
+    const double half = elements ? 1.12 : measured ? (K < 3000 ? 1.4 : 1.5) : K < 1024 ? 1.1 : K < 2048 ? 1.2 : 1.3;
+    const double quarter = elements ? 1.3 : measured ? (K < 3000 ? 2.2 : 2.3) : K < 1024 ? 1.3 : K < 2048 ? 1.4 : 1.65;
+    const double lone = elements ? 1.2 : measured ? 1.9 : K < 2048 ? 1.25 : 1.5;
     const double side_n = measured && P.b_load == kLoadRVec ? 1.1 : 1.0, side_m = measured && P.a_load == kLoadRVec ? 1.1 : 1.0;
     const Choice choices[] = {{128, 128, 1.0, lone}, {128, 64, half * side_n, lone}, {64, 128, half * side_m, lone}, {64, 64, quarter, lone}};
     auto cost = [&](const Choice& c) {
@@ -266,7 +317,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     const bool ring_pays = direct && K >= 3000 && tiles_of(128, 128) <= 256 && cost(ring) < cost(*best);
     if (direct && free_choice && cost(big) <= (ring_pays ? cost(ring) : cost(*best))) take(256, 256, 0, 0);
     else if (direct && (t_env == 1285 || (free_choice && ring_pays))) take(128, 128, 0, 0);
-    else if (t_env == 128) take(128, 128, 0, 2);
+    else if (t_env == 128 || t_env == 1282) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);
     else if (t_env == 64128) take(64, 128, 0, 2);
     else if (t_env == 6464) take(64, 64, 0, 2);
@@ -279,7 +330,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   // thin problems in many batch entries have more tiles than that, the tile kernels, whose batch is a dimension of its own, take them
   // (vectors at any alignment element by element).
   if (plan.stages && (uint64_t)tiles_of(plan.tile_m, plan.tile_n) * (plan.split_waves ? 64u * (unsigned)plan.split_waves : (unsigned)kBlock) > 0xFFFFFFFFull) {
-    if (any) P.a_direct = P.b_direct = 0;
+    if (any || indirect) P.a_direct = P.b_direct = 0;
     take(256, 256, 0, 0);
   }
   P.tiles_m = (uint32_t)((kM + plan.tile_m - 1) / plan.tile_m);
@@ -305,6 +356,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
 std::string describe(const lc_gemm_plan& plan) {
   static const char* load_name[] = {"k-vectors", "row-vectors+transpose", "elements"};
   static const char* any_name[] = {"(in unaligned k-vectors)", "(in unaligned row-vectors)"};
+  static const char* gather_name[] = {"along-rows", "along-k", "k-vectors", "row-vectors"};
   std::string s = "class=gemm-mfma32x32x16 ab=";
   s += plan.ab_dtype == LC_BF16 ? "bf16" : "f16";
   s += " c=f32 M=" + std::to_string(plan.M) + " N=" + std::to_string(plan.N) + " K=" + std::to_string(plan.K);
@@ -315,9 +367,11 @@ std::string describe(const lc_gemm_plan& plan) {
   if (plan.split_waves) s += " split_waves=" + std::to_string(plan.split_waves) + " stages=" + std::to_string(plan.stages);
   s += " tiles=" + std::to_string(plan.params.tiles_m) + "x" + std::to_string(plan.params.tiles_n) + " k_tiles=" + std::to_string(plan.params.k_tiles);
   s += " group_m=" + std::to_string(plan.params.group_m);
-  s += std::string(" a_load=") + load_name[plan.params.a_load] + (plan.params.a_direct >= 2 ? any_name[plan.params.a_direct - 2] : plan.params.a_direct ? "(direct-to-LDS)" : "");
-  s += std::string(" b_load=") + load_name[plan.params.b_load] + (plan.params.b_direct >= 2 ? any_name[plan.params.b_direct - 2] : plan.params.b_direct ? "(direct-to-LDS)" : "");
+  s += std::string(" a_load=") + load_name[plan.params.a_load] + (plan.params.a_direct >= 4 ? "" : plan.params.a_direct >= 2 ? any_name[plan.params.a_direct - 2] : plan.params.a_direct ? "(direct-to-LDS)" : "");
+  s += std::string(" b_load=") + load_name[plan.params.b_load] + (plan.params.b_direct >= 4 ? "" : plan.params.b_direct >= 2 ? any_name[plan.params.b_direct - 2] : plan.params.b_direct ? "(direct-to-LDS)" : "");
   s += " c_vec=" + std::to_string(plan.params.c_vec) + " lds_bytes=" + std::to_string(plan.lds_bytes);
+  if (plan.params.a_direct == 8) s += " k-vectors=over-leaves";
+  else if (plan.params.a_direct >= 4) s += std::string(" gathered=") + gather_name[plan.params.a_direct - 4] + "," + gather_name[plan.params.b_direct - 4];
   s += " A=[" + plan.a_text + "] B=[" + plan.b_text + "] C=[" + plan.c_text + "]";
   return s;
 }

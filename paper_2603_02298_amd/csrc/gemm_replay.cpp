@@ -40,14 +40,15 @@ struct Walker {
   // lanes: how many load a tile together (a workgroup, or one wavefront of the split kernel); zero_rows: lanes past the
   // extent are answered with zeros instead of taking the last row
   void stage(const uint16_t* base, int64_t elems, const GemmMode& rmode, const GemmMode& kmode, int32_t load, uint32_t row0, uint32_t extent,
-             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock, bool zero_rows = false) {
-    if (load == kLoadKDirect) {
+             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock, bool zero_rows = false, int32_t direct = 0) {
+    if (load == kLoadKDirect || load == kLoadKLeaves) {
       // every lane's 16 bytes land at byte 16 * lane of the 1 KiB its wavefront's instruction i fills
       const uint32_t rows_per_lane = BR * 8u / lanes;
       for (uint32_t tid = 0; tid < lanes; ++tid)
         for (uint32_t i = 0; i < rows_per_lane; ++i) {
           const uint32_t row = gemm_direct_row(rows_per_lane, tid, i), kv = gemm_direct_kvec(row, tid);
-          const int64_t off = (int64_t)gemm_mode_eval(rmode, gemm_clamp_row(load, row0 + row, extent)) + 8u * kv + gemm_mode_eval(kmode, kt * kGemmBK);
+          const int64_t off = (int64_t)gemm_mode_eval(rmode, gemm_clamp_row(load, row0 + row, extent)) +
+                              (load == kLoadKLeaves ? gemm_mode_eval(kmode, kt * kGemmBK + 8u * kv) : 8u * kv + gemm_mode_eval(kmode, kt * kGemmBK));
           const uint32_t lds_at = ((tid >> 6) * rows_per_lane + i) * 1024u + (tid & 63u) * 16u;
           if (lds_at != gemm_lds_offset(row, kv)) { ok = false; return; }
           if (kt * kGemmBK + 8u * kv >= P.K || (zero_rows && row0 + row >= extent)) {   // past K in a short last k tile: the lane's offset is out of range, zeros arrive
@@ -55,6 +56,8 @@ struct Walker {
             continue;
           }
           if (off % 8 != 0 || off + 8 > elems || kt * kGemmBK + 8u * kv + 8u > P.K) { ok = false; return; }
+          for (uint32_t e = 1; e < 8; ++e)   // eight neighbours in memory
+            if (gemm_mode_eval(kmode, kt * kGemmBK + 8u * kv + e) != gemm_mode_eval(kmode, kt * kGemmBK + 8u * kv) + e) { ok = false; return; }
           std::memcpy(tile + lds_at, base + off, 16);
         }
       return;
@@ -118,6 +121,34 @@ struct Walker {
           for (uint32_t e = 0; e < 8; ++e) {
             const uint32_t from = e + move + k_move;
             const uint16_t x = from < 8u && at_k < P.K ? v[from] : 0;
+            std::memcpy(tile + lds_at + 2u * e, &x, 2);
+          }
+        }
+      return;
+    }
+    if (gemm_load_is_gather(load)) {
+      // units of eight elements (or one vector) packed by their lane into the slot the fragment reads expect
+      const uint32_t R = BR * 8u / lanes;
+      for (uint32_t tid = 0; tid < lanes; ++tid)
+        for (uint32_t i = 0; i < R; ++i) {
+          uint32_t row, k;
+          gemm_gather_unit(load, gemm_gather_vectors(direct), BR, R, tid, i, &row, &k);
+          const uint32_t lds_at = load == kLoadKGather ? gemm_lds_offset(row, k / 8u) : gemm_rdirect_lds_offset(BR, k, row);
+          if (row >= BR || k >= (uint32_t)kGemmBK || (load == kLoadKGather ? k % 8u : row % 8u) != 0) { ok = false; return; }
+          if (gemm_gather_vectors(direct) && lds_at != ((tid >> 6) * R + i) * 1024u + (tid & 63u) * 16u) { ok = false; return; }
+          for (uint32_t e = 0; e < 8; ++e) {
+            const uint32_t at_row = row0 + row + (load == kLoadRGather ? e : 0u), at_k = kt * kGemmBK + k + (load == kLoadKGather ? e : 0u);
+            uint16_t x = 0;
+            if (at_k < P.K && (at_row < extent || (load == kLoadRGather && !gemm_gather_vectors(direct)))) {
+              const int64_t off = (int64_t)gemm_mode_eval(rmode, at_row < extent ? at_row : extent - 1u) + gemm_mode_eval(kmode, at_k);
+              if (off >= elems) { ok = false; return; }
+              x = base[off];
+              // a vector: eight neighbours in memory, all of them inside
+              if (gemm_gather_vectors(direct)) {
+                const int64_t first = (int64_t)gemm_mode_eval(rmode, row0 + row) + gemm_mode_eval(kmode, kt * kGemmBK + k);
+                if (off != first + e || first % 8 != 0 || first + 8 > elems) { ok = false; return; }
+              }
+            } else if (gemm_gather_vectors(direct) && e > 0 && row0 + row < extent && kt * kGemmBK + k < P.K) { ok = false; return; }   // a vector straddles an end
             std::memcpy(tile + lds_at + 2u * e, &x, 2);
           }
         }
@@ -255,8 +286,8 @@ lc_status_t replay_sums(const lc_gemm_plan& plan, Walker& w, FragmentProduct& pr
     for (uint32_t wave = 0; wave < W; ++wave) {
       std::fill(acc.begin(), acc.end(), 0.f);
       for (uint32_t kt = wave; kt < P.k_tiles; kt += W) {
-        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), lanes, true);
-        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, lanes, true);
+        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), lanes, true, P.a_direct);
+        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, lanes, true, P.b_direct);
         if (!w.ok) return LC_ERR_INVALID_ARG;
         for (uint32_t kk = 0; kk < kGemmBK / 16; ++kk)
           for (uint32_t i = 0; i < TM / 32; ++i)

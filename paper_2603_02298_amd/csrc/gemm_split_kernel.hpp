@@ -29,8 +29,9 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
   constexpr int FM = TM / 32, FN = (TN + 31) / 32, KSTEPS = kGemmBK / 16;
   constexpr uint32_t A_BYTES = TM * 128u, STAGE = (TM + TN) * 128u, RING = STAGES * STAGE, PARTIAL = TM * TN * 4u;
   constexpr int R = (TM + TN) / 8;   // load instructions per k tile
-  constexpr bool ANY = gemm_load_is_any(A_LOAD);
-  static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
+  constexpr bool ANY = gemm_load_in_registers(A_LOAD);
+  static_assert(ANY == gemm_load_in_registers(B_LOAD), "both operands straight into LDS or both through registers");
+  static_assert((A_LOAD == kLoadKLeaves) == (B_LOAD == kLoadKLeaves), "compiled for pairs");
   static_assert(TN != 16 || !gemm_load_is_k_major(B_LOAD), "16 rows: row-major tiles only");
   static_assert(PARTIAL <= RING, "a wavefront's partial tile takes the place of its own ring");
   static_assert((STAGES - 1) * R < 64, "vmcnt has six bits");
@@ -56,8 +57,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
 
   TileLoader<TM, A_LOAD, 1> la;
   TileLoader<TN, B_LOAD, 1> lb;
-  la.init(A, P.a_r, P.a_k, m0, P.M, P.K, lane);
-  lb.init(B, P.b_r, P.b_k, n0, P.N, P.K, lane);
+  init_loader<A_LOAD>(la, A, P.a_r, P.a_k, m0, P.M, P.K, lane, P.a_direct);
+  init_loader<B_LOAD>(lb, B, P.b_r, P.b_k, n0, P.N, P.K, lane, P.b_direct);
 
   f32x16 acc[FM][FN];
   static_for<FM>([&](auto i) {
@@ -90,8 +91,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
     auto fetch = [&]() {
       asked = wave + next * WAVES;
       next = next + 1u == n_mine ? 0u : next + 1u;
-      la.fetch(asked);
-      lb.fetch(asked);
+      fetch_tile<A_LOAD>(la, asked, P.a_k);
+      fetch_tile<B_LOAD>(lb, asked, P.b_k);
     };
     if (n_mine > 0u) fetch();
     for (uint32_t t = 0; t < n_mine; ++t) {
@@ -111,8 +112,13 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_split_kernel(GemmParams P, co
       const uint32_t kt = wave + next * WAVES;
       next = next + 1u == n_mine ? 0u : next + 1u;
       const bool tail = kt + 1u == P.k_tiles;
-      la.fetch(2u * gemm_mode_eval(P.a_k, kt * kGemmBK), at, tail);
-      lb.fetch(2u * gemm_mode_eval(P.b_k, kt * kGemmBK), at + A_BYTES, tail);
+      if constexpr (A_LOAD == kLoadKLeaves) {
+        la.fetch(kt, P.a_k, at);
+        lb.fetch(kt, P.b_k, at + A_BYTES);
+      } else {
+        la.fetch(2u * gemm_mode_eval(P.a_k, kt * kGemmBK), at, tail);
+        lb.fetch(2u * gemm_mode_eval(P.b_k, kt * kGemmBK), at + A_BYTES, tail);
+      }
     };
     static_for<STAGES>([&](auto s) {
       if ((uint32_t)s < n_mine) request(ring + (uint32_t)s * STAGE);
@@ -176,11 +182,12 @@ static inline hipError_t launch_split_ab(const lc_gemm_plan& plan, const uint16_
   return plan.params.c_vec ? launch_split_abc<BF16, TM, TN, WAVES, STAGES, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
                            : launch_split_abc<BF16, TM, TN, WAVES, STAGES, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
-// K_LOAD, R_LOAD: the pair of load kinds (straight into LDS, or vectors at any alignment) this translation unit holds
+// K_LOAD, R_LOAD: the pair of load kinds (or the one kind) this translation unit holds
 template <bool BF16, int TM, int TN, int WAVES, int STAGES, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_split(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
   if (la == K_LOAD && lb == K_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, K_LOAD, K_LOAD>(plan, a, b, c, s);
+  if constexpr (K_LOAD == R_LOAD) return hipErrorInvalidValue;
   if (la == R_LOAD && lb == K_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, R_LOAD, K_LOAD>(plan, a, b, c, s);
   if constexpr (TN >= 32) {
     if (la == K_LOAD && lb == R_LOAD) return launch_split_ab<BF16, TM, TN, WAVES, STAGES, K_LOAD, R_LOAD>(plan, a, b, c, s);
@@ -190,8 +197,9 @@ static inline hipError_t launch_split(const lc_gemm_plan& plan, const uint16_t* 
 }
 template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_split_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  constexpr bool ANY = gemm_load_is_any(K_LOAD);   // the k tile after the parked one waits in registers: one pair of tiles each
-  if (plan.tile_m == 32 && plan.tile_n == 16) return launch_split<BF16, 32, 16, 8, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
+  constexpr bool ANY = gemm_load_in_registers(K_LOAD);   // the k tile after the parked one waits in registers: one pair of tiles each
+  if constexpr (!gemm_load_is_gather(K_LOAD) && K_LOAD != kLoadKLeaves)
+    if (plan.tile_m == 32 && plan.tile_n == 16) return launch_split<BF16, 32, 16, 8, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (plan.tile_m == 32 && plan.tile_n == 32) return launch_split<BF16, 32, 32, 8, ANY ? 1 : 2, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (plan.tile_m == 32 && plan.tile_n == 64) return launch_split<BF16, 32, 64, 4, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (plan.tile_m == 64 && plan.tile_n == 32) return launch_split<BF16, 64, 32, 4, ANY ? 1 : 3, K_LOAD, R_LOAD>(plan, a, b, c, s);

@@ -33,8 +33,9 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
   constexpr int FM = BM / 64, FN = BN / 64, KSTEPS = kGemmBK / 16;
   constexpr uint32_t A_BYTES = BM * 128u, STAGE = (BM + BN) * 128u;
   static_assert(BM * BN * 4 <= kStreamStages * (BM + BN) * 128, "the sums of the tile fit the ring");
-  constexpr bool ANY = gemm_load_is_any(A_LOAD);
-  static_assert(ANY == gemm_load_is_any(B_LOAD), "both operands straight into LDS or both through registers");
+  constexpr bool ANY = gemm_load_in_registers(A_LOAD);
+  static_assert(ANY == gemm_load_in_registers(B_LOAD), "both operands straight into LDS or both through registers");
+  static_assert((A_LOAD == kLoadKLeaves) == (B_LOAD == kLoadKLeaves), "compiled for pairs");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   touch_kernel_arguments<(int)sizeof(GemmParams) + 24>();
 
@@ -59,8 +60,8 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
   // registers they need: asked for at the end then)
   constexpr bool EARLY_C = C_VEC && !ANY;
   if constexpr (EARLY_C) units.request(P, C, m0, n0, tid);
-  la.init(A, P.a_r, P.a_k, m0, P.M, P.K, tid);
-  lb.init(B, P.b_r, P.b_k, n0, P.N, P.K, tid);
+  init_loader<A_LOAD>(la, A, P.a_r, P.a_k, m0, P.M, P.K, tid, P.a_direct);
+  init_loader<B_LOAD>(lb, B, P.b_r, P.b_k, n0, P.N, P.K, tid, P.b_direct);
 
   f32x16 acc[FM][FN];
   static_for<FM>([&](auto i) {
@@ -83,13 +84,13 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
   const uint32_t a_at = wave * (BM * 32u), b_at = A_BYTES + wave * (BN * 32u);   // this wavefront's quarter of either tile
   if constexpr (ANY) {
     // Through registers: k tile t + 1 is parked in the stage k tile t - 1 leaves, k tile t + 2 asked for, then k tile t multiplied.
-    la.fetch(0u);
-    lb.fetch(0u);
+    fetch_tile<A_LOAD>(la, 0u, P.a_k);
+    fetch_tile<B_LOAD>(lb, 0u, P.b_k);
     la.park(lds + a_at, 0u);
     lb.park(lds + b_at, 0u);
     if (P.k_tiles > 1u) {
-      la.fetch(1u);
-      lb.fetch(1u);
+      fetch_tile<A_LOAD>(la, 1u, P.a_k);
+      fetch_tile<B_LOAD>(lb, 1u, P.b_k);
     }
     for (uint32_t t = 0; t < P.k_tiles; ++t) {
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): parked, and the fragments of k tile t - 1 read
@@ -99,8 +100,8 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
         la.park(next + a_at, t + 1u);
         lb.park(next + b_at, t + 1u);
         if (t + 2u < P.k_tiles) {
-          la.fetch(t + 2u);
-          lb.fetch(t + 2u);
+          fetch_tile<A_LOAD>(la, t + 2u, P.a_k);
+          fetch_tile<B_LOAD>(lb, t + 2u, P.b_k);
         }
       }
       multiply(lds + (t & 1u) * STAGE);
@@ -112,12 +113,18 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
     uint32_t asked = 0;
     auto request = [&](uint32_t at) {   // the next k tile, to the stage at LDS offset `at`
       const bool tail = asked + 1u == P.k_tiles;
-      la.fetch(ka.bytes, at + a_at, tail);
-      lb.fetch(kb.bytes, at + b_at, tail);
-      ++asked;
-      if (asked < P.k_tiles) {
-        ka.next(P.a_k, asked);
-        kb.next(P.b_k, asked);
+      if constexpr (A_LOAD == kLoadKLeaves) {
+        la.fetch(asked, P.a_k, at + a_at);
+        lb.fetch(asked, P.b_k, at + b_at);
+        ++asked;
+      } else {
+        la.fetch(ka.bytes, at + a_at, tail);
+        lb.fetch(kb.bytes, at + b_at, tail);
+        ++asked;
+        if (asked < P.k_tiles) {
+          ka.next(P.a_k, asked);
+          kb.next(P.b_k, asked);
+        }
       }
     };
     request(0u);
@@ -169,11 +176,12 @@ static inline hipError_t launch_stream_ab(const lc_gemm_plan& plan, const uint16
   return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
                            : launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
-// K_LOAD, R_LOAD: the pair of load kinds (straight into LDS, or vectors at any alignment) this translation unit holds
+// K_LOAD, R_LOAD: the pair of load kinds (or the one kind) this translation unit holds
 template <bool BF16, int BM, int BN, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   const int la = gemm_effective_load(plan.params.a_load, plan.params.a_direct), lb = gemm_effective_load(plan.params.b_load, plan.params.b_direct);
   if (la == K_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, K_LOAD, K_LOAD>(plan, a, b, c, s);
+  if constexpr (K_LOAD == R_LOAD) return hipErrorInvalidValue;
   if (la == K_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (la == R_LOAD && lb == K_LOAD) return launch_stream_ab<BF16, BM, BN, R_LOAD, K_LOAD>(plan, a, b, c, s);
   if (la == R_LOAD && lb == R_LOAD) return launch_stream_ab<BF16, BM, BN, R_LOAD, R_LOAD>(plan, a, b, c, s);

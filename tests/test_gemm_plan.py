@@ -439,3 +439,31 @@ def test_as_many_tiles_as_one_dimension_of_a_grid_holds(monkeypatch):
     monkeypatch.setenv("LC_TUNE_GEMM_TILE", "6464")
     text = lc.GemmPlan("(1,8,65535):(8,1,8)", "(16384,8,65535):(8,1,0)", "(1,16384,65535):(1,1,16384)").describe()
     assert " stream " in text and "L=65535" in text and "tiles=256x1 " in text, text   # 256 x 65535 workgroups of 256 lanes
+
+
+def gathered_workloads(values="ints"):
+    """Operands that vectors along one mode of a single leaf do not cover, on either side or both: general strides, filters stored
+    K,C,R,S beside an activation in vectors, channels too few for a k tile, odd channels, folded k modes of row vectors."""
+    def w(name, dt, a, b, c, M, N, K, L=1):
+        return W.GemmWorkload(name, dt, a, b, c, *(lc.Layout(x).cosize for x in (a, b, c)), M, N, K, values, "", L)
+    return [
+        (W.gemm_workload("blis", 70, 45, 37, values=values), "gathered=along-k,along-rows"),
+        (W.gemm_workload("blis", 131, 67, 200, ab_dtype="f16", values=values), "gathered=along-k,along-rows"),
+        (W.conv_gemm_workload(1, 9, 8, 16, 40, 3, 3, "kcrs", values=values), "gathered=along-k,k-vectors"),
+        (W.conv_gemm_workload(2, 8, 7, 72, 33, 3, 3, "kcrs", ab_dtype="f16", values=values), "gathered=along-k,k-vectors"),
+        (W.conv_gemm_workload(1, 7, 8, 5, 33, 3, 3, "krsc", values=values), "gathered=along-k,along-k"),
+        (W.conv_gemm_workload(2, 9, 8, 24, 44, 3, 3, "krsc", values=values), "k-vectors=over-leaves"),
+        (W.conv_gemm_workload(1, 12, 9, 8, 136, 3, 3, "krsc", ab_dtype="f16", values=values), "k-vectors=over-leaves"),
+        (W.conv_gemm_workload(1, 8, 8, 96, 70, 2, 3, "krsc", values=values), "k-vectors=over-leaves"),
+        (w("folded_k_rows", "bf16", "(72,(8,9)):(1,(80,704))", "(136,(8,9)):(1,(136,1200))", "(72,136):(1,72)", 72, 136, 72), "gathered=row-vectors,row-vectors"),
+        (w("folded_k_mixed", "f16", "(72,(8,9)):(1,(80,704))", "(33,(8,9)):(3,(100,1100))", "(72,33):(1,72)", 72, 33, 72), "gathered=row-vectors,along-rows"),
+        (w("folded_k_kr", "bf16", "(65,(16,5)):(104,(1,20))", "(40,(16,5)):(5,(203,4000))", "(65,40):(41,1)", 65, 40, 80), "gathered=along-k,along-rows"),
+        (w("batched", "bf16", "(33,20,3):(61,3,2101)", "(40,20,3):(1,41,0)", "(33,40,3):(1,35,1501)", 33, 40, 20, 3), "gathered=along-k,along-rows"),
+        (w("reversed_lead", "f16", "(1,9):(9,2)", "(7,9):(2,15)", "(1,7):(1,3)", 1, 7, 9), "gathered=")]
+
+
+@pytest.mark.parametrize("tile", [0, 32, 3264, 6432, 64, 1282, 12864, 64128, 6464])
+def test_walk_gathered_operands(oracle, tile):
+    # eight elements (or a vector) a lane, every address inside the operand, in the slot the fragments are read from
+    for w, expect in gathered_workloads():
+        _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, [expect, "split_waves=" if tile in (32, 3264, 6432, 64) else "tile="])

@@ -304,3 +304,28 @@ def test_gemm_vectors_at_any_alignment_of_an_operand_that_ends_at_the_offset_lim
     print("case", layout, flush=True)
     lc.gemm_tensor(far, layout, near.to(torch.bfloat16).ravel(), "(3,%d):(%d,1)" % (K, K), c, "(%d,3):(1,%d)" % (rows, rows))
     assert (c.reshape(3, rows).T.cpu() == (values.cpu().float() @ near.cpu().float().T)).all()
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [0, 32, 3264, 6432, 64, 1282, 12864, 64128, 6464])
+def test_gemm_gathered_operands(oracle, tile, values):
+    # element by element along either mode, vectors over folded k modes, and both beside each other, on the split and stream kernels
+    from test_gemm_plan import gathered_workloads
+    for w, expect in gathered_workloads(values):
+        assert expect in _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
+
+
+def test_gemm_gathered_vectors_at_an_odd_pointer(oracle):
+    # beside an operand of elements the vectors of the other one may start at any element
+    w = W.conv_gemm_workload(1, 9, 8, 16, 40, 3, 3, "kcrs", values="ints")
+    a, b, c0 = W.gemm_operand_bits(w, "a"), W.gemm_operand_bits(w, "b"), W.gemm_c_values(w)
+    dev = torch.device("cuda:0")
+    plan = lc.GemmPlan(w.a_layout, w.b_layout, w.c_layout, w.ab_dtype)
+    assert "gathered=along-k,k-vectors" in plan.describe()
+    a_t = torch.from_numpy(a.view(np.int16)).to(dev)
+    c_t = torch.from_numpy(c0.copy()).to(dev)
+    b_t = torch.from_numpy(np.concatenate([b[:1], b]).view(np.int16)).to(dev)[1:]
+    plan.execute(a_t.data_ptr(), b_t.data_ptr(), c_t.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    want = oracle.gemm(W.bits_to_float64(a, w.ab_dtype), w.a_layout, W.bits_to_float64(b, w.ab_dtype), w.b_layout, c0.astype(np.float64), w.c_layout)
+    assert (c_t.cpu().numpy().astype(np.float64) == want).all()
