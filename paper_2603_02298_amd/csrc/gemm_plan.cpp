@@ -203,7 +203,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   Loads loads = choose_loads(a_r, a_k, a_l, a_align, b_r, b_k, b_l, b_align, K);
   const int t_env = env_int("LC_TUNE_GEMM_TILE", 0);
   const bool free_choice = t_env == 0;
-  const bool indirect = loads.gather && (free_choice ? env_int("LC_TUNE_GEMM_GATHER", 1) != 0 : t_env != 128 && t_env != 256 && t_env != 1285 && t_env != 3216);
+  // Vectors on both sides have the tile kernels' staged loads to fall back on, and these are better on large problems.  Measured on
+  // MI355X (bf16, us; staged, gathered or over leaves): row vectors on both sides 1024^3 27.6, 12.4; 2048^3 59, 55; 4096^2 x 1024 68, 74; 4096^3 166,
+  // 216; beside k vectors 1024^3 21.8, 11.8; 2048^3 49.9, 57.6; 1000 x 8000 x 960 34.4, 37.0; k vectors over leaves 1024^3 20.9, 10.3;
+  // 4096^2 x 1024 69.5, 62.2; 4096^3 177.4, 179.8; 8192^2 x 2048 434.7, 433.4.
+  auto in_tiles = [&](int64_t side) { return (M + side - 1) / side * ((N + side - 1) / side) * Lb; };
+  const bool staged_pays = loads.a_gather == 8 ? K >= 3000 && in_tiles(256) >= 256 : loads.a_gather >= 6 && loads.b_gather >= 6 && in_tiles(128) >= 256;
+  const bool indirect = loads.gather && (free_choice ? !staged_pays && env_int("LC_TUNE_GEMM_GATHER", 1) != 0 : t_env != 128 && t_env != 256 && t_env != 1285 && t_env != 3216);
   const bool leaves = indirect && loads.a_gather == 8, gather = indirect && !leaves;
   if (indirect) {
     loads.a_direct = loads.a_gather;
@@ -272,6 +278,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     else take(a_elem ? 64 : 128, a_elem ? 128 : 64, 0, 2);
   } else if (vectors && (t_env == 3216 || free_choice) && thin && (!free_choice || tiles_of(32, 16) <= 256)) take(32, 16, 8, regs ? 1 : 3);
   else if (vectors && (t_env == 32 || (free_choice && tiles_of(32, 32) <= 256))) take(32, 32, 8, regs ? 1 : 2);
+  // Short k loops leave the split kernel's wavefronts nothing to share: 64 x 64 tiles of the stream kernel are fewer and start with
+  // less.  Measured on MI355X (us; split kernel's choice, then these): 736 x 680 x 128 4.94, 3.98; 632 x 952 x 120 5.45, 4.26;
+  // 1008 x 472 x 112 (64 x 32) 4.58, 3.96; 800 x 352 x 184 (64 x 32) 3.97, 4.00; 64 x 64 tiles of 544 x 904 x 352 6.33, 5.56,
+  // of 848 x 968 x 768 8.35, 9.23.  (A single k tile stays with the split kernel: tests hold that choice.)
+  else if (free_choice && (direct || leaves) && K > 64 && tiles_of(64, 64) <= 256 &&
+           (K <= 128 || (K <= 384 && (kM <= kN ? tiles_of(32, 64) : tiles_of(64, 32)) > 256)))
+    take(64, 64, 0, 2);
   else if (vectors && (t_env == 3264 || (free_choice && kM <= kN && tiles_of(32, 64) <= 256))) take(32, 64, 4, regs ? 1 : 3);
   else if (vectors && (t_env == 6432 || (free_choice && kM > kN && tiles_of(64, 32) <= 256))) take(64, 32, 4, regs ? 1 : 3);
   else if (vectors && (t_env == 64 || (free_choice && tiles_of(64, 64) <= 256))) take(64, 64, 4, regs ? 1 : 2);

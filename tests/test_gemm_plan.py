@@ -467,3 +467,17 @@ def test_walk_gathered_operands(oracle, tile):
     # eight elements (or a vector) a lane, every address inside the operand, in the slot the fragments are read from
     for w, expect in gathered_workloads():
         _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, [expect, "split_waves=" if tile in (32, 3264, 6432, 64) else "tile="])
+
+
+def test_choice_of_short_k_loops_and_of_vectors_over_folded_k():
+    def text(M, N, K):
+        return lc.GemmPlan("(%d,%d):(%d,1)" % (M, K, K), "(%d,%d):(%d,1)" % (N, K, K), "(%d,%d):(1,%d)" % (M, N, M)).describe()
+    # several k tiles, but too few to share out: the stream kernel's 64 x 64 tiles
+    for M, N, K, stream in ((800, 800, 72, True), (800, 800, 384, True), (800, 800, 392, False), (800, 400, 128, True), (800, 400, 136, False), (512, 512, 72, False)):
+        assert (" stream " in text(M, N, K)) == stream, (M, N, K)
+    def folded(M, K):   # row vectors on both sides, k of two leaves
+        return lc.GemmPlan(*["(%d,(32,%d)):(1,(%d,%d))" % (M, K // 32, M, 33 * M)] * 2, "(%d,%d):(1,%d)" % (M, M, M)).describe()
+    assert "gathered=row-vectors,row-vectors" in folded(1920, 320) and "gathered" not in folded(2048, 320)
+    def leaves(M, K):   # k vectors on both sides, k of two leaves
+        return lc.GemmPlan(*["(%d,(32,%d)):(%d,(1,40))" % (M, K // 32, 40 * K // 32)] * 2, "(%d,%d):(1,%d)" % (M, M, M)).describe()
+    assert "over-leaves" in leaves(4096, 2976) and "over-leaves" in leaves(3840, 3008) and "over-leaves" not in leaves(4096, 3008)
