@@ -88,6 +88,8 @@ struct DirectParams {
   uint32_t n_items;                // items excluding the looped mode (< 2^31)
   uint32_t blocked;                // 1: a workgroup owns one contiguous range of items; 0: grid-stride
 };
+// Strided gathers of 16-bit elements, E neighbours a lane: dwords from the first one's address that hold them
+LC_HD constexpr int packed_dwords(int stride, int elems) { return (stride * (elems - 1) * 2 + 2 + 3) / 4; }
 LC_HD void direct_offsets(const DirectParams& P, uint32_t item, int64_t* so, int64_t* dof) {
   int64_t s = 0, d = 0;
   for (int k = 0; k + 1 < P.n_modes; ++k) {

@@ -353,6 +353,49 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const u32x4* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------------
+// Strided gather of 16-bit elements (source stride S of 2 to 7 elements, destination contiguous): a lane loads the up to 16
+// bytes that hold E neighbours of the gather, picks them and stores one word of E elements.  One element a lane spends a load and a
+// store instruction of 64 addresses on 128 bytes of destination, and the vector memory path, which takes a few addresses a
+// clock whatever their size, falls behind HBM; packed, a load brings E and a store writes E.
+// Lanes lie E elements apart, so a wavefront still reads one contiguous span and every line of it once.  Bound by HBM from 2^23 elements on.
+// Measured on MI355X (bf16, 2^26 elements, us, one element a lane -> this): stride 2 147 -> 63, 3 154 -> 86, 4 157 -> 105, 5 169 -> 126,
+// 6 179 -> 155, 7 192 -> 180 (the span read and the run written at 6.3 TB/s: 64, 85, 107, 128, 149, 170); 1283818 elements 4.2-6.6 -> 3.5-4.2.
+// Stride 8 needs a load for every element again and got slower (202 -> 223).
+// The last one to E elements of the run are moved one by one: a load of theirs could reach past the last element.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPackedUnroll = 2;   // words a lane has under way
+template <int S, int E>
+__global__ __launch_bounds__(kBlock) void packed_gather_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, uint32_t n) {
+  constexpr int U = kPackedUnroll, D = packed_dwords(S, E);   // dwords that hold the E elements
+  static_assert(D >= 2 && D <= 4, "one load");
+  typedef uint32_t Words __attribute__((ext_vector_type(D)));
+  typedef uint32_t Packed __attribute__((ext_vector_type(E / 2)));
+  const uint32_t whole = (n - 1u) / E, step = gridDim.x * kBlock;
+  for (uint32_t base = blockIdx.x * kBlock + threadIdx.x; base < whole; base += step * U) {
+    Words w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t it = base + (uint32_t)j * step;
+      w[j] = gload_at<1, 2, Words>(src + (uint64_t)(it < whole ? it : base) * (2 * S * E));
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t it = base + (uint32_t)j * step;
+      Packed o;
+#pragma unroll
+      for (int d = 0; d < E / 2; ++d) {
+        const int h0 = 2 * d * S, h1 = (2 * d + 1) * S;   // halves of w that hold the two elements
+        const uint32_t lo = w[j][h0 / 2] >> (16 * (h0 % 2)), hi = w[j][h1 / 2] >> (16 * (h1 % 2));
+        o[d] = (lo & 0xffffu) | (hi << 16);
+      }
+      if (it < whole) gstore_at<2, 2, Packed>(dst + (uint64_t)it * (2 * E), o);
+    }
+  }
+  const uint32_t rest = whole * E + blockIdx.x * kBlock + threadIdx.x;   // at most E elements, by the first lanes
+  if (rest < n) gstore_at<0, 2, uint16_t>(dst + 2 * (uint64_t)rest, gload_at<0, 2, uint16_t>(src + (uint64_t)rest * (2 * S)));
+}
+
+// ---------------------------------------------------------------------------------------------
 // Transpose through LDS.  Persistent workgroups walk the grid of tiles (the rest mode of
 // zipped_divide, Sec. 3.5.2); per tile each lane owns MT micro-tiles of V x V elements.
 //   load : V global loads of V*ES bytes along the source-contiguous mode p (one per step along q)
@@ -817,6 +860,24 @@ static bool launch_gather(const lc_plan& plan, const void* src, void* dst, unsig
   }
   return false;
 }
+template <int S, int E>
+static bool launch_packed_s(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+  if (plan.packed_elems != E) return false;
+  hipLaunchKernelGGL((packed_gather_kernel<S, E>), dim3(grid), dim3(kBlock), 0, s, static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst),
+                     plan.direct.n_items);
+  return true;
+}
+static bool launch_packed(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s) {
+  switch (plan.direct.sa[0]) {
+    case 2: return launch_packed_s<2, 4>(plan, src, dst, grid, s);
+    case 3: return launch_packed_s<3, 2>(plan, src, dst, grid, s);
+    case 4: return launch_packed_s<4, 2>(plan, src, dst, grid, s);
+    case 5: return launch_packed_s<5, 2>(plan, src, dst, grid, s);
+    case 6: return launch_packed_s<6, 2>(plan, src, dst, grid, s);
+    case 7: return launch_packed_s<7, 2>(plan, src, dst, grid, s);
+  }
+  return false;
+}
 template <int W>
 static void launch_direct(const lc_plan& plan, const void* src, void* dst, unsigned grid, hipStream_t s, unsigned int* queue) {
   switch (plan.unroll) {
@@ -1110,7 +1171,8 @@ static lc_status_t execute_with(const lc_plan& plan, const void* src, void* dst,
       default: return LC_ERR_UNSUPPORTED_DTYPE;
     }
   } else if (plan.cls == KernelClass::Direct) {
-    uint64_t want = ((uint64_t)plan.direct.n_items + (uint64_t)kBlock * plan.unroll - 1) / ((uint64_t)kBlock * plan.unroll);
+    const uint64_t per_lane = plan.packed_elems > 0 ? (uint64_t)kPackedUnroll * (uint64_t)plan.packed_elems : (uint64_t)plan.unroll;
+    uint64_t want = ((uint64_t)plan.direct.n_items + (uint64_t)kBlock * per_lane - 1) / ((uint64_t)kBlock * per_lane);
     unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(want, plan.grid_override > 0 ? (uint64_t)plan.grid_override : (uint64_t)cus * plan.wgs_per_cu));
     // long copies take their chunks on request, through the stream's block of counters (none to be had: the fixed order)
     unsigned int* dq = nullptr;
@@ -1121,6 +1183,10 @@ static lc_status_t execute_with(const lc_plan& plan, const void* src, void* dst,
     for (int64_t j = 0; j < plan.n_launches; ++j) {
       const void* sj = static_cast<const unsigned char*>(src) + j * plan.launch_src_step * plan.elem_bytes;
       void* dj = static_cast<unsigned char*>(dst) + j * plan.launch_dst_step * plan.elem_bytes;
+      if (plan.packed_elems > 0) {
+        if (!launch_packed(plan, sj, dj, grid, s)) return LC_ERR_UNSUPPORTED_DTYPE;
+        continue;
+      }
       if (plan.gather_stride > 0) {
         bool launched = false;
         switch (plan.elem_bytes) {

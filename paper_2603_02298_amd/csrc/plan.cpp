@@ -29,6 +29,7 @@ Tuning tuning_from_env() {
   t.grid = env_int("LC_TUNE_GRID", t.grid);
   t.early_loads = env_int("LC_TUNE_EARLY_LOADS", t.early_loads);
   t.gather = env_int("LC_TUNE_GATHER", t.gather);
+  t.packed = env_int("LC_TUNE_PACKED", t.packed);
   t.shifted = env_int("LC_TUNE_SHIFTED", t.shifted);
   t.direct_queue = env_int("LC_TUNE_DIRECT_QUEUE", t.direct_queue);
   t.max_items = env_int("LC_TUNE_MAX_ITEMS", (int)t.max_items);
@@ -1220,6 +1221,15 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       plan->queue_counters = tune.queue_counters >= 1 ? tune.queue_counters : 8;
     }
   }
+  // A strided gather of 16-bit elements into a contiguous run: two or four of them a lane (see packed_gather_kernel), while one load
+  // of up to 16 bytes holds them: strides up to 7.  Four workgroups a CU; eight for stride 3, whose loads bring only 8 bytes (2^26
+  // elements 94 -> 86 us; stride 4 105 -> 109, stride 7 180 -> 185).
+  plan->packed_elems = 0;
+  if (es == 2 && W == 2 && plan->gather_stride == 0 && P.n_modes == 1 && P.loop_extent == 1 && plan->n_launches == 1 && P.sb[0] == 1 &&
+      P.sa[0] >= 2 && P.sa[0] <= 7 && P.blocked == 0 && plan->direct_queue_items == 0 && tune.packed != 0) {
+    plan->packed_elems = P.sa[0] == 2 ? 4 : 2;
+    if (tune.wgs_per_cu <= 0 && P.sa[0] == 3) plan->wgs_per_cu = 8;
+  }
   if (tune.nontemporal < 0 && ((int64_t)W * (q >= 0 ? J[(size_t)q].extent / VEC : 1)) % 128 == 0) plan->nontemporal |= 2;
   plan->src_align = (unsigned)(VEC * es);
   plan->dst_align = (unsigned)(VEC * es);
@@ -1277,6 +1287,7 @@ std::string describe(const lc_plan& plan) {
     s += " launches=" + std::to_string(plan.n_launches);
     s += " unroll=" + std::to_string(plan.unroll);
     if (plan.gather_stride) s += " gather_stride=" + std::to_string(plan.gather_stride);
+    if (plan.packed_elems) s += " packed=" + std::to_string(plan.packed_elems);
     if (plan.direct_queue_items) s += " chunk_items=" + std::to_string(plan.direct_queue_items) + " queue_counters=" + std::to_string(plan.queue_counters);
     s += " early_loads=" + std::to_string(!plan.gather_stride && plan.early_loads && plan.direct.n_modes == 1 && plan.direct.loop_extent < (1u << 30) ? 1 : 0);
   }

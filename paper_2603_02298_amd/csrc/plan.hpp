@@ -35,6 +35,7 @@ struct Tuning {
   int grid = -1;               // workgroups of the launch (overrides CUs * wgs_per_cu)
   int leftover_lead = -1;      // transpose, fixed order: the tiles left after the last whole round go to this many leading workgroups
   int direct_queue = -1;       // direct: KiB of destination per chunk handed out on request; 0 = grid-stride order
+  int packed = -1;             // direct: 0 = strided gathers of 16-bit elements one element a lane
   int gather = -1;             // direct: 1 = a small source stride along the destination-contiguous mode is read in whole 16-byte words (gather_kernel)
   int shifted = -1;            // transpose: 1 = shifted tiles whatever the size, 0 = never
   int early_loads = -1;        // transpose: 0 = the first loads wait for the whole argument block (no TransposeHead)
@@ -65,6 +66,7 @@ struct lc_plan {
   lc::DirectParams direct{};
   int unroll = 4;
   int direct_queue_items = 0;              // > 0: items per chunk; wavefronts take chunks on request (long copies)
+  int packed_elems = 0;                    // > 0: a strided gather of 16-bit elements into a contiguous run, that many of them a lane (packed_gather_kernel)
   int gather_stride = 0;                   // > 0: the destination-contiguous mode is read with this stride; 16-byte words on both sides (gather_kernel)
   int64_t n_launches = 1;                  // slices along the outermost mode, one launch each
   int64_t launch_src_step = 0, launch_dst_step = 0;   // elements between consecutive slices

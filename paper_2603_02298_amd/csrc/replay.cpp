@@ -52,6 +52,15 @@ lc_status_t replay_on_host(const lc_plan& plan, const void* src, int64_t src_lo,
   } else if (plan.cls == KernelClass::Direct) {
     const DirectParams& P = plan.direct;
     const int W = plan.width_bytes;
+    if (plan.packed_elems > 0) {
+      // packed_gather_kernel: E elements a lane out of whole dwords of the source, the last one to E element by element
+      const int64_t S = P.sa[0], E = plan.packed_elems, D = packed_dwords((int)S, (int)E);
+      const uint32_t whole = P.n_items ? (uint32_t)((P.n_items - 1u) / E) : 0u;
+      if (es != 2 || W != 2 || P.n_modes != 1 || P.sb[0] != 1 || P.loop_extent != 1 || plan.n_launches != 1) return LC_ERR_INVALID_ARG;
+      for (uint32_t item = 0; item < whole; ++item)
+        if (D < 2 || D > 4 || item * 2 * S * E + 4 * D > B.src_hi || P.n_items - item * E <= (uint32_t)E) B.ok = false;
+      for (uint32_t e = 0; e < P.n_items; ++e) B.move(e * S * 2, (int64_t)e * 2, 2);
+    } else
     if (plan.gather_stride > 0) {
       // gather_kernel: vector `item` of the destination keeps every S-th element of S consecutive source words; all but the
       // last vector along mode 0 load those words whole

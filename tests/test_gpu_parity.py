@@ -447,3 +447,19 @@ def test_shifted_tiles(oracle, monkeypatch, dt, micro, queue):
         s = "(%d,%d,%d):(1,%d,%d)" % (M, N, B, M + pad, (M + pad) * N)
         d = "(%d,%d,%d):(%d,1,%d)" % (M, N, B, N + pad, M * (N + pad))
         assert "shifted_tiles=1" in _parity(oracle, s, d, dt, seed=n)
+
+
+@pytest.mark.parametrize("stride", range(2, 8))
+def test_packed_gathers_of_16_bit_elements(oracle, stride):
+    # edges of a lane's elements and of the grid, pointers at any element (the plan asks for no more alignment than an element's)
+    from test_plan_replay import PACKED_SIZES
+    for n in PACKED_SIZES + ((1 << 20) + 3, 5000001):
+        desc = _parity(oracle, "%d:%d" % (n, stride), "%d:1" % n, "bf16", seed=n, tag="packed gather")
+        assert (" packed=" in desc) == (n > 1), desc
+    n, stream = 1003, torch.cuda.current_stream().cuda_stream
+    plan = lc.Plan("%d:%d" % (n, stride), "%d:1" % n, "f16")
+    src = torch.randint(-30000, 30000, (n * stride + 8,), dtype=torch.int16, device="cuda")
+    for a, b in ((1, 0), (0, 1), (1, 3), (3, 1)):
+        dst = torch.zeros(n + 8, dtype=torch.int16, device="cuda")
+        plan.execute(src.data_ptr() + 2 * a, dst.data_ptr() + 2 * b, stream)
+        assert (dst[b:b + n] == src[a:a + (n - 1) * stride + 1:stride]).all() and (dst[:b] == 0).all() and (dst[b + n:] == 0).all()

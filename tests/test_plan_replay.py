@@ -502,3 +502,20 @@ def test_large_windows_by_their_pitch():
         a, b = "(%d,%d):(1,%d)" % (row, n, pitch), "(%d,%d):(1,%d)" % (row, n, row)
         for s, d, unroll in ((a, b, out_of), (b, a, into)):
             assert "unroll=%d " % unroll in lc.Plan(s, d, "bf16").describe(), (row, pitch, s)
+
+
+PACKED_SIZES = (1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65, 1021, 4096, 100003)
+
+
+@pytest.mark.parametrize("stride", range(2, 10))
+def test_packed_gathers_of_16_bit_elements(oracle, monkeypatch, stride):
+    # two or four elements a lane out of one load that never reaches past the last element; from stride 8 on, and for other
+    # destinations and widths, one element a lane as before
+    for n in PACKED_SIZES:
+        desc, _ = _check(oracle, "%d:%d" % (n, stride), "%d:1" % n, "bf16")
+        assert (" packed=" in desc) == (stride <= 7 and n > 1), desc
+    for s, d, dt in (("64:%d" % stride, "64:1", "f32"), ("64:%d" % stride, "64:2", "bf16"), ("(64,3):(%d,1000)" % stride, "(64,3):(1,64)", "f16")):
+        assert " packed=" not in _check(oracle, s, d, dt)[0]
+    _check_signed(oracle, "65:-%d" % stride, "65:-1", "bf16")
+    monkeypatch.setenv("LC_TUNE_PACKED", "0")
+    assert " packed=" not in _check(oracle, "65:%d" % stride, "65:1", "bf16")[0]
