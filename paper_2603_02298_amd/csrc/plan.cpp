@@ -31,6 +31,7 @@ Tuning tuning_from_env() {
   t.gather = env_int("LC_TUNE_GATHER", t.gather);
   t.packed = env_int("LC_TUNE_PACKED", t.packed);
   t.shifted = env_int("LC_TUNE_SHIFTED", t.shifted);
+  t.moved = env_int("LC_TUNE_MOVED", t.moved);
   t.direct_queue = env_int("LC_TUNE_DIRECT_QUEUE", t.direct_queue);
   t.max_items = env_int("LC_TUNE_MAX_ITEMS", (int)t.max_items);
   if (const char* v = std::getenv("LC_TUNE_TILE")) {
@@ -310,10 +311,11 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
 // grid has ceil(extent / tile) tiles along such a mode and the kernel checks coordinates at the edge.
 // shifted: likewise, for vectors at any alignment (V need not divide anything); the last tile along such a mode is moved back
 // until it ends with the mode, so the kernel without predicates runs them; whole workgroups only.
-enum class Tiling { Exact, Ragged, Shifted };
+// moved: shifted, along modes of the tile other than p and q as well (at most two modes that the tile does not divide).
+enum class Tiling { Exact, Ragged, Shifted, Moved };
 static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, int q, int64_t n, const Tuning& tune, lc_plan* plan,
                        Tiling tiling = Tiling::Exact) {
-  const bool ragged = tiling != Tiling::Exact, shifted = tiling == Tiling::Shifted;
+  const bool ragged = tiling != Tiling::Exact, shifted = tiling == Tiling::Shifted || tiling == Tiling::Moved;
   const int nj = (int)J.size();
   // Tile size: up to 4 micro-tiles per lane (64 KiB of fp32), but never so large that fewer than
   // ~1024 tiles remain for the 256 CUs; growth stops early once both sides move >= 512-byte runs.
@@ -354,7 +356,13 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
       const int64_t e = J[(size_t)k].extent, old = t[(size_t)k];
       if (old >= e) continue;
       const int64_t grown = std::min<int64_t>(old * 2, e);
-      if (shifted && (grown != old * 2 || (k != p && k != q && e % grown != 0))) continue;
+      if (shifted && (grown != old * 2 || (tiling == Tiling::Shifted && k != p && k != q && e % grown != 0))) continue;
+      if (tiling == Tiling::Moved) {
+        int cut = e % grown != 0 ? 1 : 0;
+        for (int j = 0; j < nj; ++j)
+          if (j != k && J[(size_t)j].extent % t[(size_t)j] != 0) ++cut;
+        if (cut > 2) continue;
+      }
       t[(size_t)k] = grown;
       const bool fits = spans_fit(t) && micro_of(t) <= target && grown < (1 << 15);
       int64_t rs = run_length(J, src_order, t, true), rd = run_length(J, dst_order, t, false);
@@ -1004,13 +1012,13 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       plan->note = "no common vector on both sides for a transposing tile";
       return false;
     };
-    auto plan_shifted = [&](lc_plan* sh) {
+    auto plan_shifted = [&](lc_plan* sh, Tiling tiling = Tiling::Shifted) {
       if ((es != 2 && es != 4) || tune.max_vec_bytes > 0 || tune.tile.size() == (size_t)nj) return false;
       sh->cls = KernelClass::Generic;
-      return plan_tiled(J, es, 16 / es, p, q, n, tune, sh, Tiling::Shifted);
+      return plan_tiled(J, es, 16 / es, p, q, n, tune, sh, tiling);
     };
     lc_plan shifted = *plan;
-    if (tune.shifted > 0 && plan_shifted(&shifted)) {
+    if (tune.shifted > 0 && plan_shifted(&shifted, tune.shifted == 2 ? Tiling::Moved : Tiling::Shifted)) {
       *plan = shifted;
       return LC_OK;
     }
@@ -1046,12 +1054,41 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       return plan->tile_extent[(size_t)k] == row && shifted.tile_extent[(size_t)k] < row && run_bytes == row * es && other_run_bytes >= 128 &&
              pitch >= 2 * row;
     };
+    // Tiles of three modes and more, where a mode beside p and q has an extent with few small factors: moved tiles cut it
+    // anywhere and keep whole workgroups and balanced runs.  In place of ragged tiles, of whole tiles that leave most lanes idle and of
+    // shifted tiles with a shorter run; within 1.15 times the elements.  Measured on MI355X over 120 copies of 2^19 to 2^26 elements whose plan
+    // they change (random extents and orders, 0.77 of the time on average) and 60 relayouts of 8 x 8 blocks, us, before -> with them:
+    //   whole tiles of up to 96 lanes: relayout 664 x 244 15.8 -> 8.6, 492 x 668 22.9 -> 16.5, 464 x 508 14.6 -> 11.4; 20 lanes fp32 (4,179,4,22340) 554 -> 93;
+    //     but 72 x 484 4.6 -> 4.9 and 132 x 344 4.8 -> 5.0 (48 lanes, below 3 * 2^20 elements), 144 x 236 4.2 -> 4.4; beyond 96 lanes 484 x 672 17.9 -> 16.6,
+    //     472 x 820 20.7 -> 20.9, 940 x 636 32.3 -> 34.2;
+    //   ragged tiles: relayout 148 x 748 11.6 -> 7.7, 92 x 776 8.9 -> 6.0; full fp32 ones from 5 * 2^20 elements on (7.5M 17.2 -> 12.4, 5.3M
+    //     14.9 -> 10.1; 4.4M 9.3 -> 10.5, 4.7M 11.3 -> 12.4); not bf16 ones of the same extents on long grids, where the ragged kernel has five
+    //     workgroups a CU ((8,64,8,10886) 34 -> 44, (16,151,8,1713) 33.9 -> 32.5; shorter ones 24.1 -> 21.0), nor those of more than 512 lanes
+    //     (fp32 96 x 2316 x 116 51 -> 55, (16,112,8,1213) 33 -> 35);
+    //   not where the shorter run falls below 256 bytes for it (28 x 4 x 38576 fp32, 224 -> 64 bytes, 10.6 -> 14.1);
+    //   shifted tiles with runs shorter than a line: bf16 (166,8,64,719) 146 -> 61, (225,8,14864) 42 -> 28; but of 128 bytes (168,3048,8,8) 29 -> 33.
+    lc_plan moved = *plan;
+    auto moved_pays = [&](bool in_place_of_plain) {
+      if (!may_shift || tune.moved == 0 || V * es != 16 || nj < 3 || !plan_shifted(&moved, Tiling::Moved) || covered(moved) > 1.15 * (double)n) return false;
+      const int64_t run = std::min(plan->src_run_bytes, plan->dst_run_bytes), moved_run = std::min(moved.src_run_bytes, moved.dst_run_bytes);
+      if (!in_place_of_plain) return run < 128 && moved_run > run;
+      if (moved_run < std::min<int64_t>(run, 256)) return false;
+      const uint32_t lanes = plan->transpose.n_micro;
+      if (plan->transpose.n_ragged > 0) {
+        if (lanes > 2u * kBlock) return false;
+        if (es == 2) return plan->tile_extent != moved.tile_extent || moved.transpose.n_tiles < 1280u;
+        return lanes < 224u || n >= (5 << 20);
+      }
+      return lanes <= 96u && n >= (lanes <= 32u ? 2 << 20 : lanes <= 56u ? 3 << 20 : 4 << 20);
+    };
     if (limit > 0.0 && (shifts || plan_shifted(&shifted)) &&
         (!plain || (covered(shifted) <= limit * covered(*plan) && !cuts_rows(p, true, plan->src_run_bytes, plan->dst_run_bytes) &&
                     !cuts_rows(q, false, plan->dst_run_bytes, plan->src_run_bytes)))) {
       *plan = shifted;
+      if (moved_pays(false)) *plan = moved;
       return LC_OK;
     }
+    if (plain && moved_pays(true)) *plan = moved;
     if (plain) return LC_OK;
   }
   if (tune.force_class == 0) return plan_generic(S, D, n, plan, "forced");

@@ -38,6 +38,7 @@ struct Tuning {
   int packed = -1;             // direct: 0 = strided gathers of 16-bit elements one element a lane
   int gather = -1;             // direct: 1 = a small source stride along the destination-contiguous mode is read in whole 16-byte words (gather_kernel)
   int shifted = -1;            // transpose: 1 = shifted tiles whatever the size, 0 = never
+  int moved = -1;              // transpose: 0 = modes other than the two vectors' are only tiled evenly
   int early_loads = -1;        // transpose: 0 = the first loads wait for the whole argument block (no TransposeHead)
 };
 Tuning tuning_from_env();

@@ -463,3 +463,12 @@ def test_packed_gathers_of_16_bit_elements(oracle, stride):
         dst = torch.zeros(n + 8, dtype=torch.int16, device="cuda")
         plan.execute(src.data_ptr() + 2 * a, dst.data_ptr() + 2 * b, stream)
         assert (dst[b:b + n] == src[a:a + (n - 1) * stride + 1:stride]).all() and (dst[:b] == 0).all() and (dst[b + n:] == 0).all()
+
+
+@pytest.mark.parametrize("shifted", ["2", "-1"])
+def test_moved_tiles(oracle, monkeypatch, shifted):
+    from test_plan_replay import MOVED_CASES
+    monkeypatch.setenv("LC_TUNE_SHIFTED", shifted)
+    for n, case in enumerate(MOVED_CASES):
+        desc = _parity(oracle, *case, seed=n, tag="moved tiles")
+        assert shifted != "2" or "shifted_tiles=1" in desc, desc

@@ -519,3 +519,31 @@ def test_packed_gathers_of_16_bit_elements(oracle, monkeypatch, stride):
     _check_signed(oracle, "65:-%d" % stride, "65:-1", "bf16")
     monkeypatch.setenv("LC_TUNE_PACKED", "0")
     assert " packed=" not in _check(oracle, "65:%d" % stride, "65:1", "bf16")[0]
+
+
+MOVED_CASES = [  # blocks of 8 x 8 permuted, extents with few small factors; three to five modes, both widths
+    ("((8,244),(8,264)):((1,8),(1952,15616))", "((8,244),(8,264)):((8,16896),(1,64))", "bf16"),      # whole tiles of few lanes
+    ("((8,148),(8,188)):((1,8),(1184,9472))", "((8,148),(8,188)):((8,12032),(1,64))", "f16"),        # ragged tiles
+    ("(4,61,4,1153):(4,16,1,976)", "(4,61,4,1153):(1,18448,4,16)", "f32"), ("(8,211,16,99):(211,1,26752,1688)", "(8,211,16,99):(1,12672,8,128)", "bf16"),
+    ("(8,16,16,1110):(284160,16,1,256)", "(8,16,16,1110):(256,1,16,2048)", "bf16"), ("(61,8,67,9,8):(1,61,488,294264,32696)", "(61,8,67,9,8):(38592,1,576,64,8)", "bf16")]
+
+
+@pytest.mark.parametrize("case", MOVED_CASES)
+def test_moved_tiles(oracle, monkeypatch, case):
+    # tiles cut a mode beside the two vectors' anywhere, the last one along it moved back: whole workgroups, every element
+    # written and every access inside; the plan without them copies the same
+    monkeypatch.setenv("LC_TUNE_SHIFTED", "2")
+    desc, conflicts = _check(oracle, *case)
+    assert "shifted_tiles=1" in desc and ("micro_tiles=256 " in desc), desc
+    monkeypatch.delenv("LC_TUNE_SHIFTED")
+    _check(oracle, *case)
+    monkeypatch.setenv("LC_TUNE_MOVED", "0")
+    _check(oracle, *case)
+
+
+def test_where_moved_tiles_are_taken():
+    def desc(a, b, dt="bf16"):
+        return lc.Plan("((8,%d),(8,%d)):((1,8),(%d,%d))" % (a, b, 8 * a, 64 * a), "((8,%d),(8,%d)):((8,%d),(1,64))" % (a, b, 64 * b), dt).describe()
+    assert "tile=[8,8,8,32]" in desc(664, 244) and "tile=[8,8,8,32]" in desc(148, 748) and "tile=[8,8,8,32]" in desc(452, 208)
+    assert "shifted_tiles" not in desc(132, 344) and "shifted_tiles" not in desc(940, 636) and "shifted_tiles" not in desc(512, 1024)
+    assert "shifted_tiles" not in lc.Plan("(28,4,38576):(1,28,112)", "(28,4,38576):(154304,38576,1)", "f32").describe()   # a shorter run
