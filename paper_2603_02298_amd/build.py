@@ -13,15 +13,17 @@ SOURCES = ["layout.cpp", "algebra.cpp", "semimodule.cpp", "plan.cpp", "replay.cp
            "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip", "gemm_inst_bf16_split.hip", "gemm_inst_f16_split.hip",
            "gemm_inst_bf16_stream.hip", "gemm_inst_f16_stream.hip", "gemm_inst_bf16_split_any.hip", "gemm_inst_f16_split_any.hip",
            "gemm_inst_bf16_stream_any.hip", "gemm_inst_f16_stream_any.hip",
-           "gemm_inst_bf16_gather.hip", "gemm_inst_f16_gather.hip", "gemm_inst_bf16_leaves.hip", "gemm_inst_f16_leaves.hip"]
+           "gemm_inst_bf16_gather.hip", "gemm_inst_f16_gather.hip", "gemm_inst_bf16_leaves.hip", "gemm_inst_f16_leaves.hip",
+           "gemm_inst_bf16_wide.hip", "gemm_inst_f16_wide.hip"]
 HEADERS = ["layout.hpp", "algebra.hpp", "semimodule.hpp", "plan.hpp", "kernel_params.hpp", "gemm_plan.hpp", "gemm_params.hpp", "plan_cache.hpp", "kernarg.hpp"]
 # header -> the only sources that include it
 _TILE = ["gemm_inst_bf16_256.hip", "gemm_inst_bf16_128.hip", "gemm_inst_f16_256.hip", "gemm_inst_f16_128.hip"]
 _SPLIT = ["gemm_inst_%s_split%s.hip" % (t, a) for t in ("bf16", "f16") for a in ("", "_any")]
 _STREAM = ["gemm_inst_%s_stream%s.hip" % (t, a) for t in ("bf16", "f16") for a in ("", "_any")]
 _GATHER = ["gemm_inst_%s_%s.hip" % (t, g) for t in ("bf16", "f16") for g in ("gather", "leaves")]
-KERNEL_HEADERS = {"gemm_kernel.hpp": _TILE, "gemm_split_kernel.hpp": _SPLIT + _GATHER, "gemm_stream_kernel.hpp": _STREAM + _GATHER,
-                  "gemm_device.hpp": _TILE + _SPLIT + _STREAM + _GATHER}
+_WIDE = ["gemm_inst_%s_wide.hip" % t for t in ("bf16", "f16")]
+KERNEL_HEADERS = {"gemm_kernel.hpp": _TILE, "gemm_split_kernel.hpp": _SPLIT + _GATHER, "gemm_stream_kernel.hpp": _STREAM + _GATHER, "gemm_wide_kernel.hpp": _WIDE,
+                  "gemm_device.hpp": _TILE + _SPLIT + _STREAM + _GATHER + _WIDE}
 
 
 def _hipcc():

@@ -130,14 +130,17 @@ struct DirectTileLoader {
       tail_mask |= (k < k_rem ? 1u : 0u) << i;
     }
   }
-  // k_bytes: the k tile's byte offset along the k mode (uniform); at: where this wavefront's first KiB of the tile lies in LDS (uniform)
+  // k_bytes: the k tile's byte offset along the k mode (uniform); at: where this wavefront's first KiB of the tile lies in LDS (uniform);
+  // FIRST, END: which of the instructions
+  template <int FIRST = 0, int END = R>
   __device__ __forceinline__ void fetch(uint32_t k_bytes, uint32_t at, bool tail) {
     typedef __attribute__((address_space(3))) void lds_void;
     // dynamic LDS under a second name: the compiler sees no alias between these writes and the fragment reads and adds no
     // waits of its own; the kernels state the order by hand
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_bytes[];
-    static_for<R>([&](auto i) {
-      const uint32_t voff = (tail && ((tail_mask >> (int)i) & 1u) == 0u) ? 0xFFFFFFFFu : off[i];
+    static_for<END - FIRST>([&](auto d) {
+      constexpr int i = FIRST + decltype(d)::value;
+      const uint32_t voff = (tail && ((tail_mask >> i) & 1u) == 0u) ? 0xFFFFFFFFu : off[i];
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(lds_bytes + at + (uint32_t)i * 1024u), 16, (int)voff, (int)k_bytes, 0, 0);
     });
   }

@@ -25,6 +25,8 @@ hipError_t launch_gemm_bf16_split_gather(const lc_gemm_plan& plan, const uint16_
 hipError_t launch_gemm_bf16_stream_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_split_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_stream_gather(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_bf16_wide(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
+hipError_t launch_gemm_f16_wide(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_bf16_split_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_bf16_stream_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
 hipError_t launch_gemm_f16_split_leaves(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s);
@@ -73,6 +75,8 @@ lc_status_t execute_gemm_plan(const lc_gemm_plan& plan, const void* a, const voi
     pre = bf16 ? launch_gemm_bf16_stream_any(plan, ka, kb, kc, s) : launch_gemm_f16_stream_any(plan, ka, kb, kc, s);
   else if (plan.stages > 0)
     pre = bf16 ? launch_gemm_bf16_stream(plan, ka, kb, kc, s) : launch_gemm_f16_stream(plan, ka, kb, kc, s);
+  else if (way == 1 && plan.tile_m != plan.tile_n)
+    pre = bf16 ? launch_gemm_bf16_wide(plan, ka, kb, kc, s) : launch_gemm_f16_wide(plan, ka, kb, kc, s);
   else if (way > 1)
     return LC_ERR_INVALID_ARG;
   else if (plan.tile_m == 256 && plan.tile_n == 256 && plan.lds_bytes == tiles_in_lds * 256u * 128u)

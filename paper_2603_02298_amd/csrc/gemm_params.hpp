@@ -143,7 +143,8 @@ LC_HD uint32_t gemm_lane_row(int32_t load, uint32_t lane, uint32_t i) {
 // ---------------------------------------------------------------------------------------------
 // Narrower tiles hold several k rows per 256 bytes of banks: with 64 rows (8 slots per k) two k rows share them and the XOR
 // only has to part k rows 2 apart; with 32 rows (4 slots per k) four k rows fill them and nothing is folded.
-LC_HD uint32_t gemm_rdirect_fold(uint32_t BR, uint32_t k) { return BR >= 128u ? 4u * (k & 3u) : BR == 64u ? 2u * (k & 2u) : 0u; }
+// (192 rows are 24 slots: k rows 1 apart lie half the banks apart, k rows 2 apart are parted by the XOR)
+LC_HD uint32_t gemm_rdirect_fold(uint32_t BR, uint32_t k) { return BR == 192u ? 2u * (k & 2u) : BR >= 128u ? 4u * (k & 3u) : BR == 64u ? 2u * (k & 2u) : 0u; }
 LC_HD uint32_t gemm_rdirect_lds_offset(uint32_t BR, uint32_t k, uint32_t row) { return k * (BR * 2u) + ((((row >> 3) ^ gemm_rdirect_fold(BR, k))) << 4) + (row & 7u) * 2u; }
 // Instruction i of wavefront w fills 1 KiB = 64 slots; lane l's slot is unit (w R + i) 64 + l of the tile: its k row and
 // the 8-row group it must ask memory for.

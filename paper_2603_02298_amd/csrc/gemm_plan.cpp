@@ -262,7 +262,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   // 6.2.  16 x 8192 x 8192 78 us; 32 x 32 27.6, 64 x 64 36.  64 x 8192 x 8192 92 us; 32 x 32 (512 tiles) 42.8, 64 x 32 (256) 33.4.
   // 1024^3 17.6 us; 32 x 64 (512 tiles) 10.8, 64 x 64 (256) 8.3.
   auto tiles_of = [&](int64_t tm, int64_t tn) { return (kM + tm - 1) / tm * ((kN + tn - 1) / tn) * Lb; };
-  // LC_TUNE_GEMM_TILE: 256, 128 (gathered operands: 1282), 12864 (128 x 64), 64128, 1285 (the ring of five 128 x 128 tiles); split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
+  // LC_TUNE_GEMM_TILE: 256, 256192 (256 x 192), 192256, 128 (gathered operands: 1282), 12864 (128 x 64), 64128, 1285 (the ring of five 128 x 128 tiles); split kernel: 32, 64, 3216 (32 x 16), 3264 (32 x 64), 6432; 6464: the
   // stream kernel's 64 x 64
   auto take = [&](int tm, int tn, int waves, int stages) { plan.tile_m = tm; plan.tile_n = tn; plan.split_waves = waves; plan.stages = stages; };
   const bool thin = kN <= 16 && !indirect && (P.b_load == kLoadKVec || P.b_direct == 2), vectors = direct || any || indirect;
@@ -328,7 +328,24 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
                                       std::min(1.0, fill + (1.0 - fill) * (double)tiles_of(256, 256) / 256.0), 1.0};
     const Choice ring = {128, 128, 1.0, 1.35};
     const bool ring_pays = direct && K >= 3000 && tiles_of(128, 128) <= 256 && cost(ring) < cost(*best);
-    if (direct && free_choice && cost(big) <= (ring_pays ? cost(ring) : cost(*best))) take(256, 256, 0, 0);
+    // Tiles of 256 x 192 and 192 x 256 (their own kernel; C in vectors) from K = 768 on: 0.91, 0.82 from 2048 on, 0.8 from 3000 on, for at least
+    // 128 of them; below K = 1200, where C's update weighs too much for a second round, for one nearly full round (tn 2600 x 4112 x 880 40.1 -> 36.8, 242
+    // tiles; but 192 tiles 5992 x 1368 x 896 30.9 -> 32.3, three rounds 5984 x 6072 x 960 112 -> 130).  Of 460 problems drawn (all forms, K from 128 to
+    // 8192, up to 32 batch entries) they are chosen for 90 and take 0.89 of the time of the others' best on average, 1.03 at worst; figures
+    // beside the kernel.  Pairs along the rows between 2048 and 3000 keep the others' tiles, which tests hold for 4240 x 5248 x 2872 (168 us, 161 here).
+    const bool wide_fits = direct && P.c_vec != 0, rows_pair = P.a_load == kLoadRVec && P.b_load == kLoadRVec;
+    const double wide_weight = K < 2048 ? 0.91 : K < 3000 ? (rows_pair ? 1.0 : 0.82) : 0.8;
+    auto wide_cost = [&](int64_t tm, int64_t tn) {
+      const int64_t tiles = tiles_of(tm, tn);
+      if (K < 768 || tiles < (K < 1200 ? 216 : 128) || (K < 1200 && tiles > 256)) return 1e30;
+      return cost({(int)tm, (int)tn, wide_weight * std::min(1.0, fill + (1.0 - fill) * (double)tiles / 256.0), 1.0});
+    };
+    const bool tall = wide_cost(256, 192) <= wide_cost(192, 256);
+    const int wide_m = tall ? 256 : 192, wide_n = tall ? 192 : 256;
+    const bool wide_pays = wide_fits && wide_cost(wide_m, wide_n) < std::min(cost(big), ring_pays ? cost(ring) : cost(*best));
+    if (wide_fits && (t_env == 256192 || t_env == 192256)) take(t_env / 1000, t_env % 1000, 0, 0);
+    else if (free_choice && wide_pays) take(wide_m, wide_n, 0, 0);
+    else if (direct && free_choice && cost(big) <= (ring_pays ? cost(ring) : cost(*best))) take(256, 256, 0, 0);
     else if (direct && (t_env == 1285 || (free_choice && ring_pays))) take(128, 128, 0, 0);
     else if (t_env == 128 || t_env == 1282) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);
@@ -353,7 +370,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   P.group_m = (uint32_t)std::max(1, env_int("LC_TUNE_GEMM_GROUP_M", 8));
   // two stages of (rows x 128 bytes) for A and B; direct loads: a ring of five operand tiles
   // (split and stream kernels: rings of pairs of tiles, one per wavefront or one for all)
-  plan.lds_bytes = plan.stages ? (unsigned)(std::max(1, plan.split_waves) * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)plan.tile_m * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
+  plan.lds_bytes = plan.stages ? (unsigned)(std::max(1, plan.split_waves) * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)std::max(plan.tile_m, plan.tile_n) * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
   plan.a_text = mode_text(a_r) + " x " + mode_text(a_k);
   plan.b_text = mode_text(b_r) + " x " + mode_text(b_k);
   plan.c_text = mode_text(c_m) + " x " + mode_text(c_n);

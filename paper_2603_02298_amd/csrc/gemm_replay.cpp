@@ -2,6 +2,7 @@
 // workgroups, lanes and k tiles with the same index functions (gemm_params.hpp), every global access
 // checked against the buffers, the operand tiles passed through a byte model of LDS, and the matrix
 // instruction replaced by its definition taken through the fragments' thread-value layouts.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -345,7 +346,7 @@ lc_status_t gemm_replay_on_host(const lc_gemm_plan& plan, const uint16_t* a, int
   product.to_float = plan.ab_dtype == LC_BF16 ? bf16_to_float : f16_to_float;
   if (plan.stages > 0) return replay_sums(plan, w, product, c, c_elems);
   const uint32_t BM = (uint32_t)plan.tile_m, BN = (uint32_t)plan.tile_n, WMB = BM / 64, WNB = BN / 64;
-  if (plan.lds_bytes != (P.a_direct ? 5u * BM * 128u : 2u * (BM + BN) * 128u)) return LC_ERR_INVALID_ARG;
+  if (plan.lds_bytes != (P.a_direct ? 5u * std::max(BM, BN) * 128u : 2u * (BM + BN) * 128u)) return LC_ERR_INVALID_ARG;
   std::vector<unsigned char> lds((BM + BN) * 128u);   // one k tile of A and B is enough for a sequential walk
   std::vector<float> acc((size_t)BM * BN);
   std::vector<char> covered((size_t)P.tiles_m * P.tiles_n, 0);

@@ -481,3 +481,36 @@ def test_choice_of_short_k_loops_and_of_vectors_over_folded_k():
     def leaves(M, K):   # k vectors on both sides, k of two leaves
         return lc.GemmPlan(*["(%d,(32,%d)):(%d,(1,40))" % (M, K // 32, 40 * K // 32)] * 2, "(%d,%d):(1,%d)" % (M, M, M)).describe()
     assert "over-leaves" in leaves(4096, 2976) and "over-leaves" in leaves(3840, 3008) and "over-leaves" not in leaves(4096, 3008)
+
+
+WIDE_CASES = [("tn", (300, 200, 8)), ("nt", (264, 400, 136)), ("nn_rowmajor_c", (200, 300, 200)), ("gett", (320, 200, 64)), ("tn", (388, 396, 320)),
+              ("nt", (200, 264, 384)), ("strided_batch", (136, 72, 40, 3)), ("shared_b", (256, 192, 200, 2))]
+
+
+@pytest.mark.parametrize("tile,shape", [(256192, "256x192"), (192256, "192x256")])
+def test_walk_wide_tiles(oracle, tile, shape):
+    # one to six k tiles through a ring whose slots hold tiles of 256 and of 192 rows, short last k tiles, ragged rows and columns
+    for name, sizes in WIDE_CASES:
+        w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, values="ints")
+        _walk_and_compare(oracle, w, {"LC_TUNE_GEMM_TILE": tile}, ["tile=%sx64 tiles" % shape, "lds_bytes=163840"])
+
+
+def test_k_major_tiles_of_192_rows_are_free_of_bank_conflicts():
+    from paper_2603_02298_amd.binding import lib
+    addr = lib().lc_debug_gemm_lds_address
+    assert sorted(addr(1, 192, 0, k, 8 * g) // 16 for k in range(64) for g in range(24)) == list(range(8 * 192))
+    for row_base in range(0, 192, 32):
+        for k_base in range(0, 64, 4):
+            for half in (0, 32):
+                banks = [addr(2, 192, half + l, row_base, k_base) // 4 % 64 + d for l in range(32) for d in range(2)]
+                assert sorted(banks) == list(range(64)), (row_base, k_base, half)
+
+
+def test_where_wide_tiles_are_taken():
+    def tile(form, M, N, K, c="col", L=1):
+        a = "(%d,%d):" % (M, K) + ("(%d,1)" % K if form[0] == "t" else "(1,%d)" % M)
+        b = "(%d,%d):" % (N, K) + ("(%d,1)" % K if form[1] == "t" else "(1,%d)" % N)
+        return lc.GemmPlan(a, b, "(%d,%d):" % (M, N) + ("(1,%d)" % M if c == "col" else "(%d,1)" % N)).describe().split("tile=")[1].split("x64 ")[0]
+    assert tile("nt", 3368, 5336, 6576) == "256x192" and tile("tt", 1872, 5312, 2008) == "192x256" and tile("tn", 2600, 4112, 880) == "256x192" and tile("tt", 5656, 2968, 8048) == "256x192"
+    assert tile("tt", 1872, 5312, 760) == "128x128" and tile("nt", 5984, 6072, 960) == "128x128" and tile("tt", 1816, 5256, 5080) == "192x256" and tile("tt", 8192, 8192, 8192) == "256x256" and tile("nn", 4376, 4376, 4808) == "256x192"
+    assert tile("tt", 3370, 5336, 6576) not in ("256x192", "192x256")   # C without vectors

@@ -329,3 +329,14 @@ def test_gemm_gathered_vectors_at_an_odd_pointer(oracle):
     torch.cuda.synchronize()
     want = oracle.gemm(W.bits_to_float64(a, w.ab_dtype), w.a_layout, W.bits_to_float64(b, w.ab_dtype), w.b_layout, c0.astype(np.float64), w.c_layout)
     assert (c_t.cpu().numpy().astype(np.float64) == want).all()
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+@pytest.mark.parametrize("tile", [256192, 192256])
+def test_gemm_wide_tiles(oracle, tile, values):
+    # the ring of 256- and 192-row tiles: one to six k tiles, short last ones, ragged edges, every pair of loads, batches, both types
+    from test_gemm_plan import WIDE_CASES
+    for n, (name, sizes) in enumerate(WIDE_CASES):
+        w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, ab_dtype=("bf16", "f16")[n % 2], values=values)
+        desc = _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
+        assert "tile=%dx%dx64 tiles" % (tile // 1000, tile % 1000) in desc and desc.count("direct-to-LDS") == 2, desc
