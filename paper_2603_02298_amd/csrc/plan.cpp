@@ -715,7 +715,21 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
     }
     // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
     // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
-    if (shifted) want = P.n_tiles >= 8192 ? 1 : (P.n_tiles >= 1280 ? 2 : 4);
+    // -- but a grid whose last round is nearly empty, or that gives a few CUs one tile more than the rest, waits for those.  Square tiles: 1100 to 1350
+    // go in one round of five a CU or close to it (bf16 1128 18.1 -> 14.1, 1206 20.6 -> 17.1, 1300 12.9 -> 11.9; fp32 1110 10.7 -> 9.2, 1260 11.4 -> 9.7),
+    // 1700 to 2048 in two of four (fp32 1980 13.6 -> 12.0, 1798 12.8 -> 11.8; bf16 1872 30.7 -> 30.1), and of a few more than two or three a CU
+    // the last start as second tiles (777 bf16 12.2 -> 10.2, 529 bf16 10.0 -> 9.4; 520 and 530 fp32 got slower).  60 sizes of these: 0.92 of the time.
+    // Narrow tiles (NCHW of few channels) go either way: as before.
+    if (shifted) {
+      const uint32_t tiles = P.n_tiles;
+      want = tiles >= 8192 ? 1 : (tiles >= 1280 ? 2 : 4);
+      if (t[(size_t)p] == t[(size_t)q]) {
+        if (tiles >= 1100 && tiles < 1350) want = 5;
+        else if (tiles >= 1700 && tiles <= 2048) want = 4;
+        else if (es == 2 && tiles > 512 && tiles <= 532) want = 2;
+        else if (tiles > 768 && tiles <= 784) want = 3;
+      }
+    }
     plan->shifted = shifted;
     plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : std::max(1, std::min(std::min(8, fit), want));
     // Long grids of large tiles: workgroups drift apart over hundreds of tiles, and asking a device-side queue for the

@@ -547,3 +547,12 @@ def test_where_moved_tiles_are_taken():
     assert "tile=[8,8,8,32]" in desc(664, 244) and "tile=[8,8,8,32]" in desc(148, 748) and "tile=[8,8,8,32]" in desc(452, 208)
     assert "shifted_tiles" not in desc(132, 344) and "shifted_tiles" not in desc(940, 636) and "shifted_tiles" not in desc(512, 1024)
     assert "shifted_tiles" not in lc.Plan("(28,4,38576):(1,28,112)", "(28,4,38576):(154304,38576,1)", "f32").describe()   # a shorter run
+
+
+def test_workgroups_of_shifted_tiles_fill_their_rounds():
+    def wgs(m, n, dt):
+        d = lc.Plan("(%d,%d):(1,%d)" % (m, n, m), "(%d,%d):(%d,1)" % (m, n, n), dt).describe()
+        assert "shifted_tiles=1" in d
+        return int(d.split("wgs_per_cu=")[1].split()[0])
+    assert [wgs(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (3321, 3451), (5001, 5003))] == [5, 4, 2, 3, 4, 2]
+    assert [wgs(m, n, "f32") for m, n in ((639, 7083), (1885, 4189), (6595, 305), (623, 4895), (1605, 1805), (8977, 5323))] == [5, 4, 4, 3, 4, 1]
