@@ -78,17 +78,18 @@ __device__ __forceinline__ void lds_barrier() {
 
 // Byte offset of k tile t along an operand's k mode, for operands whose k tiles lie inside the mode's first leaf: stepping
 // to the next tile adds 64 strides of that leaf until the leaf is exhausted; only then is the layout function evaluated again.
-struct KTileOffset {
+template <int BK>   // k extent of a tile
+struct KStepOffset {
   uint32_t bytes, step, left;   // left: k tiles from the current one to the end of the first leaf's run
   __device__ __forceinline__ void seek(const GemmMode& k, uint32_t t) {
-    bytes = 2u * gemm_mode_eval(k, t * kGemmBK);
-    step = 2u * kGemmBK * k.lead_stride;
+    bytes = 2u * gemm_mode_eval(k, t * BK);
+    step = 2u * BK * k.lead_stride;
     if (k.n == 1) {
       left = 0xFFFFFFFFu;
     } else {
       uint32_t q, r;
-      fd_divmod(t * kGemmBK, k.div[0], &q, &r);
-      left = (k.div[0].div - r) / kGemmBK;
+      fd_divmod(t * BK, k.div[0], &q, &r);
+      left = (k.div[0].div - r) / BK;
     }
   }
   __device__ __forceinline__ void next(const GemmMode& k, uint32_t t) {
@@ -96,14 +97,17 @@ struct KTileOffset {
     else bytes += step;
   }
 };
+using KTileOffset = KStepOffset<kGemmBK>;
 
 // One operand's tile of a k tile sent straight from global memory into LDS by WAVES wavefronts together: R instructions of
 // 1 KiB per wavefront (lane t's 16 bytes land at byte 16 t of the KiB).
 // Rows past the operand's extent, and k past K in a short last k tile, present an offset outside the buffer's range: zeros
 // arrive and no access is made.
-template <int BR, int LOAD, int WAVES>
+// BK: k extent of the tile (32: k-major tiles only, a piece of 32 k rows)
+template <int BR, int LOAD, int WAVES, int BK = kGemmBK>
 struct DirectTileLoader {
-  static constexpr int R = BR / 8 / WAVES;
+  static constexpr int R = BR * BK / 512 / WAVES;
+  static_assert(BK == kGemmBK || LOAD == kLoadRDirect, "row-major tiles hold whole rows of 64");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t off[R];       // bytes from the k tile's first k
   uint32_t tail_mask;    // bit i: instruction i of this lane asks for k below K in the last k tile
@@ -113,7 +117,7 @@ struct DirectTileLoader {
                                        uint32_t t) {
     rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, 0xFFFFFFFFu, 0x00020000);
     tail_mask = 0u;
-    const uint32_t k_rem = K - (K - 1u) / kGemmBK * kGemmBK;
+    const uint32_t k_rem = K - (K - 1u) / BK * BK;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       uint32_t row, k, in_k;   // in_k: elements from the k tile's first k

@@ -347,7 +347,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     else if (free_choice && wide_pays) take(wide_m, wide_n, 0, 0);
     else if (direct && free_choice && cost(big) <= (ring_pays ? cost(ring) : cost(*best))) take(256, 256, 0, 0);
     else if (direct && (t_env == 1285 || (free_choice && ring_pays))) take(128, 128, 0, 0);
-    else if (t_env == 128 || t_env == 1282) take(128, 128, 0, 2);
+    else if (t_env == 128 || t_env == 1282 || t_env == 1284) take(128, 128, 0, 2);
     else if (t_env == 12864) take(128, 64, 0, 2);
     else if (t_env == 64128) take(64, 128, 0, 2);
     else if (t_env == 6464) take(64, 64, 0, 2);
@@ -356,6 +356,13 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   else if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
   else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);   // through registers: 256 x 256 when that gives every CU a tile
   else take(128, 128, 0, 0);
+  // The stream kernel's 128 x 128 tiles of two k-major operands over short k loops: pieces of 32 k rows.  Measured on MI355X (us, k tiles of 64 -> this):
+  // 16 x (1000 x 1504 x 776) 85.3 -> 81.8, 20 x 1000^3 86.4 -> 81.0, 22 x (824 x 464 x 1088) 47.7 -> 44.4, 3000^2 x 320 23.5 -> 21.6, 16 x (1536^2 x 128)
+  // 71.4 -> 66.8, 30 x (1300 x 700 x 900) 123.5, 123.7; 4 x (2000^2 x 1184) 63.9 -> 65.2, 6872 x 680 x 1752 33.5 -> 33.8, 4240 x 5248 x 2872 168 -> 181;
+  // 128 x 64 tiles of 824 x 464 x 1088 46.9 -> 51.4; operands along k read half lines (4096^3 150 -> 181).  (LC_TUNE_GEMM_TILE 1284: whatever K is.)
+  if (direct && plan.stages == 2 && plan.split_waves == 0 && plan.tile_m == 128 && plan.tile_n == 128 && P.a_load == kLoadRVec && P.b_load == kLoadRVec &&
+      (t_env == 1284 || (free_choice && K <= 1100)))
+    plan.stages = 4;
   // The split and stream kernels put every batch entry's tiles into one dimension of the grid, which counts lanes in 32 bits; where
   // thin problems in many batch entries have more tiles than that, the tile kernels, whose batch is a dimension of its own, take them
   // (vectors at any alignment element by element).
@@ -370,7 +377,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   P.group_m = (uint32_t)std::max(1, env_int("LC_TUNE_GEMM_GROUP_M", 8));
   // two stages of (rows x 128 bytes) for A and B; direct loads: a ring of five operand tiles
   // (split and stream kernels: rings of pairs of tiles, one per wavefront or one for all)
-  plan.lds_bytes = plan.stages ? (unsigned)(std::max(1, plan.split_waves) * plan.stages * (plan.tile_m + plan.tile_n)) * 128u : direct ? 5u * (unsigned)std::max(plan.tile_m, plan.tile_n) * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
+  plan.lds_bytes = plan.stages ? (unsigned)(std::max(1, plan.split_waves) * plan.stages * (plan.tile_m + plan.tile_n)) * (plan.stages == 4 ? 64u : 128u) : direct ? 5u * (unsigned)std::max(plan.tile_m, plan.tile_n) * 128u : 2u * (unsigned)(plan.tile_m + plan.tile_n) * 128u;
   plan.a_text = mode_text(a_r) + " x " + mode_text(a_k);
   plan.b_text = mode_text(b_r) + " x " + mode_text(b_k);
   plan.c_text = mode_text(c_m) + " x " + mode_text(c_n);

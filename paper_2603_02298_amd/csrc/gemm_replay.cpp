@@ -41,7 +41,7 @@ struct Walker {
   // lanes: how many load a tile together (a workgroup, or one wavefront of the split kernel); zero_rows: lanes past the
   // extent are answered with zeros instead of taking the last row
   void stage(const uint16_t* base, int64_t elems, const GemmMode& rmode, const GemmMode& kmode, int32_t load, uint32_t row0, uint32_t extent,
-             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock, bool zero_rows = false, int32_t direct = 0) {
+             uint32_t BR, uint32_t kt, unsigned char* tile, uint32_t lanes = (uint32_t)kBlock, bool zero_rows = false, int32_t direct = 0, uint32_t bk = (uint32_t)kGemmBK) {
     if (load == kLoadKDirect || load == kLoadKLeaves) {
       // every lane's 16 bytes land at byte 16 * lane of the 1 KiB its wavefront's instruction i fills
       const uint32_t rows_per_lane = BR * 8u / lanes;
@@ -65,22 +65,22 @@ struct Walker {
     }
     if (load == kLoadRDirect) {
       // k-major tile: lane l of instruction i of wavefront w fills 16-byte unit (w R + i) 64 + l
-      const uint32_t rows_per_lane = BR * 8u / lanes;
+      const uint32_t rows_per_lane = BR * bk / 8u / lanes;   // (bk: 64, or pieces of 32 k rows)
       for (uint32_t tid = 0; tid < lanes; ++tid)
         for (uint32_t i = 0; i < rows_per_lane; ++i) {
           uint32_t k, row;
           gemm_rdirect_unit(BR, rows_per_lane, tid, i, &k, &row);
           const int64_t off = (int64_t)gemm_mode_eval(rmode, gemm_clamp_row(load, row0 + row, extent)) + (int64_t)k * kmode.lead_stride +
-                              gemm_mode_eval(kmode, kt * kGemmBK);
+                              gemm_mode_eval(kmode, kt * bk);
           const uint32_t lds_at = ((tid >> 6) * rows_per_lane + i) * 1024u + (tid & 63u) * 16u;
-          if (k >= (uint32_t)kGemmBK || row + 8 > BR || lds_at != gemm_rdirect_lds_offset(BR, k, row)) { ok = false; return; }
-          if (kt * kGemmBK + k >= P.K || (zero_rows && row0 + row >= extent)) {   // past K in a short last k tile: zeros arrive
+          if (k >= bk || row + 8 > BR || lds_at != gemm_rdirect_lds_offset(BR, k, row)) { ok = false; return; }
+          if (kt * bk + k >= P.K || (zero_rows && row0 + row >= extent)) {   // past K in a short last k tile: zeros arrive
             std::memset(tile + lds_at, 0, 16);
             continue;
           }
           // the k row's offset is what the k mode's layout function gives, and the slot is the one fragment reads expect
           if (off % 8 != 0 || off + 8 > elems ||
-              (int64_t)k * kmode.lead_stride + gemm_mode_eval(kmode, kt * kGemmBK) != (int64_t)gemm_mode_eval(kmode, kt * kGemmBK + k)) {
+              (int64_t)k * kmode.lead_stride + gemm_mode_eval(kmode, kt * bk) != (int64_t)gemm_mode_eval(kmode, kt * bk + k)) {
             ok = false;
             return;
           }
@@ -263,7 +263,9 @@ lc_status_t replay_sums(const lc_gemm_plan& plan, Walker& w, FragmentProduct& pr
   const bool split = plan.split_waves > 0;
   const uint32_t W = split ? (uint32_t)plan.split_waves : 1u, lanes = split ? 64u : (uint32_t)kBlock, QM = split ? TM : TM / 2u, QN = split ? TN : TN / 2u;
   const int32_t a_kind = gemm_effective_load(P.a_load, P.a_direct), b_kind = gemm_effective_load(P.b_load, P.b_direct);
-  if (plan.stages < 1 || TM * TN * 4u > plan.lds_bytes || plan.lds_bytes != W * (unsigned)plan.stages * (TM + TN) * 128u || !P.a_direct || !P.b_direct) return LC_ERR_INVALID_ARG;
+  const bool pieces = !split && plan.stages == 4;   // k tiles of 32
+  const uint32_t bk = pieces ? 32u : (uint32_t)kGemmBK, k_steps = pieces ? (P.K + 31u) / 32u : P.k_tiles;
+  if (plan.stages < 1 || TM * TN * 4u > plan.lds_bytes || plan.lds_bytes != W * (unsigned)plan.stages * (TM + TN) * (pieces ? 64u : 128u) || (pieces && (a_kind != kLoadRDirect || b_kind != kLoadRDirect)) || !P.a_direct || !P.b_direct) return LC_ERR_INVALID_ARG;
   const uint32_t per_batch = P.tiles_m * P.tiles_n, n_tiles = per_batch * P.L;
   std::vector<unsigned char> lds((TM + TN) * 128u);
   std::vector<float> acc((size_t)TM * TN), parts((size_t)W * units * 4u);
@@ -286,11 +288,11 @@ lc_status_t replay_sums(const lc_gemm_plan& plan, Walker& w, FragmentProduct& pr
     const int64_t c_elems = c_all_elems - co;
     for (uint32_t wave = 0; wave < W; ++wave) {
       std::fill(acc.begin(), acc.end(), 0.f);
-      for (uint32_t kt = wave; kt < P.k_tiles; kt += W) {
-        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), lanes, true, P.a_direct);
-        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, lanes, true, P.b_direct);
+      for (uint32_t kt = wave; kt < k_steps; kt += W) {
+        w.stage(w.A, w.a_elems, P.a_r, P.a_k, a_kind, m0, P.M, TM, kt, lds.data(), lanes, true, P.a_direct, bk);
+        w.stage(w.B, w.b_elems, P.b_r, P.b_k, b_kind, n0, P.N, TN, kt, lds.data() + TM * 128u, lanes, true, P.b_direct, bk);
         if (!w.ok) return LC_ERR_INVALID_ARG;
-        for (uint32_t kk = 0; kk < kGemmBK / 16; ++kk)
+        for (uint32_t kk = 0; kk < bk / 16; ++kk)
           for (uint32_t i = 0; i < TM / 32; ++i)
             for (uint32_t j = 0; j < (TN + 31) / 32; ++j)
               if (!product.run(w, lds.data(), a_kind, TM, 32u * i, lds.data() + TM * 128u, b_kind, TN, 32u * j, kk, acc.data())) return LC_ERR_INVALID_ARG;

@@ -9,7 +9,7 @@
 // What bounds it: for a short k loop C's way from and to HBM (128 x 100352 x 64: 5.4-6.3 TB/s), for a longer one the waits: for
 // a k tile asked for one k tile before, for C's old values ahead of the first, at the barrier (16 x (1000 x 1504 x 776): wavefronts wait
 // half of their time, matrix cores are busy 19 % of the clocks, LDS 12 %).
-// Measured on MI355X (bf16, whole ring kernel of 128 x 128 tiles -> this kernel's 128 x 128): 16 x (1000 x 1504 x 776) 100 -> 83 us,
+// Measured on MI355X (bf16, whole ring kernel of 128 x 128 tiles -> this kernel's 128 x 128): 16 x (1000 x 1504 x 776) 100 -> 83 us (in pieces of 32 k rows 82),
 // a 3 x 3 convolution of 128 x 100352 x 576 39 -> 34 us (128 x 64 tiles: 32.6), 4096^3 158 -> 149 us.  Three stages and more
 // (fewer workgroups per CU) measured slower wherever there are more tiles than CUs, and gained 0-7 % where there are not; so did
 // 256 x 128 tiles of eight wavefronts (the batched problem 82, but 4 x 1024^3 16.5 -> 21.5) and old values of C asked for two
@@ -26,8 +26,11 @@
 namespace lc {
 
 constexpr int kStreamStages = 2;   // pairs of operand tiles in LDS: one being multiplied, one on its way
+constexpr int kStreamPieces = 4;   // the same LDS as pairs of 32 k rows: one being multiplied, three on their way
 
-template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC>
+// PIECES (both operands k-major): k tiles of 32, four pairs in the LDS of two of 64.  The first products start after half as much and three pieces
+// are under way, at the price of a barrier every 32 k: better over short k loops, worse over long ones (the rule has the figures).
+template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC, bool PIECES = false>
 __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 128)) void gemm_stream_kernel(GemmParams P, const uint16_t* __restrict__ A,
                                                                                                    const uint16_t* __restrict__ B, float* __restrict__ C) {
   constexpr int FM = BM / 64, FN = BN / 64, KSTEPS = kGemmBK / 16;
@@ -53,8 +56,9 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
   B += gemm_mode_eval(P.b_l, batch);
   C += gemm_mode_eval(P.c_l, batch);
 
-  TileLoader<BM, A_LOAD, 4> la;
-  TileLoader<BN, B_LOAD, 4> lb;
+  static_assert(!PIECES || (A_LOAD == kLoadRDirect && B_LOAD == kLoadRDirect), "pieces of k rows: k-major tiles");
+  std::conditional_t<PIECES, DirectTileLoader<BM, kLoadRDirect, 4, 32>, TileLoader<BM, A_LOAD, 4>> la;
+  std::conditional_t<PIECES, DirectTileLoader<BN, kLoadRDirect, 4, 32>, TileLoader<BN, B_LOAD, 4>> lb;
   SumUnits<BM, BN, kBlock, C_VEC> units;
   // (element by element, or with k tiles on their way through registers, the old values would not leave the products the
   // registers they need: asked for at the end then)
@@ -105,6 +109,45 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
         }
       }
       multiply(lds + (t & 1u) * STAGE);
+    }
+  } else if constexpr (PIECES) {
+    constexpr uint32_t PIECE = (BM + BN) * 64u;
+    constexpr int LOADS = BM * 32 / 512 / 4 + BN * 32 / 512 / 4, N = (kStreamPieces - 2) * LOADS;   // per piece; of the pieces behind the one that is waited for
+    const uint32_t pieces = (P.K + 31u) / 32u;
+    KStepOffset<32> ka, kb;   // of the next piece to request
+    ka.seek(P.a_k, 0u);
+    kb.seek(P.b_k, 0u);
+    uint32_t asked = 0;
+    auto request = [&]() {
+      const bool tail = asked + 1u == pieces;
+      const uint32_t at = (asked % kStreamPieces) * PIECE;
+      la.fetch(ka.bytes, at + wave * (BM * 16u), tail);
+      lb.fetch(kb.bytes, at + BM * 64u + wave * (BN * 16u), tail);
+      ++asked;
+      if (asked < pieces) {
+        ka.next(P.a_k, asked);
+        kb.next(P.b_k, asked);
+      }
+    };
+    static_for<kStreamPieces - 1>([&](auto) {
+      if (asked < pieces) request();
+    });
+    for (uint32_t t = 0; t < pieces; ++t) {
+      // piece t has landed for every wavefront past the barrier, which also has its fragments of piece t - 1 in registers: that place may be
+      // filled again
+      if (t + kStreamPieces - 1u <= pieces) __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+      lds_barrier();
+      if (asked < pieces) request();
+      const unsigned char* piece = lds + (t % kStreamPieces) * PIECE;
+      static_for<2>([&](auto kk) {
+        u32x4 af[FM], bf[FN];
+        static_for<FM>([&](auto i) { af[i] = direct_fragment<BM, A_LOAD>(piece, lane, wm * (BM / 2) + 32u * (uint32_t)i, kk); });
+        static_for<FN>([&](auto j) { bf[j] = direct_fragment<BN, B_LOAD>(piece + BM * 64u, lane, wn * (BN / 2) + 32u * (uint32_t)j, kk); });
+        static_for<FM>([&](auto i) {
+          static_for<FN>([&](auto j) { acc[i][j] = mfma_32x32x16<BF16>(af[i], bf[j], acc[i][j]); });
+        });
+      });
     }
   } else {
     KTileOffset ka, kb;   // of the next k tile to request
@@ -157,22 +200,27 @@ __global__ __launch_bounds__(kBlock, 160 * 1024 / (kStreamStages * (BM + BN) * 1
   units.add(P, C, m0, n0, tid, [&](uint32_t unit) { return *reinterpret_cast<const f32x4*>(lds + unit * 16u); });
 }
 
-template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC>
+template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD, bool C_VEC, bool PIECES = false>
 static inline hipError_t launch_stream_abc(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
   if (plan.lds_bytes != (unsigned)(kStreamStages * (BM + BN) * 128)) return hipErrorInvalidValue;
   static std::atomic<bool> raised{false};   // one flag per instantiation: the attribute belongs to the kernel function
   if (plan.lds_bytes > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC, PIECES>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     raised.store(true, std::memory_order_release);
   }
   const unsigned grid = plan.params.tiles_m * plan.params.tiles_n * plan.params.L;
-  hipLaunchKernelGGL((gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC>), dim3(grid), dim3(kBlock), plan.lds_bytes, s, plan.params, a, b, c);
+  hipLaunchKernelGGL((gemm_stream_kernel<BF16, BM, BN, A_LOAD, B_LOAD, C_VEC, PIECES>), dim3(grid), dim3(kBlock), plan.lds_bytes, s, plan.params, a, b, c);
   return hipSuccess;
 }
 template <bool BF16, int BM, int BN, int A_LOAD, int B_LOAD>
 static inline hipError_t launch_stream_ab(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
+  if constexpr (BM == 128 && BN == 128 && A_LOAD == kLoadRDirect && B_LOAD == kLoadRDirect)
+    if (plan.stages == kStreamPieces)
+      return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, true, true>(plan, a, b, c, s)
+                               : launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, false, true>(plan, a, b, c, s);
+  if (plan.stages != kStreamStages) return hipErrorInvalidValue;
   return plan.params.c_vec ? launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, true>(plan, a, b, c, s)
                            : launch_stream_abc<BF16, BM, BN, A_LOAD, B_LOAD, false>(plan, a, b, c, s);
 }
@@ -189,7 +237,6 @@ static inline hipError_t launch_stream(const lc_gemm_plan& plan, const uint16_t*
 }
 template <bool BF16, int K_LOAD, int R_LOAD>
 static inline hipError_t launch_stream_shape(const lc_gemm_plan& plan, const uint16_t* a, const uint16_t* b, float* c, hipStream_t s) {
-  if (plan.stages != kStreamStages) return hipErrorInvalidValue;
   if (plan.tile_m == 128 && plan.tile_n == 128) return launch_stream<BF16, 128, 128, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (plan.tile_m == 128 && plan.tile_n == 64) return launch_stream<BF16, 128, 64, K_LOAD, R_LOAD>(plan, a, b, c, s);
   if (plan.tile_m == 64 && plan.tile_n == 128) return launch_stream<BF16, 64, 128, K_LOAD, R_LOAD>(plan, a, b, c, s);

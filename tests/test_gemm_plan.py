@@ -514,3 +514,14 @@ def test_where_wide_tiles_are_taken():
     assert tile("nt", 3368, 5336, 6576) == "256x192" and tile("tt", 1872, 5312, 2008) == "192x256" and tile("tn", 2600, 4112, 880) == "192x256" and tile("tt", 5656, 2968, 8048) == "256x192"
     assert tile("tt", 1872, 5312, 760) == "128x64" and tile("nt", 5984, 6072, 960) == "128x128" and tile("tt", 1816, 5256, 5080) == "192x256" and tile("tt", 8192, 8192, 8192) == "256x256" and tile("nn", 4376, 4376, 4808) == "256x192"
     assert tile("tt", 3370, 5336, 6576) not in ("256x192", "192x256")   # C without vectors
+
+
+def test_walk_pieces_of_32_k_rows(oracle):
+    # one to eleven pieces through four places in LDS, short last ones, ragged rows and columns, batches
+    for name, sizes in [("nt", (200, 136, K)) for K in (8, 24, 32, 40, 64, 72, 96, 104, 136, 328)] + [("nt", (128, 264, 200))]:
+        _walk_and_compare(oracle, W.gemm_workload(name, *sizes, values="ints"), {"LC_TUNE_GEMM_TILE": 1284}, ["tile=128x128x64 stream stages=4", "lds_bytes=65536"])
+    def stages(form, M, N, K, L):
+        a = "(%d,%d,%d):" % (M, K, L) + ("(%d,1,%d)" % (K, M * K) if form[0] == "t" else "(1,%d,%d)" % (M, M * K))
+        b = "(%d,%d,%d):" % (N, K, L) + ("(%d,1,%d)" % (K, N * K) if form[1] == "t" else "(1,%d,%d)" % (N, N * K))
+        return lc.GemmPlan(a, b, "(%d,%d,%d):(1,%d,%d)" % (M, N, L, M, M * N)).describe()
+    assert [" stream stages=4 " in stages(f, 1000, 1504, K, 16) for f, K in (("nn", 776), ("nn", 1096), ("nn", 1104), ("tt", 776), ("tn", 776))] == [True, True, False, False, False]

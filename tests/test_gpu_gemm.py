@@ -340,3 +340,14 @@ def test_gemm_wide_tiles(oracle, tile, values):
         w = (W.batched_gemm_workload if len(sizes) == 4 else W.gemm_workload)(name, *sizes, ab_dtype=("bf16", "f16")[n % 2], values=values)
         desc = _parity(oracle, w, {"LC_TUNE_GEMM_TILE": tile})
         assert "tile=%dx%dx64 tiles" % (tile // 1000, tile % 1000) in desc and desc.count("direct-to-LDS") == 2, desc
+
+
+@pytest.mark.parametrize("values", ["ints", "normal"])
+def test_gemm_pieces_of_32_k_rows(oracle, values):
+    # k-major operands in k tiles of 32 through four places in LDS: every number of pieces around the ring, short last ones, both types
+    for n, K in enumerate((8, 24, 32, 40, 64, 96, 104, 128, 136, 160, 328, 512)):
+        w = W.gemm_workload("nt", 200, 136, K, ab_dtype=("bf16", "f16")[n % 2], values=values)
+        for env in ({}, {"LC_TUNE_GEMM_CVEC": 0}):
+            assert " stream stages=4" in _parity(oracle, w, dict(env, LC_TUNE_GEMM_TILE=1284))
+    w = W.batched_gemm_workload("folded_batch", 33, 20, 9, 6, values=values)
+    _parity(oracle, w)
