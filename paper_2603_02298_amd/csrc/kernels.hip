@@ -1207,7 +1207,8 @@ static lc_status_t execute_with(const lc_plan& plan, const void* src, void* dst,
       }
     }
   } else {
-    unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(plan.transpose.n_tiles, plan.grid_override > 0 ? (uint64_t)plan.grid_override : (uint64_t)cus * plan.wgs_per_cu));
+    const int wgs = plan.wgs_fit > 0 && cus != kPlannedCus ? shifted_wgs_per_cu(plan.transpose.n_tiles, cus, plan.wgs_fit) : plan.wgs_per_cu;
+    unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(plan.transpose.n_tiles, plan.grid_override > 0 ? (uint64_t)plan.grid_override : (uint64_t)cus * wgs));
     const int key = plan.tile_elem_bytes * 100 + plan.V;
     if (plan.shifted) {
       if (key == 404) pre = launch_shifted<4, 4>(plan, src, dst, grid, s);

@@ -304,6 +304,38 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
   }
 }
 
+// Workgroups a CU for the persistent grid of shifted tiles (16 or 32 KiB; `fit` of them in a CU's LDS).  A grid of more tiles than
+// workgroups goes in rounds.  A full round of w a CU takes w tile times, 2 % more for each that shares the CU from the third on.  A last round
+// that is not full takes as long as its own tiles do, but no less than 3.3 tile times (from a tile's first load to its last store)
+// or than a full round; one of a twentieth of a round or less starts beside the round before it (two of 16 KiB leave it too little to
+// start beside).  Every round takes a tenth of a tile time by itself.  The number whose rounds cost least is taken.
+// Measured on MI355X with two to five a CU over 2104 copies of 257 tiles and more (transposes of odd sides, NCHW -> NHWC, relayouts and permutes in
+// moved tiles; both widths), time over the best of the four on average: by this rule 1.015, with four up to 1280 tiles and two from there on 1.026.  Some
+// of the ranges, two, three, four and five a CU: 539 to 640 tiles 1.20, 1.00, 1.00, 1.00; 769 to 806 1.17, 1.01, 1.06, 1.06; 1076 to 1150 1.08, 1.11, 1.14,
+// 1.00; 1151 to 1280 1.09, 1.08, 1.22, 1.02; 1345 to 1536 1.01, 1.02, 1.15, 1.18; 1793 to 2048 1.02, 1.08, 1.01, 1.11; 2049 to 2304 1.04, 1.01, 1.10, 1.05.
+// From ten tiles a CU on the rounds no longer tell: two; from 32 on one, whose next tile's loads run under the stores of the one before with
+// nothing between (15876 fp32 tiles 118 us, 143 with two).
+int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit) {
+  const double per_cu = (double)tiles / cus;
+  if (per_cu >= 32.0) return 1;
+  if (per_cu >= 10.0) return std::min(2, fit);
+  double best = 0.0;
+  int best_w = 1;
+  for (int w : {2, 4, 5, 3}) {   // (ties: the first)
+    if (w > fit) continue;
+    const int64_t full = (int64_t)tiles / ((int64_t)w * cus);
+    const double rest = per_cu - (double)(full * w), pace = 1.0 + 0.02 * (w - 2);
+    const bool beside = full > 0 && rest <= 0.05 * w && (w > 2 || fit <= 5);
+    const double last = beside ? rest * pace : std::max(std::min(3.3, w * pace), rest * pace);
+    const double cost = (double)full * w * pace + (rest > 0.0 ? last + 0.1 : 0.0) + 0.1 * (double)full;
+    if (best_w == 1 || cost < best - 1e-9) {
+      best = cost;
+      best_w = w;
+    }
+  }
+  return best_w;
+}
+
 // Tiles a copy over joint modes J (extents and strides in units of `es` bytes) for the transposing
 // kernel with V x V micro-tiles; p / q are the modes the micro-tile extends along on the source /
 // destination side.  Fills the plan and returns true, or leaves the class undecided.
@@ -713,25 +745,10 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
       if (P.n_ragged > 0) want = 4;
       else want = middle && P.n_tiles >= 1792 ? 3 : plan->lds_bytes >= 32 * 1024 && P.n_tiles >= 8192 ? 2 : 4;
     }
-    // shifted tiles (32 or 16 KiB): one workgroup per CU on long grids, two and four on shorter ones (15876 fp32 tiles 118 us
-    // against 143 with two; 1024 bf16 tiles 15.7, 12.8 and 12.7; 960 fp32 tiles 8.3, 7.6 and 7.0)
-    // -- but a grid whose last round is nearly empty, or that gives a few CUs one tile more than the rest, waits for those.  Square tiles: 1100 to 1350
-    // go in one round of five a CU or close to it (bf16 1128 18.1 -> 14.1, 1206 20.6 -> 17.1, 1300 12.9 -> 11.9; fp32 1110 10.7 -> 9.2, 1260 11.4 -> 9.7),
-    // 1700 to 2048 in two of four (fp32 1980 13.6 -> 12.0, 1798 12.8 -> 11.8; bf16 1872 30.7 -> 30.1), and of a few more than two or three a CU
-    // the last start as second tiles (777 bf16 12.2 -> 10.2, 529 bf16 10.0 -> 9.4; 520 and 530 fp32 got slower).  60 sizes of these: 0.92 of the time.
-    // Narrow tiles (NCHW of few channels) go either way: as before.
-    if (shifted) {
-      const uint32_t tiles = P.n_tiles;
-      want = tiles >= 8192 ? 1 : (tiles >= 1280 ? 2 : 4);
-      if (t[(size_t)p] == t[(size_t)q]) {
-        if (tiles >= 1100 && tiles < 1350) want = 5;
-        else if (tiles >= 1700 && tiles <= 2048) want = 4;
-        else if (es == 2 && tiles > 512 && tiles <= 532) want = 2;
-        else if (tiles > 768 && tiles <= 784) want = 3;
-      }
-    }
+    if (shifted) want = shifted_wgs_per_cu(P.n_tiles, kPlannedCus, fit);
     plan->shifted = shifted;
     plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : std::max(1, std::min(std::min(8, fit), want));
+    plan->wgs_fit = shifted && tune.wgs_per_cu <= 0 ? fit : 0;
     // Long grids of large tiles: workgroups drift apart over hundreds of tiles, and asking a device-side queue for the
     // next tiles (one request ahead) evens that out.  Measured on MI355X: one request per 64 KiB of tile data is best
     // (64 KiB tiles one at a time: 71 -> 79 % of the HBM peak; 32 KiB tiles two at a time: 73 -> 81 %, one at a time 65 %:

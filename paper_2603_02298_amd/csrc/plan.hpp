@@ -43,6 +43,9 @@ struct Tuning {
 };
 Tuning tuning_from_env();
 
+constexpr int kPlannedCus = 256;   // plans are made without a device: MI355X, unpartitioned
+int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit);
+
 }  // namespace lc
 
 struct lc_plan {
@@ -96,6 +99,7 @@ struct lc_plan {
   int64_t workspace_bias = 0;              // the record of destination offset o is word o + workspace_bias (negative strides reach below 0)
 
   int wgs_per_cu = 0;
+  int wgs_fit = 0;                         // > 0: shifted tiles; wgs_per_cu came from shifted_wgs_per_cu for kPlannedCus and is asked again on a card with another number
   int grid_override = 0;                   // > 0: workgroups of the launch, whatever the CU count
   int tile_queue = 0;                      // transposing class: tiles past the first rounds of the grid are handed out on request, this many at a time
   int queue_static_rounds = 1;             // ... whole rounds of the grid that go by workgroup index first

@@ -550,9 +550,23 @@ def test_where_moved_tiles_are_taken():
 
 
 def test_workgroups_of_shifted_tiles_fill_their_rounds():
-    def wgs(m, n, dt):
-        d = lc.Plan("(%d,%d):(1,%d)" % (m, n, m), "(%d,%d):(%d,1)" % (m, n, n), dt).describe()
+    def wgs(src, dst, dt):
+        d = lc.Plan(src, dst, dt).describe()
         assert "shifted_tiles=1" in d
-        return int(d.split("wgs_per_cu=")[1].split()[0])
-    assert [wgs(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (3321, 3451), (5001, 5003))] == [5, 4, 2, 3, 4, 2]
-    assert [wgs(m, n, "f32") for m, n in ((639, 7083), (1885, 4189), (6595, 305), (623, 4895), (1605, 1805), (8977, 5323))] == [5, 4, 4, 3, 4, 1]
+        return int(d.split(" tiles=")[1].split()[0]), int(d.split("wgs_per_cu=")[1].split()[0])
+    def transpose(m, n, dt):
+        return wgs("(%d,%d):(1,%d)" % (m, n, m), "(%d,%d):(%d,1)" % (m, n, n), dt)
+    def nchw(n, c, side, dt):
+        hw = side * side
+        return wgs("(%d,%d,%d):(%d,%d,1)" % (n, c, hw, c * hw, hw), "(%d,%d,%d):(%d,1,%d)" % (n, c, hw, hw * c, c), dt)
+    # up to five tiles a CU (256 of them): one round, or a last one that is worth its time or has so few tiles that they start beside
+    # the round before it
+    for tiles, w in [transpose(m, n, "bf16") for m, n in ((5967, 3033), (2821, 2883), (5169, 2367), (3321, 3451), (411, 34767), (1501, 9003))] + \
+                    [transpose(m, n, "f32") for m, n in ((639, 7083), (6595, 305), (623, 4895), (1605, 1805), (2201, 1901))] + \
+                    [nchw(15, 24, 95, "f32"), nchw(23, 52, 55, "f32"), nchw(47, 24, 109, "bf16"), nchw(14, 40, 149, "bf16"), nchw(60, 84, 23, "f32")]:
+        assert 256 < tiles <= 1280 and 2 <= w <= 5
+        full, rest = divmod(tiles, 256 * w)
+        assert full == 0 or rest <= 256 * w // 20 or rest >= 128 * w, (tiles, w)
+    # far from every edge: one round of five, two of four, the last few tiles beside the round before them, long grids
+    assert [transpose(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (6469, 7521))] == [(1128, 5), (1872, 4), (529, 2), (779, 3), (3009, 2)]
+    assert [transpose(m, n, "f32") for m, n in ((639, 7083), (1885, 4189), (8977, 5323))] == [(1110, 5), (1980, 4), (11844, 1)]
