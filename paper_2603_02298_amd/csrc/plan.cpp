@@ -305,12 +305,12 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
 }
 
 // Workgroups a CU for the persistent grid of shifted tiles (16 or 32 KiB; `fit` of them in a CU's LDS).  A grid of more tiles than
-// workgroups goes in rounds.  A full round of w a CU takes w tile times, 2 % more for each that shares the CU from the third on.  A last round
-// that is not full takes as long as its own tiles do, but no less than 3.3 tile times (from a tile's first load to its last store)
+// workgroups goes in rounds.  A full round of w a CU takes w tile times, 2 % more with three or four sharing it, 6 % with five.  A last round
+// that is not full takes as long as its own tiles do, but no less than four tile times (from a tile's first load to its last store)
 // or than a full round; one of a twentieth of a round or less starts beside the round before it (not beside two of 16 KiB, nor behind
 // several rounds of two).  Any other round takes a tenth of a tile time by itself.  The number whose rounds cost least is taken.
 // Measured on MI355X with two to five a CU over 2104 copies of 257 tiles and more (transposes of odd sides, NCHW -> NHWC, relayouts and permutes in
-// moved tiles; both widths), time over the best of the four on average: by this rule 1.015, with four up to 1280 tiles and two from there on 1.026.  Some
+// moved tiles; both widths), time over the best of the four on average: by this rule 1.014, with four up to 1280 tiles and two from there on 1.026.  Some
 // of the ranges, two, three, four and five a CU: 539 to 640 tiles 1.20, 1.00, 1.00, 1.00; 769 to 806 1.17, 1.01, 1.06, 1.06; 1076 to 1150 1.08, 1.11, 1.14,
 // 1.00; 1151 to 1280 1.09, 1.08, 1.22, 1.02; 1345 to 1536 1.01, 1.02, 1.15, 1.18; 1793 to 2048 1.02, 1.08, 1.01, 1.11; 2049 to 2304 1.04, 1.01, 1.10, 1.05.
 // From ten tiles a CU on the rounds no longer tell: two; from 32 on one, whose next tile's loads run under the stores of the one before with
@@ -324,9 +324,9 @@ int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit) {
   for (int w : {2, 4, 5, 3}) {   // (ties: the first)
     if (w > fit) continue;
     const int64_t full = (int64_t)tiles / ((int64_t)w * cus);
-    const double rest = per_cu - (double)(full * w), pace = 1.0 + 0.02 * (w - 2);
+    const double rest = per_cu - (double)(full * w), pace = w == 2 ? 1.0 : w == 5 ? 1.06 : 1.02;
     const bool beside = full > 0 && rest <= 0.05 * w && (w > 2 || (fit <= 5 && full == 1));
-    const double last = rest <= 0.0 ? 0.0 : beside ? rest * pace : 0.1 + std::max(std::min(3.3, w * pace), rest * pace);
+    const double last = rest <= 0.0 ? 0.0 : beside ? rest * pace : 0.1 + std::max(std::min(4.0, w * pace), rest * pace);
     const double cost = (double)full * (w * pace + 0.1) + last;
     if (best_w == 1 || cost < best - 1e-9) {
       best = cost;

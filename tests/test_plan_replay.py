@@ -569,5 +569,5 @@ def test_workgroups_of_shifted_tiles_fill_their_rounds():
         assert full == 0 or rest <= 256 * w // 20 or rest >= 128 * w, (tiles, w)
     # far from every edge: one round of five, two of four, the last few tiles beside the round before them, long grids
     assert [transpose(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (6469, 7521))] == [(1128, 5), (1872, 4), (529, 2), (779, 3), (3009, 2)]
-    assert [transpose(m, n, "bf16") for m, n in ((7817, 2151), (5191, 3161))] == [(1054, 4), (1025, 4)]   # a few more than one round of four
+    assert [transpose(m, n, "bf16") for m, n in ((7817, 2151), (5191, 3161))] == [(1054, 4), (1025, 4)] and transpose(2041, 8177, "bf16") == (1024, 4)   # one round of four, and a few more
     assert [transpose(m, n, "f32") for m, n in ((639, 7083), (1885, 4189), (8977, 5323))] == [(1110, 5), (1980, 4), (11844, 1)]
