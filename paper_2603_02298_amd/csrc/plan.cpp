@@ -1087,30 +1087,41 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
     };
     // Tiles of three modes and more, where a mode beside p and q has an extent with few small factors: moved tiles cut it
     // anywhere and keep whole workgroups and balanced runs.  In place of ragged tiles, of whole tiles that leave most lanes idle and of
-    // shifted tiles with a shorter run; within 1.15 times the elements.  Measured on MI355X over 120 copies of 2^19 to 2^26 elements whose plan
-    // they change (random extents and orders, 0.77 of the time on average) and 60 relayouts of 8 x 8 blocks, us, before -> with them:
-    //   whole tiles of up to 96 lanes: relayout 664 x 244 15.8 -> 8.6, 492 x 668 22.9 -> 16.5, 464 x 508 14.6 -> 11.4; 20 lanes fp32 (4,179,4,22340) 554 -> 93;
-    //     but 72 x 484 4.6 -> 4.9 and 132 x 344 4.8 -> 5.0 (48 lanes, below 3 * 2^20 elements), 144 x 236 4.2 -> 4.4; beyond 96 lanes 484 x 672 17.9 -> 16.6,
-    //     472 x 820 20.7 -> 20.9, 940 x 636 32.3 -> 34.2;
-    //   ragged tiles: relayout 148 x 748 11.6 -> 7.7, 92 x 776 8.9 -> 6.0; full fp32 ones from 5 * 2^20 elements on (7.5M 17.2 -> 12.4, 5.3M
-    //     14.9 -> 10.1; 4.4M 9.3 -> 10.5, 4.7M 11.3 -> 12.4); not bf16 ones of the same extents on long grids, where the ragged kernel has five
-    //     workgroups a CU ((8,64,8,10886) 34 -> 44, (16,151,8,1713) 33.9 -> 32.5; shorter ones 24.1 -> 21.0), nor those of more than 512 lanes
-    //     (fp32 96 x 2316 x 116 51 -> 55, (16,112,8,1213) 33 -> 35);
+    // shifted tiles with a shorter run; within 1.15 times the elements.  Measured on MI355X over 1400 copies of 2^19 to 2^26 elements (700 relayouts of
+    // 8 x 8 blocks, 700 of random extents and orders; moved over before: 0.77 of the time on average where the rule takes them), us, before -> with them:
+    //   whole tiles of up to 56 lanes: 0.69 of the time; relayout 664 x 244 15.8 -> 8.6; 20 lanes fp32 (4,179,4,22340) 554 -> 93; but 72 x 484 4.6 -> 4.9 and
+    //     132 x 344 4.8 -> 5.0 (48 lanes, below 3 * 2^20 elements), 144 x 236 4.2 -> 4.4, and not 56 lanes that go in one round of four a CU (392 x 132,
+    //     924 tiles, 4.4 -> 5.3; 476 x 124, 1054 tiles, 6.2 -> 5.5);
+    //   of 57 to 96 lanes, bf16: up to three moved tiles a CU 0.90 (464 x 508 before 14.6 -> 11.4), from there on their rounds cost more than the idle
+    //     lanes: 1.05 (312 x 636 12.3 -> 14.4, 424 x 612 15.2 -> 19.1, 848 x 772 34.6 -> 37.7); still taken for runs of 1 KiB and more (12 copies, 0.83) and in
+    //     place of whole tiles whose shorter run is one line and a part of one, or less (15 copies, 0.89);
+    //     fp32 0.76 on long grids too; beyond 96 lanes 484 x 672 17.9 -> 16.6, 940 x 636 32.3 -> 34.2;
+    //   ragged tiles: relayout 148 x 748 11.6 -> 7.7, 92 x 776 8.9 -> 6.0, also where fewer than 256 moved ones are left (relayout ones 0.87 over 170 copies;
+    //     worst 1.08); ragged tiles of the same extents run five (bf16) or eight (fp32) workgroups a CU: not bf16 ones (0.997), fp32
+    //     ones below six a CU (0.92) and from twelve on (0.85), not between (1.05) and not below 5 * 2^20 elements (4.4M 9.3 -> 10.5); nor
+    //     those of more than 512 lanes (fp32 96 x 2316 x 116 51 -> 55, (16,112,8,1213) 33 -> 35);
     //   not where the shorter run falls below 256 bytes for it (28 x 4 x 38576 fp32, 224 -> 64 bytes, 10.6 -> 14.1);
-    //   shifted tiles with runs shorter than a line: bf16 (166,8,64,719) 146 -> 61, (225,8,14864) 42 -> 28; but of 128 bytes (168,3048,8,8) 29 -> 33.
+    //   shifted tiles with runs shorter than a line: bf16 (166,8,64,719) 146 -> 61, (225,8,14864) 42 -> 28; but of 128 bytes (168,3048,8,8) 29 -> 33; fp32 runs
+    //     of 64 bytes only on the source's side, or on grids of 16 a CU and more (on the destination's side, whose half lines the L2 joins,
+    //     (8,74,1948) 4.6 -> 5.1, (4,1163,4,156) 6.6 -> 7.3).
     lc_plan moved = *plan;
     auto moved_pays = [&](bool in_place_of_plain) {
       if (!may_shift || tune.moved == 0 || V * es != 16 || nj < 3 || !plan_shifted(&moved, Tiling::Moved) || covered(moved) > 1.15 * (double)n) return false;
       const int64_t run = std::min(plan->src_run_bytes, plan->dst_run_bytes), moved_run = std::min(moved.src_run_bytes, moved.dst_run_bytes);
-      if (!in_place_of_plain) return run < 128 && moved_run > run;
+      const uint32_t tiles = moved.transpose.n_tiles;
+      if (!in_place_of_plain) return run < 128 && moved_run > run && (es == 2 || run < 64 || plan->src_run_bytes == run || tiles >= 16u * kPlannedCus);
       if (moved_run < std::min<int64_t>(run, 256)) return false;
       const uint32_t lanes = plan->transpose.n_micro;
       if (plan->transpose.n_ragged > 0) {
         if (lanes > 2u * kBlock) return false;
-        if (es == 2) return plan->tile_extent != moved.tile_extent || moved.transpose.n_tiles < 1280u;
-        return lanes < 224u || n >= (5 << 20);
+        const bool same = plan->tile_extent == moved.tile_extent;
+        if (es == 2) return !same;
+        return lanes < 224u || (n >= (5 << 20) && (!same || tiles < 6u * kPlannedCus || tiles >= 12u * kPlannedCus));
       }
-      return lanes <= 96u && n >= (lanes <= 32u ? 2 << 20 : lanes <= 56u ? 3 << 20 : 4 << 20);
+      if (lanes > 96u || n < (lanes <= 32u ? 2 << 20 : lanes <= 56u ? 3 << 20 : 4 << 20)) return false;
+      if (lanes <= 48u || es == 4) return true;
+      if (lanes <= 56u) return plan->transpose.n_tiles > 4u * kPlannedCus;
+      return tiles <= 3u * kPlannedCus || run >= 1024 || (run < 192 && run % 128 != 0);
     };
     if (limit > 0.0 && (shifts || plan_shifted(&shifted)) &&
         (!plain || (covered(shifted) <= limit * covered(*plan) && !cuts_rows(p, true, plan->src_run_bytes, plan->dst_run_bytes) &&

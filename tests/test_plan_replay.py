@@ -541,12 +541,25 @@ def test_moved_tiles(oracle, monkeypatch, case):
     _check(oracle, *case)
 
 
-def test_where_moved_tiles_are_taken():
+def test_where_moved_tiles_are_taken(monkeypatch):
     def desc(a, b, dt="bf16"):
         return lc.Plan("((8,%d),(8,%d)):((1,8),(%d,%d))" % (a, b, 8 * a, 64 * a), "((8,%d),(8,%d)):((8,%d),(1,64))" % (a, b, 64 * b), dt).describe()
     assert "tile=[8,8,8,32]" in desc(664, 244) and "tile=[8,8,8,32]" in desc(148, 748) and "tile=[8,8,8,32]" in desc(452, 208)
     assert "shifted_tiles" not in desc(132, 344) and "shifted_tiles" not in desc(940, 636) and "shifted_tiles" not in desc(512, 1024)
     assert "shifted_tiles" not in lc.Plan("(28,4,38576):(1,28,112)", "(28,4,38576):(154304,38576,1)", "f32").describe()   # a shorter run
+    # whole tiles of 57 to 96 lanes: up to three moved tiles a CU, or in place of runs of a line and a part; 56 lanes in one round of four a CU stay
+    for a, b, taken in ((480, 260, True), (312, 636, False), (464, 508, False), (600, 724, False), (476, 124, True), (392, 132, False), (644, 88, False)):
+        assert ("tile=[8,8,8,32]" in desc(a, b)) == taken, (a, b)
+    def moved(src, dst, dt="f32"):
+        monkeypatch.delenv("LC_TUNE_MOVED", raising=False)
+        taken = lc.Plan(src, dst, dt).describe()
+        monkeypatch.setenv("LC_TUNE_MOVED", "0")
+        return taken != lc.Plan(src, dst, dt).describe()
+    # ragged fp32 tiles of the same extents: below six a CU and from twelve on
+    assert moved("(40,32,4156):(4156,166240,1)", "(40,32,4156):(32,1,1280)") and moved("(4,8,1091,571):(1,4,32,34912)", "(4,8,1091,571):(4983688,1,4568,8)")
+    assert not moved("(4,346,550,8):(1,4,1384,761200)", "(4,346,550,8):(2768,8,11072,1)")
+    # fp32 shifted tiles with runs of 64 bytes on the destination's side stay, on the source's they go
+    assert not moved("(8,74,1948):(144152,1948,1)", "(8,74,1948):(1,8,592)") and moved("(8,74,1948):(1,8,592)", "(8,74,1948):(144152,1948,1)")
 
 
 def test_workgroups_of_shifted_tiles_fill_their_rounds():
