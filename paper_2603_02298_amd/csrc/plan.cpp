@@ -2,6 +2,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <functional>
 #include <cstring>
 
 namespace lc {
@@ -344,9 +345,15 @@ int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit) {
 // shifted: likewise, for vectors at any alignment (V need not divide anything); the last tile along such a mode is moved back
 // until it ends with the mode, so the kernel without predicates runs them; whole workgroups only.
 // moved: shifted, along modes of the tile other than p and q as well (at most two modes that the tile does not divide).
+// accept: asked once the tiles are known, before the longer part of the planning; false: no plan.
 enum class Tiling { Exact, Ragged, Shifted, Moved };
+struct TileSketch {
+  const std::vector<int64_t>& extent;   // per joint mode
+  double tiles, covered;                // how many, and the elements they cover
+  int64_t src_run_bytes, dst_run_bytes;
+};
 static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, int q, int64_t n, const Tuning& tune, lc_plan* plan,
-                       Tiling tiling = Tiling::Exact) {
+                       Tiling tiling = Tiling::Exact, const std::function<bool(const TileSketch&)>& accept = {}) {
   const bool ragged = tiling != Tiling::Exact, shifted = tiling == Tiling::Shifted || tiling == Tiling::Moved;
   const int nj = (int)J.size();
   // Tile size: up to 4 micro-tiles per lane (64 KiB of fp32), but never so large that fewer than
@@ -453,6 +460,15 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
       if (!spans_fit(t)) { t[(size_t)k] /= f; break; }
       micro *= f;
     }
+  if (accept) {
+    double tiles = 1.0, covered = 1.0;
+    for (int k = 0; k < nj; ++k) {
+      const int64_t count = (J[(size_t)k].extent + t[(size_t)k] - 1) / t[(size_t)k];
+      tiles *= (double)count;
+      covered *= (double)(count * t[(size_t)k]);
+    }
+    if (!accept({t, tiles, covered, run_length(J, src_order, t, true) * es, run_length(J, dst_order, t, false) * es})) return false;
+  }
   // tiling = zipped_divide of both joint layouts by the tile extents (Sec. 3.5.2): mode 0 is
   // the tile, mode 1 the grid of tiles; a workgroup slices mode 1 with its tile id.
   Modes js, jd, tl;
@@ -1043,10 +1059,10 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
       plan->note = "no common vector on both sides for a transposing tile";
       return false;
     };
-    auto plan_shifted = [&](lc_plan* sh, Tiling tiling = Tiling::Shifted) {
+    auto plan_shifted = [&](lc_plan* sh, Tiling tiling = Tiling::Shifted, const std::function<bool(const TileSketch&)>& accept = {}) {
       if ((es != 2 && es != 4) || tune.max_vec_bytes > 0 || tune.tile.size() == (size_t)nj) return false;
       sh->cls = KernelClass::Generic;
-      return plan_tiled(J, es, 16 / es, p, q, n, tune, sh, tiling);
+      return plan_tiled(J, es, 16 / es, p, q, n, tune, sh, tiling, accept);
     };
     lc_plan shifted = *plan;
     if (tune.shifted > 0 && plan_shifted(&shifted, tune.shifted == 2 ? Tiling::Moved : Tiling::Shifted)) {
@@ -1104,34 +1120,44 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
     //   shifted tiles with runs shorter than a line: bf16 (166,8,64,719) 146 -> 61, (225,8,14864) 42 -> 28; but of 128 bytes (168,3048,8,8) 29 -> 33; fp32 runs
     //     of 64 bytes only on the source's side, or on grids of 16 a CU and more (on the destination's side, whose half lines the L2 joins,
     //     (8,74,1948) 4.6 -> 5.1, (4,1163,4,156) 6.6 -> 7.3).
-    lc_plan moved = *plan;
-    auto moved_pays = [&](bool in_place_of_plain) {
-      if (!may_shift || tune.moved == 0 || V * es != 16 || nj < 3 || !plan_shifted(&moved, Tiling::Moved) || covered(moved) > 1.15 * (double)n) return false;
-      const int64_t run = std::min(plan->src_run_bytes, plan->dst_run_bytes), moved_run = std::min(moved.src_run_bytes, moved.dst_run_bytes);
-      const uint32_t tiles = moved.transpose.n_tiles;
-      if (!in_place_of_plain) return run < 128 && moved_run > run && (es == 2 || run < 64 || plan->src_run_bytes == run || tiles >= 16u * kPlannedCus);
-      if (moved_run < std::min<int64_t>(run, 256)) return false;
+    // What the plan in hand rules out is asked first, what the moved tiles themselves do as soon as they are known: planning a tiling to its end takes
+    // longer than all else here (relayout 512 x 1024 297 us with the moved one planned in any case, 166 without; 68 x 228 347, 240).
+    auto try_moved = [&](bool in_place_of_plain) {
+      if (!may_shift || tune.moved == 0 || V * es != 16 || nj < 3) return;
+      const int64_t run = std::min(plan->src_run_bytes, plan->dst_run_bytes);
       const uint32_t lanes = plan->transpose.n_micro;
-      if (plan->transpose.n_ragged > 0) {
-        if (lanes > 2u * kBlock) return false;
-        const bool same = plan->tile_extent == moved.tile_extent;
-        if (es == 2) return !same;
-        return lanes < 224u || (n >= (5 << 20) && (!same || tiles < 6u * kPlannedCus || tiles >= 12u * kPlannedCus));
+      const bool ragged = plan->transpose.n_ragged > 0;
+      if (!in_place_of_plain) {
+        if (run >= 128) return;
+      } else if (ragged) {
+        if (lanes > 2u * kBlock || (es == 4 && lanes >= 224u && n < (5 << 20))) return;
+      } else if (lanes > 96u || n < (lanes <= 32u ? 2 << 20 : lanes <= 56u ? 3 << 20 : 4 << 20) ||
+                 (es == 2 && lanes > 48u && lanes <= 56u && plan->transpose.n_tiles <= 4u * kPlannedCus)) {
+        return;
       }
-      if (lanes > 96u || n < (lanes <= 32u ? 2 << 20 : lanes <= 56u ? 3 << 20 : 4 << 20)) return false;
-      if (lanes <= 48u || es == 4) return true;
-      if (lanes <= 56u) return plan->transpose.n_tiles > 4u * kPlannedCus;
-      return tiles <= 3u * kPlannedCus || run >= 1024 || (run < 192 && run % 128 != 0);
+      auto pays = [&](const TileSketch& m) {
+        if (m.covered > 1.15 * (double)n) return false;
+        const int64_t moved_run = std::min(m.src_run_bytes, m.dst_run_bytes);
+        if (!in_place_of_plain) return moved_run > run && (es == 2 || run < 64 || plan->src_run_bytes == run || m.tiles >= 16.0 * kPlannedCus);
+        if (moved_run < std::min<int64_t>(run, 256)) return false;
+        if (ragged && plan->tile_extent == m.extent) return es == 4 && (lanes < 224u || m.tiles < 6.0 * kPlannedCus || m.tiles >= 12.0 * kPlannedCus);
+        if (!ragged && es == 2 && lanes > 56u) return m.tiles <= 3.0 * kPlannedCus || run >= 1024 || (run < 192 && run % 128 != 0);
+        return true;
+      };
+      lc_plan moved = *plan;
+      if (plan_shifted(&moved, Tiling::Moved, pays)) *plan = moved;
     };
     if (limit > 0.0 && (shifts || plan_shifted(&shifted)) &&
         (!plain || (covered(shifted) <= limit * covered(*plan) && !cuts_rows(p, true, plan->src_run_bytes, plan->dst_run_bytes) &&
                     !cuts_rows(q, false, plan->dst_run_bytes, plan->src_run_bytes)))) {
       *plan = shifted;
-      if (moved_pays(false)) *plan = moved;
+      try_moved(false);
       return LC_OK;
     }
-    if (plain && moved_pays(true)) *plan = moved;
-    if (plain) return LC_OK;
+    if (plain) {
+      try_moved(true);
+      return LC_OK;
+    }
   }
   if (tune.force_class == 0) return plan_generic(S, D, n, plan, "forced");
 
