@@ -1,4 +1,5 @@
 // extern "C" boundary of the library (include/layoutcopy.h): argument checks and marshalling only.
+#include <algorithm>
 #include <cstring>
 #include <new>
 
@@ -269,22 +270,12 @@ lc_status_t lc_copy(const void* src, const lc_layout_t* src_layout, void* dst, c
   try {
     // plans of recent calls are kept: planning is host work of some 10 us, several times a short kernel
     // (key by contents: 1024 x 1024 fp32, call to call, 8.4 us with the layouts' text and every setting asked for by name)
-    const bool tuned = lc::tuning_in_environment();
-    const lc::Tuning tune = tuned ? lc::tuning_from_env() : lc::Tuning();
     static thread_local std::string key;
     key.clear();
     lc::key_layout(&key, src_layout->L);
     lc::key_layout(&key, dst_layout->L);
-    for (int64_t v : {(int64_t)es, (int64_t)align_of(src), (int64_t)align_of(dst), (int64_t)tuned}) lc::key_number(&key, v);
-    if (tuned) {
-      for (int64_t v : {(int64_t)tune.micro_per_thread, (int64_t)tune.rest_order, (int64_t)tune.wgs_per_cu, (int64_t)tune.unroll,
-                        (int64_t)tune.swizzle_shift, (int64_t)tune.nontemporal, (int64_t)tune.blocked, tune.max_items, (int64_t)tune.force_class,
-                        (int64_t)tune.max_vec_bytes, (int64_t)tune.tile_queue, (int64_t)tune.queue_rounds, (int64_t)tune.queue_counters,
-                        (int64_t)tune.leftover_lead, (int64_t)tune.grid, (int64_t)tune.early_loads, (int64_t)tune.gather, (int64_t)tune.shifted,
-                        (int64_t)tune.direct_queue, (int64_t)tune.tile.size()})
-        lc::key_number(&key, v);
-      for (int64_t v : tune.tile) lc::key_number(&key, v);
-    }
+    for (int64_t v : {(int64_t)es, (int64_t)align_of(src), (int64_t)align_of(dst)}) lc::key_number(&key, v);
+    const lc::Tuning tune = lc::key_tuning(&key) ? lc::tuning_from_env() : lc::Tuning();
     std::shared_ptr<const lc_plan_t> plan = copy_plans().find(key);
     if (!plan) {
       auto fresh = std::make_shared<lc_plan_t>();
@@ -311,6 +302,14 @@ lc_status_t lc_plan_time_each(const lc_plan_t* plan, const void* const* srcs, vo
                               void* hip_stream, float* ms_each) {
   if (!plan) return LC_ERR_INVALID_ARG;
   return lc::time_plan_each(*plan, srcs, dsts, n_buffers, warmup, iters, hip_stream, ms_each);
+}
+
+// The part of a one-shot call's plan key that stands for the tuning settings in force (test instrumentation): its length, and up to cap bytes of it.
+size_t lc_debug_tuning_key(char* buf, size_t cap) {
+  std::string key;
+  lc::key_tuning(&key);
+  if (buf) std::memcpy(buf, key.data(), std::min(cap, key.size()));
+  return key.size();
 }
 
 // Checking device for tests: replays the plan's index arithmetic on HOST buffers (see plan.hpp).

@@ -60,18 +60,11 @@ lc_status_t lc_gemm(const void* a, const lc_layout_t* a_layout, const void* b, c
   if (!a || !b || !c || !a_layout || !b_layout || !c_layout) return LC_ERR_INVALID_ARG;
   try {
     // plans of recent calls are kept (see plan_cache.hpp); the planner's tuning knobs are part of the key
-    const bool tuned = lc::tuning_in_environment();
     static thread_local std::string key;
     key.clear();
     for (const lc_layout_t* l : {a_layout, b_layout, c_layout}) lc::key_layout(&key, l->L);
-    for (int64_t v : {(int64_t)ab_dtype, (int64_t)pointer_alignment(a), (int64_t)pointer_alignment(b), (int64_t)pointer_alignment(c), (int64_t)tuned})
-      lc::key_number(&key, v);
-    if (tuned)
-      for (const char* knob : {"LC_TUNE_GEMM_LOAD", "LC_TUNE_GEMM_DIRECT", "LC_TUNE_GEMM_CVEC", "LC_TUNE_GEMM_TILE", "LC_TUNE_GEMM_GROUP_M",
-                               "LC_TUNE_GEMM_EXCHANGE", "LC_TUNE_GEMM_KTAIL"}) {
-        const char* v = std::getenv(knob);
-        key += std::string(",") + (v ? v : "");
-      }
+    for (int64_t v : {(int64_t)ab_dtype, (int64_t)pointer_alignment(a), (int64_t)pointer_alignment(b), (int64_t)pointer_alignment(c)}) lc::key_number(&key, v);
+    lc::key_tuning(&key);
     static lc::PlanCache<lc_gemm_plan> plans;
     std::shared_ptr<const lc_gemm_plan> plan = plans.find(key);
     if (!plan) {

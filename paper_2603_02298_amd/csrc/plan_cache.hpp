@@ -15,14 +15,6 @@
 
 namespace lc {
 
-// Is any tuning setting in the environment?  One pass over its names; asked for one by one the twenty-odd settings cost a call
-// more than the rest of its look-up.
-inline bool tuning_in_environment() {
-  for (char** e = environ; e && *e; ++e)
-    if (std::strncmp(*e, "LC_TUNE_", 8) == 0) return true;
-  return false;
-}
-
 // Keys are bytes: numbers as they lie in memory, sequences behind their lengths, so that no two different keys read the same.
 inline void key_number(std::string* key, int64_t v) { key->append(reinterpret_cast<const char*>(&v), sizeof(v)); }
 inline void key_layout(std::string* key, const Layout& L) {
@@ -33,6 +25,20 @@ inline void key_layout(std::string* key, const Layout& L) {
     key_number(key, m.extent);
     key_number(key, m.stride);
   }
+}
+
+// Every tuning setting in the environment, by name and value, whoever reads it: a list of names here would miss the next one.
+// One pass over the environment's names; asked for one by one the thirty settings cost a call more than the rest of its look-up.
+// false: there is none, and nothing is added.
+inline bool key_tuning(std::string* key) {
+  bool any = false;
+  for (char** e = environ; e && *e; ++e)
+    if (std::strncmp(*e, "LC_TUNE_", 8) == 0) {
+      any = true;
+      key_number(key, (int64_t)std::strlen(*e));
+      key->append(*e);
+    }
+  return any;
 }
 
 template <typename Plan>

@@ -49,3 +49,33 @@ def test_null_arguments_are_errors_not_crashes():
     assert L.lc_plan_create(a._h, a._h, 0, 3, 256, ctypes.byref(h)) == 1      # alignment not a power of two
     k = ctypes.c_int64()
     assert L.lc_max_common_vector(a._h, lc.Layout("9:1")._h, ctypes.byref(k)) == 6
+
+
+def test_one_shot_calls_key_their_plans_by_every_tuning_setting(monkeypatch):
+    # the sources' own list of settings: each one, set, changed or taken away, makes another key, so that no call runs the plan of other settings
+    import paper_2603_02298_amd as lc
+    L = lc.lib()
+    L.lc_debug_tuning_key.argtypes = [ctypes.c_char_p, ctypes.c_size_t]
+    L.lc_debug_tuning_key.restype = ctypes.c_size_t
+    def key():
+        buf = ctypes.create_string_buffer(1 << 16)
+        return buf.raw[:L.lc_debug_tuning_key(buf, len(buf))]
+    csrc = os.path.join(ROOT, "paper_2603_02298_amd", "csrc")
+    names = set()
+    for f in os.listdir(csrc):
+        names.update(re.findall(r'(?:env_int|getenv)\("(LC_TUNE_[A-Z_]+)"', open(os.path.join(csrc, f)).read()))
+    assert len(names) >= 29 and {"LC_TUNE_PACKED", "LC_TUNE_MOVED", "LC_TUNE_GEMM_GATHER", "LC_TUNE_TILE"} <= names, names
+    for n in list(os.environ):
+        if n.startswith("LC_TUNE_"):
+            monkeypatch.delenv(n)
+    assert key() == b""
+    seen = {key()}
+    for n in sorted(names):
+        for value in ("0", "1"):
+            monkeypatch.setenv(n, value)
+            assert key() not in seen, n
+            seen.add(key())
+        monkeypatch.delenv(n)
+    monkeypatch.setenv("LC_TUNE_GRID", "1")
+    monkeypatch.setenv("LC_TUNE_WGS_PER_CU", "1")
+    assert key() not in seen
