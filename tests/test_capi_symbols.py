@@ -59,7 +59,8 @@ def test_one_shot_calls_key_their_plans_by_every_tuning_setting(monkeypatch):
     L.lc_debug_tuning_key.restype = ctypes.c_size_t
     def key():
         buf = ctypes.create_string_buffer(1 << 16)
-        return buf.raw[:L.lc_debug_tuning_key(buf, len(buf))]
+        size = L.lc_debug_tuning_key(buf, len(buf))
+        return buf.raw[:size]
     csrc = os.path.join(ROOT, "paper_2603_02298_amd", "csrc")
     names = set()
     for f in os.listdir(csrc):
