@@ -65,15 +65,15 @@ struct Loads {
   bool direct, any, gather;  // both straight into LDS, both in vectors at any alignment, both gathered through registers
 };
 
-// lines of 128 bytes that the first 64 coordinates of a mode touch (elements of 2 bytes)
-int lines_of(const Modes& m) {
+// lines of 128 bytes, of line_elems elements each, that the first 64 coordinates of a mode touch
+int lines_of(const Modes& m, int line_elems) {
   int64_t size = 1;
   for (const Mode& x : m) size *= x.extent;
   std::vector<int64_t> lines;
   for (int64_t i = 0; i < std::min<int64_t>(size, 64); ++i) {
     int64_t at = 0, rest = i;
     for (const Mode& x : m) { at += rest % x.extent * x.stride; rest /= x.extent; }
-    lines.push_back(at / 64);
+    lines.push_back(at / line_elems);
   }
   std::sort(lines.begin(), lines.end());
   return (int)(std::unique(lines.begin(), lines.end()) - lines.begin());
@@ -123,7 +123,7 @@ Loads choose_loads(const Modes& a_r, const Modes& a_k, const Modes& a_l, unsigne
   l.gather = !l.direct && !l.any && force != kLoadElem && direct_env == 3 && env_int("LC_TUNE_GEMM_KTAIL", 1) != 0;
   auto gather_kind = [&](int own, const Modes& row, const Modes& k) -> int32_t {
     if (own != kLoadElem) return own == kLoadKVec ? 6 : 7;
-    return lines_of(row) <= lines_of(k) ? 4 : 5;
+    return lines_of(row, 64) <= lines_of(k, 64) ? 4 : 5;
   };
   l.a_gather = gather_kind(a_own, a_r, a_k);
   l.b_gather = gather_kind(b_own, b_r, b_k);
@@ -215,13 +215,16 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     loads.a_direct = loads.a_gather;
     loads.b_direct = loads.b_gather;
   }
-  // Without vectors of four m the lanes of the split and stream kernels' update run along n, element by element: C's contiguous
-  // mode goes there (not for a few columns, whose thin tiles are worth more).  The tile kernels of staged and element loads
-  // measured slower that way round (2 x 5560 x 64 10.8 -> 15.2 us, a convolution of 35 x 13500 x 288 16.8 -> 21.4).
-  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m)) {
-    if (gather) exchange = c_m[0].stride != 1 && lines_of(c_m) < lines_of(c_n);   // (no contiguous mode: the closer one)
-    else exchange = (loads.direct || loads.any) && c_m[0].stride == 1 && c_n[0].stride != 1 && N > 16;
-  }
+  // Without vectors of four m the lanes of the split and stream kernels' update run along n, element by element: the mode of C whose
+  // neighbours share more lines goes there, whichever way the operands come in; not for a few columns of operands with thin tiles, which are worth
+  // more, nor for a few contiguous rows, where it gains nothing (gathered 5 x 1500 x 700 8.8 -> 9.0, 56 x 3044 x 3008 27.5 -> 30.0, up to 128 rows 0.99 on
+  // average; over leaves 2 x 1500 x 216 3.8 -> 4.0, from 17 rows on faster).  Measured on MI355X over 600 problems of more than 16 rows and columns,
+  // the exchanged order's time over the other's: C contiguous along m direct 0.79 on average (0.32 at best), vectors at any alignment 0.84,
+  // gathered 0.88 (2382 x 1376 x 27 29.2 -> 24.9 us), over leaves 0.73; the closer mode along m and none contiguous 0.82, 0.84, 0.89, 0.81; the closer mode
+  // along n 1.04 to 1.30.  The tile kernels of staged and element loads measured slower that way round (2 x 5560 x 64 10.8 -> 15.2 us, a
+  // convolution of 35 x 13500 x 288 16.8 -> 21.4).
+  if (!c_vec_ok(c_m, c_n) && !c_vec_ok(c_n, c_m))
+    exchange = (gather ? M > 64 || c_m[0].stride != 1 : leaves ? M > 16 : (loads.direct || loads.any) && N > 16) && lines_of(c_m, 32) < lines_of(c_n, 32);
   if (env_int("LC_TUNE_GEMM_EXCHANGE", -1) >= 0) exchange = env_int("LC_TUNE_GEMM_EXCHANGE", 0) != 0;
   if (exchange) {
     std::swap(a_r, b_r);

@@ -394,16 +394,23 @@ def test_which_operands_take_vectors_at_any_alignment():
     assert loads("(70,(3,3)):(12,(1,4))", "(33,9):(9,1)", "(70,33):(33,1)")[0] == "elements"     # k of two leaves
 
 
-def test_c_without_vectors_is_exchanged_where_the_update_passes_through_lds_only():
-    # C contiguous along m, but without whole vectors of it: the split and stream kernels take its contiguous mode along n, the
-    # tile kernels of staged and element loads keep the roles (slower the other way round)
+def test_c_without_vectors_is_exchanged_where_the_update_passes_through_lds_only(monkeypatch):
+    # C contiguous (or closer) along m, but without whole vectors of it: the split and stream kernels take that mode along n, however the
+    # operands come in; the tile kernels of staged and element loads keep the roles (slower the other way round)
     def exchanged(*layouts):
         return lc.GemmPlan(*layouts).describe().split("exchanged=")[1][0]
     assert exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(1,70)") == "1" and exchanged("(70,9):(9,1)", "(45,9):(9,1)", "(70,45):(1,70)") == "1"
     assert exchanged("(70,64):(64,1)", "(16,64):(64,1)", "(70,16):(1,70)") == "0"                 # a few columns: thin tiles
-    assert exchanged("(2,64):(1,2)", "(5560,64):(64,1)", "(2,5560):(1,2)") == "0"                 # element loads
-    assert exchanged("(70,9):(3,211)", "(45,9):(9,1)", "(70,45):(1,70)") == "0"
-    assert exchanged("(35,144):(144,1)", "(450,(16,3,3)):(800,(1,32,128))", "(35,450):(1,35)") == "0"   # staged k vectors
+    element = ("(70,9):(3,211)", "(45,9):(9,1)", "(70,45):(1,70)")
+    staged = ("(35,144):(144,1)", "(450,(16,3,3)):(800,(1,32,128))", "(35,450):(1,35)")
+    assert exchanged(*element) == "1" and exchanged(*staged) == "1"                               # gathered, over leaves
+    assert exchanged("(1001,500):(3,3100)", "(777,500):(1100,2)", "(1001,777):(1,1001)") == "1" and exchanged("(1001,500):(3,3100)", "(777,500):(1100,2)", "(1001,777):(2,2003)") == "1"
+    assert exchanged("(1001,500):(3,3100)", "(777,500):(1100,2)", "(1001,777):(1555,2)") == "0" and exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(2,141)") == "1"
+    assert exchanged("(2,64):(1,2)", "(5560,64):(64,1)", "(2,5560):(1,2)") == "0" and exchanged("(56,3008):(4,224)", "(3044,3008):(9032,3)", "(56,3044):(1,57)") == "0"   # a few rows, gathered
+    monkeypatch.setenv("LC_TUNE_GEMM_GATHER", "0")
+    for layouts in (element, staged, ("(2,64):(1,2)", "(5560,64):(64,1)", "(2,5560):(1,2)")):
+        assert exchanged(*layouts) == "0" and " stream " not in lc.GemmPlan(*layouts).describe()
+    monkeypatch.delenv("LC_TUNE_GEMM_GATHER")
     assert exchanged("(70,64):(64,1)", "(45,64):(64,1)", "(70,45):(45,1)") == "0"                 # contiguous along n already
 
 
