@@ -332,12 +332,12 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
     const Choice ring = {128, 128, 1.0, 1.35};
     const bool ring_pays = direct && K >= 3000 && tiles_of(128, 128) <= 256 && cost(ring) < cost(*best);
     // Tiles of 256 x 192 and 192 x 256 (their own kernel; C in vectors) from K = 768 on: 0.91, 0.82 from 2048 on, 0.8 from 3000 on, for at least
-    // 128 of them; below K = 1200, where C's update weighs too much for a second round, for one nearly full round (tn 2600 x 4112 x 880 40.1 -> 36.8, 242
+    // 128 of them; below K = 1200, where C's update weighs too much for a second round, for one nearly full round (tn 2600 x 4112 x 880 40.1 -> 36.8, 238
     // tiles; but 192 tiles 5992 x 1368 x 896 30.9 -> 32.3, three rounds 5984 x 6072 x 960 112 -> 130).  Of 460 problems drawn (all forms, K from 128 to
     // 8192, up to 32 batch entries) they are chosen for 90 and take 0.89 of the time of the others' best on average, 1.03 at worst; figures
-    // beside the kernel.  Pairs along the rows between 2048 and 3000 keep the others' tiles, which tests hold for 4240 x 5248 x 2872 (168 us, 161 here).
-    const bool wide_fits = direct && P.c_vec != 0, rows_pair = P.a_load == kLoadRVec && P.b_load == kLoadRVec;
-    const double wide_weight = K < 2048 ? 0.91 : K < 3000 ? (rows_pair ? 1.0 : 0.82) : 0.8;
+    // beside the kernel.  (Pairs along the rows with K from 2048 to 3000 too: 68 problems 0.89, 1.05 at worst; nn 4240 x 5248 x 2872 147 -> 137.)
+    const bool wide_fits = direct && P.c_vec != 0;
+    const double wide_weight = K < 2048 ? 0.91 : K < 3000 ? 0.82 : 0.8;
     auto wide_cost = [&](int64_t tm, int64_t tn) {
       const int64_t tiles = tiles_of(tm, tn);
       if (K < 768 || tiles < (K < 1200 ? 216 : 128) || (K < 1200 && tiles > 256)) return 1e30;

@@ -417,7 +417,7 @@ def test_c_without_vectors_is_exchanged_where_the_update_passes_through_lds_only
 @pytest.mark.parametrize("form,M,N,K,tile", [
     # tt: both along k, nn: both along their rows (k-major tiles)
     ("nt", 632, 7168, 7448, "128x128x64 stream"), ("tn", 1240, 4848, 3792, "128x128x64 stream"), ("nn", 2320, 2144, 3928, "128x128x64 stream"),
-    ("nn", 6872, 680, 1752, "128x128x64 stream"), ("nn", 4240, 5248, 2872, "128x128x64 stream"), ("tt", 216, 34596, 1152, "128x128x64 stream"), ("tn", 5136, 776, 3008, "128x128x64 stream"), ("tn", 2248, 2240, 2704, "128x128x64 stream"),
+    ("nn", 6872, 680, 1752, "128x128x64 stream"), ("nn", 4240, 5248, 2872, "256x192x64 tiles"), ("tt", 216, 34596, 1152, "128x128x64 stream"), ("tn", 5136, 776, 3008, "128x128x64 stream"), ("tn", 2248, 2240, 2704, "128x128x64 stream"),
     ("tt", 7816, 496, 5288, "128x128x64 tiles"), ("nt", 2296, 1688, 8000, "128x128x64 tiles"), ("tt", 1968, 1848, 8168, "128x128x64 tiles"),     # a lone tile on a CU, a long k loop: the ring
     ("tt", 1848, 1784, 2720, "128x64x64 stream"), ("tn", 1536, 2368, 2408, "64x128x64 stream"), ("nt", 2712, 1192, 2800, "128x64x64 stream"),    # 64 on the side that is contiguous along k
     ("tt", 4096, 4096, 4096, "256x256x64 tiles"), ("tt", 5000, 5000, 3000, "256x256x64 tiles"), ("tt", 2048, 2048, 2048, "128x64x64 stream")])
