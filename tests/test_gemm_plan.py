@@ -276,7 +276,8 @@ def test_split_kernel_is_the_choice_while_a_cu_has_at_most_one_tile_and_the_ring
         return d.split("tile=")[1].split()[0], "split_waves" in d
     assert tile(8192, 16, 64) == ("32x16x64", True) and tile(8192, 17, 64) == ("32x32x64", True)
     assert tile(512, 512, 512) == ("32x32x64", True) and tile(516, 512, 512) == ("64x32x64", True) and tile(512, 513, 512) == ("32x64x64", True)
-    assert tile(1024, 1024, 64) == ("64x64x64", True) and tile(1024, 1025, 64)[1] is False
+    assert tile(1024, 1024, 512) == ("64x64x64", True) and tile(1024, 1025, 512)[1] is False
+    assert tile(1024, 1024, 64) == ("64x64x64", False) and tile(512, 513, 8) == ("64x64x64", False)   # one k tile: nothing to share
     assert tile(64, 64, 64, 64) == ("32x32x64", True) and tile(64, 64, 64, 257)[1] is False
     # with tiles for every CU either way: the stream kernel's where C's update outweighs the k loop, the ring's from K = 768 on
     assert tile(4096, 4096, 760) == ("128x128x64", False) and tile(4096, 4096, 768) == ("256x256x64", False)
