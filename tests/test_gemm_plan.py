@@ -463,6 +463,11 @@ def gathered_workloads(values="ints"):
         (W.conv_gemm_workload(2, 9, 8, 24, 44, 3, 3, "krsc", values=values), "k-vectors=over-leaves"),
         (W.conv_gemm_workload(1, 12, 9, 8, 136, 3, 3, "krsc", ab_dtype="f16", values=values), "k-vectors=over-leaves"),
         (W.conv_gemm_workload(1, 8, 8, 96, 70, 2, 3, "krsc", values=values), "k-vectors=over-leaves"),
+        # 14, 23 and 35 k tiles, the last one short: past the 12 and 16 places of the split kernel's rings, and several a wavefront through registers
+        (W.conv_gemm_workload(1, 6, 7, 96, 45, 3, 3, "krsc", values=values), "k-vectors=over-leaves"),
+        (W.conv_gemm_workload(1, 7, 6, 160, 72, 3, 3, "krsc", ab_dtype="f16", values=values), "k-vectors=over-leaves"),
+        (W.conv_gemm_workload(1, 6, 6, 248, 36, 3, 3, "krsc", values=values), "k-vectors=over-leaves"),
+        (W.conv_gemm_workload(1, 6, 6, 248, 33, 3, 3, "kcrs", values=values), "gathered=along-k,k-vectors"),
         (w("folded_k_rows", "bf16", "(72,(8,9)):(1,(80,704))", "(136,(8,9)):(1,(136,1200))", "(72,136):(1,72)", 72, 136, 72), "gathered=row-vectors,row-vectors"),
         (w("folded_k_mixed", "f16", "(72,(8,9)):(1,(80,704))", "(33,(8,9)):(3,(100,1100))", "(72,33):(1,72)", 72, 33, 72), "gathered=row-vectors,along-rows"),
         (w("folded_k_kr", "bf16", "(65,(16,5)):(104,(1,20))", "(40,(16,5)):(5,(203,4000))", "(65,40):(41,1)", 65, 40, 80), "gathered=along-k,along-rows"),
