@@ -266,7 +266,8 @@ struct AnyTileLoader {
 // The same tile for operands without vectors (or with vectors over a k mode of several short leaves), through registers.  Every
 // load is an element (or a vector) at a 32-bit offset from the operand: the lanes' own part in a vector register, the part
 // all lanes share in a scalar one.  One lane evaluates the k mode for one k of the tile; the others' offsets are read from it.
-// Rows past the operand's extent, and k past K, present an offset outside the buffer's range: zeros arrive.
+// k past K, and rows past the operand's extent, present an offset outside the buffer's range: zeros arrive (elements with the lanes along k
+// repeat the last row instead: products nobody looks at).
 // What bounds it: the vector memory path takes 64 addresses per instruction whatever their size, so an element costs what a
 // vector costs; the lanes run along the mode whose neighbours share lines, and the eight elements a lane packs along the other.
 // Measured on MI355X (bf16, us; element loads of 128 x 128 tiles -> this): no contiguous mode, 162 x 114 x 972 174 -> 10, 1024^3 183 -> 25,

@@ -217,6 +217,7 @@ __global__ __launch_bounds__(kBlock, (WMB <= 2 ? 2 : 1)) void gemm_kernel(GemmPa
     // The barrier sits between k steps 2 and 3: by then every wavefront has read its last fragments of tile t (two slots
     // fall free: B(t + 2) and A(t + 3) go there), and tile t + 1 is complete: its first fragments are read while the MFMAs
     // of k step 3 run.  Past the last k tile the loads repeat it (in bounds, into slots nobody reads again).
+    // (gemm_wide_kernel.hpp runs the same ring over tiles of 256 x 192 and 192 x 256: a change here is due there.)
     static_assert(BM == BN, "the ring's slots hold a tile of either operand");
     static_assert(KSTEPS == 4, "the loop below spells out the four k steps");
     constexpr uint32_t SLOT = A_BYTES;

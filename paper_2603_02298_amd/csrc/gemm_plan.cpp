@@ -358,7 +358,7 @@ lc_status_t make_gemm_plan(const Layout& A_in, const Layout& B_in, const Layout&
   }
   else if (t_env == 128 || t_env == 256) take(t_env, t_env, 0, 0);
   else if (tiles_of(256, 256) >= 256) take(256, 256, 0, 0);   // through registers: 256 x 256 when that gives every CU a tile
-  else take(128, 128, 0, 0);
+  else take(128, 128, 0, 0);   // (elements in these tiles: only where the tuning settings ask for staged or element loads)
   // The stream kernel's 128 x 128 tiles of two k-major operands over short k loops: pieces of 32 k rows.  Measured on MI355X (us, k tiles of 64 -> this):
   // 16 x (1000 x 1504 x 776) 85.3 -> 81.8, 20 x 1000^3 86.4 -> 81.0, 22 x (824 x 464 x 1088) 47.7 -> 44.4, 3000^2 x 320 23.5 -> 21.6, 16 x (1536^2 x 128)
   // 71.4 -> 66.8, 30 x (1300 x 700 x 900) 123.5, 123.7; 4 x (2000^2 x 1184) 63.9 -> 65.2, 6872 x 680 x 1752 33.5 -> 33.8, 4240 x 5248 x 2872 168 -> 181;

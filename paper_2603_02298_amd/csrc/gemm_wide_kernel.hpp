@@ -1,9 +1,11 @@
 // Device code of the wide GEMM tiles: C(m,n) += A(m,k) * B(n,k) (Sec. 2.6.2 of "CuTe Layout Representation and Algebra") for
 // operands that go straight into LDS and a C with vectors, in tiles of 256 x 192 or 192 x 256, one workgroup a CU.
 //
-// The main loop is the ring of five operand tiles of gemm_kernel.hpp (slots as large as the larger tile).  The 256 x 256 tiles read least of LDS and
-// memory per product, but on problems with one to four of them a CU the last round is often mostly empty; these are the next best
-// per product (192 sums a lane still leave the fragments double-buffered) and fill the rounds differently.
+// The main loop is the ring of five operand tiles of gemm_kernel.hpp, described there (slots as large as the larger tile): its counted waits, the order of
+// its loads and its slots are the same in both, and a change to one is due in the other.  (Both through one function: the same sums, but
+// the registers fall differently, 256 x 256 tiles 1.010 of the time over 52 problems, 256 x 192 1.009 over 44.)
+// The 256 x 256 tiles read least of LDS and memory per product, but on problems with one to four of them a CU the last round is often
+// mostly empty; these are the next best per product (192 sums a lane still leave the fragments double-buffered) and fill the rounds differently.
 // What bounds it: the matrix cores at the power limit inside the loop, C's way from and to HBM behind it, which nothing covers.
 // Measured on MI355X (bf16, us; best of the other tiles -> this): nt 3368 x 5336 x 6576 334 -> 299, tt 3144 x 6368 x 3992 241 -> 212,
 // tt 5656 x 2968 x 8048 380 -> 311, nt 4272 x 3896 x 3376 183 -> 164, tt 1200 x 7016 x 1432 49 -> 41; where 256 x 256 fills its rounds it
