@@ -1207,7 +1207,7 @@ static lc_status_t execute_with(const lc_plan& plan, const void* src, void* dst,
       }
     }
   } else {
-    const int wgs = plan.wgs_fit > 0 && cus != kPlannedCus ? shifted_wgs_per_cu(plan.transpose.n_tiles, cus, plan.wgs_fit) : plan.wgs_per_cu;
+    const int wgs = plan.wgs_fit > 0 && cus != kPlannedCus ? shifted_wgs_per_cu(plan.transpose.n_tiles, cus, plan.wgs_fit, std::min(plan.src_run_bytes, plan.dst_run_bytes) < 128) : plan.wgs_per_cu;
     unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(plan.transpose.n_tiles, plan.grid_override > 0 ? (uint64_t)plan.grid_override : (uint64_t)cus * wgs));
     const int key = plan.tile_elem_bytes * 100 + plan.V;
     if (plan.shifted) {

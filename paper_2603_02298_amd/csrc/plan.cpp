@@ -314,16 +314,19 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
 // moved tiles; both widths), time over the best of the four on average: by this rule 1.014, with four up to 1280 tiles and two from there on 1.026.  Some
 // of the ranges, two, three, four and five a CU: 539 to 640 tiles 1.20, 1.00, 1.00, 1.00; 769 to 806 1.17, 1.01, 1.06, 1.06; 1076 to 1150 1.08, 1.11, 1.14,
 // 1.00; 1151 to 1280 1.09, 1.08, 1.22, 1.02; 1345 to 1536 1.01, 1.02, 1.15, 1.18; 1793 to 2048 1.02, 1.08, 1.01, 1.11; 2049 to 2304 1.04, 1.01, 1.10, 1.05.
-// From ten tiles a CU on the rounds no longer tell: two; from 32 on one, whose next tile's loads run under the stores of the one before with
+// Tiles with runs shorter than a line on one side (NCHW of few channels) go without five a CU: some of them gain by it, some lose more (1076 to 1360 tiles,
+// 175 copies: 1.05, 1.06, 1.21 and 1.07 of the best on average with two to five, 1.30, 1.27, 1.46 and 1.48 at worst; NCHW 13 x 40 x 145 x 145 fp16, two to five a CU, 14.4, 14.6, 13.8,
+// 17.4; 47 x 24 x 109 x 109 bf16 19.1, 18.0, 22.1, 16.0).
+// From nine tiles a CU on the rounds no longer tell: two; from 32 on one, whose next tile's loads run under the stores of the one before with
 // nothing between (15876 fp32 tiles 118 us, 143 with two).
-int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit) {
+int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit, bool short_runs) {
   const double per_cu = (double)tiles / cus;
   if (per_cu >= 32.0) return 1;
-  if (per_cu >= 10.0) return std::min(2, fit);
+  if (per_cu >= 9.0) return std::min(2, fit);
   double best = 0.0;
   int best_w = 1;
   for (int w : {2, 4, 5, 3}) {   // (ties: the first)
-    if (w > fit) continue;
+    if (w > fit || (w == 5 && short_runs)) continue;
     const int64_t full = (int64_t)tiles / ((int64_t)w * cus);
     const double rest = per_cu - (double)(full * w), pace = w == 2 ? 1.0 : w == 5 ? 1.06 : 1.02;
     const bool beside = full > 0 && rest <= 0.05 * w && (w > 2 || (fit <= 5 && full == 1));
@@ -761,7 +764,8 @@ static bool plan_tiled(const std::vector<JointMode>& J, int es, int V, int p, in
       if (P.n_ragged > 0) want = 4;
       else want = middle && P.n_tiles >= 1792 ? 3 : plan->lds_bytes >= 32 * 1024 && P.n_tiles >= 8192 ? 2 : 4;
     }
-    if (shifted) want = shifted_wgs_per_cu(P.n_tiles, kPlannedCus, fit);
+    const bool short_runs = std::min(plan->src_run_bytes, plan->dst_run_bytes) < 128;
+    if (shifted) want = shifted_wgs_per_cu(P.n_tiles, kPlannedCus, fit, short_runs);
     plan->shifted = shifted;
     plan->wgs_per_cu = tune.wgs_per_cu > 0 ? tune.wgs_per_cu : std::max(1, std::min(std::min(8, fit), want));
     plan->wgs_fit = shifted && tune.wgs_per_cu <= 0 ? fit : 0;

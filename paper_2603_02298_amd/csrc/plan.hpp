@@ -44,7 +44,7 @@ struct Tuning {
 Tuning tuning_from_env();
 
 constexpr int kPlannedCus = 256;   // plans are made without a device: MI355X, unpartitioned
-int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit);
+int shifted_wgs_per_cu(uint32_t tiles, int cus, int fit, bool short_runs);   // short_runs: below a line of 128 bytes on either side
 
 }  // namespace lc
 

@@ -593,11 +593,13 @@ def test_workgroups_of_shifted_tiles_fill_their_rounds():
     # the round before it
     for tiles, w in [transpose(m, n, "bf16") for m, n in ((5967, 3033), (2821, 2883), (5169, 2367), (3321, 3451), (411, 34767), (1501, 9003))] + \
                     [transpose(m, n, "f32") for m, n in ((639, 7083), (6595, 305), (623, 4895), (1605, 1805), (2201, 1901))] + \
-                    [nchw(15, 24, 95, "f32"), nchw(23, 52, 55, "f32"), nchw(47, 24, 109, "bf16"), nchw(14, 40, 149, "bf16"), nchw(60, 84, 23, "f32")]:
+                    [nchw(39, 212, 44, "bf16"), nchw(48, 212, 18, "f32"), nchw(60, 84, 23, "f32")]:
         assert 256 < tiles <= 1280 and 2 <= w <= 5
         full, rest = divmod(tiles, 256 * w)
         assert full == 0 or rest <= 256 * w // 20 or rest >= 128 * w, (tiles, w)
+    # runs shorter than a line: not five a CU
+    assert nchw(21, 28, 174, "bf16") == (1260, 2) and nchw(13, 40, 145, "bf16") == (1092, 2)
     # far from every edge: one round of five, two of four, the last few tiles beside the round before them, long grids
-    assert [transpose(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (6469, 7521))] == [(1128, 5), (1872, 4), (529, 2), (779, 3), (3009, 2)]
+    assert [transpose(m, n, "bf16") for m, n in ((5967, 3033), (4921, 6071), (2821, 2883), (5169, 2367), (6469, 7521), (4555, 8363))] == [(1128, 5), (1872, 4), (529, 2), (779, 3), (3009, 2), (2376, 2)]
     assert [transpose(m, n, "bf16") for m, n in ((7817, 2151), (5191, 3161))] == [(1054, 4), (1025, 4)] and transpose(2041, 8177, "bf16") == (1024, 4)   # one round of four, and a few more
     assert [transpose(m, n, "f32") for m, n in ((639, 7083), (1885, 4189), (8977, 5323))] == [(1110, 5), (1980, 4), (11844, 1)]
