@@ -311,7 +311,7 @@ static void fill_transpose_head(const TransposeParams& P, int micro_per_thread, 
 // or than a full round; one of a twentieth of a round or less starts beside the round before it (not beside two of 16 KiB, nor behind
 // several rounds of two).  Any other round takes a tenth of a tile time by itself.  The number whose rounds cost least is taken.
 // Measured on MI355X with two to five a CU over 2104 copies of 257 tiles and more (transposes of odd sides, NCHW -> NHWC, relayouts and permutes in
-// moved tiles; both widths), time over the best of the four on average: by this rule 1.014, with four up to 1280 tiles and two from there on 1.026.  Some
+// moved tiles; both widths), time over the best of the four on average: by this rule 1.015, with four up to 1280 tiles and two from there on 1.026.  Some
 // of the ranges, two, three, four and five a CU: 539 to 640 tiles 1.20, 1.00, 1.00, 1.00; 769 to 806 1.17, 1.01, 1.06, 1.06; 1076 to 1150 1.08, 1.11, 1.14,
 // 1.00; 1151 to 1280 1.09, 1.08, 1.22, 1.02; 1345 to 1536 1.01, 1.02, 1.15, 1.18; 1793 to 2048 1.02, 1.08, 1.01, 1.11; 2049 to 2304 1.04, 1.01, 1.10, 1.05.
 // Tiles with runs shorter than a line on one side (NCHW of few channels) go without five a CU: some of them gain by it, some lose more (1076 to 1360 tiles,
