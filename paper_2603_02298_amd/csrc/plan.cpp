@@ -115,7 +115,7 @@ static int common_pow2(int cap, const std::vector<int64_t>& must_divide) {
 // A pass takes as many cycles as the most loaded bank has distinct dwords; cost = cycles beyond one per pass.
 // ---------------------------------------------------------------------------------------------
 static int lds_pass_of_lane(int lane, int access_bytes, bool is_write) {
-  if (is_write) return lane / (128 / std::max(4, std::min(16, access_bytes)));
+  if (is_write) return access_bytes >= 16 ? lane / 8 : access_bytes >= 8 ? lane / 16 : lane / 32;
   if (access_bytes >= 16) {
     const int group = (lane / 4) % 8;
     const int parity = (group ^ (group >> 1) ^ (group >> 2)) & 1;
@@ -124,31 +124,29 @@ static int lds_pass_of_lane(int lane, int access_bytes, bool is_write) {
   return lane / 32;
 }
 int lds_pass_conflicts(const uint32_t* byte_addr, const bool* active, int lanes, int access_bytes, bool is_write) {
+  // Once over the lanes, with the banks of every pass at hand: this is the longer part of planning a tile, and one sweep per pass made it more than
+  // twice as long (lc.Plan of relayout 664 x 244 198 us, 113 this way; transpose 8001 x 8003 138, 65).
   const int words = access_bytes >= 4 ? access_bytes / 4 : 1;
   const uint32_t banks = (is_write || access_bytes <= 4) ? 32u : 64u;
-  int cost = 0;
-  for (int pass = 0; pass < 8; ++pass) {
-    uint8_t cnt[64];
-    uint32_t seen[64][8];
-    std::memset(cnt, 0, sizeof(cnt));
-    bool any = false;
-    for (int l = 0; l < lanes; ++l) {
-      if (!active[l] || lds_pass_of_lane(l, access_bytes, is_write) != pass) continue;
-      any = true;
-      for (int w = 0; w < words; ++w) {
-        const uint32_t dword = byte_addr[l] / 4 + (uint32_t)w, bank = dword % banks;
-        bool again = false;
-        for (int k = 0; k < cnt[bank] && k < 8; ++k) if (seen[bank][k] == dword) again = true;   // the same dword: one access
-        if (again) continue;
-        if (cnt[bank] < 8) seen[bank][cnt[bank]] = dword;
-        cnt[bank]++;
-      }
+  uint8_t cnt[8][64];
+  uint32_t seen[8][64][8];
+  int worst[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  std::memset(cnt, 0, sizeof(cnt));
+  for (int l = 0; l < lanes; ++l) {
+    if (!active[l]) continue;
+    const int pass = lds_pass_of_lane(l, access_bytes, is_write);
+    for (int w = 0; w < words; ++w) {
+      const uint32_t dword = byte_addr[l] / 4 + (uint32_t)w, bank = dword & (banks - 1u);
+      uint8_t& n = cnt[pass][bank];
+      bool again = false;
+      for (int k = 0; k < n && k < 8; ++k) if (seen[pass][bank][k] == dword) again = true;   // the same dword: one access
+      if (again) continue;
+      if (n < 8) seen[pass][bank][n] = dword;
+      worst[pass] = std::max<int>(worst[pass], ++n);
     }
-    if (!any) continue;
-    int worst = 1;
-    for (uint32_t b = 0; b < banks; ++b) worst = std::max<int>(worst, cnt[b]);
-    cost += worst - 1;
   }
+  int cost = 0;
+  for (int w : worst) cost += std::max(0, w - 1);
   return cost;
 }
 
@@ -1125,7 +1123,7 @@ lc_status_t make_plan(const Layout& src, const Layout& dst, int es, unsigned src
     //     of 64 bytes only on the source's side, or on grids of 16 a CU and more (on the destination's side, whose half lines the L2 joins,
     //     (8,74,1948) 4.6 -> 5.1, (4,1163,4,156) 6.6 -> 7.3).
     // What the plan in hand rules out is asked first, what the moved tiles themselves do as soon as they are known: planning a tiling to its end takes
-    // longer than all else here (relayout 512 x 1024 297 us with the moved one planned in any case, 166 without; 68 x 228 347, 240).
+    // longer than all else here (relayout 512 x 1024 310 us with the moved one planned in any case, 169 without, both with the bank model once per pass).
     auto try_moved = [&](bool in_place_of_plain) {
       if (!may_shift || tune.moved == 0 || V * es != 16 || nj < 3) return;
       const int64_t run = std::min(plan->src_run_bytes, plan->dst_run_bytes);
